@@ -71,7 +71,7 @@ enum { QE_LIB_NCV = 0,      /* {I, NOT, CNOT, CV, CV+} */
        QE_LIB_ISING = 2 };  /* {R_x, R_y, R_z, J} with angles (QEQEA only) */
 enum { QE_ALG_QEQEA = 0, QE_ALG_GA = 1 };
 enum { QE_PATH_FP32 = 0,        /* per-gate row updates, FP32, tuned schedule per width */
-       QE_PATH_FP32_REG = 1,    /* forced: matrix held in registers, one wave per circuit */
+       QE_PATH_FP32_REG = 1,    /* forced: matrix held in registers */
        QE_PATH_FP32_LDS = 2,    /* forced: matrix staged in LDS, columns split over waves */
        QE_PATH_MFMA_BF16 = 3,   /* fused 4-wire gate blocks on MFMA, bf16 hi+lo, FP32
                                    accumulation, columns renormalised after each block */
@@ -409,7 +409,8 @@ qe_status qe_lib_table(int32_t library, int32_t n_qubits, uint16_t* table_host);
 
 /* Schedule of the QE_PATH_FP32 path: for width n (1..6), lds != 0 selects
  * the LDS-staged kernel, 0 the register-resident one (n <= 3 always use the
- * one-element-per-lane kernel).  Process-wide; the defaults come from the
+ * one-element-per-lane kernel; mixed-width batches evaluated in one launch
+ * the register-resident one).  Process-wide; the defaults come from the
  * tuning table measured on MI355X and can be overridden by the environment
  * variable QE_SCHEDULE="n:lds,n:lds,...". */
 qe_status qe_set_schedule(int32_t n_qubits, int32_t lds);
@@ -418,14 +419,14 @@ qe_status qe_get_schedule(int32_t n_qubits, int32_t* lds);
 /* The whole schedule of width n for circuits of length class lclass (0: L <
  * 32, 1: L >= 32; batches of uneven lengths use class 1): lds as above,
  * waves = wavefronts per circuit of the LDS-staged kernels (1 for n <= 4, 1
- * or 2 for n = 5, 4 for n = 6), cpb = circuits per workgroup of the
- * one-wavefront population kernels (1 or 4).  Process-wide, like
+ * or 2 for n = 5, 4 for n = 6; the register-resident kernels have a fixed
+ * number), cpb = circuits per workgroup of the one-wavefront population
+ * kernels (1 or 4).  Process-wide, like
  * qe_set_schedule; the tuning table (lines "n lclass lds waves cpb") and
- * QE_SCHEDULE="n:lds[:waves[:cpb]],..." set it too.  Every LDS-staged
- * schedule gives the same results bit for bit (the fitness reduction runs
- * in an order fixed by the width); the register-resident kernel agrees
- * within the FP32 tolerance.  A mixed-population context keeps the width-5
- * wave count it was created with.  Unknown combinations: QE_ERR_INVALID. */
+ * QE_SCHEDULE="n:lds[:waves[:cpb]],..." set it too.  Every schedule gives
+ * the same results bit for bit (the same operations on each element, the
+ * fitness reduction in an order fixed by the width).  Unknown combinations:
+ * QE_ERR_INVALID. */
 qe_status qe_set_schedule_ex(int32_t n_qubits, int32_t lclass, int32_t lds, int32_t waves, int32_t cpb);
 qe_status qe_get_schedule_ex(int32_t n_qubits, int32_t lclass, int32_t* lds, int32_t* waves, int32_t* cpb);
 
@@ -435,8 +436,7 @@ qe_status qe_get_schedule_ex(int32_t n_qubits, int32_t lclass, int32_t* lds, int
  * circuits the QEQEA sampler decodes from the encoding of Sec. IV-D (only
  * I, NOT, CNOT, CV, CV+: qe_sample_eval and the generation kernels);
  * QE_SCHED_ISING: circuits of the Ising library (Sec. III), whose gates
- * carry angles (batches with angles_dev, Ising contexts).  Angled circuits
- * of 4 or more wires always take the LDS-staged kernels, whatever lds says. */
+ * carry angles (batches with angles_dev, Ising contexts). */
 enum { QE_SCHED_DISCRETE = 0, QE_SCHED_SAMPLED = 1, QE_SCHED_ISING = 2 };
 
 /* The schedule of one (width, length class, library class).

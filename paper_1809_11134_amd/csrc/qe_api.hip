@@ -238,7 +238,6 @@ qe_status to_args(const qe_batch* b, BatchArgs* a, bool need_targets) {
     a->targets = b->targets_dev;
     a->num_telems = b->num_target_elems;
     a->mode = b->fitness_mode;
-    a->mix_w5 = schedule_for(5, 32, b->angles_dev ? SCHED_ISING : SCHED_DISCRETE).waves;
     a->angles = b->angles_dev;
     return device_error_word(&a->err);
 }
@@ -307,7 +306,6 @@ struct qe_ctx {
     int32_t* mix_eval_work = nullptr;
     size_t mix_work_bytes = 0;
     uint32_t* check_word = nullptr;   // flags of the phase-insensitive target check
-    int32_t mix_w5 = 1;               // the schedule the mixed order was computed for
 };
 
 namespace {
@@ -375,7 +373,6 @@ BatchArgs mixed_batch(const qe_ctx* c, const uint16_t* gates) {
     b.targets = c->la.target32;
     b.num_telems = c->target_elems;
     b.mode = c->prob.fitness_mode;
-    b.mix_w5 = c->mix_w5;
     b.angles = nullptr;
     b.err = c->la.err;
     return b;
@@ -811,7 +808,6 @@ qe_status create_impl(const qe_problem* p_in, const int32_t* inst_n, const int32
         if (e == hipSuccess)
             e = hipMemcpy(c->circ_toff, h_ctoff.data(), I * P * sizeof(int64_t), hipMemcpyHostToDevice);
         // the cost order of the circuits: widths and lengths never change
-        c->mix_w5 = schedule_for(5, 32).waves;
         if (e == hipSuccess) e = launch_mix_sort(mixed_batch(c, c->gates), c->mix_order, nullptr);
     }
     if (p->algorithm == QE_ALG_QEQEA) {

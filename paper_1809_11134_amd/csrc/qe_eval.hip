@@ -2,6 +2,7 @@
 #include "../../include/qe.h"
 #include "qe_eval_core.hpp"
 #include "qe_internal.hpp"
+#include "qe_reg_core.hpp"
 
 namespace qe {
 
@@ -22,11 +23,10 @@ __device__ __forceinline__ auto batch_gate(const Item& it, int p) {
 }
 
 // ------------------------------------------------------- FP32, one wave each
-// Register-resident path (n = 4..6) or one-element-per-lane path (n <= 3);
-// WPB circuits per workgroup.  FILTER: a mixed-width batch is served by one
-// launch per width, each skipping the circuits of other widths.  ANG: the
-// batch carries angles (one-element-per-lane path only).
-template <int NQ, bool FILTER, bool ANG = false>
+// One-element-per-lane path (n <= 3), WPB circuits per workgroup.  FILTER: a
+// mixed-width batch is served by one launch per width, each skipping the
+// circuits of other widths.  ANG: the batch carries angles.
+template <int NQ, bool FILTER, bool ANG>
 __global__ __launch_bounds__(64 * WPB) void wave_kernel(BatchArgs a, float* __restrict__ f,
                                                         float* __restrict__ g,
                                                         float* __restrict__ delta) {
@@ -41,8 +41,7 @@ __global__ __launch_bounds__(64 * WPB) void wave_kernel(BatchArgs a, float* __re
         const int L = it.L;
         auto src = [&](int ch) { return batch_gate<ANG>(it, ch * 64 + lane); };
         const float* T = reinterpret_cast<const float*>(a.targets) + 2 * it.toff;
-        static_assert(!ANG || NQ <= 3, "angled circuits of 4 or more wires take the LDS-staged path");
-        const bool ok = run_width<NQ, false>(NQ, T, L, src, nullptr, &o, a.mode);
+        const bool ok = run_small_path<NQ, false>(T, L, src, nullptr, &o, a.mode);
         if (!ok) {
             it.err = QE_DEVERR_DESC;
             o = FitOut{__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
@@ -56,6 +55,64 @@ __global__ __launch_bounds__(64 * WPB) void wave_kernel(BatchArgs a, float* __re
         if (delta) delta[b] = o.delta;
         if (it.err) atomicOr(a.err, it.err);
     }
+}
+
+// ------------------------------------------- register-resident, n = 4..6
+// One circuit on its W wavefronts (W = 4 at n = 6, else 1; `wave` the circuit's
+// wavefront): the fitness of circuit b (n = 6: every wavefront of the workgroup
+// calls it, red is LDS).
+// strict: a NaN residual gives NaN (QE_PATH_FP32_REG and FP64); without it the
+// radicand is clamped as in the LDS-staged kernels.
+__device__ __forceinline__ int64_t uniform64(int64_t v) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+template <typename Real, int NQ, bool ANG>
+__device__ __forceinline__ void reg_item(const BatchArgs& a, int b, Item it, int wave, bool strict,
+                                         Real (*red)[3], Real* __restrict__ f, Real* __restrict__ g,
+                                         Real* __restrict__ delta) {
+    const int lane = (int)lane_id();
+    if (it.err == 0 && it.n != NQ) it.err = QE_DEVERR_WIDTH;
+    // (wave-uniform, and in scalar registers from here on)
+    it.err = (uint32_t)__builtin_amdgcn_readfirstlane((int)it.err);
+    it.toff = uniform64(it.toff);
+    Real fv, gv, dv;
+    fv = gv = dv = (Real)__builtin_nan("");
+    if (it.err == 0) {
+        RegMatrix<Real, NQ> M;
+        M.place(wave);
+        auto src = [&](int ch) { return batch_gate<ANG>(it, ch * 64 + lane); };
+        const auto dv0 = src(0);
+        M.load(reinterpret_cast<const Real*>(a.targets) + 2 * it.toff);
+        if (!M.template run<true>(it.L, src, dv0)) {
+            it.err = QE_DEVERR_DESC;
+        } else {
+            fv = M.fitness(a.mode, &gv, &dv, wave, red);
+            if (strict && !(dv == dv)) fv = dv;
+            if (!(fv == fv)) it.err = QE_DEVERR_NUMERIC;
+        }
+    }
+    if (wave == 0 && lane == 0) {
+        f[b] = fv;
+        if (g) g[b] = gv;
+        if (delta) delta[b] = dv;
+        if (it.err) atomicOr(a.err, it.err);
+    }
+}
+
+// Four circuits per workgroup, one per wavefront; n = 6: one per workgroup.
+template <typename Real, int NQ, bool FILTER, bool ANG>
+__global__ __launch_bounds__(256) void reg_kernel(BatchArgs a, Real* __restrict__ f, Real* __restrict__ g,
+                                                  Real* __restrict__ delta, bool strict) {
+    __shared__ Real red[4][3];
+    const int wave = (int)(threadIdx.x >> 6);
+    constexpr bool WHOLE = RegGeom<NQ>::W == 4;
+    const int b = __builtin_amdgcn_readfirstlane(WHOLE ? (int)blockIdx.x : (int)blockIdx.x * WPB + wave);
+    if (b >= a.B) return;
+    const Item it = resolve(a, b);
+    if (FILTER && it.n != NQ) return;
+    reg_item<Real, NQ, ANG>(a, b, it, WHOLE ? wave : 0, strict, red, f, g, delta);
 }
 
 // Marks circuits whose width is outside 1..6 (mixed-width batches only).
@@ -76,7 +133,7 @@ __global__ __launch_bounds__(64 * W) void lds32_kernel(BatchArgs a, float* __res
                                                        float* __restrict__ g,
                                                        float* __restrict__ delta,
                                                        float* __restrict__ U_out) {
-    constexpr int N = 1 << NQ, CW = N / W;
+    constexpr int N = 1 << NQ;
     __shared__ float2 M[N * N];
     __shared__ uint4 GT[W][ANG ? GATE_TABLE_ANGLED : GATE_TABLE];
     const int b = blockIdx.x;
@@ -123,9 +180,9 @@ __global__ __launch_bounds__(64 * W) void lds32_kernel(BatchArgs a, float* __res
 // Circuits of a mixed-width batch are ordered by cost, widest first and,
 // within a width, longest first (classes of 8 gates), by a one-workgroup
 // counting sort; one launch then gives every workgroup (4 wavefronts) one
-// work item: a circuit of width 6 (4 waves), two of width 5 (2 waves each),
-// or four of width <= 4 (one wave each; LDS-staged for 4, one entry per lane
-// below), so an item's circuits have similar lengths.  Workgroups are
+// work item: a circuit of width 6 (4 waves) or four of the other widths (one
+// wave each; register-resident for 4 and 5, one entry per lane below), so an
+// item's circuits have similar lengths.  Workgroups are
 // dispatched in index order, so the heaviest items start first
 // (longest-processing-time order).
 constexpr int MIX_BUCKETS = 7;          // widths 6..1, then malformed widths
@@ -140,13 +197,8 @@ __device__ __forceinline__ int mix_key(const BatchArgs& a, int b) {
     const int lc = len >= 120 ? 0 : (len < 8 ? MIX_LCLASSES - 1 : MIX_LCLASSES - 1 - (int)(len >> 3));
     return mix_bucket(a.nq[b]) * MIX_LCLASSES + lc;
 }
-// circuits per work item: one of width 6 (four wavefronts), three of width
-// 5 with one wavefront each (their 8 KB matrices and gate tables fill the
-// 32 KB of LDS; the fourth wavefront idles) or two with two wavefronts each,
-// four of the other widths
-__device__ __forceinline__ int mix_per_item(int k, int w5) {
-    return k == 0 ? 1 : (k == 1 ? (w5 == 2 ? 2 : 3) : 4);
-}
+// circuits per work item: one of width 6 (four wavefronts), four of the others
+__device__ __forceinline__ int mix_per_item(int k) { return k == 0 ? 1 : 4; }
 
 // meta: [0..7) first order position, [8..15) first item (8 entries, the last
 // the total), [16..23) count per bucket.
@@ -184,7 +236,7 @@ __global__ __launch_bounds__(1024) void mix_bucket_kernel(BatchArgs a, int32_t* 
             meta[k] = pos;
             meta[8 + k] = item;
             meta[16 + k] = end - pos;
-            item += (end - pos + mix_per_item(k, a.mix_w5) - 1) / mix_per_item(k, a.mix_w5);
+            item += (end - pos + mix_per_item(k) - 1) / mix_per_item(k);
         }
         meta[8 + MIX_BUCKETS] = item;
     }
@@ -192,46 +244,9 @@ __global__ __launch_bounds__(1024) void mix_bucket_kernel(BatchArgs a, int32_t* 
     for (int b = tid; b < a.B; b += blockDim.x) order[atomicAdd(&cursor[mix_key(a, b)], 1)] = b;
 }
 
-template <int NQ, int W>
-__device__ __forceinline__ void mix_lds_item(const BatchArgs& a, int b, float2* M, uint4* gt,
-                                             float (*red)[3], float* f, float* g, float* delta) {
-    const int lane = (int)lane_id(), wave = (int)(threadIdx.x >> 6);
-    Item it;
-    it.err = 1;
-    if (b >= 0) it = resolve(a, b);
-    bool ok = it.err == 0;
-    RowMap map{};
-    if (ok) {
-        const uint16_t* gp = it.g;
-        const int L = it.L;
-        auto src = [&](int ch) -> uint32_t {
-            const int p = ch * 64 + lane;
-            return p < L ? (uint32_t)gp[p] : 0u;
-        };
-        const float* T = reinterpret_cast<const float*>(a.targets) + 2 * it.toff;
-        ok = run_lds_path<NQ, W, false>(M, gt, T, L, src, &map, wave % W);
-        if (!ok) it.err = QE_DEVERR_DESC;
-    }
-    constexpr int WR = reduction_waves<NQ>();
-    static_assert(WR == 1 || WR == W, "the reduction's wavefronts are the circuit's");
-    if constexpr (W > 1) __syncthreads();     // every wavefront's columns are in place
-    if (WR == 1 && wave % W != 0) return;
-    float gv, dv;
-    const float fv = canonical_fitness<NQ, WR>(M, map, a.mode, &gv, &dv, WR == 1 ? 0 : wave % W, red);
-    if (b >= 0 && wave % W == 0 && lane == 0) {
-        const float nan = __builtin_nanf("");
-        if (ok && !(fv == fv)) it.err = QE_DEVERR_NUMERIC;
-        f[b] = ok ? fv : nan;
-        if (g) g[b] = ok ? gv : nan;
-        if (delta) delta[b] = ok ? dv : nan;
-        if (it.err) atomicOr(a.err, it.err);
-    }
-}
-
 template <int NQ>
 __device__ __forceinline__ void mix_wave_item(const BatchArgs& a, int b, float* f, float* g,
                                               float* delta) {
-    if (b < 0) return;
     const int lane = (int)lane_id();
     Item it = resolve(a, b);
     FitOut o{__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
@@ -262,36 +277,28 @@ __global__ __launch_bounds__(256) void mix_kernel(BatchArgs a, const int32_t* __
                                                   const int32_t* __restrict__ meta,
                                                   float* __restrict__ f, float* __restrict__ g,
                                                   float* __restrict__ delta) {
-    __shared__ float2 M[4096];
     __shared__ float red[4][3];
     const int item = blockIdx.x;
     if (item >= meta[8 + MIX_BUCKETS]) return;
     int k = 0;
     while (k + 1 < MIX_BUCKETS && item >= meta[8 + k + 1]) ++k;
     const int wave = (int)(threadIdx.x >> 6);
-    const int per = mix_per_item(k, a.mix_w5);
+    const int per = mix_per_item(k);
     const int local = (item - meta[8 + k]) * per;
-    const int sub = per == 1 ? 0 : (per == 2 ? wave >> 1 : wave);
-    int b = sub < per && local + sub < meta[16 + k] ? order[meta[k] + local + sub] : -1;
+    const int sub = per == 1 ? 0 : wave;
+    int b = local + sub < meta[16 + k] ? order[meta[k] + local + sub] : -1;
     if (b >= a.B) b = -1;        // an order written for another batch never indexes past this one
+    b = __builtin_amdgcn_readfirstlane(b);
+    if (b < 0) return;           // (width 6: the whole workgroup)
     switch (k) {
-        // (widths 4 and 5 run one circuit per wavefront, each with its gate table)
-        case 0: mix_lds_item<6, 4>(a, b, M, nullptr, red, f, g, delta); break;
-        case 1:
-            if (a.mix_w5 == 2) mix_lds_item<5, 2>(a, b, M + sub * 1024, nullptr, red, f, g, delta);
-            else if (wave < 3)   // gate tables in the last quarter of M
-                mix_lds_item<5, 1>(a, b, M + sub * 1024, reinterpret_cast<uint4*>(M + 3072) + wave * GATE_TABLE,
-                                   red, f, g, delta);
-            break;
-        case 2:   // gate tables after the four 16 x 16 matrices
-            mix_lds_item<4, 1>(a, b, M + sub * 256, reinterpret_cast<uint4*>(M + 1024) + wave * GATE_TABLE, red,
-                               f, g, delta);
-            break;
+        case 0: reg_item<float, 6, false>(a, b, resolve(a, b), wave, false, red, f, g, delta); break;
+        case 1: reg_item<float, 5, false>(a, b, resolve(a, b), 0, false, red, f, g, delta); break;
+        case 2: reg_item<float, 4, false>(a, b, resolve(a, b), 0, false, red, f, g, delta); break;
         case 3: mix_wave_item<3>(a, b, f, g, delta); break;
         case 4: mix_wave_item<2>(a, b, f, g, delta); break;
         case 5: mix_wave_item<1>(a, b, f, g, delta); break;
         default:
-            if (b >= 0 && lane_id() == 0) {
+            if (lane_id() == 0) {
                 const float nan = __builtin_nanf("");
                 f[b] = nan;
                 if (g) g[b] = nan;
@@ -329,58 +336,44 @@ static size_t lds_kernel_bytes(const BatchArgs& a, size_t real_bytes) {
 // Per-width schedule: which kernel evaluates a circuit of width n on the
 // FP32 path.  path: QE_PATH_FP32 (default schedule), QE_PATH_FP32_REG,
 // QE_PATH_FP32_LDS.
-static bool use_lds(int n, int path, int L) {
+static bool use_lds(int n, int path, int L, int lib_class) {
     if (n <= 3) return false;
     if (path == QE_PATH_FP32_REG) return false;
     if (path == QE_PATH_FP32_LDS) return true;
-    return schedule_for(n, L).lds != 0;
+    return schedule_for(n, L, lib_class).lds != 0;
 }
 
 // length of the batch's circuits for the schedule (uneven batches: the long class)
 static int sched_len(const BatchArgs& a) { return a.uniform_L > 0 ? a.uniform_L : 32; }
 
-// Angled batches (ANG): the one-element-per-lane kernel for n <= 3 and the
-// LDS-staged one above (the register-resident path has no Ising kinds).
-template <bool FILTER, bool ANG = false>
-static void launch_width(const BatchArgs& a, int n, bool lds, float* f, float* g, float* delta,
+// One launch over the batch's circuits of width n.  n <= 3: the
+// one-element-per-lane kernel; above, the register-resident or the LDS-staged
+// one.
+template <bool FILTER, bool ANG>
+static void launch_width(const BatchArgs& a, int n, int path, float* f, float* g, float* delta,
                          hipStream_t s) {
     const dim3 wgrid((a.B + WPB - 1) / WPB), wblock(64 * WPB);
-    if constexpr (ANG) {
-        switch (n) {
-            case 1: wave_kernel<1, FILTER, true><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
-            case 2: wave_kernel<2, FILTER, true><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
-            case 3: wave_kernel<3, FILTER, true><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
-            case 4: lds32_kernel<4, 1, FILTER, false, true><<<a.B, 64, 0, s>>>(a, f, g, delta, nullptr); break;
-            case 5:
-                if (schedule_for(5, sched_len(a), SCHED_ISING).waves == 2)
-                    lds32_kernel<5, 2, FILTER, false, true><<<a.B, 128, 0, s>>>(a, f, g, delta, nullptr);
-                else
-                    lds32_kernel<5, 1, FILTER, false, true><<<a.B, 64, 0, s>>>(a, f, g, delta, nullptr);
-                break;
-            default: lds32_kernel<6, 4, FILTER, false, true><<<a.B, 256, 0, s>>>(a, f, g, delta, nullptr); break;
-        }
-        return;
-    }
-    if (lds) {
-        switch (n) {
-            case 4: lds32_kernel<4, 1, FILTER, false><<<a.B, 64, 0, s>>>(a, f, g, delta, nullptr); break;
-            case 5:
-                if (schedule_for(5, sched_len(a)).waves == 2)
-                    lds32_kernel<5, 2, FILTER, false><<<a.B, 128, 0, s>>>(a, f, g, delta, nullptr);
-                else
-                    lds32_kernel<5, 1, FILTER, false><<<a.B, 64, 0, s>>>(a, f, g, delta, nullptr);
-                break;
-            default: lds32_kernel<6, 4, FILTER, false><<<a.B, 256, 0, s>>>(a, f, g, delta, nullptr); break;
-        }
-        return;
-    }
+    constexpr int LIB = ANG ? SCHED_ISING : SCHED_DISCRETE;
+    const bool lds = use_lds(n, path, sched_len(a), LIB), strict = path == QE_PATH_FP32_REG;
     switch (n) {
-        case 1: wave_kernel<1, FILTER><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
-        case 2: wave_kernel<2, FILTER><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
-        case 3: wave_kernel<3, FILTER><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
-        case 4: wave_kernel<4, FILTER><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
-        case 5: wave_kernel<5, FILTER><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
-        default: wave_kernel<6, FILTER><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
+        case 1: wave_kernel<1, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
+        case 2: wave_kernel<2, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
+        case 3: wave_kernel<3, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
+        case 4:
+            if (lds) lds32_kernel<4, 1, FILTER, false, ANG><<<a.B, 64, 0, s>>>(a, f, g, delta, nullptr);
+            else reg_kernel<float, 4, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta, strict);
+            break;
+        case 5:
+            if (!lds) reg_kernel<float, 5, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta, strict);
+            else if (schedule_for(5, sched_len(a), LIB).waves == 2)
+                lds32_kernel<5, 2, FILTER, false, ANG><<<a.B, 128, 0, s>>>(a, f, g, delta, nullptr);
+            else
+                lds32_kernel<5, 1, FILTER, false, ANG><<<a.B, 64, 0, s>>>(a, f, g, delta, nullptr);
+            break;
+        default:
+            if (lds) lds32_kernel<6, 4, FILTER, false, ANG><<<a.B, 256, 0, s>>>(a, f, g, delta, nullptr);
+            else reg_kernel<float, 6, FILTER, ANG><<<a.B, 256, 0, s>>>(a, f, g, delta, strict);
+            break;
     }
 }
 
@@ -389,21 +382,20 @@ hipError_t launch_eval_fp32(const BatchArgs& a, int path, float* f, float* g, fl
     if (a.B == 0) return hipSuccess;
     if (a.angles) {
         if (a.uniform_n > 0) {
-            launch_width<false, true>(a, a.uniform_n, true, f, g, delta, s);
+            launch_width<false, true>(a, a.uniform_n, path, f, g, delta, s);
         } else {
             width_check_kernel<<<(a.B + 255) / 256, 256, 0, s>>>(a, f, g, delta);
-            for (int n = 1; n <= MAX_QUBITS; ++n) launch_width<true, true>(a, n, true, f, g, delta, s);
+            for (int n = 1; n <= MAX_QUBITS; ++n) launch_width<true, true>(a, n, path, f, g, delta, s);
         }
     } else if (a.uniform_n > 0) {
-        launch_width<false>(a, a.uniform_n, use_lds(a.uniform_n, path, sched_len(a)), f, g, delta, s);
+        launch_width<false, false>(a, a.uniform_n, path, f, g, delta, s);
     } else if (path == QE_PATH_FP32 && work) {
         // one launch over width-sorted work items (LDS-staged for n >= 4)
         mix_bucket_kernel<<<1, 1024, 0, s>>>(a, work + MIX_WORK_META, work);
         mix_kernel<<<a.B, 256, 0, s>>>(a, work + MIX_WORK_META, work, f, g, delta);
     } else {
         width_check_kernel<<<(a.B + 255) / 256, 256, 0, s>>>(a, f, g, delta);
-        for (int n = 1; n <= MAX_QUBITS; ++n)
-            launch_width<true>(a, n, use_lds(n, path, sched_len(a)), f, g, delta, s);
+        for (int n = 1; n <= MAX_QUBITS; ++n) launch_width<true, false>(a, n, path, f, g, delta, s);
     }
     return hipGetLastError();
 }

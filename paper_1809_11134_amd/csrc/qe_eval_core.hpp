@@ -6,19 +6,8 @@
 // gives Eq. 11 of Sec. IV-E; the residual ||M_L - e^{i arg tr} I||_F^2 / 2
 // gives the same radicand without cancellation.
 //
-// Register layout (n = 4, 5, 6): the N x N complex matrix (N = 2^n) is spread
-// over the 64 lanes of a wavefront and E = N^2 / 64 registers per lane.  The
-// column index j occupies lane bits 0..n-1 and never moves (gates act on rows
-// only).  The n row bits ("slots") live either in register-index bits
-// 0..EB-1 (EB = 2n - 6) or in lane bits n..5.  A wave-uniform map records
-// which wire sits in which slot.  Before a gate the target wire is moved to
-// register bit 0 and a register-resident control to register bit EB-1, by
-// exchanging register bits (register renames) or a lane bit with a register
-// bit (v_permlane16/32_swap); a lane-resident control becomes an exec
-// predicate.  Every gate body is then one of a handful of fully unrolled
-// register loops, and no shuffle or LDS traffic is needed for the arithmetic.
-//
-// LDS-staged layout (n = 4..6, the tuned default; run_lds_path): M lives in
+// Register-resident layout (n = 4..6; qe_reg_core.hpp): M lives in VGPRs.
+// LDS-staged layout (n = 4..6; run_lds_path): M lives in
 // LDS, W wavefronts split its columns, each lane updates the row pairs of one
 // column per pass, and the gate constants come from a per-chunk gate program.
 // One entry per lane (n <= 3; run_small_path): lane l holds M[l / N][l % N].
@@ -27,8 +16,7 @@
 // returns this lane's gate of the chunk: a uint32 descriptor for the
 // discrete libraries, or a uint2 {descriptor, angle} when the circuit may
 // hold Ising gates (kinds 7-10, angle a u32 turn fraction).  The angled
-// form compiles the Ising kinds in; the register-resident path takes the
-// discrete form only.
+// form compiles the Ising kinds in.
 #pragma once
 #include <type_traits>
 
@@ -100,177 +88,6 @@ __device__ __forceinline__ float2 phase_plus(float2 x, float c, float s) {    //
 }
 __device__ __forceinline__ uint32_t f_bits(float f) { return __float_as_uint(f); }
 
-// ----------------------------------------------------------- lane-bit swaps
-// Exchange lane bit 5 (LB = 5) or lane bit 4 (LB = 4) of the elements of
-// registers a (register bit 0) and b (register bit 1): after the call a holds
-// in its upper half-lanes what b held in its lower ones and vice versa.
-template <int LB>
-__device__ __forceinline__ void lane_swap(float& a, float& b) {
-    if constexpr (LB == 5) {
-        auto r = __builtin_amdgcn_permlane32_swap(f_bits(a), f_bits(b), false, false);
-        a = bits_f(r[0]);
-        b = bits_f(r[1]);
-    } else {
-        static_assert(LB == 4, "lane bit");
-        auto r = __builtin_amdgcn_permlane16_swap(f_bits(a), f_bits(b), false, false);
-        a = bits_f(r[0]);
-        b = bits_f(r[1]);
-    }
-}
-
-// ------------------------------------------------------------ register swaps
-// In-place exchange of two VGPRs.  Written as v_swap_b32 so that the values
-// stay in the registers the allocator gave the two variables: a plain C++
-// swap becomes a pair of renamed values that must be copied back at every
-// control-flow merge of the gate dispatch.
-__device__ __forceinline__ void vswap(float& a, float& b) {
-    asm volatile("v_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-}
-
-// Exchange register bits A < B: element k with bit A set and bit B clear
-// trades places with k ^ (1<<A) ^ (1<<B).
-template <int E, int A, int B>
-__device__ __forceinline__ void swap_reg_bits(float* re, float* im) {
-#pragma unroll
-    for (int k = 0; k < E; ++k) {
-        if (((k >> A) & 1) == 1 && ((k >> B) & 1) == 0) {
-            const int k2 = k ^ (1 << A) ^ (1 << B);
-            vswap(re[k], re[k2]);
-            vswap(im[k], im[k2]);
-        }
-    }
-}
-
-// Exchange register bit R with lane bit LB.
-template <int E, int R, int LB>
-__device__ __forceinline__ void swap_lane_reg(float* re, float* im) {
-#pragma unroll
-    for (int k = 0; k < E; ++k) {
-        if (((k >> R) & 1) == 0) {
-            const int k2 = k | (1 << R);
-            lane_swap<LB>(re[k], re[k2]);
-            lane_swap<LB>(im[k], im[k2]);
-        }
-    }
-}
-
-template <int E, int EB>
-__device__ __forceinline__ void swap_reg_rt(int a, int b, float* re, float* im) {
-    // a < b < EB (wave-uniform)
-#define QE_SW(A, B)                                                  \
-    case (A)*8 + (B):                                                \
-        if constexpr ((B) < EB) swap_reg_bits<E, A, B>(re, im);      \
-        break;
-    switch (a * 8 + b) {
-        QE_SW(0, 1) QE_SW(0, 2) QE_SW(0, 3) QE_SW(0, 4) QE_SW(0, 5)
-        QE_SW(1, 2) QE_SW(1, 3) QE_SW(1, 4) QE_SW(1, 5)
-        QE_SW(2, 3) QE_SW(2, 4) QE_SW(2, 5)
-        QE_SW(3, 4) QE_SW(3, 5)
-        QE_SW(4, 5)
-        default: break;
-    }
-#undef QE_SW
-}
-
-template <int E, int EB>
-__device__ __forceinline__ void swap_lane_reg_rt(int r, int lb, float* re, float* im) {
-#define QE_LR(R)                                                                   \
-    case R:                                                                        \
-        if constexpr ((R) < EB) {                                                  \
-            if (lb == 5) swap_lane_reg<E, R, 5>(re, im);                           \
-            else swap_lane_reg<E, R, 4>(re, im);                                   \
-        }                                                                          \
-        break;
-    switch (r) {
-        QE_LR(0) QE_LR(1) QE_LR(2) QE_LR(3) QE_LR(4) QE_LR(5)
-        default: break;
-    }
-#undef QE_LR
-}
-
-// ------------------------------------------------------------------ slot map
-// Wave-uniform map between wires and slots, 4 bits per entry.
-struct SlotMap {
-    uint32_t w2s, s2w;
-    __device__ __forceinline__ int slot(int w) const { return (w2s >> (4 * w)) & 15; }
-    __device__ __forceinline__ int wire(int s) const { return (s2w >> (4 * s)) & 15; }
-    __device__ __forceinline__ void exchange(int a, int b) {
-        const int wa = wire(a), wb = wire(b);
-        s2w = (s2w & ~(15u << (4 * a)) & ~(15u << (4 * b))) | ((uint32_t)wb << (4 * a)) |
-              ((uint32_t)wa << (4 * b));
-        w2s = (w2s & ~(15u << (4 * wa)) & ~(15u << (4 * wb))) | ((uint32_t)b << (4 * wa)) |
-              ((uint32_t)a << (4 * wb));
-    }
-};
-
-// Exchange the contents of slots a != b (register bit < EB or lane bit).
-template <int NQ, int E, int EB>
-__device__ __forceinline__ void swap_slots(int a, int b, float* re, float* im, SlotMap& map) {
-    if (a > b) { const int t = a; a = b; b = t; }
-    if constexpr (EB == NQ) {   // every slot is a register bit
-        swap_reg_rt<E, EB>(a, b, re, im);
-    } else if (b < EB) {
-        swap_reg_rt<E, EB>(a, b, re, im);
-    } else if (a < EB) {
-        swap_lane_reg_rt<E, EB>(a, NQ + b - EB, re, im);
-    } else {
-        // both in lanes (n = 4): route through register bit 0
-        swap_lane_reg_rt<E, EB>(0, NQ + a - EB, re, im);
-        swap_lane_reg_rt<E, EB>(0, NQ + b - EB, re, im);
-        swap_lane_reg_rt<E, EB>(0, NQ + a - EB, re, im);
-    }
-    map.exchange(a, b);
-}
-
-// ---------------------------------------------------------------- gate bodies
-// Target at register bit 0.  CTL: 0 = uncontrolled, 1 = control at register
-// bit EB-1 (only the upper half of the registers is transformed).
-template <int E, int CTL>
-__device__ __forceinline__ void body_x(float* re, float* im) {
-#pragma unroll
-    for (int k = (CTL ? E / 2 : 0); k < E; k += 2) {
-        vswap(re[k], re[k + 1]);
-        vswap(im[k], im[k + 1]);
-    }
-}
-
-// V = (1/2)[[1+i, 1-i], [1-i, 1+i]]:  a' = (s + i d)/2, b' = (s - i d)/2 with
-// s = a + b, d = a - b.  V^dagger swaps the two outputs.
-template <int E, int CTL, bool DAG>
-__device__ __forceinline__ void body_v(float* re, float* im) {
-#pragma unroll
-    for (int k = (CTL ? E / 2 : 0); k < E; k += 2) {
-        const float p = re[k] + re[k + 1], q = im[k] + im[k + 1];
-        const float u = re[k] - re[k + 1], v = im[k] - im[k + 1];
-        const float xr = 0.5f * (p - v), xi = 0.5f * (q + u);
-        const float yr = 0.5f * (p + v), yi = 0.5f * (q - u);
-        if (DAG) { re[k] = yr; im[k] = yi; re[k + 1] = xr; im[k + 1] = xi; }
-        else     { re[k] = xr; im[k] = xi; re[k + 1] = yr; im[k + 1] = yi; }
-    }
-}
-
-template <int E>
-__device__ __forceinline__ void body_h(float* re, float* im) {
-    const float r = 0.70710678118654752f;
-#pragma unroll
-    for (int k = 0; k < E; k += 2) {
-        const float ar = re[k], ai = im[k], br = re[k + 1], bi = im[k + 1];
-        re[k] = (ar + br) * r; im[k] = (ai + bi) * r;
-        re[k + 1] = (ar - br) * r; im[k + 1] = (ai - bi) * r;
-    }
-}
-
-template <int E>
-__device__ __forceinline__ void body_t(float* re, float* im) {
-    const float r = 0.70710678118654752f;   // e^{i pi/4} = (1 + i)/sqrt(2)
-#pragma unroll
-    for (int k = 1; k < E; k += 2) {
-        const float br = re[k], bi = im[k];
-        re[k] = (br - bi) * r;
-        im[k] = (br + bi) * r;
-    }
-}
-
 // --------------------------------------------------------- fitness reduction
 struct FitOut {
     float f, g, delta;
@@ -319,117 +136,6 @@ __device__ __forceinline__ FitOut finish_fitness(float off, float dre, float dim
     o.delta = delta;
     if (!(o.f == o.f) || !(delta == delta)) o.f = __builtin_nanf("");
     return o;
-}
-
-// -------------------------------------------------------- register-path core
-// GateSrc: callable chunk(c) -> this lane's descriptor for position
-// c*64 + lane (0 beyond the circuit), evaluated by all lanes.
-// Returns false if a descriptor was invalid (the result is then garbage).
-template <int NQ, bool IDENT, typename GateSrc>
-__device__ __forceinline__ bool run_register_path(const float* __restrict__ T, int L,
-                                                  GateSrc&& src, float* U_out, FitOut* fit,
-                                                  int mode = QE_FIT_EQ11) {
-    constexpr int N = 1 << NQ;
-    constexpr int E = N * N / 64;
-    constexpr int EB = 2 * NQ - 6;
-    const int lane = (int)lane_id();
-    const int j = lane & (N - 1);
-    const int lr = lane >> NQ;
-    const uint32_t dv0 = L > 0 ? src(0) : 0u;   // before the target: latencies overlap
-    float re[E], im[E];
-    if (IDENT) {
-#pragma unroll
-        for (int k = 0; k < E; ++k) {
-            re[k] = ((k | (lr << EB)) == j) ? 1.0f : 0.0f;
-            im[k] = 0.0f;
-        }
-    } else {
-        // M_0 = T^dagger: element (i, j) = conj(T[j][i]); this lane's rows are
-        // i = lr*E + k, contiguous in row j of T.
-        const float2* src2 = reinterpret_cast<const float2*>(T) + (size_t)j * N + (size_t)lr * E;
-#pragma unroll
-        for (int k = 0; k < E; ++k) {
-            const float2 v = src2[k];
-            re[k] = v.x;
-            im[k] = -v.y;
-        }
-    }
-    // canonical map: wire w in slot n-1-w
-    SlotMap map;
-    map.w2s = 0; map.s2w = 0;
-#pragma unroll
-    for (int w = 0; w < NQ; ++w) {
-        map.w2s |= (uint32_t)(NQ - 1 - w) << (4 * w);
-        map.s2w |= (uint32_t)w << (4 * (NQ - 1 - w));
-    }
-    bool ok = true;
-    const int chunks = (L + 63) >> 6;
-    for (int ch = 0; ch < chunks; ++ch) {
-        const uint32_t dv = ch == 0 ? dv0 : src(ch);
-        const int cnt = min(64, L - ch * 64);
-        const bool bad = (lane < cnt) && !desc_valid(dv, NQ);
-        if (__ballot(bad)) { ok = false; break; }
-        for (int g = 0; g < cnt; ++g) {
-            const uint32_t d = __builtin_amdgcn_readlane(dv, g);
-            const int kind = d & 15;
-            if (kind == KIND_I) continue;
-            const int t = (d >> 4) & 15;
-            const int st = map.slot(t);
-            if (st != 0) swap_slots<NQ, E, EB>(st, 0, re, im, map);
-            if (kind_controlled(kind)) {
-                const int c = (d >> 8) & 15;
-                const int sc = map.slot(c);
-                if (sc < EB) {
-                    if (sc != EB - 1) swap_slots<NQ, E, EB>(sc, EB - 1, re, im, map);
-                    if (kind == KIND_CNOT) body_x<E, 1>(re, im);
-                    else if (kind == KIND_CV) body_v<E, 1, false>(re, im);
-                    else body_v<E, 1, true>(re, im);
-                } else {
-                    const bool on = (lane >> (NQ + sc - EB)) & 1;
-                    if (on) {
-                        if (kind == KIND_CNOT) body_x<E, 0>(re, im);
-                        else if (kind == KIND_CV) body_v<E, 0, false>(re, im);
-                        else body_v<E, 0, true>(re, im);
-                    }
-                }
-            } else if (kind == KIND_NOT) {
-                body_x<E, 0>(re, im);
-            } else if (kind == KIND_H) {
-                body_h<E>(re, im);
-            } else {
-                body_t<E>(re, im);
-            }
-        }
-    }
-    // back to the canonical map (wire w in slot n-1-w)
-#pragma unroll
-    for (int w = 0; w < NQ; ++w) {
-        const int want = NQ - 1 - w;
-        const int s = map.slot(w);
-        if (s != want) swap_slots<NQ, E, EB>(s, want, re, im, map);
-    }
-    if (U_out) {
-        float2* dst = reinterpret_cast<float2*>(U_out);
-#pragma unroll
-        for (int k = 0; k < E; ++k) {
-            const int i = k | (lr << EB);
-            dst[(size_t)i * N + j] = make_float2(re[k], im[k]);
-        }
-    }
-    if (fit) {
-        const int key = ((j >> EB) == lr) ? (j & (E - 1)) : -1;
-        float off = 0.0f, dre = 0.0f, dim = 0.0f;
-#pragma unroll
-        for (int k = 0; k < E; ++k) {
-            const bool dg = (k == key);
-            const float m2 = re[k] * re[k] + im[k] * im[k];
-            off += dg ? 0.0f : m2;
-            dre = dg ? re[k] : dre;
-            dim = dg ? im[k] : dim;
-        }
-        *fit = finish_fitness(off, dre, dim, key >= 0, N, mode);
-    }
-    return ok;
 }
 
 // ----------------------------------------------------- small widths (n <= 3)
@@ -1323,26 +1029,5 @@ __device__ __forceinline__ float canonical_fitness(const float2* M, const RowMap
 // wavefronts of the canonical reduction per width
 template <int NQ>
 constexpr int reduction_waves() { return NQ == 6 ? 4 : 1; }
-
-template <bool IDENT, typename GateSrc>
-__device__ __forceinline__ bool run_any_width(int n, const float* __restrict__ T, int L,
-                                              GateSrc&& src, float* U_out, FitOut* fit, int mode) {
-    switch (n) {
-        case 1: return run_small_path<1, IDENT>(T, L, src, U_out, fit, mode);
-        case 2: return run_small_path<2, IDENT>(T, L, src, U_out, fit, mode);
-        case 3: return run_small_path<3, IDENT>(T, L, src, U_out, fit, mode);
-        case 4: return run_register_path<4, IDENT>(T, L, src, U_out, fit, mode);
-        case 5: return run_register_path<5, IDENT>(T, L, src, U_out, fit, mode);
-        default: return run_register_path<6, IDENT>(T, L, src, U_out, fit, mode);
-    }
-}
-
-template <int NQ, bool IDENT, typename GateSrc>
-__device__ __forceinline__ bool run_width(int n, const float* __restrict__ T, int L, GateSrc&& src,
-                                          float* U_out, FitOut* fit, int mode = QE_FIT_EQ11) {
-    if constexpr (NQ == 0) return run_any_width<IDENT>(n, T, L, src, U_out, fit, mode);
-    else if constexpr (NQ <= 3) return run_small_path<NQ, IDENT>(T, L, src, U_out, fit, mode);
-    else return run_register_path<NQ, IDENT>(T, L, src, U_out, fit, mode);
-}
 
 }  // namespace qe

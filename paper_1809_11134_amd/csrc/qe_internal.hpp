@@ -19,7 +19,7 @@ struct BatchArgs {
     const void* targets;
     int64_t num_telems;
     int32_t mode;           // QE_FIT_*
-    int32_t mix_w5;         // wavefronts per width-5 circuit in the sorted mixed launch (1 or 2)
+
     const uint32_t* angles; // per-gate angles (u32 turn fractions, parallel to gates) or null
     uint32_t* err;          // device error word (atomicOr of QE_DEVERR_*)
 };

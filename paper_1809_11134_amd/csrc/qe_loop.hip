@@ -14,6 +14,7 @@
 #include "../../include/qe.h"
 #include "qe_eval_core.hpp"
 #include "qe_internal.hpp"
+#include "qe_reg_core.hpp"
 
 #pragma clang fp contract(off)
 
@@ -315,10 +316,15 @@ __device__ void commit_alone(const LoopArgs& a, uint32_t i, uint32_t s, float v,
 // decision of individual k (both run over 0..P-1) and empties its part of the
 // decision mask of the other generation parity.
 // ISING: circuits of the Ising library, whose gates carry angles (read from
-// angles_in, or with SAMPLE decoded and written to angles_out).  With W > 1
-// and SAMPLE only the first wavefront samples; the others take its
+// angles_in, or with SAMPLE decoded and written to angles_out).  W: wavefronts
+// per circuit of the LDS-staged layout, 0 the one-entry-per-lane (n <= 3) or
+// register-resident layout (one wavefront per circuit, four at n = 6).  With
+// several wavefronts and SAMPLE only the first samples; the others take its
 // descriptors from xch (two buffers of 64 entries, by chunk parity, so one
 // barrier per chunk separates a chunk's writes from the next chunk's).
+template <int NQ, int W>
+constexpr int circuit_waves() { return W == 0 ? (NQ == 6 ? 4 : 1) : W; }
+
 template <int NQ, int W, bool SAMPLE, bool ISING>
 __device__ __forceinline__ void eval_circuit(const LoopArgs& a, uint32_t gen, uint32_t ci,
                                              const uint16_t* gates_in, const uint32_t* angles_in,
@@ -326,6 +332,7 @@ __device__ __forceinline__ void eval_circuit(const LoopArgs& a, uint32_t gen, ui
                                              uint32_t* angles_out, float* f_out, bool writer,
                                              bool decide, float2* M, uint4* gt, float (*red)[3],
                                              void* xch = nullptr) {
+    constexpr int WV = circuit_waves<NQ, W>();
     const uint32_t i = ci / (uint32_t)a.P, k = ci % (uint32_t)a.P;
     const int lane = (int)lane_id();
     const int L = a.L;
@@ -396,7 +403,7 @@ __device__ __forceinline__ void eval_circuit(const LoopArgs& a, uint32_t gen, ui
     // the circuit's descriptors, chunk ch (every wavefront of the circuit
     // calls this the same number of times: the chunk loop is uniform)
     auto src = [&](int ch) -> SrcT {
-        if constexpr (SAMPLE && W > 1) {
+        if constexpr (SAMPLE && WV > 1) {
             SrcT* buf = reinterpret_cast<SrcT*>(xch) + (ch & 1) * 64;
             const bool first = threadIdx.x < 64;
             SrcT d{};
@@ -412,10 +419,19 @@ __device__ __forceinline__ void eval_circuit(const LoopArgs& a, uint32_t gen, ui
     };
     float fv;
     bool ok;
-    if constexpr (W == 0) {
+    if constexpr (W == 0 && NQ <= 3) {
         FitOut o;
-        ok = run_width<NQ, false>(NQ, T, L, src, nullptr, &o, a.fit_mode);
+        ok = run_small_path<NQ, false>(T, L, src, nullptr, &o, a.fit_mode);
         fv = o.f;
+    } else if constexpr (W == 0) {
+        float gd, dd;
+        const int wave = WV == 1 ? 0 : (int)(threadIdx.x >> 6);
+        RegMatrix<float, NQ> mat;
+        mat.place(wave);
+        const SrcT dv0 = src(0);
+        mat.load(T);
+        ok = mat.template run<true>(L, src, dv0);
+        fv = mat.fitness(a.fit_mode, &gd, &dd, wave, red);
     } else {
         float gd, dd;
         RowMap map{};
@@ -462,7 +478,7 @@ __device__ __forceinline__ void eval_circuit(const LoopArgs& a, uint32_t gen, ui
         mark_mutation(a, gen, i, k);
 }
 
-template <int NQ, int W, bool SAMPLE, bool ISING = false, int CPB = (W == 1 ? 4 : 1)>
+template <int NQ, int W, bool SAMPLE, bool ISING = false, int CPB = (circuit_waves<NQ, W>() == 1 ? 4 : 1)>
 __global__ __launch_bounds__(256) void population_kernel(LoopArgs a, uint64_t gen64,
                                                          const uint16_t* __restrict__ gates_in,
                                                          const uint32_t* __restrict__ angles_in,
@@ -473,12 +489,19 @@ __global__ __launch_bounds__(256) void population_kernel(LoopArgs a, uint64_t ge
     const uint32_t gen = gen_of(a, gen64);
     const uint32_t total = (uint32_t)a.I * (uint32_t)a.P;
     const uint32_t bid = xcd_swizzle(blockIdx.x, gridDim.x);
+    const int wave = (int)(threadIdx.x >> 6);
     if constexpr (W == 0) {
-        static_assert(!ISING || NQ <= 3, "Ising circuits of 4 or more wires take the LDS-staged path");
-        const uint32_t ci = __builtin_amdgcn_readfirstlane(bid * 4 + (threadIdx.x >> 6));
+        // CPB circuits per workgroup, one per wavefront; n = 6: one per
+        // workgroup of four
+        constexpr int WV = circuit_waves<NQ, W>();
+        static_assert(WV == 1 || CPB == 1, "one circuit per workgroup of several wavefronts");
+        __shared__ float red[4][3];
+        __shared__ uint2 xch[WV > 1 ? 128 : 1];
+        const uint32_t ci = __builtin_amdgcn_readfirstlane(WV == 1 ? bid * CPB + (uint32_t)wave : bid);
         if (ci >= total) return;
         eval_circuit<NQ, 0, SAMPLE, ISING>(a, gen, ci, gates_in, angles_in, slots_out, gates_out,
-                                           angles_out, f_out, true, decide, nullptr, nullptr, nullptr);
+                                           angles_out, f_out, WV == 1 || threadIdx.x < 64, decide, nullptr,
+                                           nullptr, red, WV == 1 ? nullptr : static_cast<void*>(xch));
     } else {
         // W = 1: CPB circuits per workgroup, one per wavefront (no barrier
         // is shared, so a wavefront past the end may leave); W > 1: one
@@ -488,7 +511,6 @@ __global__ __launch_bounds__(256) void population_kernel(LoopArgs a, uint64_t ge
         __shared__ __align__(16) float2 M[CPB][N * N];
         __shared__ uint4 GT[W == 1 ? CPB : W][ISING ? GATE_TABLE_ANGLED : GATE_TABLE];
         __shared__ float red[4][3];
-        const int wave = (int)(threadIdx.x >> 6);
         const uint32_t ci = W == 1 ? bid * CPB + (uint32_t)wave : bid;
         if (ci >= total) return;
         // (W > 1: the gate tables are unused, the first one is the
@@ -1484,55 +1506,48 @@ static void launch_population(const LoopArgs& a, uint64_t gen, const uint16_t* g
                               uint32_t* sout, uint16_t* gout, uint32_t* aout, float* f, hipStream_t s,
                               bool decide = false) {
     const uint32_t total = (uint32_t)a.I * (uint32_t)a.P;
-    const unsigned wb = blocks(total, 4);
     const Sched sc = schedule_for(a.n, a.L, a.lib == LIB_ISING ? SCHED_ISING : (SAMPLE ? SCHED_SAMPLED : SCHED_DISCRETE));
-    // the LDS-staged kernels of widths 4 and 5 under the schedule (waves per
-    // circuit; circuits per workgroup with one wavefront per circuit)
-    auto lds45 = [&](auto nq, auto ising) {
-        constexpr int NQ = decltype(nq)::value;
-        constexpr bool IS = decltype(ising)::value;
-        if constexpr (NQ == 5) {
-            if (sc.waves == 2) {
-                population_kernel<NQ, 2, SAMPLE, IS><<<total, 128, 0, s>>>(a, gen, gin, ain, sout, gout, aout, f, decide);
+    auto go = [&](auto nq, auto w, auto cpb, auto ising) {
+        constexpr int NQ = decltype(nq)::value, W = decltype(w)::value, CPB = decltype(cpb)::value;
+        constexpr int WV = circuit_waves<NQ, W>();
+        population_kernel<NQ, W, SAMPLE, decltype(ising)::value, CPB>
+            <<<blocks(total, CPB), 64 * WV * CPB, 0, s>>>(a, gen, gin, ain, sout, gout, aout, f, decide);
+    };
+    using std::integral_constant;
+    auto width = [&](auto ising) {
+        const integral_constant<int, 0> c0{};
+        const integral_constant<int, 1> c1{};
+        const integral_constant<int, 4> c4{};
+        // widths 4 and 5: register-resident or LDS-staged, circuits per workgroup
+        auto w45 = [&](auto nq) {
+            if (!sc.lds) {
+                if (sc.cpb == 1) go(nq, c0, c1, ising);
+                else go(nq, c0, c4, ising);
                 return;
             }
+            if constexpr (decltype(nq)::value == 5) {
+                if (sc.waves == 2) {
+                    go(nq, integral_constant<int, 2>{}, c1, ising);
+                    return;
+                }
+            }
+            if (sc.cpb == 1) go(nq, c1, c1, ising);
+            else go(nq, c1, c4, ising);
+        };
+        switch (a.n) {
+            case 1: go(integral_constant<int, 1>{}, c0, c4, ising); break;
+            case 2: go(integral_constant<int, 2>{}, c0, c4, ising); break;
+            case 3: go(integral_constant<int, 3>{}, c0, c4, ising); break;
+            case 4: w45(integral_constant<int, 4>{}); break;
+            case 5: w45(integral_constant<int, 5>{}); break;
+            default:
+                if (sc.lds) go(integral_constant<int, 6>{}, c4, c1, ising);
+                else go(integral_constant<int, 6>{}, c0, c1, ising);
+                break;
         }
-        if (sc.cpb == 1)
-            population_kernel<NQ, 1, SAMPLE, IS, 1><<<total, 64, 0, s>>>(a, gen, gin, ain, sout, gout, aout, f, decide);
-        else
-            population_kernel<NQ, 1, SAMPLE, IS, 4><<<wb, 256, 0, s>>>(a, gen, gin, ain, sout, gout, aout, f, decide);
     };
-    using I4 = std::integral_constant<int, 4>;
-    using I5 = std::integral_constant<int, 5>;
-    using T_ = std::true_type;
-    using F_ = std::false_type;
-    if (a.lib == LIB_ISING) {
-        // one wavefront per circuit below 4 wires, the LDS-staged layout above
-        switch (a.n) {
-            case 2: population_kernel<2, 0, SAMPLE, true><<<wb, 256, 0, s>>>(a, gen, gin, ain, sout, gout, aout, f, decide); break;
-            case 3: population_kernel<3, 0, SAMPLE, true><<<wb, 256, 0, s>>>(a, gen, gin, ain, sout, gout, aout, f, decide); break;
-            case 4: lds45(I4{}, T_{}); break;
-            case 5: lds45(I5{}, T_{}); break;
-            default: population_kernel<6, 4, SAMPLE, true><<<total, 256, 0, s>>>(a, gen, gin, ain, sout, gout, aout, f, decide); break;
-        }
-        return;
-    }
-    if (sc.lds && a.n >= 4) {
-        switch (a.n) {
-            case 4: lds45(I4{}, F_{}); break;
-            case 5: lds45(I5{}, F_{}); break;
-            default: population_kernel<6, 4, SAMPLE><<<total, 256, 0, s>>>(a, gen, gin, ain, sout, gout, aout, f, decide); break;
-        }
-        return;
-    }
-    switch (a.n) {
-        case 1: population_kernel<1, 0, SAMPLE><<<wb, 256, 0, s>>>(a, gen, gin, ain, sout, gout, aout, f, decide); break;
-        case 2: population_kernel<2, 0, SAMPLE><<<wb, 256, 0, s>>>(a, gen, gin, ain, sout, gout, aout, f, decide); break;
-        case 3: population_kernel<3, 0, SAMPLE><<<wb, 256, 0, s>>>(a, gen, gin, ain, sout, gout, aout, f, decide); break;
-        case 4: population_kernel<4, 0, SAMPLE><<<wb, 256, 0, s>>>(a, gen, gin, ain, sout, gout, aout, f, decide); break;
-        case 5: population_kernel<5, 0, SAMPLE><<<wb, 256, 0, s>>>(a, gen, gin, ain, sout, gout, aout, f, decide); break;
-        default: population_kernel<6, 0, SAMPLE><<<wb, 256, 0, s>>>(a, gen, gin, ain, sout, gout, aout, f, decide); break;
-    }
+    if (a.lib == LIB_ISING) width(std::true_type{});
+    else width(std::false_type{});
 }
 
 hipError_t launch_eval_population(const LoopArgs& a, const uint16_t* gates, const uint32_t* angles,

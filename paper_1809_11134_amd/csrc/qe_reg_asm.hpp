@@ -1,0 +1,401 @@
+// Gate loop of the register-resident core (qe_reg_core.hpp), in assembly.
+//
+// One block runs a chunk of gates on a matrix held in a fixed run of VGPRs
+// (element k: real part, then imaginary part).  A gate's word gives its table
+// and its wires; the wires' slots pick the table's entry, which leads to a
+// body that updates the registers in place and returns to the loop.  Written
+// in C++ the same bodies under a dispatch cost 16 to 50 register moves per gate
+// (the compiler turns the dispatch into a chain of merges and copies what a
+// body swapped at each) and a tree of compares; here a gate costs its
+// arithmetic, about 20 scalar instructions and three branches.
+//
+// Tables of 16 entries (target 4 t, control c; t = c: a single-wire gate):
+//   0 CV, H   1 CV+, T   2 CNOT, NOT   3 interaction, R_x   4 R_y   5 R_z
+// and, with 16 registers per lane, the exchanges of register bits 0..3 and
+// lane slots 4, 5 (row: the higher, column: the lower, always a register
+// bit).  Entries that nothing has lead to the block's end.
+//
+// 16 registers (widths 5, 6): a wire is in any slot (maps W: wire to slot, S:
+// slot to wire, 4 bits each).  A gate whose wire is in a lane slot first
+// exchanges that slot with a register bit, by choice one that the next gate
+// does not use.  4 registers (width 4): every wire keeps its slot (entries 0,
+// 1: register bits, 2, 3: lane slots); a body brings a lane slot into the
+// registers and back itself (4 exchanges each way), which costs less than
+// keeping the maps: with 4 registers one gate in one needs an exchange.
+//
+// Multiplies and adds stay separate (one rounding each) except in CV, whose
+// last step is a fused multiply-add of exact halves.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace qe {
+
+// The lane's registers: element k is values 2k and 2k + 1.  (An asm operand
+// holds at most 32 VGPRs, so 32 doubles are two.)
+typedef float f32x32 __attribute__((ext_vector_type(32)));
+typedef float f32x8 __attribute__((ext_vector_type(8)));
+typedef double f64x16 __attribute__((ext_vector_type(16)));
+typedef double f64x8 __attribute__((ext_vector_type(8)));
+struct f64x32 {
+    f64x16 lo, hi;
+};
+template <typename V>
+__device__ __forceinline__ auto reg_get(const V& x, int i) { return x[i]; }
+__device__ __forceinline__ double reg_get(const f64x32& x, int i) { return i < 16 ? x.lo[i] : x.hi[i - 16]; }
+template <typename V, typename R>
+__device__ __forceinline__ void reg_set(V& x, int i, R v) { x[i] = v; }
+__device__ __forceinline__ void reg_set(f64x32& x, int i, double v) {
+    if (i < 16) x.lo[i] = v;
+    else x.hi[i - 16] = v;
+}
+
+// Wave-uniform maps between wires and slots, 4 bits per entry: register bit k is
+// slot k, lane slot s slot 4 + s.
+struct SlotMap {
+    uint32_t w2s, s2w;
+};
+
+// ------------------------------------------------------------ assembler text
+// Registers of element k (x real, y imaginary part), the temporaries and the
+// gate's scalars, then the arithmetic, per precision.
+#define QR_X32(k) "v[QRB+2*(" k ")]"
+#define QR_Y32(k) "v[QRB+2*(" k ")+1]"
+#define QR_T32(i) "v[QRT+" #i "]"
+#define QR_A32 "s60"
+#define QR_B32 "s62"
+#define QR_ADD32(d, a, b) "v_add_f32 " d "," a "," b "\n"
+#define QR_SUB32(d, a, b) "v_sub_f32 " d "," a "," b "\n"
+#define QR_MUL32(d, a, b) "v_mul_f32 " d "," a "," b "\n"
+#define QR_FMA32(d, a, b, c) "v_fma_f32 " d "," a "," b "," c "\n"
+#define QR_FMAC32(d, a, b) "v_fmac_f32 " d "," a "," b "\n"
+#define QR_XCH32(ins, k, l)                                                                          \
+    ins " v[QRB+2*(" k ")],v[QRB+2*(" l ")]\n" ins " v[QRB+2*(" k ")+1],v[QRB+2*(" l ")+1]\n"
+// 1 / sqrt 2, for H and T
+#define QR_CONST32 "s_mov_b32 s60,0x3f3504f3\n"
+#define QR_ANGLE32 "v_readlane_b32 s60,%[gc],s42\nv_readlane_b32 s62,%[gs],s42\n"
+
+#define QR_X64(k) "v[QRB+4*(" k "):QRB+4*(" k ")+1]"
+#define QR_Y64(k) "v[QRB+4*(" k ")+2:QRB+4*(" k ")+3]"
+#define QR_T64(i) "v[QRT+2*" #i ":QRT+2*" #i "+1]"
+#define QR_A64 "s[60:61]"
+#define QR_B64 "s[62:63]"
+#define QR_ADD64(d, a, b) "v_add_f64 " d "," a "," b "\n"
+#define QR_SUB64(d, a, b) "v_add_f64 " d "," a ",-" b "\n"
+#define QR_MUL64(d, a, b) "v_mul_f64 " d "," a "," b "\n"
+#define QR_FMA64(d, a, b, c) "v_fma_f64 " d "," a "," b "," c "\n"
+#define QR_FMAC64(d, a, b) "v_fmac_f64 " d "," a "," b "\n"
+#define QR_XCH64(ins, k, l)                                                                          \
+    ins " v[QRB+4*(" k ")],v[QRB+4*(" l ")]\n" ins " v[QRB+4*(" k ")+1],v[QRB+4*(" l ")+1]\n"        \
+    ins " v[QRB+4*(" k ")+2],v[QRB+4*(" l ")+2]\n" ins " v[QRB+4*(" k ")+3],v[QRB+4*(" l ")+3]\n"
+#define QR_CONST64 "s_mov_b32 s60,0x667f3bcd\ns_mov_b32 s61,0x3fe6a09e\n"
+#define QR_ANGLE64                                                                                   \
+    "v_readlane_b32 s60,%[gcl],s42\nv_readlane_b32 s61,%[gch],s42\n"                                 \
+    "v_readlane_b32 s62,%[gsl],s42\nv_readlane_b32 s63,%[gsh],s42\n"
+
+#define QR_ELEMS16 "0,1,2,3,4,5,6,7,8,9,10,11,12,13,14,15"
+#define QR_ELEMS4 "0,1,2,3"
+
+// The rows a of a gate whose target and control are register bits QT, QC, and
+// their partners.
+#define QR_A "\\a"
+#define QR_P "\\a+(1<<QT)"
+#define QR_ROWS(E, cond, text) ".irp a," QR_ELEMS##E "\n.if " cond "\n" text ".endif\n.endr\n"
+#define QR_ROWS1(E, text) QR_ROWS(E, "((\\a>>QT)&1)==0", text)
+#define QR_ROWS2(E, text) QR_ROWS(E, "(((\\a>>QT)&1)==0)&(((\\a>>QC)&1)==1)", text)
+
+// u + iv = a - b, p + iq = (a + b) / 2: a' = p - hs v + i (q + hs u), b' = p + hs v
+// + i (q - hs u); HP = hs, HM = -hs
+#define QR_CV(P, E, HP, HM)                                                                          \
+    QR_ROWS2(E, QR_SUB##P(QR_T##P(0), QR_X##P(QR_A), QR_X##P(QR_P))                                  \
+                QR_SUB##P(QR_T##P(1), QR_Y##P(QR_A), QR_Y##P(QR_P))                                  \
+                QR_ADD##P(QR_X##P(QR_A), QR_X##P(QR_A), QR_X##P(QR_P))                               \
+                QR_ADD##P(QR_Y##P(QR_A), QR_Y##P(QR_A), QR_Y##P(QR_P))                               \
+                QR_MUL##P(QR_X##P(QR_P), "0.5", QR_X##P(QR_A))                                       \
+                QR_MUL##P(QR_Y##P(QR_P), "0.5", QR_Y##P(QR_A))                                       \
+                QR_FMA##P(QR_X##P(QR_A), HM, QR_T##P(1), QR_X##P(QR_P))                              \
+                QR_FMA##P(QR_Y##P(QR_A), HP, QR_T##P(0), QR_Y##P(QR_P))                              \
+                QR_FMAC##P(QR_X##P(QR_P), HP, QR_T##P(1))                                            \
+                QR_FMAC##P(QR_Y##P(QR_P), HM, QR_T##P(0)))
+#define QR_CNOT(P, E) QR_ROWS2(E, QR_XCH##P("v_swap_b32", QR_A, QR_P))
+#define QR_NOT(P, E) QR_ROWS1(E, QR_XCH##P("v_swap_b32", QR_A, QR_P))
+#define QR_H(P, E)                                                                                   \
+    QR_ROWS1(E, QR_SUB##P(QR_T##P(0), QR_X##P(QR_A), QR_X##P(QR_P))                                  \
+                QR_SUB##P(QR_T##P(1), QR_Y##P(QR_A), QR_Y##P(QR_P))                                  \
+                QR_ADD##P(QR_X##P(QR_A), QR_X##P(QR_A), QR_X##P(QR_P))                               \
+                QR_ADD##P(QR_Y##P(QR_A), QR_Y##P(QR_A), QR_Y##P(QR_P))                               \
+                QR_MUL##P(QR_X##P(QR_A), QR_A##P, QR_X##P(QR_A))                                     \
+                QR_MUL##P(QR_Y##P(QR_A), QR_A##P, QR_Y##P(QR_A))                                     \
+                QR_MUL##P(QR_X##P(QR_P), QR_A##P, QR_T##P(0))                                        \
+                QR_MUL##P(QR_Y##P(QR_P), QR_A##P, QR_T##P(1)))
+#define QR_TG(P, E)                                                                                  \
+    QR_ROWS1(E, QR_SUB##P(QR_T##P(0), QR_X##P(QR_P), QR_Y##P(QR_P))                                  \
+                QR_ADD##P(QR_Y##P(QR_P), QR_X##P(QR_P), QR_Y##P(QR_P))                               \
+                QR_MUL##P(QR_X##P(QR_P), QR_A##P, QR_T##P(0))                                        \
+                QR_MUL##P(QR_Y##P(QR_P), QR_A##P, QR_Y##P(QR_P)))
+// rotations, A + iB = e^{i theta/2}: temporaries B times the four parts, then
+// the parts scaled by A
+#define QR_ROT(P, E, t0, t1, t2, t3, rest)                                                           \
+    QR_ROWS1(E, QR_MUL##P(QR_T##P(0), QR_B##P, t0) QR_MUL##P(QR_T##P(1), QR_B##P, t1)                \
+                QR_MUL##P(QR_T##P(2), QR_B##P, t2) QR_MUL##P(QR_T##P(3), QR_B##P, t3)                \
+                QR_MUL##P(QR_X##P(QR_A), QR_A##P, QR_X##P(QR_A))                                     \
+                QR_MUL##P(QR_Y##P(QR_A), QR_A##P, QR_Y##P(QR_A))                                     \
+                QR_MUL##P(QR_X##P(QR_P), QR_A##P, QR_X##P(QR_P))                                     \
+                QR_MUL##P(QR_Y##P(QR_P), QR_A##P, QR_Y##P(QR_P)) rest)
+// a' = c a - i s b, b' = c b - i s a
+#define QR_RX(P, E)                                                                                  \
+    QR_ROT(P, E, QR_Y##P(QR_P), QR_X##P(QR_P), QR_Y##P(QR_A), QR_X##P(QR_A),                         \
+           QR_ADD##P(QR_X##P(QR_A), QR_X##P(QR_A), QR_T##P(0))                                       \
+           QR_SUB##P(QR_Y##P(QR_A), QR_Y##P(QR_A), QR_T##P(1))                                       \
+           QR_ADD##P(QR_X##P(QR_P), QR_X##P(QR_P), QR_T##P(2))                                       \
+           QR_SUB##P(QR_Y##P(QR_P), QR_Y##P(QR_P), QR_T##P(3)))
+// a' = c a - s b, b' = s a + c b
+#define QR_RY(P, E)                                                                                  \
+    QR_ROT(P, E, QR_X##P(QR_P), QR_Y##P(QR_P), QR_X##P(QR_A), QR_Y##P(QR_A),                         \
+           QR_SUB##P(QR_X##P(QR_A), QR_X##P(QR_A), QR_T##P(0))                                       \
+           QR_SUB##P(QR_Y##P(QR_A), QR_Y##P(QR_A), QR_T##P(1))                                       \
+           QR_ADD##P(QR_X##P(QR_P), QR_T##P(2), QR_X##P(QR_P))                                       \
+           QR_ADD##P(QR_Y##P(QR_P), QR_T##P(3), QR_Y##P(QR_P)))
+// a' = (c - i s) a, b' = (c + i s) b
+#define QR_RZ(P, E)                                                                                  \
+    QR_ROT(P, E, QR_Y##P(QR_A), QR_X##P(QR_A), QR_Y##P(QR_P), QR_X##P(QR_P),                         \
+           QR_ADD##P(QR_X##P(QR_A), QR_X##P(QR_A), QR_T##P(0))                                       \
+           QR_SUB##P(QR_Y##P(QR_A), QR_Y##P(QR_A), QR_T##P(1))                                       \
+           QR_SUB##P(QR_X##P(QR_P), QR_X##P(QR_P), QR_T##P(2))                                       \
+           QR_ADD##P(QR_Y##P(QR_P), QR_Y##P(QR_P), QR_T##P(3)))
+// e^{-i theta/2} where the two wires' bits agree, e^{i theta/2} where they differ
+#define QR_ZZ(P, E)                                                                                  \
+    ".irp a," QR_ELEMS##E "\n"                                                                       \
+    QR_MUL##P(QR_T##P(0), QR_B##P, QR_Y##P(QR_A)) QR_MUL##P(QR_T##P(1), QR_B##P, QR_X##P(QR_A))      \
+    QR_MUL##P(QR_X##P(QR_A), QR_A##P, QR_X##P(QR_A)) QR_MUL##P(QR_Y##P(QR_A), QR_A##P, QR_Y##P(QR_A)) \
+    ".if ((\\a>>QT)&1)==((\\a>>QC)&1)\n"                                                             \
+    QR_ADD##P(QR_X##P(QR_A), QR_X##P(QR_A), QR_T##P(0))                                              \
+    QR_SUB##P(QR_Y##P(QR_A), QR_Y##P(QR_A), QR_T##P(1))                                              \
+    ".else\n"                                                                                        \
+    QR_SUB##P(QR_X##P(QR_A), QR_X##P(QR_A), QR_T##P(0))                                              \
+    QR_ADD##P(QR_Y##P(QR_A), QR_Y##P(QR_A), QR_T##P(1))                                              \
+    ".endif\n.endr\n"
+
+// Lane slot S with register bit K.  v_permlane*_swap reads a register two wait
+// states or more after the VALU wrote it, hence the s_nop.
+#define QR_SWAPS(P, E, SW, K) QR_ROWS(E, "((\\a>>(" K "))&1)==0", QR_XCH##P(SW, QR_A, "\\a+(1<<(" K "))"))
+#define QR_LANE2(P, E, S, K)                                                                         \
+    "s_nop 1\n.if (" S ")==0\n" QR_SWAPS(P, E, "v_permlane16_swap_b32", K) ".else\n"                 \
+    QR_SWAPS(P, E, "v_permlane32_swap_b32", K) ".endif\n"
+#define QR_LANE1(P, E, S, K) "s_nop 1\n" QR_SWAPS(P, E, "v_permlane32_swap_b32", K)
+
+#define QR_BODY(name, list, text) ".irp n," list "\n.Lqr%=" name "\\n:\n" text "s_branch .Lqr%=l\n.endr\n"
+#define QR_TWO16 "1,2,3,4,6,7,8,9,11,12,13,14"
+#define QR_ONE16 "0,5,10,15"
+#define QR_SETTC ".set QT,\\n>>2\n.set QC,\\n&3\n"
+// widths 5, 6: target and control are register bits
+#define QR_TWO_16(P, LS, name, text) QR_BODY(name, QR_TWO16, QR_SETTC text)
+#define QR_ONE_16(P, LS, name, text) QR_BODY(name, QR_ONE16, QR_SETTC text)
+// width 4: slots 2, 3 are lane slots, exchanged with a register bit around the
+// body
+#define QR_AROUND4(P, text)                                                                          \
+    ".set QT,\\n>>2\n.set QC,\\n&3\n.set QS0,-1\n.set QS1,-1\n"                                      \
+    ".if (QT>1)&(QC<2)\n.set QS0,QT-2\n.set QK0,1-QC\n.set QT,QK0\n.endif\n"                         \
+    ".if (QT<2)&(QC>1)\n.set QS0,QC-2\n.set QK0,1-QT\n.set QC,QK0\n.endif\n"                         \
+    ".if (QT>1)&(QC>1)\n.set QS0,QT-2\n.set QK0,0\n.if QT!=QC\n.set QS1,QC-2\n.endif\n"              \
+    ".set QT,0\n.set QC,1\n.endif\n"                                                                 \
+    ".if QS0>=0\n" QR_LANE2(P, 4, "QS0", "QK0") ".endif\n"                                           \
+    ".if QS1>=0\n" QR_LANE2(P, 4, "QS1", "1") ".endif\n" text                                        \
+    ".if QS1>=0\n" QR_LANE2(P, 4, "QS1", "1") ".endif\n"                                             \
+    ".if QS0>=0\n" QR_LANE2(P, 4, "QS0", "QK0") ".endif\n"
+#define QR_TWO_4(P, LS, name, text) QR_BODY(name, QR_TWO16, QR_AROUND4(P, text))
+#define QR_ONE_4(P, LS, name, text) QR_BODY(name, QR_ONE16, QR_AROUND4(P, text))
+
+#define QR_TAB(two, one)                                                                             \
+    ".irp n," QR_ELEMS16 "\n.if (\\n>>2)==(\\n&3)\ns_branch .Lqr%=" one "\\n\n.else\n"               \
+    "s_branch .Lqr%=" two "\\n\n.endif\n.endr\n"
+#define QR_TAB1(one)                                                                                 \
+    ".irp n," QR_ELEMS16 "\n.if (\\n>>2)==(\\n&3)\ns_branch .Lqr%=" one "\\n\n.else\n"               \
+    "s_branch .Lqr%=e\n.endif\n.endr\n"
+#define QR_TABLES0 QR_TAB("cv", "h") QR_TAB("cd", "t") QR_TAB("cx", "x")
+#define QR_TABLES1 QR_TABLES0 QR_TAB("zz", "rx") QR_TAB1("ry") QR_TAB1("rz")
+#define QR_BODIES0(P, E, LS)                                                                         \
+    QR_TWO_##E(P, LS, "cv", QR_CV(P, E, "0.5", "-0.5"))                                              \
+    QR_TWO_##E(P, LS, "cd", QR_CV(P, E, "-0.5", "0.5"))                                              \
+    QR_TWO_##E(P, LS, "cx", QR_CNOT(P, E)) QR_ONE_##E(P, LS, "h", QR_H(P, E))                        \
+    QR_ONE_##E(P, LS, "t", QR_TG(P, E)) QR_ONE_##E(P, LS, "x", QR_NOT(P, E))
+#define QR_BODIES1(P, E, LS)                                                                         \
+    QR_BODIES0(P, E, LS) QR_TWO_##E(P, LS, "zz", QR_ZZ(P, E)) QR_ONE_##E(P, LS, "rx", QR_RX(P, E))   \
+    QR_ONE_##E(P, LS, "ry", QR_RY(P, E)) QR_ONE_##E(P, LS, "rz", QR_RZ(P, E))
+#define QR_SCALARS0(P)
+#define QR_SCALARS1(P) QR_ANGLE##P
+#define QR_START0(P) QR_CONST##P
+#define QR_START1(P)
+
+// s[40:41] the tables' address, s42 the next gate's lane, s43 its word
+#define QR_HEAD(P, BASE, TMP, ANG)                                                                   \
+    ".set QRB," BASE "\n.set QRT," TMP "\n"                                                          \
+    "s_getpc_b64 s[40:41]\n.Lqr%=p:\ns_add_u32 s40,s40,.Lqr%=tab-.Lqr%=p\ns_addc_u32 s41,s41,0\n"    \
+    "s_mov_b32 s42,0\n" QR_START##ANG(P) "v_readlane_b32 s43,%[p],s42\n"
+
+// Widths 4: the word is the gate's entry (bytes).
+#define QR_TEXT4(P, BASE, TMP, ANG)                                                                  \
+    QR_HEAD(P, BASE, TMP, ANG)                                                                       \
+    ".Lqr%=l:\n"                                                                                     \
+    "s_cmp_ge_u32 s42,%[cnt]\ns_cbranch_scc1 .Lqr%=e\n"                                              \
+    "s_add_u32 s48,s40,s43\ns_addc_u32 s49,s41,0\n" QR_SCALARS##ANG(P)                               \
+    "s_add_u32 s42,s42,1\n"                                                                          \
+    "v_readlane_b32 s43,%[p],s42\n"                                                                  \
+    "s_setpc_b64 s[48:49]\n"                                                                         \
+    ".Lqr%=tab:\n" QR_TABLES##ANG QR_BODIES##ANG(P, 4, 2)                                            \
+    ".Lqr%=e:\n"
+
+// Widths 5, 6: the word is 4 * target wire, 4 * control wire (target again for a
+// single-wire gate) in bits 8.., the table (bytes) in bits 16...
+#define QR_WANT(slot, wire, label)                                                                   \
+    "s_bfe_u32 s47,%[W],0x40000+4*" wire "\ns_cmp_eq_u32 s47," slot "\ns_cbranch_scc1 " label "\n"
+#define QR_CALL(label)                                                                               \
+    "s_getpc_b64 s[58:59]\n.Lqr%=p" label ":\ns_add_u32 s58,s58,.Lqr%=" label "-.Lqr%=p" label "\n"  \
+    "s_addc_u32 s59,s59,0\ns_branch .Lqr%=x\n.Lqr%=" label ":\n"
+// canonical order: the lane slots, then register bits 0..2; L0, L1: the wires of
+// lane slots 4, 5, R0..R2: those of register bits 0..2
+#define QR_LANE_BACK2(L0, L1)                                                                        \
+    QR_WANT("4", L0, ".Lqr%=r1")                                                                     \
+    /* (from the other lane slot by way of register bit 0) */                                        \
+    "s_mov_b32 s50,s47\ns_cmp_lt_u32 s47,4\ns_cbranch_scc1 .Lqr%=r0\n"                               \
+    "s_mov_b32 s50,0\n" QR_CALL("c0") "s_mov_b32 s50,0\n"                                            \
+    ".Lqr%=r0:\ns_mov_b32 s47,4\n" QR_CALL("c1") ".Lqr%=r1:\n"                                       \
+    QR_WANT("5", L1, ".Lqr%=r2") "s_mov_b32 s50,s47\ns_mov_b32 s47,5\n" QR_CALL("c2") ".Lqr%=r2:\n"
+#define QR_LANE_BACK1(L0, L1)                                                                        \
+    QR_WANT("4", L0, ".Lqr%=r2") "s_mov_b32 s50,s47\ns_mov_b32 s47,4\n" QR_CALL("c2") ".Lqr%=r2:\n"
+#define QR_TEXT16(P, BASE, TMP, LS, ANG, L0, L1, R0, R1, R2)                                         \
+    QR_HEAD(P, BASE, TMP, ANG)                                                                       \
+    "s_getpc_b64 s[58:59]\n.Lqr%=q:\ns_add_u32 s58,s58,.Lqr%=g-.Lqr%=q\ns_addc_u32 s59,s59,0\n"      \
+    ".Lqr%=l:\n"                                                                                     \
+    "s_cmp_ge_u32 s42,%[cnt]\ns_cbranch_scc1 .Lqr%=b\n"                                              \
+    "s_mov_b32 s44,s43\n" QR_SCALARS##ANG(P)                                                         \
+    "s_add_u32 s42,s42,1\n"                                                                          \
+    "v_readlane_b32 s43,%[p],s42\n" /* (past the last gate it only steers a choice) */               \
+    ".Lqr%=g:\n"                                                                                     \
+    "s_lshr_b32 s47,s44,8\ns_lshr_b32 s45,%[W],s44\ns_lshr_b32 s46,%[W],s47\n"                       \
+    "s_and_b32 s45,s45,15\ns_and_b32 s46,s46,15\ns_or_b32 s47,s45,s46\n"                             \
+    "s_cmp_gt_u32 s47,3\ns_cbranch_scc1 .Lqr%=s\n"                                                   \
+    "s_lshr_b32 s47,s44,16\ns_lshl2_add_u32 s47,s46,s47\ns_lshl4_add_u32 s47,s45,s47\n"              \
+    "s_add_u32 s48,s40,s47\ns_addc_u32 s49,s41,0\ns_setpc_b64 s[48:49]\n"                            \
+    /* a wire of the gate in lane slot s47: the register bit s50 it goes to is not the gate's */     \
+    /* other wire's nor, if it can be, the next gate's */                                            \
+    ".Lqr%=s:\n"                                                                                     \
+    "s_cmp_gt_u32 s45,3\ns_cselect_b32 s47,s45,s46\n"                                                \
+    "s_mov_b32 s50,0\ns_bitset1_b32 s50,s45\ns_bitset1_b32 s50,s46\n"                                \
+    "s_lshr_b32 s52,s43,8\ns_lshr_b32 s51,%[W],s43\ns_lshr_b32 s52,%[W],s52\n"                       \
+    "s_and_b32 s51,s51,15\ns_and_b32 s52,s52,15\n"                                                   \
+    "s_mov_b32 s53,s50\ns_bitset1_b32 s53,s51\ns_bitset1_b32 s53,s52\n"                              \
+    "s_andn2_b32 s53,15,s53\ns_cselect_b32 s51,s53,0\ns_andn2_b32 s50,15,s50\n"                      \
+    "s_cmp_eq_u32 s51,0\ns_cselect_b32 s50,s50,s51\ns_ff1_i32_b32 s50,s50\n"                         \
+    /* slots s47 and s50 change wires, in the maps and in the registers; then to s[58:59] */         \
+    ".Lqr%=x:\n"                                                                                     \
+    "s_lshl_b32 s51,s50,2\ns_lshl_b32 s52,s47,2\ns_lshr_b32 s53,%[S],s51\ns_lshr_b32 s54,%[S],s52\n" \
+    "s_and_b32 s53,s53,15\ns_and_b32 s54,s54,15\ns_xor_b32 s55,s53,s54\n"                            \
+    "s_lshl_b32 s51,s55,s51\ns_lshl_b32 s52,s55,s52\ns_xor_b32 %[S],%[S],s51\ns_xor_b32 %[S],%[S],s52\n" \
+    "s_lshl_b32 s53,s53,2\ns_lshl_b32 s54,s54,2\ns_xor_b32 s55,s50,s47\n"                            \
+    "s_lshl_b32 s53,s55,s53\ns_lshl_b32 s54,s55,s54\ns_xor_b32 %[W],%[W],s53\ns_xor_b32 %[W],%[W],s54\n" \
+    "s_lshl2_add_u32 s51,s50,.Lqr%=xt-.Lqr%=tab\ns_lshl4_add_u32 s51,s47,s51\n"                      \
+    "s_add_u32 s48,s40,s51\ns_addc_u32 s49,s41,0\ns_setpc_b64 s[48:49]\n"                            \
+    ".Lqr%=tab:\n" QR_TABLES##ANG                                                                    \
+    ".Lqr%=xt:\n.irp n,0,1,2,3,4,5,6,7,8,9,10,11,12,13,14,15,16,17,18,19,20,21,22,23\n"              \
+    ".if ((\\n>>2)>(\\n&3))&((\\n>>2)<4+" #LS ")\ns_branch .Lqr%=v\\n\n.else\ns_branch .Lqr%=e\n.endif\n.endr\n" \
+    QR_BODIES##ANG(P, 16, LS)                                                                        \
+    ".irp n,4,8,9,12,13,14\n.Lqr%=v\\n:\n"                                                           \
+    QR_ROWS(16, "(((\\a>>(\\n>>2))&1)==0)&(((\\a>>(\\n&3))&1)==1)",                                  \
+            QR_XCH##P("v_swap_b32", QR_A, "\\a+(1<<(\\n>>2))-(1<<(\\n&3))"))                         \
+    "s_setpc_b64 s[58:59]\n.endr\n"                                                                  \
+    ".irp n,16,17,18,19,20,21,22,23\n.if (\\n>>2)<4+" #LS "\n.Lqr%=v\\n:\n"                          \
+    QR_LANE##LS(P, 16, "(\\n>>2)-4", "\\n&3") "s_setpc_b64 s[58:59]\n.endif\n.endr\n"                \
+    /* after the last gate */                                                                        \
+    ".Lqr%=b:\ns_cmp_eq_u32 %[restore],0\ns_cbranch_scc1 .Lqr%=e\n" QR_LANE_BACK##LS(L0, L1)         \
+    QR_WANT("0", R0, ".Lqr%=r3") "s_mov_b32 s50,0\n" QR_CALL("c3") ".Lqr%=r3:\n"                     \
+    QR_WANT("1", R1, ".Lqr%=r4") "s_mov_b32 s50,1\n" QR_CALL("c4") ".Lqr%=r4:\n"                     \
+    QR_WANT("2", R2, ".Lqr%=e") "s_mov_b32 s50,2\n" QR_CALL("c5")                                    \
+    ".Lqr%=e:\n"
+
+#define QR_CLOBBER                                                                                   \
+    "scc", "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", "s48", "s49", "s50", "s51", "s52", \
+        "s53", "s54", "s55", "s58", "s59", "s60", "s61", "s62", "s63"
+
+// A wave-uniform value, into a scalar register.
+__device__ __forceinline__ uint32_t scalar(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+
+// A chunk's gates: words in p (gate i in lane i, cnt of them), with ANG the
+// gates' scalars (cos, sin of theta / 2; 1 / sqrt 2 for H and T) in gc, gs.
+// restore: leaves the slots in canonical order (slot: row bit; lane slot s:
+// row bit s, register bit k: row bit LS + k).  Every lane is active.
+template <int NQ, bool ANG>
+__device__ __forceinline__ void reg_gates(f32x8& x, uint32_t p, uint32_t cnt, float gc, float gs, SlotMap&, bool) {
+    static_assert(NQ == 4, "4 registers: width 4");
+    cnt = scalar(cnt);
+    if constexpr (ANG)
+        asm volatile(QR_TEXT4(32, "16", "24", 1)
+                     : "+{v[16:23]}"(x) : [p] "v"(p), [cnt] "s"(cnt), [gc] "v"(gc), [gs] "v"(gs)
+                     : QR_CLOBBER, "v24", "v25", "v26", "v27");
+    else
+        asm volatile(QR_TEXT4(32, "16", "24", 0)
+                     : "+{v[16:23]}"(x) : [p] "v"(p), [cnt] "s"(cnt)
+                     : QR_CLOBBER, "v24", "v25", "v26", "v27");
+}
+template <int NQ, bool ANG>
+__device__ __forceinline__ void reg_gates(f64x8& x, uint32_t p, uint32_t cnt, double gc, double gs, SlotMap&, bool) {
+    static_assert(NQ == 4, "4 registers: width 4");
+    cnt = scalar(cnt);
+    if constexpr (ANG)
+        asm volatile(QR_TEXT4(64, "16", "32", 1)
+                     : "+{v[16:31]}"(x)
+                     : [p] "v"(p), [cnt] "s"(cnt), [gcl] "v"(__double2loint(gc)), [gch] "v"(__double2hiint(gc)),
+                       [gsl] "v"(__double2loint(gs)), [gsh] "v"(__double2hiint(gs))
+                     : QR_CLOBBER, "v32", "v33", "v34", "v35", "v36", "v37", "v38", "v39");
+    else
+        asm volatile(QR_TEXT4(64, "16", "32", 0)
+                     : "+{v[16:31]}"(x) : [p] "v"(p), [cnt] "s"(cnt)
+                     : QR_CLOBBER, "v32", "v33", "v34", "v35", "v36", "v37", "v38", "v39");
+}
+// (row bit b is wire NQ - 1 - b)
+#define QR_W5(P, TMP, ANG) QR_TEXT16(P, "16", TMP, 1, ANG, "4", "", "3", "2", "1")
+#define QR_W6(P, TMP, ANG) QR_TEXT16(P, "16", TMP, 2, ANG, "5", "4", "3", "2", "1")
+template <int NQ, bool ANG>
+__device__ __forceinline__ void reg_gates(f32x32& x, uint32_t p, uint32_t cnt, float gc, float gs, SlotMap& map,
+                                          bool restore) {
+    const uint32_t rs = scalar(restore ? 1u : 0u);
+    uint32_t w2s = scalar(map.w2s), s2w = scalar(map.s2w);
+    cnt = scalar(cnt);
+#define QR_ASM32(TEXT, ANG)                                                                          \
+    asm volatile(TEXT(32, "48", ANG)                                                                 \
+                 : "+{v[16:47]}"(x), [W] "+s"(w2s), [S] "+s"(s2w)                            \
+                 : [p] "v"(p), [cnt] "s"(cnt), [restore] "s"(rs), [gc] "v"(gc), [gs] "v"(gs) \
+                 : QR_CLOBBER, "v48", "v49", "v50", "v51")
+    if constexpr (NQ == 5) {
+        if constexpr (ANG) QR_ASM32(QR_W5, 1); else QR_ASM32(QR_W5, 0);
+    } else {
+        if constexpr (ANG) QR_ASM32(QR_W6, 1); else QR_ASM32(QR_W6, 0);
+    }
+#undef QR_ASM32
+    map.w2s = w2s;
+    map.s2w = s2w;
+}
+template <int NQ, bool ANG>
+__device__ __forceinline__ void reg_gates(f64x32& x, uint32_t p, uint32_t cnt, double gc, double gs, SlotMap& map,
+                                          bool restore) {
+    const uint32_t rs = scalar(restore ? 1u : 0u);
+    uint32_t w2s = scalar(map.w2s), s2w = scalar(map.s2w);
+    cnt = scalar(cnt);
+#define QR_ASM64(TEXT, ANG)                                                                          \
+    asm volatile(TEXT(64, "80", ANG)                                                                 \
+                 : "+{v[16:47]}"(x.lo), "+{v[48:79]}"(x.hi), [W] "+s"(w2s), [S] "+s"(s2w)    \
+                 : [p] "v"(p), [cnt] "s"(cnt), [restore] "s"(rs),                        \
+                   [gcl] "v"(__double2loint(gc)), [gch] "v"(__double2hiint(gc)),                     \
+                   [gsl] "v"(__double2loint(gs)), [gsh] "v"(__double2hiint(gs))                      \
+                 : QR_CLOBBER, "v80", "v81", "v82", "v83", "v84", "v85", "v86", "v87")
+    if constexpr (NQ == 5) {
+        if constexpr (ANG) QR_ASM64(QR_W5, 1); else QR_ASM64(QR_W5, 0);
+    } else {
+        if constexpr (ANG) QR_ASM64(QR_W6, 1); else QR_ASM64(QR_W6, 0);
+    }
+#undef QR_ASM64
+    map.w2s = w2s;
+    map.s2w = s2w;
+}
+
+}  // namespace qe

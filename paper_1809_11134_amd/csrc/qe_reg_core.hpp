@@ -1,0 +1,271 @@
+// Register-resident evaluation core of widths 4, 5 and 6 (FP32 and FP64).
+//
+// The circuit's N x N product M = U T^dagger (N = 2^n) never leaves the
+// registers: a wavefront holds CW columns (16; 32 at n = 5), lane l owns
+// column j = l mod CW (plus the wavefront's first column) and, with
+// q = l div CW, the rows whose lane-slot bits equal q, in E = N * CW / 64
+// complex registers.  n = 6 takes four wavefronts, the others one.  Row bits
+// sit in slots: the lane bits above the column (LB = 2; 1 at n = 5) and the
+// bits of the register index.  The gates run in reg_gates (qe_reg_asm.hpp): at
+// n = 5, 6 a wire that a gate needs and that sits in a lane slot is exchanged
+// with a register slot (v_permlane16/32_swap, one instruction per pair of
+// registers) and stays there (0.29 exchanges per two-wire gate of random
+// circuits at n = 5, 0.51 at n = 6).
+//
+// What bounds it: the VALU instructions of the gate bodies (10 per row pair of
+// a CV).  Against the same gates on M in LDS (run_lds_path) there is no LDS
+// traffic, no address arithmetic, no gate table and no LDS round trip per
+// gate, and the occupancy is set by about 60 VGPRs instead of 8 to 32 KB of
+// LDS per circuit.
+//
+// The arithmetic of each element (one rounding per operation, the same
+// operations in the same gate order) and the order of the reduction are those
+// of run_lds_path and canonical_fitness, so the results are the same bits.
+#pragma once
+#include "qe_eval_core.hpp"
+#include "qe_reg_asm.hpp"
+
+namespace qe {
+
+template <int NQ>
+struct RegGeom {
+    static_assert(NQ >= 4 && NQ <= 6, "widths 4 to 6");
+    static constexpr int N = 1 << NQ, W = NQ == 6 ? 4 : 1, CW = N / W;
+    static constexpr int LB = NQ == 5 ? 1 : 2, Q = 1 << LB, EB = NQ - LB, E = 1 << EB;
+    static_assert(CW * Q == 64, "a wavefront holds whole columns");
+};
+
+// Two complex numbers (one 16-byte load from memory aligned for one float2).
+struct __attribute__((aligned(8))) float2x2 {
+    float ax, ay, bx, by;
+};
+
+template <typename Real, int E>
+struct RegVec;
+template <> struct RegVec<float, 16> { using type = f32x32; };
+template <> struct RegVec<float, 4> { using type = f32x8; };
+template <> struct RegVec<double, 16> { using type = f64x32; };
+template <> struct RegVec<double, 4> { using type = f64x8; };
+
+template <typename Real, int NQ>
+struct RegMatrix {
+    using G = RegGeom<NQ>;
+    static constexpr int N = G::N, E = G::E, EB = G::EB, LB = G::LB, Q = G::Q;
+    typename RegVec<Real, E>::type x;     // the lane's E elements
+    SlotMap map;
+    int j;                 // the lane's column
+    uint32_t q;            // its lane-slot bits (lane slot s: bit s)
+
+    __device__ __forceinline__ Real re(int m) const { return reg_get(x, 2 * m); }
+    __device__ __forceinline__ Real im(int m) const { return reg_get(x, 2 * m + 1); }
+    __device__ __forceinline__ void put(int m, Real r, Real i) {
+        reg_set(x, 2 * m, r);
+        reg_set(x, 2 * m + 1, i);
+    }
+
+    __device__ __forceinline__ void place(int wave) {
+        const int lane = (int)lane_id();
+        j = wave * G::CW + lane % G::CW;
+        q = (uint32_t)lane / G::CW;
+        // n = 5, 6: register slots hold the low row bits, lane slots the high
+        // ones, so that a lane's E elements of M_0 = T^dagger are contiguous
+        // in T; wire w is row bit NQ-1-w
+        map.w2s = map.s2w = 0u;
+        if constexpr (NQ > 4) {
+#pragma unroll
+            for (int p = 0; p < NQ; ++p) {
+                const uint32_t w = NQ - 1 - p;
+                map.w2s |= (uint32_t)p << (4 * w);
+                map.s2w |= w << (4 * p);
+            }
+        }
+    }
+    // M_0 = T^dagger: M[r][j] = conj(T[j][r])
+    __device__ __forceinline__ void load(const float* __restrict__ T) {
+        if constexpr (NQ == 4) {
+            const float2* t = reinterpret_cast<const float2*>(T) + ((size_t)j * N + q);
+#pragma unroll
+            for (int m = 0; m < E; ++m) {
+                const float2 v = t[Q * m];
+                put(m, v.x, -v.y);
+            }
+        } else {
+            const float2x2* t = reinterpret_cast<const float2x2*>(T + 2 * ((size_t)j * N + q * E));
+#pragma unroll
+            for (int m = 0; m < E; m += 2) {
+                const float2x2 v = t[m / 2];
+                put(m, v.ax, -v.ay);
+                put(m + 1, v.bx, -v.by);
+            }
+        }
+    }
+    __device__ __forceinline__ void load(const double* __restrict__ T) {
+        const double2* t = reinterpret_cast<const double2*>(T) + ((size_t)j * N + q * (NQ == 4 ? 1 : E));
+#pragma unroll
+        for (int m = 0; m < E; ++m) {
+            const double2 v = t[(NQ == 4 ? Q : 1) * m];
+            put(m, v.x, -v.y);
+        }
+    }
+    __device__ __forceinline__ void identity() {
+#pragma unroll
+        for (int m = 0; m < E; ++m)
+            put(m, (int)(NQ == 4 ? q + Q * m : q * E + m) == j ? (Real)1 : (Real)0, (Real)0);
+    }
+
+    // The word of a gate (its descriptor checked) for reg_gates: table, target and
+    // control (the target again for a single-wire gate).
+    static __device__ __forceinline__ uint32_t gate_word(uint32_t d) {
+        const uint32_t kind = d & 15u, t = (d >> 4) & 15u;
+        const uint32_t c = kind_two_wire((int)kind) ? (d >> 8) & 15u : t;
+        // tables by kind: NOT, CNOT 2, CV 0, CV+ 1, H 0, T 1, R_x 3, R_y 4, R_z 5, J 3
+        const uint32_t table = (uint32_t)(0x35431010220ull >> (4u * kind)) & 15u;
+        if constexpr (NQ == 4) {
+            // entries 0, 1: row bits 2, 3 (register bits); 2, 3: row bits 0, 1 (lane
+            // slots); wire w is row bit 3 - w
+            const uint32_t ts = (5u - t) & 3u, cs = (5u - c) & 3u;
+            return 64u * table + 16u * ts + 4u * cs;
+        } else {
+            return (table << 22) | (4u * c << 8) | (4u * t);
+        }
+    }
+
+    // ------------------------------------------------------------ circuits
+    // Applies the circuit; false if a descriptor was invalid (M is then
+    // garbage).  RESTORE: and leaves the slots in canonical order.  dv0: the
+    // source's first chunk, fetched by the caller.
+    template <bool RESTORE, typename GateSrc, typename SrcT>
+    __device__ __forceinline__ bool run(int L, GateSrc&& src, const SrcT dv0) {
+        constexpr bool ANG = src_angled<GateSrc>();
+        const int lane = (int)lane_id();
+        L = __builtin_amdgcn_readfirstlane(L);
+        const int chunks = (L + 63) >> 6;
+        // (an empty circuit still restores the slots)
+        for (int ch = 0; ch < (chunks > 0 ? chunks : 1); ++ch) {
+            const SrcT dvv = ch == 0 ? dv0 : src(ch);
+            const uint32_t dv = desc_of(dvv);
+            const bool in = lane < min(64, L - ch * 64);
+            if (__ballot(in && !desc_valid<ANG>(dv, NQ))) return false;
+            const int kind = (int)(dv & 15u);
+            const bool live = in && kind != KIND_I;
+            // the gates in order into lanes 0, 1, ... (the others behind them)
+            const uint64_t todo = __ballot(live);
+            const uint32_t cnt = (uint32_t)__popcll(todo);
+            const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(todo >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)todo, 0u));
+            const int to = 4 * (int)(live ? rank : cnt + (uint32_t)lane - rank);
+            const uint32_t word = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(live ? gate_word(dv) : 0u));
+            Real gc = (Real)0.70710678118654752440084436210485, gs = (Real)0;
+            if constexpr (ANG) {
+                if (in && kind_ising(kind)) half_angle(angle_of(dvv), &gc, &gs);
+                gc = permute(to, gc);
+                gs = permute(to, gs);
+            }
+            reg_gates<NQ, ANG>(x, word, cnt, gc, gs, map, RESTORE && ch + 1 >= chunks);
+        }
+        return true;
+    }
+    static __device__ __forceinline__ float permute(int to, float v) {
+        return __int_as_float(__builtin_amdgcn_ds_permute(to, __float_as_int(v)));
+    }
+    static __device__ __forceinline__ double permute(int to, double v) {
+        return __hiloint2double(__builtin_amdgcn_ds_permute(to, __double2hiint(v)),
+                                __builtin_amdgcn_ds_permute(to, __double2loint(v)));
+    }
+
+    // Row-major store of M (the slots in any order).
+    template <typename C2>
+    __device__ __forceinline__ void store(C2* U, bool ok) const {
+        auto bit = [&](int slot) -> uint32_t { return NQ - 1 - ((map.s2w >> (4 * slot)) & 15u); };
+        uint32_t row = q;                       // the lane slots' part
+        if constexpr (NQ > 4) {
+            row = 0u;
+#pragma unroll
+            for (int s = 0; s < LB; ++s) row |= ((q >> s) & 1u) << bit(4 + s);
+        }
+#pragma unroll
+        for (int m = 0; m < E; ++m) {
+            uint32_t r = row;
+#pragma unroll
+            for (int k = 0; k < EB; ++k)
+                if ((m >> k) & 1) r |= NQ > 4 ? 1u << bit(k) : (uint32_t)Q << k;
+            const Real nan = (Real)__builtin_nan("");
+            C2 v;
+            v.x = ok ? re(m) : nan;
+            v.y = ok ? im(m) : nan;
+            U[(size_t)r * N + j] = v;
+        }
+    }
+
+    // Eq. 11 (or, by `mode`, the phase-insensitive form) in the order of
+    // canonical_fitness, of a matrix whose slots were restored.  n = 6: all four
+    // wavefronts of the circuit call it, red 4 x 3 values of LDS, w the
+    // wavefront.  Returns f on every lane.
+    __device__ __forceinline__ Real fitness(int mode, Real* g_out, Real* delta_out, int w, Real (*red)[3]) {
+        const int lane = (int)lane_id();
+        const int key = (j % Q) == (int)q ? j / Q : -1;       // register of the diagonal entry
+        Real off = (Real)0, dr = (Real)0, di = (Real)0;
+#pragma unroll
+        for (int m = 0; m < E; ++m) {
+            const bool dg = m == key;
+            const Real xr = re(m), xi = im(m), m2 = xr * xr + xi * xi;
+            off += dg ? (Real)0 : m2;
+            dr = dg ? xr : dr;
+            di = dg ? xi : di;
+        }
+        // sums over the circuit's wavefronts, added in order
+        auto total = [&](Real x) -> Real {
+            const Real s = wave_sum(x);
+            if constexpr (G::W == 1) {
+                return s;
+            } else {
+                __syncthreads();
+                if (lane == 0) red[w][0] = s;
+                __syncthreads();
+                Real t = (Real)0;
+#pragma unroll
+                for (int k = 0; k < G::W; ++k) t += red[k][0];
+                return t;
+            }
+        };
+        const Real offs = total(off);
+        if (mode == QE_FIT_PHASE_INSENSITIVE) {
+            Real fv;
+            fitness_pi(offs, N, &fv, g_out, delta_out);
+            return fv;
+        }
+        Real tr, ti;
+        if constexpr (G::W == 1) {
+            tr = wave_sum(dr);
+            ti = wave_sum(di);
+        } else {
+            // (one pair of barriers for both components)
+            const Real sr = wave_sum(dr), si = wave_sum(di);
+            __syncthreads();
+            if (lane == 0) { red[w][1] = sr; red[w][2] = si; }
+            __syncthreads();
+            tr = (Real)0;
+            ti = (Real)0;
+#pragma unroll
+            for (int k = 0; k < G::W; ++k) { tr += red[k][1]; ti += red[k][2]; }
+        }
+        const Real am = real_sqrt(tr * tr + ti * ti);
+        Real er = (Real)1, ei = (Real)0;
+        if (am > (Real)0) { er = tr / am; ei = ti / am; }
+        Real dl = (Real)0;
+        if (key >= 0) { const Real xr = dr - er, xi = di - ei; dl = xr * xr + xi * xi; }
+        const Real dlt = (Real)0.5 * (offs + total(dl));
+        const Real qq = clamp01(dlt / (Real)N);
+        *g_out = am / (Real)N;
+        *delta_out = dlt;
+        return (Real)1 - real_sqrt(qq);
+    }
+    static __device__ __forceinline__ float real_sqrt(float x) { return sqrtf(x); }
+    static __device__ __forceinline__ double real_sqrt(double x) { return sqrt(x); }
+    // as the FP32 LDS-staged and the generic FP64 kernels clamp (they differ
+    // for NaN)
+    static __device__ __forceinline__ float clamp01(float x) { return fminf(fmaxf(x, 0.0f), 1.0f); }
+    static __device__ __forceinline__ double clamp01(double x) { return x < 0.0 ? 0.0 : (x > 1.0 ? 1.0 : x); }
+};
+
+}  // namespace qe

@@ -14,17 +14,16 @@ gates stand for L < 32, of 48 gates for L >= 32) and library class:
   a QEQEA generation over the Ising library.
 
 Every schedule libqe can run for the class is timed -- the register-resident
-kernel (not for angled circuits, which always take the LDS-staged kernels),
-and the LDS-staged kernels with each allowed number of wavefronts per circuit
-and circuits per workgroup; timings are medians of repeated launches between
-HIP events, and the schedule with the smallest sum wins (libqe's default
-when it is within 2 %, the run-to-run noise).  The table (lines
+kernel and the LDS-staged ones with each allowed number of wavefronts per
+circuit, and circuits per workgroup; timings are medians of repeated launches between
+HIP events, and the schedule with the smallest sum wins (the first
+candidate when it is within 2 %, the run-to-run noise).  The table (lines
 "n lclass lib lds waves cpb", then "mfma n lclass min_block": the
 fewest gates a fused MFMA block needs, smaller groups going gate by gate
 in FP32) goes to tune_mi355x.txt, which libqe reads at
 first use (QE_TUNE_TABLE points elsewhere, QE_SCHEDULE overrides single
 widths).  Widths 1..3 always use the one-entry-per-lane kernel.  Every
-LDS-staged schedule gives the same bits, so the choice changes only speed.
+schedule gives the same bits, so the choice changes only speed.
 
     python -m paper_1809_11134_amd.tune [--out PATH]
 """
@@ -41,11 +40,10 @@ from . import inputs, qe
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 # (lds, waves, cpb) per width: the register kernel, then the LDS schedules
-CANDIDATES = {4: [(0, 1, 4), (1, 1, 4), (1, 1, 1)],
-              5: [(0, 1, 4), (1, 1, 4), (1, 1, 1), (1, 2, 1)],
+CANDIDATES = {4: [(0, 1, 4), (0, 1, 1), (1, 1, 4), (1, 1, 1)],
+              5: [(0, 1, 4), (0, 1, 1), (1, 1, 4), (1, 1, 1), (1, 2, 1)],
               6: [(0, 4, 1), (1, 4, 1)]}
 LENGTHS = {0: 20, 1: 48}
-DEFAULT = {4: (1, 1, 4), 5: (1, 1, 4), 6: (1, 4, 1)}    # libqe's built-in schedule
 TIE = 0.02
 CLASSES = {qe.SCHED_DISCRETE: "discrete", qe.SCHED_SAMPLED: "sampled", qe.SCHED_ISING: "ising"}
 
@@ -111,11 +109,6 @@ def time_schedule(n, L, cls, sched, reps, rng, dev, log):
     return sum(parts.values())
 
 
-def candidates(n, cls):
-    c = CANDIDATES[n]
-    return [s for s in c if s[0] == 1] if cls == qe.SCHED_ISING else c
-
-
 def sweep(reps=7, log=print, widths=(4, 5, 6)):
     dev = torch.device("cuda", 0)
     saved = {(n, c, k): qe.get_schedule_lib(n, c, k) for n in widths for c in (0, 1) for k in CLASSES}
@@ -125,14 +118,14 @@ def sweep(reps=7, log=print, widths=(4, 5, 6)):
             for lclass, L in LENGTHS.items():
                 for cls in CLASSES:
                     times = {}
-                    for sched in candidates(n, cls):
+                    for sched in CANDIDATES[n]:
                         rng = np.random.default_rng(inputs.SEED_BASE + 77 + 10 * n + lclass)
                         times[sched] = time_schedule(n, L, cls, sched, reps, rng, dev, log)
                     best = min(times, key=times.get)
-                    # within TIE of the best, the default schedule is kept (the
+                    # within TIE of the best, the first candidate is kept (the
                     # differences are run-to-run noise)
-                    if times.get(DEFAULT[n], math.inf) <= (1.0 + TIE) * times[best]:
-                        best = DEFAULT[n]
+                    if times[CANDIDATES[n][0]] <= (1.0 + TIE) * times[best]:
+                        best = CANDIDATES[n][0]
                     table[(n, lclass, cls)] = (best, times)
     finally:
         for (n, c, k), v in saved.items():
