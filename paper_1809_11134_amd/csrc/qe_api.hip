@@ -238,6 +238,9 @@ qe_status to_args(const qe_batch* b, BatchArgs* a, bool need_targets) {
     a->targets = b->targets_dev;
     a->num_telems = b->num_target_elems;
     a->mode = b->fitness_mode;
+    a->gates_odd = nullptr;
+    a->gen_ptr = nullptr;
+    a->gen = 0;
     a->angles = b->angles_dev;
     return device_error_word(&a->err);
 }
@@ -270,6 +273,9 @@ struct qe_ctx {
     // ctx-owned device buffers
     std::vector<void*> owned;
     uint16_t* gates = nullptr;    // [I*P*L]
+    // GA: the circuits of the last generation run are still genomes[last_parity]
+    // (-1: they have been kept in `gates`, or none was run)
+    int last_parity = -1;
     uint32_t* angles = nullptr;   // [I*P*L] (Ising library)
     float* f = nullptr;           // [I*P]
     uint64_t* d_gen = nullptr;
@@ -358,15 +364,18 @@ qe_status prepare_decisions(qe_ctx* c, uint64_t gen, uint64_t count, hipStream_t
 }
 
 // The evaluation batch of a mixed context's I*P circuits (genomes in `gates`,
-// laid out as the genome buffers).
-BatchArgs mixed_batch(const qe_ctx* c, const uint16_t* gates) {
+// laid out as the genome buffers; NULL: the population of generation gen).
+BatchArgs mixed_batch(const qe_ctx* c, const uint16_t* gates, const uint64_t* gen_ptr = nullptr, uint64_t gen = 0) {
     BatchArgs b{};
     b.B = c->prob.n_instances * c->prob.size_of_population;
     b.uniform_n = 0;
     b.nq = c->circ_n;
     b.uniform_L = 0;
     b.goff = c->circ_goff;
-    b.gates = gates;
+    b.gates = gates ? gates : c->la.genomes[0];
+    b.gates_odd = gates ? nullptr : c->la.genomes[1];
+    b.gen_ptr = gen_ptr;
+    b.gen = gen;
     b.num_gates = c->genes;
     b.tstride = -1;
     b.toff = c->circ_toff;
@@ -376,6 +385,16 @@ BatchArgs mixed_batch(const qe_ctx* c, const uint16_t* gates) {
     b.angles = nullptr;
     b.err = c->la.err;
     return b;
+}
+
+// GA: before genomes[parity] is overwritten from outside the generation loop,
+// the last generation's circuits (qe_elite_recheck without gates) move from
+// there to c->gates.
+qe_status keep_last_gates(qe_ctx* c, int parity, hipStream_t s) {
+    if (c->last_parity < 0 || c->last_parity != parity) return QE_OK;
+    QE_HIP(launch_ga_copy(c->la, (uint64_t)parity, c->gates, s));
+    c->last_parity = -1;
+    return QE_OK;
 }
 
 void note_words(qe_ctx* c, uint64_t gen) {
@@ -402,9 +421,10 @@ qe_status enqueue_generation(qe_ctx* c, const LoopArgs& a, uint64_t gen, float* 
         QE_HIP(launch_qeqea_update(a, gen, nullptr, c->gates, c->angles, f, s, a.dup != nullptr,
                                    a.dup != nullptr));
     } else {
-        QE_HIP(launch_ga_copy(a, gen, c->gates, s));
-        if (c->mixed) QE_HIP(launch_mix_eval(mixed_batch(c, c->gates), c->mix_order, f, nullptr, nullptr, s));
-        else QE_HIP(launch_eval_population(a, c->gates, nullptr, f, s));
+        if (c->mixed)
+            QE_HIP(launch_mix_eval(mixed_batch(c, nullptr, a.gen_ptr, gen), c->mix_order, f, nullptr, nullptr, s));
+        else
+            QE_HIP(launch_ga_eval(a, gen, f, s));
         QE_HIP(launch_ga_update(a, gen, f, s));
     }
     return QE_OK;
@@ -950,6 +970,7 @@ qe_status qe_update(qe_ctx* c, uint64_t gen, const uint32_t* slots, const uint16
                                    words));
         if (words) note_words(c, gen + 1);
     } else {
+        QE_TRY(keep_last_gates(c, (int)((gen + 1) & 1), s));
         QE_HIP(launch_ga_update(c->la, gen, f, s));
     }
     return QE_OK;
@@ -961,6 +982,7 @@ qe_status qe_generation(qe_ctx* c, uint64_t gen, float* f, void* stream) {
     QE_TRY(prepare_decisions(c, gen, 1, (hipStream_t)stream));
     if (c->prob.algorithm == QE_ALG_QEQEA) QE_TRY(ensure_words(c, gen, (hipStream_t)stream));
     QE_TRY(enqueue_generation(c, c->la, gen, f ? f : c->f, (hipStream_t)stream));
+    if (c->prob.algorithm == QE_ALG_GA) c->last_parity = (int)(gen & 1);
     note_words(c, gen + 1);
     return QE_OK;
 }
@@ -1031,6 +1053,7 @@ qe_status qe_run_graph(qe_ctx* c, uint64_t first_gen, int32_t n_gen, float* f_hi
     if (c->prob.algorithm == QE_ALG_QEQEA) QE_TRY(ensure_words(c, first_gen, s));
     QE_HIP(launch_gen_set(c->d_gen, first_gen, s));
     QE_HIP(hipGraphLaunch(ex, s));
+    if (c->prob.algorithm == QE_ALG_GA) c->last_parity = (int)((first_gen + (uint64_t)n_gen - 1) & 1);
     note_words(c, first_gen + (uint64_t)n_gen - 1);
     note_words(c, first_gen + (uint64_t)n_gen);
     return QE_OK;
@@ -1041,7 +1064,7 @@ qe_status qe_elite_recheck(qe_ctx* c, const uint16_t* gates, const uint32_t* ang
     QE_TRY(check_ctx(c, true));
     if (!f || !idx || !f64) return fail(QE_ERR_INVALID, "NULL buffer");
     if (!gates) {
-        gates = c->gates;
+        gates = c->last_parity >= 0 ? c->la.genomes[c->last_parity] : c->gates;
         angles = c->angles;
     } else if (is_ising(c) && !angles) {
         return fail(QE_ERR_INVALID, "the Ising library needs angles_dev");
@@ -1203,6 +1226,7 @@ qe_status qe_restore(qe_ctx* c, const void* buf, size_t size) {
     for (auto& s : secs) payload += s.bytes;
     if (h.payload != payload || size < sizeof(h) + payload) return fail(QE_ERR_INVALID, "checkpoint size mismatch");
     QE_HIP(hipDeviceSynchronize());
+    if (c->last_parity >= 0) QE_TRY(keep_last_gates(c, c->last_parity, nullptr));
     const char* p = static_cast<const char*>(buf) + sizeof(h);
     for (auto& s : secs) {
         QE_HIP(hipMemcpy(s.ptr, p, s.bytes, hipMemcpyHostToDevice));

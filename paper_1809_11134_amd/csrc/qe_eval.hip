@@ -278,6 +278,7 @@ __global__ __launch_bounds__(256) void mix_kernel(BatchArgs a, const int32_t* __
                                                   float* __restrict__ f, float* __restrict__ g,
                                                   float* __restrict__ delta) {
     __shared__ float red[4][3];
+    if (a.gates_odd && (((a.gen_ptr ? *a.gen_ptr : 0ull) + a.gen) & 1ull)) a.gates = a.gates_odd;
     const int item = blockIdx.x;
     if (item >= meta[8 + MIX_BUCKETS]) return;
     int k = 0;

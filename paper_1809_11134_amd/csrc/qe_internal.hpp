@@ -20,6 +20,11 @@ struct BatchArgs {
     int64_t num_telems;
     int32_t mode;           // QE_FIT_*
 
+    // with gates_odd (the GA's double buffer): generation gen_ptr ? *gen_ptr + gen
+    // : gen reads gates_odd when it is odd
+    const uint16_t* gates_odd;
+    const uint64_t* gen_ptr;
+    uint64_t gen;
     const uint32_t* angles; // per-gate angles (u32 turn fractions, parallel to gates) or null
     uint32_t* err;          // device error word (atomicOr of QE_DEVERR_*)
 };

@@ -487,6 +487,8 @@ __global__ __launch_bounds__(256) void population_kernel(LoopArgs a, uint64_t ge
                                                          uint32_t* __restrict__ angles_out,
                                                          float* __restrict__ f_out, bool decide) {
     const uint32_t gen = gen_of(a, gen64);
+    // (no gates given: the GA population of the generation)
+    if (!SAMPLE && !ISING && !gates_in) gates_in = a.genomes[gen & 1];
     const uint32_t total = (uint32_t)a.I * (uint32_t)a.P;
     const uint32_t bid = xcd_swizzle(blockIdx.x, gridDim.x);
     const int wave = (int)(threadIdx.x >> 6);
@@ -1009,21 +1011,32 @@ __global__ void state_gather_kernel(LoopArgs a, int which, void* __restrict__ ds
 }
 
 // ----------------------------------------------------------------------- GA
-// One workgroup per population: SUS over integer weights floor(f * 2^24),
-// two-point crossover of children j and j + P/2, gene mutation, and the best
-// parent copied unchanged into child 0.  Reads genomes[gen & 1], writes
-// genomes[(gen + 1) & 1].
+// SUS over integer weights floor(f * 2^24), two-point crossover of children j
+// and j + P/2, gene mutation, and the best parent copied unchanged into child
+// 0.  Reads genomes[gen & 1], writes genomes[(gen + 1) & 1].
+// `parts` workgroups per population: each builds the population's whole
+// weight prefix in LDS (P values, a scan over the workgroup) and then makes
+// its share of the pairs of children, one gene pair per thread: the parents
+// are the pair's two selections, exchanged between the cuts, and a mutated
+// gene replaces its parent's, so every child gene is written once and no
+// workgroup waits for another.  A population of 4096 x 20 genes on one
+// workgroup with a serial prefix took 253 us.
 constexpr int GA_MAX_P = 4096;
+constexpr int GA_BLOCK = 256;
 
-__global__ __launch_bounds__(256) void ga_update_kernel(LoopArgs a, uint64_t gen64,
-                                                        const float* __restrict__ f) {
-    __shared__ unsigned long long pre[GA_MAX_P + 1];
-    __shared__ int32_t sel[GA_MAX_P];
-    __shared__ float bestv[4];
-    __shared__ int besti[4];
+// LDS of ga_update_kernel: the prefix, then per pair of the workgroup the two
+// parents and the cuts
+static inline size_t ga_lds_bytes(int P, int pairs) { return (size_t)((P + 2) & ~1) * 8 + (size_t)pairs * 16; }
+
+__global__ __launch_bounds__(GA_BLOCK) void ga_update_kernel(LoopArgs a, uint64_t gen64,
+                                                             const float* __restrict__ f, uint32_t parts) {
+    extern __shared__ __align__(16) unsigned long long pre[];
+    __shared__ unsigned long long wsum[GA_BLOCK / 64];
+    __shared__ float bestv[GA_BLOCK / 64];
+    __shared__ int besti[GA_BLOCK / 64];
     const uint32_t gen = gen_of(a, gen64);
-    const uint32_t i = blockIdx.x;
-    const int P = a.P, tid = threadIdx.x, nt = blockDim.x;
+    const uint32_t i = blockIdx.x / parts, part = blockIdx.x % parts;
+    const int P = a.P, tid = threadIdx.x, wave = tid >> 6;
     // population i's width, genome length and genomes (mixed populations
     // carry their own)
     const int n = a.inst_n ? a.inst_n[i] : a.n, L = a.inst_L ? a.inst_L[i] : a.L;
@@ -1031,76 +1044,115 @@ __global__ __launch_bounds__(256) void ga_update_kernel(LoopArgs a, uint64_t gen
     const uint16_t* cur = a.genomes[gen & 1] + base;
     uint16_t* nxt = a.genomes[(gen + 1) & 1] + base;
     const float* fi = f + (size_t)i * P;
-    // weights and best (lowest index among the maxima)
+    // weights of the thread's consecutive circuits, and the best circuit
+    // (lowest index among the maxima; NaN never counts)
+    constexpr int PER = GA_MAX_P / GA_BLOCK;
+    const int per = (P + GA_BLOCK - 1) / GA_BLOCK, k0 = tid * per;
+    uint32_t w[PER];
     float best = -1.0f;
     int bi = 0x7FFFFFFF;
-    for (int k = tid; k < P; k += nt) {
-        const float v = fi[k];
-        pre[k + 1] = (v >= 0.0f) ? (unsigned long long)(uint32_t)floorf(v * 16777216.0f) : 0ull;
+    unsigned long long mine = 0ull;
+#pragma unroll
+    for (int c = 0; c < PER; ++c) {
+        const int k = k0 + c;
+        const float v = c < per && k < P ? fi[k] : -1.0f;
+        w[c] = v >= 0.0f ? (uint32_t)floorf(v * 16777216.0f) : 0u;
+        mine += w[c];
         if (v > best) { best = v; bi = k; }
+    }
+    unsigned long long incl = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const unsigned long long o = __shfl_up(incl, d, 64);
+        if ((tid & 63) >= d) incl += o;
     }
     for (int m = 32; m >= 1; m >>= 1) {
         const float ob = __shfl_xor(best, m, 64);
         const int oi = __shfl_xor(bi, m, 64);
         if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
     }
-    if ((tid & 63) == 0) { bestv[tid >> 6] = best; besti[tid >> 6] = bi; }
-    if (tid == 0) pre[0] = 0;
+    if ((tid & 63) == 63) wsum[wave] = incl;
+    if ((tid & 63) == 0) { bestv[wave] = best; besti[wave] = bi; }
     __syncthreads();
-    if (tid == 0) {
-        for (int w = 1; w < (nt >> 6); ++w)
-            if (bestv[w] > best || (bestv[w] == best && besti[w] < bi)) { best = bestv[w]; bi = besti[w]; }
-        bestv[0] = best; besti[0] = bi;
-        // inclusive prefix (serial: P <= 4096 additions)
-        for (int k = 1; k <= P; ++k) pre[k] += pre[k - 1];
-        if (pre[P] == 0)
-            for (int k = 0; k <= P; ++k) pre[k] = (unsigned long long)k;
+    unsigned long long run = incl - mine, W = 0ull;
+    best = bestv[0];
+    bi = besti[0];
+#pragma unroll
+    for (int v = 0; v < GA_BLOCK / 64; ++v) {
+        if (v < wave) run += wsum[v];
+        W += wsum[v];
+        if (bestv[v] > best || (bestv[v] == best && besti[v] < bi)) { best = bestv[v]; bi = besti[v]; }
+    }
+    if (bi == 0x7FFFFFFF) bi = 0;
+    const bool uniform = W == 0ull;             // all weights zero
+    if (uniform) W = (unsigned long long)P;
+    if (tid == 0) pre[0] = 0ull;
+#pragma unroll
+    for (int c = 0; c < PER; ++c) {
+        const int k = k0 + c;
+        run += w[c];
+        if (c < per && k < P) pre[k + 1] = uniform ? (unsigned long long)(k + 1) : run;
     }
     __syncthreads();
-    best = bestv[0];
-    bi = besti[0] == 0x7FFFFFFF ? 0 : besti[0];
-    const unsigned long long W = pre[P];
+    // the workgroup's pairs of children (j, j + half): parents and cuts
+    const int half = P / 2, share = (half + (int)parts - 1) / (int)parts;
+    const int j0 = min((int)part * share, half), np = min(share, half - j0);
+    int4* pair = reinterpret_cast<int4*>(pre + ((P + 2) & ~1));
     const uint32_t w0 = draw(a.seed, TAG_GA_SUS, gen, i, 0u).x;
     const unsigned long long r = (unsigned long long)w0 * (W >> 32) +
                                  (((unsigned long long)w0 * (W & 0xFFFFFFFFull)) >> 32);
-    for (int k = tid; k < P; k += nt) {
+    auto select = [&](int k) -> int {
         const unsigned long long ptr = (r + (unsigned long long)k * W) / (unsigned long long)P;
         int lo = 0, hi = P - 1;        // first m with pre[m + 1] > ptr
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
             if (pre[mid + 1] > ptr) hi = mid; else lo = mid + 1;
         }
-        sel[k] = lo;
-    }
-    __syncthreads();
-    for (size_t e = tid; e < (size_t)P * L; e += nt) {
-        const int k = (int)(e / L), pos = (int)(e % L);
-        nxt[e] = cur[(size_t)sel[k] * L + pos];
-    }
-    __syncthreads();
-    const int half = P / 2;
-    for (int j = tid; j < half; j += nt) {
-        const u32x4 w = draw(a.seed, TAG_GA_XOVER, gen, i, (uint32_t)j);
-        if (!((uint64_t)w.x < a.thr_pc)) continue;
-        const int c1 = (int)scale_u32(w.y, (uint32_t)(L + 1)), c2 = (int)scale_u32(w.z, (uint32_t)(L + 1));
-        const int lo = min(c1, c2), hi = max(c1, c2);
-        for (int pos = lo; pos < hi; ++pos) {
-            const uint16_t t = nxt[(size_t)j * L + pos];
-            nxt[(size_t)j * L + pos] = nxt[(size_t)(j + half) * L + pos];
-            nxt[(size_t)(j + half) * L + pos] = t;
+        return lo;
+    };
+    for (int q = tid; q < 2 * np; q += GA_BLOCK) {
+        const int j = j0 + (q >> 1);
+        int* p = reinterpret_cast<int*>(pair + (q >> 1));
+        if (q & 1) {
+            p[1] = select(j + half);
+        } else {
+            p[0] = select(j);
+            int lo = 0, hi = 0;
+            const u32x4 c = draw(a.seed, TAG_GA_XOVER, gen, i, (uint32_t)j);
+            if ((uint64_t)c.x < a.thr_pc) {
+                const int c1 = (int)scale_u32(c.y, (uint32_t)(L + 1)), c2 = (int)scale_u32(c.z, (uint32_t)(L + 1));
+                lo = min(c1, c2);
+                hi = max(c1, c2);
+            }
+            p[2] = lo;
+            p[3] = hi;
         }
     }
     __syncthreads();
     const uint32_t nl = (uint32_t)lib_size(a.lib, n);
-    for (size_t e = tid; e < (size_t)P * L; e += nt) {
-        const u32x4 w = draw(a.seed, TAG_GA_MUT, gen, i, (uint32_t)e);
-        if ((uint64_t)w.x < a.thr_pg) nxt[e] = lib_desc(a.lib, n, (int)scale_u32(w.y, nl));
+    auto child = [&](int k, int pos, int parent) {
+        const size_t e = (size_t)k * L + pos;
+        const u32x4 m = draw(a.seed, TAG_GA_MUT, gen, i, (uint32_t)e);
+        uint16_t g = cur[(size_t)(k == 0 ? bi : parent) * L + pos];
+        if (k != 0 && (uint64_t)m.x < a.thr_pg) g = lib_desc(a.lib, n, (int)scale_u32(m.y, nl));
+        nxt[e] = g;
+    };
+    for (int e = tid; e < np * L; e += GA_BLOCK) {
+        const int q = e / L, pos = e - q * L, j = j0 + q;
+        const int4 s = pair[q];
+        const bool cross = pos >= s.z && pos < s.w;
+        child(j, pos, cross ? s.y : s.x);
+        child(j + half, pos, cross ? s.x : s.y);
     }
-    __syncthreads();
-    for (int pos = tid; pos < L; pos += nt) nxt[pos] = cur[(size_t)bi * L + pos];
+    if (part != 0) return;
+    // an odd last child has no partner
+    if (P & 1) {
+        const int parent = select(P - 1);
+        for (int pos = tid; pos < L; pos += GA_BLOCK) child(P - 1, pos, parent);
+    }
     // best circuit ever seen by this population (rows of a.L entries)
     if (best > a.inst_best_f[i]) {
-        for (int pos = tid; pos < L; pos += nt)
+        for (int pos = tid; pos < L; pos += GA_BLOCK)
             a.inst_best_gates[(size_t)i * a.L + pos] = cur[(size_t)bi * L + pos];
         __syncthreads();
         if (tid == 0) a.inst_best_f[i] = best;
@@ -1557,12 +1609,8 @@ hipError_t launch_eval_population(const LoopArgs& a, const uint16_t* gates, cons
 }
 
 hipError_t launch_ga_eval(const LoopArgs& a, uint64_t gen, float* f, hipStream_t s) {
-    // the population of generation gen is genomes[gen & 1]; the parity is
-    // resolved on the device for graph replays
-    LoopArgs b = a;
-    b.gen_ptr = nullptr;
-    if (a.gen_ptr) return hipErrorInvalidValue;   // callers use launch_ga_copy + eval in graphs
-    launch_population<false>(b, 0, a.genomes[gen & 1], nullptr, nullptr, nullptr, nullptr, f, s);
+    // (the kernel takes the genomes of the generation's parity)
+    launch_population<false>(a, gen, nullptr, nullptr, nullptr, nullptr, nullptr, f, s);
     return hipGetLastError();
 }
 
@@ -1641,7 +1689,17 @@ hipError_t launch_state_gather(const LoopArgs& a, int which, void* dst, hipStrea
 }
 
 hipError_t launch_ga_update(const LoopArgs& a, uint64_t gen, const float* f, hipStream_t s) {
-    ga_update_kernel<<<a.I, 256, 0, s>>>(a, gen, f);
+    // one round of gene pairs per thread, as long as the populations together
+    // do not fill the GPU several times over (every workgroup repeats its
+    // population's prefix)
+    const int half = a.P / 2;
+    const uint64_t rounds = ((uint64_t)half * a.L + GA_BLOCK - 1) / GA_BLOCK;
+    const uint64_t most = std::max<uint64_t>(1, 2048 / (uint64_t)a.I);
+    // (and at most 1024 pairs a workgroup: 48 KB of LDS in all)
+    const uint64_t least = std::max<uint64_t>(1, ((uint64_t)half + 1023) / 1024);
+    const uint32_t parts = (uint32_t)std::max<uint64_t>(least, std::min({rounds, most, (uint64_t)half}));
+    const int share = (half + (int)parts - 1) / (int)parts;
+    ga_update_kernel<<<(unsigned)a.I * parts, GA_BLOCK, ga_lds_bytes(a.P, share), s>>>(a, gen, f, parts);
     return hipGetLastError();
 }
 
