@@ -602,7 +602,7 @@ qe_status qe_eval_fitness_fp64(const qe_batch* batch, double* f_dev, double* g_d
     BatchArgs a;
     QE_TRY(to_args(batch, &a, true));
     if (a.B > 0 && !f_dev) return fail(QE_ERR_INVALID, "f_dev is NULL");
-    QE_HIP(launch_eval_lds(a, true, f_dev, g_dev, delta_dev, (hipStream_t)stream));
+    QE_HIP(launch_eval_fp64(a, f_dev, g_dev, delta_dev, (hipStream_t)stream));
     QE_HIP(launch_target_check(a, true, f_dev, g_dev, delta_dev, (hipStream_t)stream));
     return QE_OK;
 }

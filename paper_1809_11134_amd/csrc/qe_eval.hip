@@ -22,29 +22,29 @@ __device__ __forceinline__ auto batch_gate(const Item& it, int p) {
         return p < it.L ? (uint32_t)it.g[p] : 0u;
 }
 
-// ------------------------------------------------------- FP32, one wave each
-// One-element-per-lane path (n <= 3), WPB circuits per workgroup.  FILTER: a
+// ------------------------------------------------------------ n <= 3
+// One-element-per-lane path, WPB circuits per workgroup.  FILTER: a
 // mixed-width batch is served by one launch per width, each skipping the
 // circuits of other widths.  ANG: the batch carries angles.
-template <int NQ, bool FILTER, bool ANG>
-__global__ __launch_bounds__(64 * WPB) void wave_kernel(BatchArgs a, float* __restrict__ f,
-                                                        float* __restrict__ g,
-                                                        float* __restrict__ delta) {
+template <typename Real, int NQ, bool FILTER, bool ANG>
+__global__ __launch_bounds__(64 * WPB) void wave_kernel(BatchArgs a, Real* __restrict__ f,
+                                                        Real* __restrict__ g,
+                                                        Real* __restrict__ delta) {
     const int b = __builtin_amdgcn_readfirstlane(blockIdx.x * WPB + (threadIdx.x >> 6));
     if (b >= a.B) return;
     const int lane = (int)lane_id();
     Item it = resolve(a, b);
     if (FILTER && it.n != NQ) return;
     if (it.err == 0 && it.n != NQ) it.err = QE_DEVERR_WIDTH;
-    FitOut o{__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
+    const Real nan = (Real)__builtin_nan("");
+    FitOut<Real> o{nan, nan, nan};
     if (it.err == 0) {
-        const int L = it.L;
         auto src = [&](int ch) { return batch_gate<ANG>(it, ch * 64 + lane); };
-        const float* T = reinterpret_cast<const float*>(a.targets) + 2 * it.toff;
-        const bool ok = run_small_path<NQ, false>(T, L, src, nullptr, &o, a.mode);
+        const Real* T = reinterpret_cast<const Real*>(a.targets) + 2 * it.toff;
+        const bool ok = run_small_path<NQ, false>(T, it.L, src, (Real*)nullptr, &o, a.mode);
         if (!ok) {
             it.err = QE_DEVERR_DESC;
-            o = FitOut{__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
+            o = FitOut<Real>{nan, nan, nan};
         } else if (!(o.f == o.f)) {
             it.err = QE_DEVERR_NUMERIC;
         }
@@ -115,6 +115,37 @@ __global__ __launch_bounds__(256) void reg_kernel(BatchArgs a, Real* __restrict_
     reg_item<Real, NQ, ANG>(a, b, it, WHOLE ? wave : 0, strict, red, f, g, delta);
 }
 
+// Unitaries of a uniform-width batch: the product started from the identity.
+template <typename Real, int NQ, bool ANG>
+__global__ __launch_bounds__(256) void unitary_kernel(BatchArgs a, Real* __restrict__ out) {
+    constexpr bool WHOLE = NQ == 6;
+    const int wave = (int)(threadIdx.x >> 6), lane = (int)lane_id();
+    const int b = __builtin_amdgcn_readfirstlane(WHOLE ? (int)blockIdx.x : (int)blockIdx.x * WPB + wave);
+    if (b >= a.B) return;
+    Item it = resolve(a, b, false);
+    it.err = (uint32_t)__builtin_amdgcn_readfirstlane((int)it.err);
+    auto src = [&](int ch) { return batch_gate<ANG>(it, ch * 64 + lane); };
+    Real* U = out + ((size_t)2 << (2 * NQ)) * b;
+    bool ok = it.err == 0;
+    if (!ok) it.L = 0;                          // (a malformed range: NaN, no gate read)
+    if constexpr (NQ <= 3) {
+        ok = run_small_path<NQ, true>((const Real*)nullptr, it.L, src, U, (FitOut<Real>*)nullptr) && ok;
+        if (it.err) {
+            const Real nan = (Real)__builtin_nan("");
+            for (int e = lane; e < (2 << (2 * NQ)); e += 64) U[e] = nan;
+        }
+    } else {
+        RegMatrix<Real, NQ> M;
+        M.place(WHOLE ? wave : 0);
+        const auto dv0 = src(0);
+        M.identity();
+        ok = M.template run<false>(it.L, src, dv0) && ok;
+        M.store(reinterpret_cast<complex_of<Real>*>(U), ok);
+    }
+    if (!ok && it.err == 0) it.err = QE_DEVERR_DESC;
+    if (lane == 0 && (!WHOLE || wave == 0) && it.err) atomicOr(a.err, it.err);
+}
+
 // Marks circuits whose width is outside 1..6 (mixed-width batches only).
 __global__ void width_check_kernel(BatchArgs a, float* f, float* g, float* delta) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
@@ -128,17 +159,16 @@ __global__ void width_check_kernel(BatchArgs a, float* f, float* g, float* delta
 }
 
 // LDS-staged path, W wavefronts per circuit (see run_lds_path).
-template <int NQ, int W, bool FILTER, bool IDENT, bool ANG = false>
+template <int NQ, int W, bool FILTER, bool ANG>
 __global__ __launch_bounds__(64 * W) void lds32_kernel(BatchArgs a, float* __restrict__ f,
                                                        float* __restrict__ g,
-                                                       float* __restrict__ delta,
-                                                       float* __restrict__ U_out) {
+                                                       float* __restrict__ delta) {
     constexpr int N = 1 << NQ;
     __shared__ float2 M[N * N];
     __shared__ uint4 GT[W][ANG ? GATE_TABLE_ANGLED : GATE_TABLE];
     const int b = blockIdx.x;
     const int lane = (int)lane_id(), wave = (int)(threadIdx.x >> 6);
-    Item it = resolve(a, b, !IDENT);
+    Item it = resolve(a, b);
     if (FILTER && it.n != NQ) return;
     if (it.err == 0 && it.n != NQ) it.err = QE_DEVERR_WIDTH;
     bool ok = it.err == 0;
@@ -146,17 +176,9 @@ __global__ __launch_bounds__(64 * W) void lds32_kernel(BatchArgs a, float* __res
     if (ok) {
         const int L = it.L;
         auto src = [&](int ch) { return batch_gate<ANG>(it, ch * 64 + lane); };
-        const float* T = IDENT ? nullptr : reinterpret_cast<const float*>(a.targets) + 2 * it.toff;
-        ok = run_lds_path<NQ, W, IDENT>(M, GT[wave], T, L, src, IDENT ? nullptr : &map);
+        const float* T = reinterpret_cast<const float*>(a.targets) + 2 * it.toff;
+        ok = run_lds_path<NQ, W>(M, GT[wave], T, L, src, &map);
         if (!ok) it.err = QE_DEVERR_DESC;
-    }
-    if (IDENT) {
-        __syncthreads();
-        float2* U = reinterpret_cast<float2*>(U_out) + (size_t)N * N * b;
-        const float nan = __builtin_nanf("");
-        for (int e = threadIdx.x; e < N * N; e += 64 * W) U[e] = ok ? M[e] : make_float2(nan, nan);
-        if (threadIdx.x == 0 && it.err) atomicOr(a.err, it.err);
-        return;
     }
     // fitness, in the width's fixed order
     constexpr int WR = reduction_waves<NQ>();
@@ -249,7 +271,7 @@ __device__ __forceinline__ void mix_wave_item(const BatchArgs& a, int b, float* 
                                               float* delta) {
     const int lane = (int)lane_id();
     Item it = resolve(a, b);
-    FitOut o{__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
+    FitOut<float> o{__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
     if (it.err == 0) {
         const uint16_t* gp = it.g;
         const int L = it.L;
@@ -258,9 +280,9 @@ __device__ __forceinline__ void mix_wave_item(const BatchArgs& a, int b, float* 
             return p < L ? (uint32_t)gp[p] : 0u;
         };
         const float* T = reinterpret_cast<const float*>(a.targets) + 2 * it.toff;
-        if (!run_small_path<NQ, false>(T, L, src, nullptr, &o, a.mode)) {
+        if (!run_small_path<NQ, false>(T, L, src, (float*)nullptr, &o, a.mode)) {
             it.err = QE_DEVERR_DESC;
-            o = FitOut{__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
+            o = FitOut<float>{__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
         } else if (!(o.f == o.f)) {
             it.err = QE_DEVERR_NUMERIC;
         }
@@ -310,27 +332,17 @@ __global__ __launch_bounds__(256) void mix_kernel(BatchArgs a, const int32_t* __
     }
 }
 
-// --------------------------------------------------------- generic LDS path
-template <typename Real, bool IDENT>
-__global__ __launch_bounds__(256) void lds_kernel(BatchArgs a, Real* __restrict__ f,
-                                                  Real* __restrict__ g, Real* __restrict__ delta,
-                                                  Real* __restrict__ U_out) {
+// ------------------------------------------- FP64, mixed widths in one launch
+__global__ __launch_bounds__(256) void lds_kernel(BatchArgs a, double* __restrict__ f, double* __restrict__ g,
+                                                  double* __restrict__ delta) {
     const int b = blockIdx.x;
-    Item it = resolve(a, b, !IDENT);
-    const Real* T = (IDENT || it.err) ? nullptr : reinterpret_cast<const Real*>(a.targets) + 2 * it.toff;
-    Real* U = nullptr;
-    if (IDENT) U = U_out + (size_t)2 * ((size_t)1 << (2 * a.uniform_n)) * b;
-    // dynamic LDS: two planes of 4^n reals for the batch's (largest) width
-    Real* Mr = generic_lds<Real>();
-    Real* Mi = Mr + ((size_t)1 << (2 * (a.uniform_n > 0 ? a.uniform_n : MAX_QUBITS)));
-    lds_generic_body<Real, IDENT>(it.n, it.L, it.g, it.ang, T, it.err, f + (f ? b : 0),
-                                  g ? g + b : nullptr, delta ? delta + b : nullptr, U, a.err, a.mode,
-                                  Mr, Mi);
-}
-
-// LDS bytes of lds_kernel for a batch
-static size_t lds_kernel_bytes(const BatchArgs& a, size_t real_bytes) {
-    return generic_lds_bytes(a.uniform_n > 0 ? a.uniform_n : MAX_QUBITS, real_bytes);
+    Item it = resolve(a, b);
+    const double* T = it.err ? nullptr : reinterpret_cast<const double*>(a.targets) + 2 * it.toff;
+    // dynamic LDS: two planes of 4^n reals for the largest width
+    double* Mr = generic_lds<double>();
+    double* Mi = Mr + ((size_t)1 << (2 * MAX_QUBITS));
+    lds_generic_body<double>(it.n, it.L, it.g, it.ang, T, it.err, f + b, g ? g + b : nullptr,
+                             delta ? delta + b : nullptr, a.err, a.mode, Mr, Mi);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -357,22 +369,22 @@ static void launch_width(const BatchArgs& a, int n, int path, float* f, float* g
     constexpr int LIB = ANG ? SCHED_ISING : SCHED_DISCRETE;
     const bool lds = use_lds(n, path, sched_len(a), LIB), strict = path == QE_PATH_FP32_REG;
     switch (n) {
-        case 1: wave_kernel<1, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
-        case 2: wave_kernel<2, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
-        case 3: wave_kernel<3, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
+        case 1: wave_kernel<float, 1, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
+        case 2: wave_kernel<float, 2, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
+        case 3: wave_kernel<float, 3, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
         case 4:
-            if (lds) lds32_kernel<4, 1, FILTER, false, ANG><<<a.B, 64, 0, s>>>(a, f, g, delta, nullptr);
+            if (lds) lds32_kernel<4, 1, FILTER, ANG><<<a.B, 64, 0, s>>>(a, f, g, delta);
             else reg_kernel<float, 4, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta, strict);
             break;
         case 5:
             if (!lds) reg_kernel<float, 5, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta, strict);
             else if (schedule_for(5, sched_len(a), LIB).waves == 2)
-                lds32_kernel<5, 2, FILTER, false, ANG><<<a.B, 128, 0, s>>>(a, f, g, delta, nullptr);
+                lds32_kernel<5, 2, FILTER, ANG><<<a.B, 128, 0, s>>>(a, f, g, delta);
             else
-                lds32_kernel<5, 1, FILTER, false, ANG><<<a.B, 64, 0, s>>>(a, f, g, delta, nullptr);
+                lds32_kernel<5, 1, FILTER, ANG><<<a.B, 64, 0, s>>>(a, f, g, delta);
             break;
         default:
-            if (lds) lds32_kernel<6, 4, FILTER, false, ANG><<<a.B, 256, 0, s>>>(a, f, g, delta, nullptr);
+            if (lds) lds32_kernel<6, 4, FILTER, ANG><<<a.B, 256, 0, s>>>(a, f, g, delta);
             else reg_kernel<float, 6, FILTER, ANG><<<a.B, 256, 0, s>>>(a, f, g, delta, strict);
             break;
     }
@@ -459,42 +471,49 @@ hipError_t launch_mix_eval(const BatchArgs& a, const int32_t* work, float* f, fl
     return hipGetLastError();
 }
 
-hipError_t launch_eval_lds(const BatchArgs& a, bool fp64, void* f, void* g, void* delta,
-                           hipStream_t s) {
+template <bool ANG>
+static void launch_fp64_width(const BatchArgs& a, double* f, double* g, double* delta, hipStream_t s) {
+    const unsigned wgs = (unsigned)((a.B + WPB - 1) / WPB);
+    switch (a.uniform_n) {
+        case 1: wave_kernel<double, 1, false, ANG><<<wgs, 64 * WPB, 0, s>>>(a, f, g, delta); break;
+        case 2: wave_kernel<double, 2, false, ANG><<<wgs, 64 * WPB, 0, s>>>(a, f, g, delta); break;
+        case 3: wave_kernel<double, 3, false, ANG><<<wgs, 64 * WPB, 0, s>>>(a, f, g, delta); break;
+        case 4: reg_kernel<double, 4, false, ANG><<<wgs, 64 * WPB, 0, s>>>(a, f, g, delta, true); break;
+        case 5: reg_kernel<double, 5, false, ANG><<<wgs, 64 * WPB, 0, s>>>(a, f, g, delta, true); break;
+        default: reg_kernel<double, 6, false, ANG><<<a.B, 256, 0, s>>>(a, f, g, delta, true); break;
+    }
+}
+
+hipError_t launch_eval_fp64(const BatchArgs& a, double* f, double* g, double* delta, hipStream_t s) {
     if (a.B == 0) return hipSuccess;
-    if (fp64)
-        lds_kernel<double, false><<<a.B, 256, lds_kernel_bytes(a, 8), s>>>(a, (double*)f, (double*)g,
-                                                                           (double*)delta, nullptr);
-    else
-        lds_kernel<float, false><<<a.B, 256, lds_kernel_bytes(a, 4), s>>>(a, (float*)f, (float*)g,
-                                                                          (float*)delta, nullptr);
+    if (a.uniform_n == 0)
+        lds_kernel<<<a.B, 256, generic_lds_bytes(MAX_QUBITS, 8), s>>>(a, f, g, delta);
+    else if (a.angles) launch_fp64_width<true>(a, f, g, delta, s);
+    else launch_fp64_width<false>(a, f, g, delta, s);
     return hipGetLastError();
+}
+
+template <typename Real, bool ANG>
+static void launch_unitary_width(const BatchArgs& a, Real* out, hipStream_t s) {
+    const unsigned wgs = (unsigned)((a.B + WPB - 1) / WPB);
+    switch (a.uniform_n) {
+        case 1: unitary_kernel<Real, 1, ANG><<<wgs, 64 * WPB, 0, s>>>(a, out); break;
+        case 2: unitary_kernel<Real, 2, ANG><<<wgs, 64 * WPB, 0, s>>>(a, out); break;
+        case 3: unitary_kernel<Real, 3, ANG><<<wgs, 64 * WPB, 0, s>>>(a, out); break;
+        case 4: unitary_kernel<Real, 4, ANG><<<wgs, 64 * WPB, 0, s>>>(a, out); break;
+        case 5: unitary_kernel<Real, 5, ANG><<<wgs, 64 * WPB, 0, s>>>(a, out); break;
+        default: unitary_kernel<Real, 6, ANG><<<a.B, 256, 0, s>>>(a, out); break;
+    }
 }
 
 hipError_t launch_unitary(const BatchArgs& a, bool fp64, void* out, hipStream_t s) {
     if (a.B == 0) return hipSuccess;
     if (fp64) {
-        lds_kernel<double, true><<<a.B, 256, lds_kernel_bytes(a, 8), s>>>(a, nullptr, nullptr, nullptr,
-                                                                          (double*)out);
+        if (a.angles) launch_unitary_width<double, true>(a, (double*)out, s);
+        else launch_unitary_width<double, false>(a, (double*)out, s);
     } else {
-        float* o = (float*)out;
-        switch (a.uniform_n) {
-            case 1: lds_kernel<float, true><<<a.B, 256, lds_kernel_bytes(a, 4), s>>>(a, nullptr, nullptr, nullptr, o); break;
-            case 2: lds_kernel<float, true><<<a.B, 256, lds_kernel_bytes(a, 4), s>>>(a, nullptr, nullptr, nullptr, o); break;
-            case 3: lds_kernel<float, true><<<a.B, 256, lds_kernel_bytes(a, 4), s>>>(a, nullptr, nullptr, nullptr, o); break;
-            case 4:
-                if (a.angles) lds32_kernel<4, 1, false, true, true><<<a.B, 64, 0, s>>>(a, nullptr, nullptr, nullptr, o);
-                else lds32_kernel<4, 1, false, true><<<a.B, 64, 0, s>>>(a, nullptr, nullptr, nullptr, o);
-                break;
-            case 5:
-                if (a.angles) lds32_kernel<5, 1, false, true, true><<<a.B, 64, 0, s>>>(a, nullptr, nullptr, nullptr, o);
-                else lds32_kernel<5, 1, false, true><<<a.B, 64, 0, s>>>(a, nullptr, nullptr, nullptr, o);
-                break;
-            default:
-                if (a.angles) lds32_kernel<6, 4, false, true, true><<<a.B, 256, 0, s>>>(a, nullptr, nullptr, nullptr, o);
-                else lds32_kernel<6, 4, false, true><<<a.B, 256, 0, s>>>(a, nullptr, nullptr, nullptr, o);
-                break;
-        }
+        if (a.angles) launch_unitary_width<float, true>(a, (float*)out, s);
+        else launch_unitary_width<float, false>(a, (float*)out, s);
     }
     return hipGetLastError();
 }

@@ -89,9 +89,30 @@ __device__ __forceinline__ float2 phase_plus(float2 x, float c, float s) {    //
 __device__ __forceinline__ uint32_t f_bits(float f) { return __float_as_uint(f); }
 
 // --------------------------------------------------------- fitness reduction
+template <typename Real>
 struct FitOut {
-    float f, g, delta;
+    Real f, g, delta;
 };
+
+// A complex number in memory that promises the alignment of its parts only.
+struct __attribute__((aligned(8))) complex128 {
+    double x, y;
+};
+template <typename Real>
+using complex_of = std::conditional_t<sizeof(Real) == 8, complex128, float2>;
+
+__device__ __forceinline__ float real_sqrt(float x) { return sqrtf(x); }
+__device__ __forceinline__ double real_sqrt(double x) { return sqrt(x); }
+// (the two treat NaN differently, each as its kernels always have)
+__device__ __forceinline__ float clamp01(float x) { return fminf(fmaxf(x, 0.0f), 1.0f); }
+__device__ __forceinline__ double clamp01(double x) { return x < 0.0 ? 0.0 : (x > 1.0 ? 1.0 : x); }
+__device__ __forceinline__ float read_lane(float v, int g) {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), g));
+}
+__device__ __forceinline__ double read_lane(double v, int g) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), g),
+                            __builtin_amdgcn_readlane(__double2loint(v), g));
+}
 
 // Phase-insensitive fitness (QE_FIT_PHASE_INSENSITIVE) from the energy of M
 // off its diagonal: for unitary M, 1 - sum_i |M_ii|^2 / N = off / N, so the
@@ -108,61 +129,61 @@ __device__ __forceinline__ void fitness_pi(Real offs, int N, Real* f, Real* g, R
 // Reduction of M (held as per-lane partial sums: off-diagonal |m|^2 and the
 // lane's diagonal element, if any) into Eq. 11, or (mode) the
 // phase-insensitive fitness.
-__device__ __forceinline__ FitOut finish_fitness(float off, float dre, float dim, bool hasd,
-                                                 int N, int mode = QE_FIT_EQ11) {
-    const float offs = wave_sum(off);
+template <typename Real>
+__device__ __forceinline__ FitOut<Real> finish_fitness(Real off, Real dre, Real dim, bool hasd, int N,
+                                                       int mode = QE_FIT_EQ11) {
+    FitOut<Real> o;
+    const Real nan = (Real)__builtin_nan("");
+    const Real offs = wave_sum(off);
     if (mode == QE_FIT_PHASE_INSENSITIVE) {
-        FitOut o;
         fitness_pi(offs, N, &o.f, &o.g, &o.delta);
-        if (!(o.f == o.f)) o.f = __builtin_nanf("");
+        if (!(o.f == o.f)) o.f = nan;
         return o;
     }
-    const float tre = wave_sum(dre), tim = wave_sum(dim);
-    const float a = sqrtf(tre * tre + tim * tim);
-    float er = 1.0f, ei = 0.0f;
-    if (a > 0.0f) { er = tre / a; ei = tim / a; }
-    float dl = 0.0f;
+    const Real tre = wave_sum(dre), tim = wave_sum(dim);
+    const Real a = real_sqrt(tre * tre + tim * tim);
+    Real er = (Real)1, ei = (Real)0;
+    if (a > (Real)0) { er = tre / a; ei = tim / a; }
+    Real dl = (Real)0;
     if (hasd) {
-        const float xr = dre - er, xi = dim - ei;
+        const Real xr = dre - er, xi = dim - ei;
         dl = xr * xr + xi * xi;
     }
-    const float D = wave_sum(dl);
-    const float delta = 0.5f * (offs + D);
-    float q = delta / (float)N;
-    q = fminf(fmaxf(q, 0.0f), 1.0f);
-    FitOut o;
-    o.f = 1.0f - sqrtf(q);
-    o.g = a / (float)N;
+    const Real D = wave_sum(dl);
+    const Real delta = (Real)0.5 * (offs + D);
+    o.f = (Real)1 - real_sqrt(clamp01(delta / (Real)N));
+    o.g = a / (Real)N;
     o.delta = delta;
-    if (!(o.f == o.f) || !(delta == delta)) o.f = __builtin_nanf("");
+    if (!(o.f == o.f) || !(delta == delta)) o.f = nan;
     return o;
 }
 
 // ----------------------------------------------------- small widths (n <= 3)
 // One matrix element per lane (lane = i*N + j); a gate exchanges rows through
 // a lane xor.  Lanes >= N^2 hold nothing and only exchange among themselves.
-template <int NQ, bool IDENT, typename GateSrc>
-__device__ __forceinline__ bool run_small_path(const float* __restrict__ T, int L, GateSrc&& src,
-                                               float* U_out, FitOut* fit, int mode = QE_FIT_EQ11) {
+template <int NQ, bool IDENT, typename Real, typename GateSrc>
+__device__ __forceinline__ bool run_small_path(const Real* __restrict__ T, int L, GateSrc&& src,
+                                               Real* U_out, FitOut<Real>* fit, int mode = QE_FIT_EQ11) {
     constexpr int N = 1 << NQ;
     constexpr bool ANG = src_angled<GateSrc>();
     using SrcT = std::decay_t<decltype(src(0))>;
+    using C2 = complex_of<Real>;
     const int lane = (int)lane_id();
     const bool live = lane < N * N;
     const int i = (lane >> NQ) & (N - 1), j = lane & (N - 1);
     const SrcT dv0 = L > 0 ? src(0) : SrcT{};   // before the target: latencies overlap
-    float mr = 0.0f, mi = 0.0f;
+    Real mr = (Real)0, mi = (Real)0;
     if (live) {
         if (IDENT) {
-            mr = (i == j) ? 1.0f : 0.0f;
+            mr = (i == j) ? (Real)1 : (Real)0;
         } else {
-            const float2 v = reinterpret_cast<const float2*>(T)[(size_t)j * N + i];
+            const C2 v = reinterpret_cast<const C2*>(T)[(size_t)j * N + i];
             mr = v.x;
             mi = -v.y;
         }
     }
     bool ok = true;
-    const float r = 0.70710678118654752f;
+    const Real r = (Real)0.70710678118654752440084436210485, half = (Real)0.5;
     const int chunks = (L + 63) >> 6;
     for (int ch = 0; ch < chunks; ++ch) {
         const SrcT dvv = ch == 0 ? dv0 : src(ch);
@@ -171,37 +192,37 @@ __device__ __forceinline__ bool run_small_path(const float* __restrict__ T, int 
         const bool bad = (lane < cnt) && !desc_valid<ANG>(dv, NQ);
         if (__ballot(bad)) { ok = false; break; }
         // angled gates: lane g computes cos, sin of half of gate g's angle
-        float gc = 1.0f, gs = 0.0f;
+        Real gc = (Real)1, gs = (Real)0;
         if constexpr (ANG)
             if (lane < cnt && kind_ising((int)(dv & 15u))) half_angle(angle_of(dvv), &gc, &gs);
-        for (int g = 0; g < cnt; ++g) {
+        uint64_t todo = __ballot(lane < cnt && (dv & 15u) != (uint32_t)KIND_I);
+        while (todo) {
+            const int g = (int)__builtin_ctzll(todo);
+            todo &= todo - 1;
             const uint32_t d = __builtin_amdgcn_readlane(dv, g);
             const int kind = d & 15;
-            if (kind == KIND_I) continue;
-            const int t = (d >> 4) & 15;
-            const int tb = 1 << (NQ - 1 - t);
-            const int mask = tb << NQ;
-            const bool hi = (i & tb) != 0;
+            const int tp = NQ - 1 - (int)((d >> 4) & 15);
+            const bool hi = ((i >> tp) & 1) != 0;
+            const int mask = 1 << (tp + NQ);
             if constexpr (ANG) {
                 if (kind >= KIND_RX) {
-                    const float c = bits_f(__builtin_amdgcn_readlane(f_bits(gc), g));
-                    const float s = bits_f(__builtin_amdgcn_readlane(f_bits(gs), g));
+                    const Real c = read_lane(gc, g), s = read_lane(gs, g);
                     if (kind == KIND_RZ || kind == KIND_ZZ) {
                         // diagonal: e^{-i theta/2} where the (two-wire) parity is
                         // even, e^{i theta/2} where it is odd
                         bool odd = hi;
-                        if (kind == KIND_ZZ) odd = ((i >> (NQ - 1 - t)) ^ (i >> (NQ - 1 - (int)((d >> 8) & 15)))) & 1;
-                        const float sg = odd ? s : -s;
-                        const float br = mr, bi = mi;
+                        if (kind == KIND_ZZ) odd = ((i >> tp) ^ (i >> (NQ - 1 - (int)((d >> 8) & 15)))) & 1;
+                        const Real sg = odd ? s : -s;
+                        const Real br = mr, bi = mi;
                         mr = c * br - sg * bi;
                         mi = c * bi + sg * br;
                     } else {
-                        const float pr = __shfl_xor(mr, mask, 64), pi = __shfl_xor(mi, mask, 64);
+                        const Real pr = __shfl_xor(mr, mask, 64), pi = __shfl_xor(mi, mask, 64);
                         if (kind == KIND_RX) {       // c m - i s p on both rows
                             mr = c * mr + s * pi;
                             mi = c * mi - s * pr;
                         } else {                     // c m -+ s p (R_y)
-                            const float sg = hi ? s : -s;
+                            const Real sg = hi ? s : -s;
                             mr = c * mr + sg * pr;
                             mi = c * mi + sg * pi;
                         }
@@ -209,7 +230,7 @@ __device__ __forceinline__ bool run_small_path(const float* __restrict__ T, int 
                     continue;
                 }
             }
-            const float pr = __shfl_xor(mr, mask, 64), pi = __shfl_xor(mi, mask, 64);
+            const Real pr = __shfl_xor(mr, mask, 64), pi = __shfl_xor(mi, mask, 64);
             bool on = true;
             if (kind_controlled(kind)) on = (i >> (NQ - 1 - ((d >> 8) & 15))) & 1;
             if (!on) continue;
@@ -217,24 +238,30 @@ __device__ __forceinline__ bool run_small_path(const float* __restrict__ T, int 
                 mr = pr; mi = pi;
             } else if (kind == KIND_CV || kind == KIND_CVDG) {
                 // both rows of the pair: (m + p)/2 +- i (m - p)/2
-                const float sr = mr + pr, si = mi + pi, dr = mr - pr, di = mi - pi;
-                if (kind == KIND_CV) { mr = 0.5f * (sr - di); mi = 0.5f * (si + dr); }
-                else { mr = 0.5f * (sr + di); mi = 0.5f * (si - dr); }
+                const Real sr = mr + pr, si = mi + pi, dr = mr - pr, di = mi - pi;
+                if (kind == KIND_CV) { mr = half * (sr - di); mi = half * (si + dr); }
+                else { mr = half * (sr + di); mi = half * (si - dr); }
             } else if (kind == KIND_H) {
-                const float xr = hi ? pr - mr : mr + pr, xi = hi ? pi - mi : mi + pi;
+                const Real xr = hi ? pr - mr : mr + pr, xi = hi ? pi - mi : mi + pi;
                 mr = xr * r; mi = xi * r;
             } else if (hi) {   // T
-                const float br = mr, bi = mi;
+                const Real br = mr, bi = mi;
                 mr = (br - bi) * r;
                 mi = (br + bi) * r;
             }
         }
     }
-    if (U_out && live) reinterpret_cast<float2*>(U_out)[(size_t)i * N + j] = make_float2(mr, mi);
+    if (U_out && live) {
+        const Real nan = (Real)__builtin_nan("");
+        C2 v;
+        v.x = ok ? mr : nan;
+        v.y = ok ? mi : nan;
+        reinterpret_cast<C2*>(U_out)[(size_t)i * N + j] = v;
+    }
     if (fit) {
         const bool dg = live && (i == j);
-        const float off = (live && !dg) ? mr * mr + mi * mi : 0.0f;
-        *fit = finish_fitness(off, dg ? mr : 0.0f, dg ? mi : 0.0f, dg, N, mode);
+        const Real off = (live && !dg) ? mr * mr + mi * mi : (Real)0;
+        *fit = finish_fitness(off, dg ? mr : (Real)0, dg ? mi : (Real)0, dg, N, mode);
     }
     return ok;
 }
@@ -260,8 +287,7 @@ __device__ __forceinline__ bool run_small_path(const float* __restrict__ T, int 
 // adds column pt to column pc.  Every other gate addresses its logical rows
 // through phi, which is linear in the pair-index bits, so its offsets are
 // the images of the logical ones and combine by XOR.  The fitness reads the
-// diagonal entry of column j at stored row phi(j).  (Unitary outputs keep
-// the rows in place: IDENT moves them.)
+// diagonal entry of column j at stored row phi(j).
 __device__ __forceinline__ int ins0(int x, int pos) {
     return ((x >> pos) << (pos + 1)) | (x & ((1 << pos) - 1));
 }
@@ -289,7 +315,7 @@ struct RowMap {
     uint32_t b;
 };
 
-template <int NQ, int W, bool IDENT, bool NCV = false, typename GateSrc>
+template <int NQ, int W, bool NCV = false, typename GateSrc>
 __device__ __forceinline__ bool run_lds_path(float2* M, uint4* gt, const float* __restrict__ T, int L,
                                              GateSrc&& src, RowMap* map_out, int wave = -1) {
     // CV body of one wavefront per circuit (a gate table of per-row-group
@@ -321,8 +347,7 @@ __device__ __forceinline__ bool run_lds_path(float2* M, uint4* gt, const float* 
         const int r = m * RG + rg;
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
-            if (IDENT) tv[c][m] = make_float2(r == j + c ? 1.0f : 0.0f, 0.0f);
-            else tv[c][m] = T2[(size_t)(j + c) * N + r];
+            tv[c][m] = T2[(size_t)(j + c) * N + r];
         }
     }
     const SrcT dv0 = L > 0 ? src(0) : SrcT{};
@@ -331,7 +356,7 @@ __device__ __forceinline__ bool run_lds_path(float2* M, uint4* gt, const float* 
         const int r = m * RG + rg;
 #pragma unroll
         for (int c = 0; c < CPL; ++c)
-            M[r * N + j + c] = IDENT ? tv[c][m] : make_float2(tv[c][m].x, -tv[c][m].y);
+            M[r * N + j + c] = make_float2(tv[c][m].x, -tv[c][m].y);
     }
     wave_lds_fence();
     bool ok = true;
@@ -347,7 +372,6 @@ __device__ __forceinline__ bool run_lds_path(float2* M, uint4* gt, const float* 
         return *reinterpret_cast<float2*>(reinterpret_cast<char*>(M) + byte_off);
     };
     constexpr uint32_t ROWB = NQ + 3;      // log2 of a row's byte stride (N * 8)
-    constexpr bool RELABEL = !IDENT;
     // the logical-to-stored row map (wave-uniform): column p of A in bits
     // 6p..6p+5, translation b
     uint64_t Amap = 0;
@@ -429,27 +453,25 @@ __device__ __forceinline__ bool run_lds_path(float2* M, uint4* gt, const float* 
         const int cpos = NQ - 1 - (int)((dv >> 8) & 15u);
         const bool ctl = kind_two_wire(kind);
         const int lo = ctl ? min(tpos, cpos) : tpos, hi = ctl ? max(tpos, cpos) : tpos;
-        const bool perm = RELABEL && (kind == KIND_NOT || kind == KIND_CNOT);
+        const bool perm = kind == KIND_NOT || kind == KIND_CNOT;
         // fold this chunk's NOT / CNOT into the row map, in circuit order; each
         // lane keeps the map in force at its own gate
         uint64_t myA = Amap;
         uint32_t myB = bmap;
-        if constexpr (RELABEL) {
-            uint64_t pm = __ballot(lane < cnt && perm);
-            while (pm) {
-                const int g = (int)__builtin_ctzll(pm);
-                pm &= pm - 1;
-                const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)dv, g);
-                const int pt = NQ - 1 - (int)((d >> 4) & 15u);
-                const uint32_t colt = (uint32_t)(Amap >> (6 * pt)) & 63u;
-                if ((d & 15u) == (uint32_t)KIND_NOT) {
-                    bmap ^= colt;
-                } else {
-                    const int pc = NQ - 1 - (int)((d >> 8) & 15u);
-                    Amap ^= (uint64_t)colt << (6 * pc);
-                }
-                if (lane > g) { myA = Amap; myB = bmap; }
+        uint64_t pm = __ballot(lane < cnt && perm);
+        while (pm) {
+            const int g = (int)__builtin_ctzll(pm);
+            pm &= pm - 1;
+            const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)dv, g);
+            const int pt = NQ - 1 - (int)((d >> 4) & 15u);
+            const uint32_t colt = (uint32_t)(Amap >> (6 * pt)) & 63u;
+            if ((d & 15u) == (uint32_t)KIND_NOT) {
+                bmap ^= colt;
+            } else {
+                const int pc = NQ - 1 - (int)((d >> 8) & 15u);
+                Amap ^= (uint64_t)colt << (6 * pc);
             }
+            if (lane > g) { myA = Amap; myB = bmap; }
         }
         // stored byte offset of logical row bit q under the lane's map
         auto colb = [&](int q) -> uint32_t { return ((uint32_t)(myA >> (6 * q)) & 63u) << ROWB; };
@@ -551,7 +573,7 @@ __device__ __forceinline__ bool run_lds_path(float2* M, uint4* gt, const float* 
                     return;
                 }
             }
-            static_assert(!NCV || (RELABEL && !ANG), "the NCV body needs the relabelling");
+            static_assert(!NCV || !ANG, "the NCV body has no angles");
             if (NCV || (k >= KIND_CNOT && k <= KIND_CVDG)) {
                 constexpr int NIT = (N / 4) / RG;
                 uint32_t offm[NIT];
@@ -563,10 +585,7 @@ __device__ __forceinline__ bool run_lds_path(float2* M, uint4* gt, const float* 
 #pragma unroll
                 for (int m = 0; m < NIT; ++m) { A[m] = at(a0 ^ offm[m]); B[m] = at(a1 ^ offm[m]); }
                 // (with the row relabelling, NOT and CNOT never get here)
-                if (!RELABEL && !NCV && k == KIND_CNOT) {
-#pragma unroll
-                    for (int m = 0; m < NIT; ++m) { at(a0 ^ offm[m]) = B[m]; at(a1 ^ offm[m]) = A[m]; }
-                } else {
+                {
                     // CV: (a, b) -> V (a, b); CV+ is CV with a - b negated: one
                     // fused multiply-add of the exact halves and the factor
                     // +-1/2 per result, as in the CV body of sampled circuits
@@ -602,16 +621,11 @@ __device__ __forceinline__ bool run_lds_path(float2* M, uint4* gt, const float* 
                     float2 A[NIT], B[NIT];
 #pragma unroll
                     for (int m = 0; m < NIT; ++m) { A[m] = at(a0 ^ offm[m]); B[m] = at(a1 ^ offm[m]); }
-                    if (!RELABEL && k == KIND_NOT) {
 #pragma unroll
-                        for (int m = 0; m < NIT; ++m) { at(a0 ^ offm[m]) = B[m]; at(a1 ^ offm[m]) = A[m]; }
-                    } else {   // H
-#pragma unroll
-                        for (int m = 0; m < NIT; ++m) {
-                            const float2 a = A[m], b = B[m];
-                            at(a0 ^ offm[m]) = make_float2((a.x + b.x) * r, (a.y + b.y) * r);
-                            at(a1 ^ offm[m]) = make_float2((a.x - b.x) * r, (a.y - b.y) * r);
-                        }
+                    for (int m = 0; m < NIT; ++m) {   // H
+                        const float2 a = A[m], b = B[m];
+                        at(a0 ^ offm[m]) = make_float2((a.x + b.x) * r, (a.y + b.y) * r);
+                        at(a1 ^ offm[m]) = make_float2((a.x - b.x) * r, (a.y - b.y) * r);
                     }
                 }
             }
@@ -736,12 +750,12 @@ __device__ __forceinline__ bool run_lds_path(float2* M, uint4* gt, const float* 
 }
 
 // ----------------------------------------------------- generic LDS body
-// One workgroup of 256 threads per circuit, any width 1..6, any precision:
-// M lives in LDS and every gate is one pass over the row pairs it touches,
-// followed by a workgroup barrier.  The FP64 instance re-checks elite
-// circuits and builds FP64 target unitaries; the FP32 one cross-checks the
-// tuned kernels.  err != 0 on entry: the circuit is malformed and only NaN is
-// written.  Outputs (f, g, delta: one element; U: N*N complex) may be null.
+// One workgroup of 256 threads per circuit, any width 1..6: M lives in LDS
+// and every gate is one pass over the row pairs it touches, followed by a
+// workgroup barrier.  It serves the FP64 calls whose circuits differ in width
+// within one launch (mixed-width batches, re-checks of mixed populations).
+// err != 0 on entry: the circuit is malformed and only NaN is written.
+// Outputs (f, g, delta: one element) may be null.
 template <typename Real>
 struct Cplx {
     Real r, i;
@@ -855,11 +869,11 @@ __host__ __device__ inline size_t generic_lds_bytes(int n, size_t real_bytes) {
 // NULL, in which case the Ising kinds are invalid descriptors.  Mr, Mi: LDS
 // for the real and imaginary parts of the 2^n x 2^n matrix (the caller sizes
 // them for its widths).
-template <typename Real, bool IDENT>
+template <typename Real>
 __device__ __forceinline__ void lds_generic_body(int n, int L, const uint16_t* gates,
                                                  const uint32_t* angles, const Real* T, uint32_t err,
-                                                 Real* f, Real* g, Real* delta, Real* U,
-                                                 uint32_t* errw, int mode, Real* Mr, Real* Mi) {
+                                                 Real* f, Real* g, Real* delta, uint32_t* errw, int mode,
+                                                 Real* Mr, Real* Mi) {
     __shared__ Real red[8];
     const int tid = threadIdx.x, nt = blockDim.x;
     const int lg = err == QE_DEVERR_WIDTH ? 1 : n;     // log2 of the matrix size
@@ -869,13 +883,8 @@ __device__ __forceinline__ void lds_generic_body(int n, int L, const uint16_t* g
     if (ok) {
         for (int e = tid; e < NN; e += nt) {
             const int i = e >> lg, j = e & (N - 1);
-            if (IDENT) {
-                Mr[e] = (i == j) ? (Real)1 : (Real)0;
-                Mi[e] = 0;
-            } else {
-                Mr[e] = T[2 * ((size_t)j * N + i)];
-                Mi[e] = -T[2 * ((size_t)j * N + i) + 1];
-            }
+            Mr[e] = T[2 * ((size_t)j * N + i)];
+            Mi[e] = -T[2 * ((size_t)j * N + i) + 1];
         }
         __syncthreads();
         for (int l = 0; l < L; ++l) {
@@ -923,16 +932,6 @@ __device__ __forceinline__ void lds_generic_body(int n, int L, const uint16_t* g
             __syncthreads();
         }
         if (!ok) err = QE_DEVERR_DESC;
-    }
-    const Real nan = (Real)__builtin_nan("");
-    if (IDENT) {
-        if (U)
-            for (int e = tid; e < NN; e += nt) {
-                U[2 * e] = ok ? Mr[e] : nan;
-                U[2 * e + 1] = ok ? Mi[e] : nan;
-            }
-        if (tid == 0 && err) atomicOr(errw, err);
-        return;
     }
     lds_fitness<Real>(Mr, Mi, N, ok, err, f, g, delta, errw, mode, red);
 }

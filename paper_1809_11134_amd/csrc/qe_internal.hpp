@@ -67,8 +67,7 @@ hipError_t launch_target_check(const BatchArgs& a, bool fp64, void* f, void* g, 
 hipError_t launch_mix_sort(const BatchArgs& a, int32_t* work, hipStream_t s);
 hipError_t launch_mix_eval(const BatchArgs& a, const int32_t* work, float* f, float* g, float* delta,
                            hipStream_t s);
-hipError_t launch_eval_lds(const BatchArgs& a, bool fp64, void* f, void* g, void* delta,
-                           hipStream_t s);
+hipError_t launch_eval_fp64(const BatchArgs& a, double* f, double* g, double* delta, hipStream_t s);
 hipError_t launch_unitary(const BatchArgs& a, bool fp64, void* out, hipStream_t s);
 
 // dense.hip: every gate expanded to its full segment matrix and multiplied

@@ -420,8 +420,8 @@ __device__ __forceinline__ void eval_circuit(const LoopArgs& a, uint32_t gen, ui
     float fv;
     bool ok;
     if constexpr (W == 0 && NQ <= 3) {
-        FitOut o;
-        ok = run_small_path<NQ, false>(T, L, src, nullptr, &o, a.fit_mode);
+        FitOut<float> o;
+        ok = run_small_path<NQ, false>(T, L, src, (float*)nullptr, &o, a.fit_mode);
         fv = o.f;
     } else if constexpr (W == 0) {
         float gd, dd;
@@ -437,7 +437,7 @@ __device__ __forceinline__ void eval_circuit(const LoopArgs& a, uint32_t gen, ui
         RowMap map{};
         // circuits the sampler decodes hold only {I, NOT, CNOT, CV, CV+}
         constexpr bool NCV = SAMPLE && !ISING;
-        ok = run_lds_path<NQ, W, false, NCV>(M, gt, T, L, src, &map, W == 1 ? 0 : -1);
+        ok = run_lds_path<NQ, W, NCV>(M, gt, T, L, src, &map, W == 1 ? 0 : -1);
         constexpr int WR = reduction_waves<NQ>();
         static_assert(WR == 1 || WR == W, "the reduction's wavefronts are the circuit's");
         if constexpr (W > 1) __syncthreads();     // every wavefront's columns are in place
@@ -1102,7 +1102,11 @@ __global__ __launch_bounds__(GA_BLOCK) void ga_update_kernel(LoopArgs a, uint64_
     const unsigned long long r = (unsigned long long)w0 * (W >> 32) +
                                  (((unsigned long long)w0 * (W & 0xFFFFFFFFull)) >> 32);
     auto select = [&](int k) -> int {
-        const unsigned long long ptr = (r + (unsigned long long)k * W) / (unsigned long long)P;
+        // floor((r + k W) / P): the numerator stays below 2^49, so the double
+        // quotient (below 2^37, spacing 2^-15) never reaches an integer that
+        // the exact one, at least 1 / 4096 away, lies under
+        const unsigned long long ptr =
+            (unsigned long long)((double)(r + (unsigned long long)k * W) / (double)P);
         int lo = 0, hi = P - 1;        // first m with pre[m + 1] > ptr
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
@@ -1259,243 +1263,70 @@ __global__ __launch_bounds__(1024) void elite_select_kernel(LoopArgs a, const fl
     }
 }
 
+// Mixed populations (discrete libraries): widths differ from circuit to circuit.
 __global__ __launch_bounds__(256) void elite_eval_kernel(LoopArgs a, const uint16_t* __restrict__ gates,
-                                                         const uint32_t* __restrict__ angles,
                                                          int k, const int32_t* __restrict__ idx,
                                                          double* __restrict__ f64) {
     const int i = blockIdx.x / k, e = blockIdx.x % k;
     const int c = idx[(size_t)i * k + e];
     uint32_t err = (c < 0 || c >= a.P) ? (uint32_t)QE_DEVERR_RANGE : 0u;
-    const int n = a.inst_n ? a.inst_n[i] : a.n, L = a.inst_L ? a.inst_L[i] : a.L;
-    const size_t row = (a.inst_goff ? (size_t)a.inst_goff[i] : (size_t)i * a.P * L) + (size_t)(err ? 0 : c) * L;
-    const double* T = a.target64 + 2 * (a.inst_toff ? (size_t)a.inst_toff[i] : (size_t)i << (2 * n));
+    const int n = a.inst_n[i], L = a.inst_L[i];
+    const size_t row = (size_t)a.inst_goff[i] + (size_t)(err ? 0 : c) * L;
+    const double* T = a.target64 + 2 * (size_t)a.inst_toff[i];
     double* Mr = generic_lds<double>();         // dynamic LDS for the context's largest width
-    lds_generic_body<double, false>(n, L, gates + row, angles ? angles + row : nullptr, T, err,
-                                    f64 + blockIdx.x, nullptr, nullptr, nullptr, a.err, a.fit_mode,
-                                    Mr, Mr + ((size_t)1 << (2 * a.n)));
+    lds_generic_body<double>(n, L, gates + row, nullptr, T, err, f64 + blockIdx.x, nullptr, nullptr, a.err,
+                             a.fit_mode, Mr, Mr + ((size_t)1 << (2 * a.n)));
 }
 
-// FP64 re-check of elite circuits of width NQ (4 or 5) over a discrete
-// library: W wavefronts per circuit (each owning N / W columns: gates mix
-// rows only, so the wavefronts of a circuit never exchange data until the
-// reduction), CPB circuits per workgroup, the product U T^dagger (Eq. 11)
-// as complex128 in LDS.  Lane l of a wavefront owns column
-// j = w N / W + l mod (N / W) and row group h = l div (N / W); a gate's row
-// pairs are its pair indices (the target bit taken out) or, for a
-// controlled gate, its quad indices (target and control bits taken out),
-// the row group supplying the low bits.  NOT and CNOT move no data: as in
-// the FP32 LDS path, logical row r is stored at row A r ^ b (A's column p in
-// bits 6p..6p+5), and they only update A and b.  CV and CV+ take the halves
-// of a + b and i (a - b); H and T are applied as their matrices say.  The
-// results agree with the generic FP64 body to rounding.
-template <int NQ, int W>
-struct Elite64Layout {
-    static constexpr int N = 1 << NQ, LPR = N / W, RG = 64 / LPR;
-    static constexpr int RGB = RG == 2 ? 1 : (RG == 4 ? 2 : 3);
-    static_assert(RG == (1 << RGB) && RG <= 8, "row groups");
-    static_assert(NQ - 2 >= RGB, "a controlled gate's quads cover the row groups");
-};
-
-// One gate on the lane's pairs: base = stored row of the lane's first pair
-// (row group bits, control row and the map's translation folded in), pass[k]
-// = stored image of pair-index bit RGB + k, tstep = stored image of the
-// target bit.
-template <int NQ, int W, bool CTL>
-__device__ __forceinline__ void elite64_pairs(double2* M, int kind, uint32_t base, const uint32_t* pass,
-                                              uint32_t tstep, int j) {
-    using LY = Elite64Layout<NQ, W>;
-    constexpr int QB = NQ - 1 - (CTL ? 1 : 0);       // bits of the pair index
-    constexpr int NP = (1 << QB) / LY::RG;           // pairs per lane
-    double2 X[NP], Y[NP];
-    int o0[NP], o1[NP];
-#pragma unroll
-    for (int m = 0; m < NP; ++m) {
-        uint32_t sr = base;
-#pragma unroll
-        for (int k = 0; (1 << k) < NP; ++k)
-            if ((m >> k) & 1) sr ^= pass[k];
-        o0[m] = (int)((sr << NQ) | (uint32_t)j);
-        o1[m] = (int)(((sr ^ tstep) << NQ) | (uint32_t)j);
-        X[m] = M[o0[m]];
-        Y[m] = M[o1[m]];
-    }
-    constexpr double S2 = 0.70710678118654752440084436210485;
-#pragma unroll
-    for (int m = 0; m < NP; ++m) {
-        const double2 a = X[m], bb = Y[m];
-        double2 x, y;
-        if (CTL) {
-            // V = [[1+i, 1-i], [1-i, 1+i]] / 2: a' = (s + i d) / 2, b' = (s - i d) / 2
-            // with s = a + b, d = a - b; V+ swaps the two
-            const double sr = 0.5 * (a.x + bb.x), si = 0.5 * (a.y + bb.y);
-            const double dr = 0.5 * (a.x - bb.x), di = 0.5 * (a.y - bb.y);
-            const double2 p = make_double2(sr - di, si + dr), q = make_double2(sr + di, si - dr);
-            x = kind == KIND_CV ? p : q;
-            y = kind == KIND_CV ? q : p;
-        } else if (kind == KIND_H) {
-            x = make_double2(S2 * (a.x + bb.x), S2 * (a.y + bb.y));
-            y = make_double2(S2 * (a.x - bb.x), S2 * (a.y - bb.y));
-        } else {   // T: b' = b (1 + i) / sqrt 2
-            x = a;
-            y = make_double2(S2 * (bb.x - bb.y), S2 * (bb.x + bb.y));
-        }
-        M[o0[m]] = x;
-        M[o1[m]] = y;
-    }
-}
-
-template <int NQ, int W, int CPB>
-__global__ __launch_bounds__(64 * W * CPB) void elite64_kernel(LoopArgs a, const uint16_t* __restrict__ gates,
-                                                               int k, const int32_t* __restrict__ idx,
-                                                               double* __restrict__ f64) {
-    using LY = Elite64Layout<NQ, W>;
-    constexpr int N = LY::N, LPR = LY::LPR, RG = LY::RG, RGB = LY::RGB;
-    __shared__ double2 Ms[CPB][N * N];
-    __shared__ double red[CPB][W];
-    const int wave = (int)(threadIdx.x >> 6), lane = (int)lane_id();
-    const int circ = wave / W, wv = wave % W;
-    const uint32_t ci = __builtin_amdgcn_readfirstlane(blockIdx.x * CPB + (uint32_t)circ);
-    const bool valid = ci < (uint32_t)a.I * (uint32_t)k;   // (every wavefront reaches the barrier)
-    const uint32_t i = valid ? ci / (uint32_t)k : 0u;
-    const int c = valid ? idx[ci] : 0;
+// FP64 re-check of elite circuits of uniform width NQ: one circuit per
+// wavefront, four per workgroup (n = 6: one per workgroup), in registers.
+template <int NQ, bool ANG>
+__global__ __launch_bounds__(256) void elite64_kernel(LoopArgs a, const uint16_t* __restrict__ gates,
+                                                      const uint32_t* __restrict__ angles, int k,
+                                                      const int32_t* __restrict__ idx,
+                                                      double* __restrict__ f64) {
+    constexpr bool WHOLE = NQ == 6;
+    __shared__ double red[4][3];
+    const int wave = WHOLE ? (int)(threadIdx.x >> 6) : 0, lane = (int)lane_id();
+    const uint32_t ci = __builtin_amdgcn_readfirstlane(WHOLE ? blockIdx.x : blockIdx.x * 4u + (threadIdx.x >> 6));
+    if (ci >= (uint32_t)a.I * (uint32_t)k) return;
+    const uint32_t i = ci / (uint32_t)k;
+    const int c = __builtin_amdgcn_readfirstlane(idx[ci]);
     uint32_t err = (c < 0 || c >= a.P) ? (uint32_t)QE_DEVERR_RANGE : 0u;
     const int L = a.L;
-    const uint16_t* g = gates + ((size_t)i * a.P + (size_t)(err ? 0 : c)) * L;
-    const double2* T = reinterpret_cast<const double2*>(a.target64) + ((size_t)i << (2 * NQ));
-    double2* M = Ms[circ];
-    const int j = wv * LPR + lane % LPR, h = lane / LPR;
-    uint64_t A = 0;                                   // the row map, identity
-#pragma unroll
-    for (int p = 0; p < NQ; ++p) A |= (uint64_t)(1u << p) << (6 * p);
-    uint32_t b = 0;
-    bool ok = valid && err == 0;
-    if (ok) {
-        // M = T^dagger on this wavefront's columns: M[r][j] = conj(T[j][r])
-#pragma unroll
-        for (int m = 0; m < N / RG; ++m) {
-            const int r = h + m * RG;
-            const double2 t = T[(size_t)j * N + r];
-            M[r * N + j] = make_double2(t.x, -t.y);
-        }
-        wave_lds_fence();
-        for (int l0 = 0; l0 < L && ok; l0 += 64) {
-            // the chunk's gate program, one gate per lane: descriptor checks,
-            // the row map in force at each gate (NOT and CNOT folded in, in
-            // circuit order), and each data-moving gate's stored offsets
-            const int cnt = min(64, L - l0);
-            const bool in = lane < cnt;
-            const uint32_t dv = in ? (uint32_t)g[l0 + lane] : 0u;
-            if (__ballot(in && !desc_valid(dv, NQ))) { ok = false; break; }
-            const int kind = (int)(dv & 15u);
-            const int tp = NQ - 1 - (int)((dv >> 4) & 15u), cp = NQ - 1 - (int)((dv >> 8) & 15u);
-            const bool perm = in && (kind == KIND_NOT || kind == KIND_CNOT);
-            uint64_t myA = A;
-            uint32_t myB = b;
-            uint64_t pm = __ballot(perm);
-            while (pm) {
-                const int gg = (int)__builtin_ctzll(pm);
-                pm &= pm - 1;
-                const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)dv, gg);
-                const int pt = NQ - 1 - (int)((d >> 4) & 15u);
-                const uint32_t colt = (uint32_t)(A >> (6 * pt)) & 63u;
-                if ((d & 15u) == (uint32_t)KIND_NOT) {
-                    b ^= colt;
-                } else {
-                    const int pc = NQ - 1 - (int)((d >> 8) & 15u);
-                    A ^= (uint64_t)colt << (6 * pc);
-                }
-                if (lane > gg) { myA = A; myB = b; }
-            }
-            const bool live = in && kind != KIND_I && !perm;
-            const bool ctl = kind == KIND_CV || kind == KIND_CVDG;
-            auto col = [&](int p) -> uint32_t { return (uint32_t)(myA >> (6 * (p & 7))) & 63u; };
-            const int lo = ctl ? min(tp, cp) : tp, hi = ctl ? max(tp, cp) : NQ;
-            auto img = [&](int kk) -> uint32_t {       // pair-index bit kk -> stored row bits
-                int pos = kk < lo ? kk : kk + 1;
-                pos = pos < hi ? pos : pos + 1;
-                return col(pos);
-            };
-            const uint32_t gbase = live ? (myB ^ (ctl ? col(cp) : 0u)) : 0u;
-            const uint32_t gt = live ? col(tp) : 0u;
-            uint32_t gimg[NQ - 1];
-#pragma unroll
-            for (int kk = 0; kk < NQ - 1; ++kk) gimg[kk] = live ? img(kk) : 0u;
-            uint64_t todo = __ballot(live);
-            while (todo) {
-                const int gg = (int)__builtin_ctzll(todo);
-                todo &= todo - 1;
-                auto rl = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, gg); };
-                const int kg = (int)rl((uint32_t)kind);
-                uint32_t base = rl(gbase);
-                uint32_t im[NQ - 1];
-#pragma unroll
-                for (int kk = 0; kk < NQ - 1; ++kk) im[kk] = rl(gimg[kk]);
-#pragma unroll
-                for (int kk = 0; kk < RGB; ++kk)
-                    if ((h >> kk) & 1) base ^= im[kk];
-                const uint32_t ts = rl(gt);
-                if (kg == KIND_CV || kg == KIND_CVDG)
-                    elite64_pairs<NQ, W, true>(M, kg, base, im + RGB, ts, j);
-                else
-                    elite64_pairs<NQ, W, false>(M, kg, base, im + RGB, ts, j);
-                wave_lds_fence();
-            }
-        }
-        if (valid && !ok && !err) err = QE_DEVERR_DESC;
-    }
-    auto stored = [&](uint32_t r) -> uint32_t {      // stored row of logical row r
-        uint32_t s = b;
-#pragma unroll
-        for (int p = 0; p < NQ; ++p)
-            if ((r >> p) & 1) s ^= (uint32_t)(A >> (6 * p)) & 63u;
-        return s;
+    const size_t row = ((size_t)i * a.P + (size_t)(err ? 0 : c)) * L;
+    using SrcT = std::conditional_t<ANG, uint2, uint32_t>;
+    auto src = [&](int ch) -> SrcT {
+        const int p = ch * 64 + lane;
+        if constexpr (ANG) return p < L ? make_uint2((uint32_t)gates[row + p], angles[row + p]) : make_uint2(0u, 0u);
+        else return p < L ? (uint32_t)gates[row + p] : 0u;
     };
-    // Eq. 11 (or the phase-insensitive form): the off-diagonal energy over
-    // the lane's logical rows h, h + RG, ..., summed over the wavefronts of
-    // the circuit in order; then the first wavefront reads the diagonal
-    double off = 0.0;
-    if (ok) {
-        const uint32_t sh = stored((uint32_t)h);
-#pragma unroll
-        for (int m = 0; m < N / RG; ++m) {
-            const uint32_t sr = sh ^ (stored((uint32_t)(m * RG)) ^ b);
-            const double2 v = M[(sr << NQ) | (uint32_t)j];
-            if (h + m * RG != j) off += v.x * v.x + v.y * v.y;
+    double fv = __builtin_nan("");
+    if (err == 0) {
+        const double* T = a.target64 + ((size_t)2 * i << (2 * NQ));
+        bool ok;
+        if constexpr (NQ <= 3) {
+            FitOut<double> o;
+            ok = run_small_path<NQ, false>(T, L, src, (double*)nullptr, &o, a.fit_mode);
+            fv = o.f;
+        } else {
+            RegMatrix<double, NQ> M;
+            M.place(wave);
+            const SrcT dv0 = src(0);
+            M.load(T);
+            ok = M.template run<true>(L, src, dv0);
+            double g, d;
+            fv = M.fitness(a.fit_mode, &g, &d, wave, red);
+        }
+        if (!ok) {
+            err = QE_DEVERR_DESC;
+            fv = __builtin_nan("");
+        } else if (!(fv == fv)) {
+            err = QE_DEVERR_NUMERIC;
         }
     }
-    off = wave_sum(off);
-    if constexpr (W > 1) {
-        if (lane == 0) red[circ][wv] = off;
-        __syncthreads();
-        off = 0.0;
-#pragma unroll
-        for (int w = 0; w < W; ++w) off += red[circ][w];
-    }
-    if (wv != 0 || !valid) return;
-    double dr = 0.0, di = 0.0;
-    if (ok && lane < N) {
-        const double2 v = M[(stored((uint32_t)lane) << NQ) | (uint32_t)lane];
-        dr = v.x;
-        di = v.y;
-    }
-    double fv, gv, dl;
-    if (a.fit_mode == QE_FIT_PHASE_INSENSITIVE) {
-        fitness_pi(off, N, &fv, &gv, &dl);
-    } else {
-        const double tr = wave_sum(dr), ti = wave_sum(di);
-        const double am = sqrt(tr * tr + ti * ti);
-        double er = 1.0, ei = 0.0;
-        if (am > 0.0) { er = tr / am; ei = ti / am; }
-        double D = 0.0;
-        if (lane < N) { const double xr = dr - er, xi = di - ei; D = xr * xr + xi * xi; }
-        dl = 0.5 * (off + wave_sum(D));
-        double q = dl / (double)N;
-        q = q < 0.0 ? 0.0 : (q > 1.0 ? 1.0 : q);
-        fv = 1.0 - sqrt(q);
-    }
-    if (lane == 0) {
-        if (ok && !(fv == fv)) err = QE_DEVERR_NUMERIC;
-        f64[ci] = ok ? fv : (double)__builtin_nan("");
+    if (wave == 0 && lane == 0) {
+        f64[ci] = fv;
         if (err) atomicOr(a.err, err);
     }
 }
@@ -1690,11 +1521,12 @@ hipError_t launch_state_gather(const LoopArgs& a, int which, void* dst, hipStrea
 
 hipError_t launch_ga_update(const LoopArgs& a, uint64_t gen, const float* f, hipStream_t s) {
     // one round of gene pairs per thread, as long as the populations together
-    // do not fill the GPU several times over (every workgroup repeats its
-    // population's prefix)
+    // make no more than two workgroups per compute unit: every workgroup
+    // repeats its population's prefix and draws (256 populations of 64: 10.8 us
+    // at 512 workgroups in all, 11.4 at 1024, 16.0 at 2048)
     const int half = a.P / 2;
     const uint64_t rounds = ((uint64_t)half * a.L + GA_BLOCK - 1) / GA_BLOCK;
-    const uint64_t most = std::max<uint64_t>(1, 2048 / (uint64_t)a.I);
+    const uint64_t most = std::max<uint64_t>(1, 512 / (uint64_t)a.I);
     // (and at most 1024 pairs a workgroup: 48 KB of LDS in all)
     const uint64_t least = std::max<uint64_t>(1, ((uint64_t)half + 1023) / 1024);
     const uint32_t parts = (uint32_t)std::max<uint64_t>(least, std::min({rounds, most, (uint64_t)half}));
@@ -1727,14 +1559,24 @@ hipError_t launch_elite_select(const LoopArgs& a, const float* f, int k, int32_t
 
 hipError_t launch_elite_eval(const LoopArgs& a, const uint16_t* gates, const uint32_t* angles, int k,
                              const int32_t* idx, double* f64, hipStream_t s) {
-    // uniform widths 4 and 5 over a discrete library: one wavefront per circuit
     const unsigned nc = (unsigned)a.I * (unsigned)k;
-    if (!a.inst_n && !angles && a.n == 5) {
-        elite64_kernel<5, 2, 2><<<(nc + 1) / 2, 256, 0, s>>>(a, gates, k, idx, f64);
-    } else if (!a.inst_n && !angles && a.n == 4) {
-        elite64_kernel<4, 1, 4><<<(nc + 3) / 4, 256, 0, s>>>(a, gates, k, idx, f64);
-    } else {
-        elite_eval_kernel<<<nc, 256, generic_lds_bytes(a.n, sizeof(double)), s>>>(a, gates, angles, k, idx, f64);
+    if (a.inst_n) {
+        elite_eval_kernel<<<nc, 256, generic_lds_bytes(a.n, sizeof(double)), s>>>(a, gates, k, idx, f64);
+        return hipGetLastError();
+    }
+    auto go = [&](auto nq) {
+        constexpr int NQ = decltype(nq)::value;
+        const unsigned wgs = NQ == 6 ? nc : (nc + 3) / 4;
+        if (angles) elite64_kernel<NQ, true><<<wgs, 256, 0, s>>>(a, gates, angles, k, idx, f64);
+        else elite64_kernel<NQ, false><<<wgs, 256, 0, s>>>(a, gates, nullptr, k, idx, f64);
+    };
+    switch (a.n) {
+        case 1: go(std::integral_constant<int, 1>{}); break;
+        case 2: go(std::integral_constant<int, 2>{}); break;
+        case 3: go(std::integral_constant<int, 3>{}); break;
+        case 4: go(std::integral_constant<int, 4>{}); break;
+        case 5: go(std::integral_constant<int, 5>{}); break;
+        default: go(std::integral_constant<int, 6>{}); break;
     }
     return hipGetLastError();
 }

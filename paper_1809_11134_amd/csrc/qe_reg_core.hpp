@@ -100,10 +100,10 @@ struct RegMatrix {
         }
     }
     __device__ __forceinline__ void load(const double* __restrict__ T) {
-        const double2* t = reinterpret_cast<const double2*>(T) + ((size_t)j * N + q * (NQ == 4 ? 1 : E));
+        const complex128* t = reinterpret_cast<const complex128*>(T) + ((size_t)j * N + q * (NQ == 4 ? 1 : E));
 #pragma unroll
         for (int m = 0; m < E; ++m) {
-            const double2 v = t[(NQ == 4 ? Q : 1) * m];
+            const complex128 v = t[(NQ == 4 ? Q : 1) * m];
             put(m, v.x, -v.y);
         }
     }
@@ -260,12 +260,6 @@ struct RegMatrix {
         *delta_out = dlt;
         return (Real)1 - real_sqrt(qq);
     }
-    static __device__ __forceinline__ float real_sqrt(float x) { return sqrtf(x); }
-    static __device__ __forceinline__ double real_sqrt(double x) { return sqrt(x); }
-    // as the FP32 LDS-staged and the generic FP64 kernels clamp (they differ
-    // for NaN)
-    static __device__ __forceinline__ float clamp01(float x) { return fminf(fmaxf(x, 0.0f), 1.0f); }
-    static __device__ __forceinline__ double clamp01(double x) { return x < 0.0 ? 0.0 : (x > 1.0 ? 1.0 : x); }
 };
 
 }  // namespace qe
