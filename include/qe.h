@@ -311,8 +311,8 @@ qe_status qe_eval_population(qe_ctx* ctx, const uint16_t* gates_dev, const uint3
  * QE_ERR_STATE); the segment keys and decisions that call left are used,
  * with the slot indices of its shared-slot search (the update then handles
  * only the slots several circuits shared, and runs the next generation's
- * search) or, for populations too large for the search, drawn again from
- * the SAMPLE stream. */
+ * search) or, for contexts without the search, drawn again from the SAMPLE
+ * stream. */
 qe_status qe_update(qe_ctx* ctx, uint64_t gen, const uint32_t* slots_dev,
                     const uint16_t* gates_dev, const uint32_t* angles_dev, const float* f_dev,
                     void* stream);
@@ -329,9 +329,9 @@ qe_status qe_generation(qe_ctx* ctx, uint64_t gen, float* f_dev, void* stream);
  * qe_run_graph make before the update): circuit construction (as qe_sample,
  * into gates_dev, and into slots_dev unless it is NULL) fused with the
  * fitness evaluation (f_dev), the segment fitness (Sec. IV-E.1) and the
- * generation's mutation decisions (Sec. IV-F).  For populations of at most
- * 4096 (circuit, position) entries and 256 positions, a search for the slots
- * that more than one circuit uses runs first (skipped when the context holds
+ * generation's mutation decisions (Sec. IV-F).  For contexts of more than
+ * 524288 (circuit, position) entries in populations of at most 4096 entries and
+ * 256 positions, a search for the slots that more than one circuit uses runs first (skipped when the context holds
  * its result already: the slots drawn depend on the seed and the generation
  * only, and the update after qe_sample_eval, qe_generation and every
  * generation of qe_run_graph searches the next generation's slots; the

@@ -68,7 +68,7 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
-template <typename Real, int NQ, bool ANG>
+template <typename Real, int NQ, bool ANG, int COLS = reg_columns<NQ>()>
 __device__ __forceinline__ void reg_item(const BatchArgs& a, int b, Item it, int wave, bool strict,
                                          Real (*red)[3], Real* __restrict__ f, Real* __restrict__ g,
                                          Real* __restrict__ delta) {
@@ -80,7 +80,7 @@ __device__ __forceinline__ void reg_item(const BatchArgs& a, int b, Item it, int
     Real fv, gv, dv;
     fv = gv = dv = (Real)__builtin_nan("");
     if (it.err == 0) {
-        RegMatrix<Real, NQ> M;
+        RegMatrix<Real, NQ, COLS> M;
         M.place(wave);
         auto src = [&](int ch) { return batch_gate<ANG>(it, ch * 64 + lane); };
         const auto dv0 = src(0);
@@ -101,18 +101,19 @@ __device__ __forceinline__ void reg_item(const BatchArgs& a, int b, Item it, int
     }
 }
 
-// Four circuits per workgroup, one per wavefront; n = 6: one per workgroup.
-template <typename Real, int NQ, bool FILTER, bool ANG>
+// Four circuits per workgroup, one per wavefront, or (n = 6 with 16 columns per
+// wavefront) one per workgroup.
+template <typename Real, int NQ, bool FILTER, bool ANG, int COLS = reg_columns<NQ>()>
 __global__ __launch_bounds__(256) void reg_kernel(BatchArgs a, Real* __restrict__ f, Real* __restrict__ g,
                                                   Real* __restrict__ delta, bool strict) {
     __shared__ Real red[4][3];
     const int wave = (int)(threadIdx.x >> 6);
-    constexpr bool WHOLE = RegGeom<NQ>::W == 4;
+    constexpr bool WHOLE = RegGeom<NQ, COLS>::W == 4;
     const int b = __builtin_amdgcn_readfirstlane(WHOLE ? (int)blockIdx.x : (int)blockIdx.x * WPB + wave);
     if (b >= a.B) return;
     const Item it = resolve(a, b);
     if (FILTER && it.n != NQ) return;
-    reg_item<Real, NQ, ANG>(a, b, it, WHOLE ? wave : 0, strict, red, f, g, delta);
+    reg_item<Real, NQ, ANG, COLS>(a, b, it, WHOLE ? wave : 0, strict, red, f, g, delta);
 }
 
 // Unitaries of a uniform-width batch: the product started from the identity.
@@ -208,6 +209,9 @@ __global__ __launch_bounds__(64 * W) void lds32_kernel(BatchArgs a, float* __res
 // dispatched in index order, so the heaviest items start first
 // (longest-processing-time order).
 constexpr int MIX_BUCKETS = 7;          // widths 6..1, then malformed widths
+// Fewest circuits of a mixed batch whose width-6 ones run with one column per
+// lane.
+constexpr int MIX_COLUMNS_MIN = 4096;
 constexpr int MIX_LCLASSES = 16;        // lengths >= 120, 112..119, ..., 8..15, < 8
 
 __device__ __forceinline__ int mix_bucket(int n) { return (n >= 1 && n <= MAX_QUBITS) ? 6 - n : 6; }
@@ -219,33 +223,64 @@ __device__ __forceinline__ int mix_key(const BatchArgs& a, int b) {
     const int lc = len >= 120 ? 0 : (len < 8 ? MIX_LCLASSES - 1 : MIX_LCLASSES - 1 - (int)(len >> 3));
     return mix_bucket(a.nq[b]) * MIX_LCLASSES + lc;
 }
-// circuits per work item: one of width 6 (four wavefronts), four of the others
-__device__ __forceinline__ int mix_per_item(int k) { return k == 0 ? 1 : 4; }
+// circuits per work item: four, or (width 6 with 16 columns per wavefront) one
+// of four wavefronts
+__host__ __device__ __forceinline__ bool mix_columns(int B) { return B >= MIX_COLUMNS_MIN; }
+__device__ __forceinline__ int mix_per_item(int k, bool columns) { return k == 0 && !columns ? 1 : 4; }
 
 // meta: [0..7) first order position, [8..15) first item (8 entries, the last
 // the total), [16..23) count per bucket.
-__global__ __launch_bounds__(1024) void mix_bucket_kernel(BatchArgs a, int32_t* order, int32_t* meta) {
-    constexpr int K = MIX_BUCKETS * MIX_LCLASSES;
+// One workgroup.  The LDS atomics bound it (the circuits of a wavefront mostly
+// share a width, so that their counts collide): each key counts in MIX_REP
+// places, by lane, and when one tile of MIX_PER circuits per thread holds the
+// batch, the first pass's counts are the ranks of the second (16384 circuits:
+// 14.4 -> 12.0 us).
+constexpr int MIX_SORT = 1024, MIX_PER = 16, MIX_REP = 4;
+__global__ __launch_bounds__(MIX_SORT) void mix_bucket_kernel(BatchArgs a, int32_t* order, int32_t* meta) {
+    constexpr int K = MIX_BUCKETS * MIX_LCLASSES * MIX_REP;
     __shared__ int cnt[K], cursor[K];
     const int tid = threadIdx.x;
-    for (int k = tid; k < K; k += blockDim.x) cnt[k] = 0;
+    for (int k = tid; k < K; k += MIX_SORT) cnt[k] = 0;
+    int key[MIX_PER], rank[MIX_PER];
+    auto read_tile = [&](int b0) {
+#pragma unroll
+        for (int c = 0; c < MIX_PER; ++c) {
+            const int b = b0 + c * MIX_SORT + tid;
+            key[c] = b < a.B ? mix_key(a, b) * MIX_REP + tid % MIX_REP : -1;
+        }
+    };
+    const bool one_tile = a.B <= MIX_PER * MIX_SORT;
+    read_tile(0);
     __syncthreads();
-    for (int b = tid; b < a.B; b += blockDim.x) atomicAdd(&cnt[mix_key(a, b)], 1);
+    for (int b0 = 0; b0 < a.B; b0 += MIX_PER * MIX_SORT) {
+        if (b0 > 0) read_tile(b0);
+#pragma unroll
+        for (int c = 0; c < MIX_PER; ++c)
+            if (key[c] >= 0) rank[c] = atomicAdd(&cnt[key[c]], 1);
+    }
     __syncthreads();
-    static_assert(K <= 128, "two keys per lane of one wavefront");
+    static_assert(K % 64 == 0, "whole runs of counts per lane");
     if (tid < 64) {
-        // exclusive prefix sum of the K counts over one wavefront, two per lane
-        const int k0 = 2 * tid;
-        const int c0 = k0 < K ? cnt[k0] : 0, c1 = k0 + 1 < K ? cnt[k0 + 1] : 0;
-        int incl = c0 + c1;
+        // exclusive prefix sum of the counts over one wavefront, a run per lane
+        constexpr int RUN = K / 64;
+        int c[RUN], sum = 0;
+#pragma unroll
+        for (int u = 0; u < RUN; ++u) {
+            c[u] = cnt[tid * RUN + u];
+            sum += c[u];
+        }
+        int incl = sum;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
             const int o = __shfl_up(incl, d, 64);
             if (tid >= d) incl += o;
         }
-        const int excl = incl - c0 - c1;
-        if (k0 < K) cursor[k0] = excl;
-        if (k0 + 1 < K) cursor[k0 + 1] = excl + c0;
+        int at = incl - sum;
+#pragma unroll
+        for (int u = 0; u < RUN; ++u) {
+            cursor[tid * RUN + u] = at;
+            at += c[u];
+        }
     }
     __syncthreads();
     if (tid == 0) {
@@ -253,17 +288,24 @@ __global__ __launch_bounds__(1024) void mix_bucket_kernel(BatchArgs a, int32_t* 
         // has a key, so the last width ends at B)
         int item = 0;
         for (int k = 0; k < MIX_BUCKETS; ++k) {
-            const int pos = cursor[k * MIX_LCLASSES];
-            const int end = k + 1 < MIX_BUCKETS ? cursor[(k + 1) * MIX_LCLASSES] : a.B;
+            const int pos = cursor[k * MIX_LCLASSES * MIX_REP];
+            const int end = k + 1 < MIX_BUCKETS ? cursor[(k + 1) * MIX_LCLASSES * MIX_REP] : a.B;
             meta[k] = pos;
             meta[8 + k] = item;
             meta[16 + k] = end - pos;
-            item += (end - pos + mix_per_item(k) - 1) / mix_per_item(k);
+            const int per = mix_per_item(k, mix_columns(a.B));
+            item += (end - pos + per - 1) / per;
         }
         meta[8 + MIX_BUCKETS] = item;
     }
     __syncthreads();
-    for (int b = tid; b < a.B; b += blockDim.x) order[atomicAdd(&cursor[mix_key(a, b)], 1)] = b;
+    for (int b0 = 0; b0 < a.B; b0 += MIX_PER * MIX_SORT) {
+        if (!one_tile) read_tile(b0);
+#pragma unroll
+        for (int c = 0; c < MIX_PER; ++c)
+            if (key[c] >= 0)
+                order[one_tile ? cursor[key[c]] + rank[c] : atomicAdd(&cursor[key[c]], 1)] = b0 + c * MIX_SORT + tid;
+    }
 }
 
 template <int NQ>
@@ -295,6 +337,11 @@ __device__ __forceinline__ void mix_wave_item(const BatchArgs& a, int b, float* 
     }
 }
 
+// COLUMNS: circuits of width 6 with one column per lane (large batches).  (They
+// and the other widths in two launches, so that the small widths keep the
+// occupancy of 52 VGPRs: no gain at 16384 circuits, 92 us either way, and 55
+// against 37 us at 4096, where each launch ends in a nearly empty round.)
+template <bool COLUMNS>
 __global__ __launch_bounds__(256) void mix_kernel(BatchArgs a, const int32_t* __restrict__ order,
                                                   const int32_t* __restrict__ meta,
                                                   float* __restrict__ f, float* __restrict__ g,
@@ -306,15 +353,18 @@ __global__ __launch_bounds__(256) void mix_kernel(BatchArgs a, const int32_t* __
     int k = 0;
     while (k + 1 < MIX_BUCKETS && item >= meta[8 + k + 1]) ++k;
     const int wave = (int)(threadIdx.x >> 6);
-    const int per = mix_per_item(k);
+    const int per = mix_per_item(k, COLUMNS);
     const int local = (item - meta[8 + k]) * per;
     const int sub = per == 1 ? 0 : wave;
     int b = local + sub < meta[16 + k] ? order[meta[k] + local + sub] : -1;
     if (b >= a.B) b = -1;        // an order written for another batch never indexes past this one
     b = __builtin_amdgcn_readfirstlane(b);
-    if (b < 0) return;           // (width 6: the whole workgroup)
+    if (b < 0) return;           // (four wavefronts per circuit: the whole workgroup)
     switch (k) {
-        case 0: reg_item<float, 6, false>(a, b, resolve(a, b), wave, false, red, f, g, delta); break;
+        case 0:
+            if constexpr (COLUMNS) reg_item<float, 6, false, 64>(a, b, resolve(a, b), 0, false, red, f, g, delta);
+            else reg_item<float, 6, false>(a, b, resolve(a, b), wave, false, red, f, g, delta);
+            break;
         case 1: reg_item<float, 5, false>(a, b, resolve(a, b), 0, false, red, f, g, delta); break;
         case 2: reg_item<float, 4, false>(a, b, resolve(a, b), 0, false, red, f, g, delta); break;
         case 3: mix_wave_item<3>(a, b, f, g, delta); break;
@@ -385,6 +435,8 @@ static void launch_width(const BatchArgs& a, int n, int path, float* f, float* g
             break;
         default:
             if (lds) lds32_kernel<6, 4, FILTER, ANG><<<a.B, 256, 0, s>>>(a, f, g, delta);
+            else if ((uint32_t)a.B >= reg6_columns_min(ANG))
+                reg_kernel<float, 6, FILTER, ANG, 64><<<wgrid, wblock, 0, s>>>(a, f, g, delta, strict);
             else reg_kernel<float, 6, FILTER, ANG><<<a.B, 256, 0, s>>>(a, f, g, delta, strict);
             break;
     }
@@ -404,8 +456,8 @@ hipError_t launch_eval_fp32(const BatchArgs& a, int path, float* f, float* g, fl
         launch_width<false, false>(a, a.uniform_n, path, f, g, delta, s);
     } else if (path == QE_PATH_FP32 && work) {
         // one launch over width-sorted work items (LDS-staged for n >= 4)
-        mix_bucket_kernel<<<1, 1024, 0, s>>>(a, work + MIX_WORK_META, work);
-        mix_kernel<<<a.B, 256, 0, s>>>(a, work + MIX_WORK_META, work, f, g, delta);
+        mix_bucket_kernel<<<1, MIX_SORT, 0, s>>>(a, work + MIX_WORK_META, work);
+        return launch_mix_eval(a, work, f, g, delta, s);
     } else {
         width_check_kernel<<<(a.B + 255) / 256, 256, 0, s>>>(a, f, g, delta);
         for (int n = 1; n <= MAX_QUBITS; ++n) launch_width<true, false>(a, n, path, f, g, delta, s);
@@ -461,13 +513,18 @@ hipError_t launch_target_check(const BatchArgs& a, bool fp64, void* f, void* g, 
 }
 
 hipError_t launch_mix_sort(const BatchArgs& a, int32_t* work, hipStream_t s) {
-    if (a.B > 0) mix_bucket_kernel<<<1, 1024, 0, s>>>(a, work + MIX_WORK_META, work);
+    if (a.B > 0) mix_bucket_kernel<<<1, MIX_SORT, 0, s>>>(a, work + MIX_WORK_META, work);
     return hipGetLastError();
 }
 
 hipError_t launch_mix_eval(const BatchArgs& a, const int32_t* work, float* f, float* g, float* delta,
                            hipStream_t s) {
-    if (a.B > 0) mix_kernel<<<a.B, 256, 0, s>>>(a, work + MIX_WORK_META, work, f, g, delta);
+    if (a.B == 0) return hipSuccess;
+    // (the workgroups past the items leave: how many there are of each width is
+    // known on the device only)
+    const int32_t* order = work + MIX_WORK_META;
+    if (mix_columns(a.B)) mix_kernel<true><<<a.B / 4 + MIX_BUCKETS, 256, 0, s>>>(a, order, work, f, g, delta);
+    else mix_kernel<false><<<a.B, 256, 0, s>>>(a, order, work, f, g, delta);
     return hipGetLastError();
 }
 

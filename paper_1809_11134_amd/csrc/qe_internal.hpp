@@ -41,6 +41,13 @@ struct Sched {
 // the CV body), circuits with angled gates (Ising library).
 enum : int { SCHED_DISCRETE = 0, SCHED_SAMPLED = 1, SCHED_ISING = 2, SCHED_CLASSES = 3 };
 Sched schedule_for(int n, int L, int lib_class = SCHED_DISCRETE);
+// Fewest circuits of width 6 for which the register-resident kernels hold one
+// column per lane (one wavefront per circuit) instead of 16 columns per
+// wavefront (four per circuit): with fewer, the longer chain of one wavefront
+// is not hidden.  48 gates: 512 circuits 23.0 us either way, 768 24.3 against
+// 27.4, 8192 93 against 153; Ising 768 44.2 against 40.6, 1024 45.5 against
+// 48.9, 8192 205 against 259.
+constexpr uint32_t reg6_columns_min(bool angled) { return angled ? 1024u : 640u; }
 // MFMA paths: the fewest non-identity gates a group needs to be fused into a
 // block (smaller groups go gate by gate in FP32), per width and length class
 int mfma_min_block(int n, int L);
@@ -152,8 +159,9 @@ struct LoopArgs {
     const int64_t* inst_goff;
     const int64_t* inst_toff;
     int64_t genes;                     // genes per genome buffer (all populations)
-    // QEQEA, populations of at most DEDUP_MAX_ENTRIES entries (P * L) of at
-    // most 256 positions and fewer than 2^31 slots: per (circuit, position)
+    // QEQEA, more than DEDUP_MIN_TOTAL entries (I * P * L), in populations of at
+    // most DEDUP_MAX_ENTRIES (P * L) of at most 256 positions and fewer than
+    // 2^31 slots: per (circuit, position)
     // entry of a generation, its slot index, with bit 31 set if another
     // circuit uses the same slot; two buffers of I * P * L words, generation g
     // in buffer g & 1, so that the search of the next generation can run
@@ -167,6 +175,13 @@ struct LoopArgs {
 };
 constexpr uint32_t DUP_SHARED = 0x80000000u;
 constexpr int DEDUP_MAX_ENTRIES = 4096;
+// Contexts of at most this many entries in all go without the search: it takes
+// one workgroup per population and 15-20 us however few there are, more than
+// the random accesses it saves while those stay in the caches (us per
+// generation with and without: n=3 P=256 L=16, 1 population 26.1 / 12.3, 64 54 /
+// 41, 128 79 / 70; n=5 P=64 L=40, 1 25.7 / 16.6, 128 62 / 58, 256 98 / 110, 512
+// 157 / 194; n=4 P=100 L=24, 128 49 / 44, 512 118 / 153).
+constexpr int DEDUP_MIN_TOTAL = 524288;
 // words of the search's LDS hash table for a population of `entries`
 // entries: at most half full, whole multiples of 256 (at most 32 KB)
 __host__ __device__ inline uint32_t dedup_table(uint32_t entries) { return (2u * entries + 255u) & ~255u; }

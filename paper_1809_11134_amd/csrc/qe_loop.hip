@@ -318,21 +318,22 @@ __device__ void commit_alone(const LoopArgs& a, uint32_t i, uint32_t s, float v,
 // ISING: circuits of the Ising library, whose gates carry angles (read from
 // angles_in, or with SAMPLE decoded and written to angles_out).  W: wavefronts
 // per circuit of the LDS-staged layout, 0 the one-entry-per-lane (n <= 3) or
-// register-resident layout (one wavefront per circuit, four at n = 6).  With
+// register-resident layout (one wavefront per circuit; n = 6: four, or with
+// CPB = 4 circuits per workgroup one, a column per lane).  With
 // several wavefronts and SAMPLE only the first samples; the others take its
 // descriptors from xch (two buffers of 64 entries, by chunk parity, so one
 // barrier per chunk separates a chunk's writes from the next chunk's).
-template <int NQ, int W>
-constexpr int circuit_waves() { return W == 0 ? (NQ == 6 ? 4 : 1) : W; }
+template <int NQ, int W, int CPB>
+constexpr int circuit_waves() { return W == 0 ? (NQ == 6 && CPB == 1 ? 4 : 1) : W; }
 
-template <int NQ, int W, bool SAMPLE, bool ISING>
+template <int NQ, int W, bool SAMPLE, bool ISING, int CPB>
 __device__ __forceinline__ void eval_circuit(const LoopArgs& a, uint32_t gen, uint32_t ci,
                                              const uint16_t* gates_in, const uint32_t* angles_in,
                                              uint32_t* slots_out, uint16_t* gates_out,
                                              uint32_t* angles_out, float* f_out, bool writer,
                                              bool decide, float2* M, uint4* gt, float (*red)[3],
                                              void* xch = nullptr) {
-    constexpr int WV = circuit_waves<NQ, W>();
+    constexpr int WV = circuit_waves<NQ, W, CPB>();
     const uint32_t i = ci / (uint32_t)a.P, k = ci % (uint32_t)a.P;
     const int lane = (int)lane_id();
     const int L = a.L;
@@ -426,7 +427,7 @@ __device__ __forceinline__ void eval_circuit(const LoopArgs& a, uint32_t gen, ui
     } else if constexpr (W == 0) {
         float gd, dd;
         const int wave = WV == 1 ? 0 : (int)(threadIdx.x >> 6);
-        RegMatrix<float, NQ> mat;
+        RegMatrix<float, NQ, NQ == 6 && WV == 1 ? 64 : reg_columns<NQ>()> mat;
         mat.place(wave);
         const SrcT dv0 = src(0);
         mat.load(T);
@@ -478,7 +479,7 @@ __device__ __forceinline__ void eval_circuit(const LoopArgs& a, uint32_t gen, ui
         mark_mutation(a, gen, i, k);
 }
 
-template <int NQ, int W, bool SAMPLE, bool ISING = false, int CPB = (circuit_waves<NQ, W>() == 1 ? 4 : 1)>
+template <int NQ, int W, bool SAMPLE, bool ISING, int CPB>
 __global__ __launch_bounds__(256) void population_kernel(LoopArgs a, uint64_t gen64,
                                                          const uint16_t* __restrict__ gates_in,
                                                          const uint32_t* __restrict__ angles_in,
@@ -493,15 +494,15 @@ __global__ __launch_bounds__(256) void population_kernel(LoopArgs a, uint64_t ge
     const uint32_t bid = xcd_swizzle(blockIdx.x, gridDim.x);
     const int wave = (int)(threadIdx.x >> 6);
     if constexpr (W == 0) {
-        // CPB circuits per workgroup, one per wavefront; n = 6: one per
+        // CPB circuits per workgroup, one per wavefront, or one circuit per
         // workgroup of four
-        constexpr int WV = circuit_waves<NQ, W>();
+        constexpr int WV = circuit_waves<NQ, W, CPB>();
         static_assert(WV == 1 || CPB == 1, "one circuit per workgroup of several wavefronts");
         __shared__ float red[4][3];
         __shared__ uint2 xch[WV > 1 ? 128 : 1];
         const uint32_t ci = __builtin_amdgcn_readfirstlane(WV == 1 ? bid * CPB + (uint32_t)wave : bid);
         if (ci >= total) return;
-        eval_circuit<NQ, 0, SAMPLE, ISING>(a, gen, ci, gates_in, angles_in, slots_out, gates_out,
+        eval_circuit<NQ, 0, SAMPLE, ISING, CPB>(a, gen, ci, gates_in, angles_in, slots_out, gates_out,
                                            angles_out, f_out, WV == 1 || threadIdx.x < 64, decide, nullptr,
                                            nullptr, red, WV == 1 ? nullptr : static_cast<void*>(xch));
     } else {
@@ -517,7 +518,7 @@ __global__ __launch_bounds__(256) void population_kernel(LoopArgs a, uint64_t ge
         if (ci >= total) return;
         // (W > 1: the gate tables are unused, the first one is the
         // descriptor exchange)
-        eval_circuit<NQ, W, SAMPLE, ISING>(a, gen, ci, gates_in, angles_in, slots_out, gates_out,
+        eval_circuit<NQ, W, SAMPLE, ISING, CPB>(a, gen, ci, gates_in, angles_in, slots_out, gates_out,
                                            angles_out, f_out, W == 1 || threadIdx.x < 64, decide,
                                            M[W == 1 ? wave : 0], GT[wave], red,
                                            W == 1 ? nullptr : static_cast<void*>(GT[0]));
@@ -1392,7 +1393,7 @@ static void launch_population(const LoopArgs& a, uint64_t gen, const uint16_t* g
     const Sched sc = schedule_for(a.n, a.L, a.lib == LIB_ISING ? SCHED_ISING : (SAMPLE ? SCHED_SAMPLED : SCHED_DISCRETE));
     auto go = [&](auto nq, auto w, auto cpb, auto ising) {
         constexpr int NQ = decltype(nq)::value, W = decltype(w)::value, CPB = decltype(cpb)::value;
-        constexpr int WV = circuit_waves<NQ, W>();
+        constexpr int WV = circuit_waves<NQ, W, CPB>();
         population_kernel<NQ, W, SAMPLE, decltype(ising)::value, CPB>
             <<<blocks(total, CPB), 64 * WV * CPB, 0, s>>>(a, gen, gin, ain, sout, gout, aout, f, decide);
     };
@@ -1425,6 +1426,7 @@ static void launch_population(const LoopArgs& a, uint64_t gen, const uint16_t* g
             case 5: w45(integral_constant<int, 5>{}); break;
             default:
                 if (sc.lds) go(integral_constant<int, 6>{}, c4, c1, ising);
+                else if (total >= reg6_columns_min(decltype(ising)::value)) go(integral_constant<int, 6>{}, c0, c4, ising);
                 else go(integral_constant<int, 6>{}, c0, c1, ising);
                 break;
         }

@@ -23,6 +23,10 @@
 // registers and back itself (4 exchanges each way), which costs less than
 // keeping the maps: with 4 registers one gate in one needs an exchange.
 //
+// 64 registers (width 6, one column per lane): every wire is a register bit, so
+// a gate's word is its entry.  Tables of 64 entries (target 8 t, control c):
+//   0 CV and CV+, H   1 CNOT, T   2 interaction (t < c), NOT   3 R_x   4 R_y   5 R_z
+//
 // Multiplies and adds stay separate (one rounding each) except in CV, whose
 // last step is a fused multiply-add of exact halves.
 #pragma once
@@ -40,11 +44,23 @@ typedef double f64x8 __attribute__((ext_vector_type(8)));
 struct f64x32 {
     f64x16 lo, hi;
 };
+struct f32x128 {
+    f32x32 a, b, c, d;
+};
 template <typename V>
 __device__ __forceinline__ auto reg_get(const V& x, int i) { return x[i]; }
 __device__ __forceinline__ double reg_get(const f64x32& x, int i) { return i < 16 ? x.lo[i] : x.hi[i - 16]; }
+__device__ __forceinline__ float reg_get(const f32x128& x, int i) {
+    return i < 32 ? x.a[i] : i < 64 ? x.b[i - 32] : i < 96 ? x.c[i - 64] : x.d[i - 96];
+}
 template <typename V, typename R>
 __device__ __forceinline__ void reg_set(V& x, int i, R v) { x[i] = v; }
+__device__ __forceinline__ void reg_set(f32x128& x, int i, float v) {
+    if (i < 32) x.a[i] = v;
+    else if (i < 64) x.b[i - 32] = v;
+    else if (i < 96) x.c[i - 64] = v;
+    else x.d[i - 96] = v;
+}
 __device__ __forceinline__ void reg_set(f64x32& x, int i, double v) {
     if (i < 16) x.lo[i] = v;
     else x.hi[i - 16] = v;
@@ -95,6 +111,9 @@ struct SlotMap {
 
 #define QR_ELEMS16 "0,1,2,3,4,5,6,7,8,9,10,11,12,13,14,15"
 #define QR_ELEMS4 "0,1,2,3"
+#define QR_ELEMS64                                                                                   \
+    "0,1,2,3,4,5,6,7,8,9,10,11,12,13,14,15,16,17,18,19,20,21,22,23,24,25,26,27,28,29,30,31,"         \
+    "32,33,34,35,36,37,38,39,40,41,42,43,44,45,46,47,48,49,50,51,52,53,54,55,56,57,58,59,60,61,62,63"
 
 // The rows a of a gate whose target and control are register bits QT, QC, and
 // their partners.
@@ -313,6 +332,43 @@ struct SlotMap {
     QR_WANT("2", R2, ".Lqr%=e") "s_mov_b32 s50,2\n" QR_CALL("c5")                                    \
     ".Lqr%=e:\n"
 
+// Width 6, 64 registers: the gate's scalars always come with it (CV and CV+
+// share a body: A, B = +-1/2, which keeps the bodies within 40 KB of
+// instruction cache).
+#define QR_SET8 ".set QT,\\n>>3\n.set QC,\\n&7\n"
+#define QR_TWO64 "1,2,3,4,5,8,10,11,12,13,16,17,19,20,21,24,25,26,28,29,32,33,34,35,37,40,41,42,43,44"
+#define QR_ONE64 "0,9,18,27,36,45"
+#define QR_UP64 "1,2,3,4,5,10,11,12,13,19,20,21,28,29,37"      /* t < c */
+#define QR_B2_64(name, text) QR_BODY(name, QR_TWO64, QR_SET8 text)
+#define QR_B1_64(name, text) QR_BODY(name, QR_ONE64, QR_SET8 text)
+#define QR_T2_64(two, one)                                                                           \
+    ".irp n," QR_ELEMS64 "\n.if ((\\n>>3)>5)|((\\n&7)>5)\ns_branch .Lqr%=e\n"                         \
+    ".elseif (\\n>>3)==(\\n&7)\ns_branch .Lqr%=" one "\\n\n.else\ns_branch .Lqr%=" two "\\n\n.endif\n.endr\n"
+#define QR_TU_64(up, one)                                                                            \
+    ".irp n," QR_ELEMS64 "\n.if ((\\n>>3)>5)|((\\n&7)>5)|((\\n>>3)>(\\n&7))\ns_branch .Lqr%=e\n"         \
+    ".elseif (\\n>>3)==(\\n&7)\ns_branch .Lqr%=" one "\\n\n.else\ns_branch .Lqr%=" up "\\n\n.endif\n.endr\n"
+#define QR_T1_64(one)                                                                                \
+    ".irp n," QR_ELEMS64 "\n.if ((\\n>>3)==(\\n&7))&((\\n>>3)<6)\ns_branch .Lqr%=" one "\\n\n.else\n"  \
+    "s_branch .Lqr%=e\n.endif\n.endr\n"
+#define QR_TABLES64_0 QR_T2_64("cv", "h") QR_T2_64("cx", "t") QR_T1_64("x")
+#define QR_TABLES64_1                                                                                \
+    QR_T2_64("cv", "h") QR_T2_64("cx", "t") QR_TU_64("zz", "x") QR_T1_64("rx") QR_T1_64("ry") QR_T1_64("rz")
+#define QR_BODIES64_0                                                                                \
+    QR_B2_64("cv", QR_CV(32, 64, QR_A32, QR_B32)) QR_B2_64("cx", QR_CNOT(32, 64))                    \
+    QR_B1_64("h", QR_H(32, 64)) QR_B1_64("t", QR_TG(32, 64)) QR_B1_64("x", QR_NOT(32, 64))
+#define QR_BODIES64_1                                                                                \
+    QR_BODIES64_0 QR_BODY("zz", QR_UP64, QR_SET8 QR_ZZ(32, 64)) QR_B1_64("rx", QR_RX(32, 64))                        \
+    QR_B1_64("ry", QR_RY(32, 64)) QR_B1_64("rz", QR_RZ(32, 64))
+#define QR_TEXT64(ANG)                                                                               \
+    ".set QRB,16\n.set QRT,144\n"                                                                    \
+    "s_getpc_b64 s[40:41]\n.Lqr%=p:\ns_add_u32 s40,s40,.Lqr%=tab-.Lqr%=p\ns_addc_u32 s41,s41,0\n"    \
+    "s_mov_b32 s42,0\nv_readlane_b32 s43,%[p],s42\n"                                                 \
+    ".Lqr%=l:\n"                                                                                     \
+    "s_cmp_ge_u32 s42,%[cnt]\ns_cbranch_scc1 .Lqr%=e\n"                                              \
+    "s_add_u32 s48,s40,s43\ns_addc_u32 s49,s41,0\n" QR_ANGLE32                                       \
+    "s_add_u32 s42,s42,1\nv_readlane_b32 s43,%[p],s42\ns_setpc_b64 s[48:49]\n"                       \
+    ".Lqr%=tab:\n" QR_TABLES64_##ANG QR_BODIES64_##ANG ".Lqr%=e:\n"
+
 #define QR_CLOBBER                                                                                   \
     "scc", "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", "s48", "s49", "s50", "s51", "s52", \
         "s53", "s54", "s55", "s58", "s59", "s60", "s61", "s62", "s63"
@@ -336,6 +392,18 @@ __device__ __forceinline__ void reg_gates(f32x8& x, uint32_t p, uint32_t cnt, fl
         asm volatile(QR_TEXT4(32, "16", "24", 0)
                      : "+{v[16:23]}"(x) : [p] "v"(p), [cnt] "s"(cnt)
                      : QR_CLOBBER, "v24", "v25", "v26", "v27");
+}
+template <int NQ, bool ANG>
+__device__ __forceinline__ void reg_gates(f32x128& x, uint32_t p, uint32_t cnt, float gc, float gs, SlotMap&, bool) {
+    static_assert(NQ == 6, "64 registers: width 6");
+    cnt = scalar(cnt);
+#define QR_ASM64C(ANG_)                                                                              \
+    asm volatile(QR_TEXT64(ANG_)                                                                     \
+                 : "+{v[16:47]}"(x.a), "+{v[48:79]}"(x.b), "+{v[80:111]}"(x.c), "+{v[112:143]}"(x.d) \
+                 : [p] "v"(p), [cnt] "s"(cnt), [gc] "v"(gc), [gs] "v"(gs)                            \
+                 : QR_CLOBBER, "v144", "v145", "v146", "v147")
+    if constexpr (ANG) QR_ASM64C(1); else QR_ASM64C(0);
+#undef QR_ASM64C
 }
 template <int NQ, bool ANG>
 __device__ __forceinline__ void reg_gates(f64x8& x, uint32_t p, uint32_t cnt, double gc, double gs, SlotMap&, bool) {

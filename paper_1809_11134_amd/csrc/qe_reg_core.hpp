@@ -4,7 +4,9 @@
 // registers: a wavefront holds CW columns (16; 32 at n = 5), lane l owns
 // column j = l mod CW (plus the wavefront's first column) and, with
 // q = l div CW, the rows whose lane-slot bits equal q, in E = N * CW / 64
-// complex registers.  n = 6 takes four wavefronts, the others one.  Row bits
+// complex registers.  n = 6 takes four wavefronts, the others one (and n = 6
+// with enough circuits to fill the GPU one, COLS = 64: a lane holds its whole
+// column in 128 VGPRs, so that no wire is ever in a lane slot).  Row bits
 // sit in slots: the lane bits above the column (LB = 2; 1 at n = 5) and the
 // bits of the register index.  The gates run in reg_gates (qe_reg_asm.hpp): at
 // n = 5, 6 a wire that a gate needs and that sits in a lane slot is exchanged
@@ -27,12 +29,16 @@
 
 namespace qe {
 
+// COLS: columns per wavefront
 template <int NQ>
+constexpr int reg_columns() { return NQ == 5 ? 32 : 16; }
+template <int NQ, int COLS>
 struct RegGeom {
     static_assert(NQ >= 4 && NQ <= 6, "widths 4 to 6");
-    static constexpr int N = 1 << NQ, W = NQ == 6 ? 4 : 1, CW = N / W;
-    static constexpr int LB = NQ == 5 ? 1 : 2, Q = 1 << LB, EB = NQ - LB, E = 1 << EB;
-    static_assert(CW * Q == 64, "a wavefront holds whole columns");
+    static constexpr int N = 1 << NQ, CW = COLS, W = N / CW;
+    static constexpr int Q = 64 / CW, LB = Q == 4 ? 2 : (Q == 2 ? 1 : 0), EB = NQ - LB, E = 1 << EB;
+    // a lane's rows never move between slots (width 4, and one column per lane)
+    static constexpr bool STATIC = NQ == 4 || LB == 0;
 };
 
 // Two complex numbers (one 16-byte load from memory aligned for one float2).
@@ -44,12 +50,13 @@ template <typename Real, int E>
 struct RegVec;
 template <> struct RegVec<float, 16> { using type = f32x32; };
 template <> struct RegVec<float, 4> { using type = f32x8; };
+template <> struct RegVec<float, 64> { using type = f32x128; };
 template <> struct RegVec<double, 16> { using type = f64x32; };
 template <> struct RegVec<double, 4> { using type = f64x8; };
 
-template <typename Real, int NQ>
+template <typename Real, int NQ, int COLS = reg_columns<NQ>()>
 struct RegMatrix {
-    using G = RegGeom<NQ>;
+    using G = RegGeom<NQ, COLS>;
     static constexpr int N = G::N, E = G::E, EB = G::EB, LB = G::LB, Q = G::Q;
     typename RegVec<Real, E>::type x;     // the lane's E elements
     SlotMap map;
@@ -71,7 +78,7 @@ struct RegMatrix {
         // ones, so that a lane's E elements of M_0 = T^dagger are contiguous
         // in T; wire w is row bit NQ-1-w
         map.w2s = map.s2w = 0u;
-        if constexpr (NQ > 4) {
+        if constexpr (!G::STATIC) {
 #pragma unroll
             for (int p = 0; p < NQ; ++p) {
                 const uint32_t w = NQ - 1 - p;
@@ -118,6 +125,13 @@ struct RegMatrix {
     static __device__ __forceinline__ uint32_t gate_word(uint32_t d) {
         const uint32_t kind = d & 15u, t = (d >> 4) & 15u;
         const uint32_t c = kind_two_wire((int)kind) ? (d >> 8) & 15u : t;
+        if constexpr (LB == 0) {
+            // tables by kind: NOT 2, CNOT 1, CV, CV+ 0, H 0, T 1, R_x 3, R_y 4, R_z 5, J 2
+            const uint32_t table = (uint32_t)(0x25431000120ull >> (4u * kind)) & 15u;
+            const uint32_t ts = NQ - 1 - t, cs = NQ - 1 - c;
+            const bool flip = kind == KIND_ZZ && ts > cs;            // (symmetric: one order)
+            return 256u * table + 32u * (flip ? cs : ts) + 4u * (flip ? ts : cs);
+        }
         // tables by kind: NOT, CNOT 2, CV 0, CV+ 1, H 0, T 1, R_x 3, R_y 4, R_z 5, J 3
         const uint32_t table = (uint32_t)(0x35431010220ull >> (4u * kind)) & 15u;
         if constexpr (NQ == 4) {
@@ -140,9 +154,11 @@ struct RegMatrix {
         const int lane = (int)lane_id();
         L = __builtin_amdgcn_readfirstlane(L);
         const int chunks = (L + 63) >> 6;
-        // (an empty circuit still restores the slots)
-        for (int ch = 0; ch < (chunks > 0 ? chunks : 1); ++ch) {
-            const SrcT dvv = ch == 0 ? dv0 : src(ch);
+        // (an empty circuit still restores the slots; the next chunk is fetched
+        // at the end of the body, so that there is one copy of the gate loop)
+        SrcT dvv = dv0;
+        int ch = 0;
+        do {
             const uint32_t dv = desc_of(dvv);
             const bool in = lane < min(64, L - ch * 64);
             if (__ballot(in && !desc_valid<ANG>(dv, NQ))) return false;
@@ -156,13 +172,20 @@ struct RegMatrix {
             const int to = 4 * (int)(live ? rank : cnt + (uint32_t)lane - rank);
             const uint32_t word = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(live ? gate_word(dv) : 0u));
             Real gc = (Real)0.70710678118654752440084436210485, gs = (Real)0;
-            if constexpr (ANG) {
+            if constexpr (LB == 0) {           // (CV and CV+ come with their signs)
+                if (kind == KIND_CV) gc = (Real)0.5;
+                if (kind == KIND_CVDG) gc = (Real)-0.5;
+                gs = -gc;
+            }
+            if constexpr (ANG)
                 if (in && kind_ising(kind)) half_angle(angle_of(dvv), &gc, &gs);
+            if constexpr (ANG || LB == 0) {
                 gc = permute(to, gc);
                 gs = permute(to, gs);
             }
             reg_gates<NQ, ANG>(x, word, cnt, gc, gs, map, RESTORE && ch + 1 >= chunks);
-        }
+            if (++ch < chunks) dvv = src(ch);
+        } while (ch < chunks);
         return true;
     }
     static __device__ __forceinline__ float permute(int to, float v) {
@@ -178,7 +201,7 @@ struct RegMatrix {
     __device__ __forceinline__ void store(C2* U, bool ok) const {
         auto bit = [&](int slot) -> uint32_t { return NQ - 1 - ((map.s2w >> (4 * slot)) & 15u); };
         uint32_t row = q;                       // the lane slots' part
-        if constexpr (NQ > 4) {
+        if constexpr (!G::STATIC) {
             row = 0u;
 #pragma unroll
             for (int s = 0; s < LB; ++s) row |= ((q >> s) & 1u) << bit(4 + s);
@@ -188,7 +211,7 @@ struct RegMatrix {
             uint32_t r = row;
 #pragma unroll
             for (int k = 0; k < EB; ++k)
-                if ((m >> k) & 1) r |= NQ > 4 ? 1u << bit(k) : (uint32_t)Q << k;
+                if ((m >> k) & 1) r |= G::STATIC ? (uint32_t)Q << k : 1u << bit(k);
             const Real nan = (Real)__builtin_nan("");
             C2 v;
             v.x = ok ? re(m) : nan;
@@ -198,10 +221,69 @@ struct RegMatrix {
     }
 
     // Eq. 11 (or, by `mode`, the phase-insensitive form) in the order of
-    // canonical_fitness, of a matrix whose slots were restored.  n = 6: all four
-    // wavefronts of the circuit call it, red 4 x 3 values of LDS, w the
+    // canonical_fitness, of a matrix whose slots were restored.  Four wavefronts
+    // per circuit (n = 6): all of them call it, red 4 x 3 values of LDS, w the
     // wavefront.  Returns f on every lane.
     __device__ __forceinline__ Real fitness(int mode, Real* g_out, Real* delta_out, int w, Real (*red)[3]) {
+        if constexpr (LB == 0) return fitness_columns(mode, g_out, delta_out);
+        else return fitness_groups(mode, g_out, delta_out, w, red);
+    }
+
+    // One column per lane (n = 6): the sums that canonical_fitness's wavefront
+    // v makes of columns 16 v.. and row groups q (rows q, q + 4, ...) are formed
+    // from the lane's four partial sums in the same order: over the 16 columns
+    // of each q, over the groups, then over the wavefronts.
+    __device__ __forceinline__ float fitness_columns(int mode, float* g_out, float* delta_out) const {
+        float off[4] = {0.0f, 0.0f, 0.0f, 0.0f}, dr = 0.0f, di = 0.0f;
+#pragma unroll
+        for (int m = 0; m < E; ++m) {
+            const bool dg = m == j;
+            const float xr = re(m), xi = im(m), m2 = xr * xr + xi * xi;
+            off[m & 3] += dg ? 0.0f : m2;
+            dr = dg ? xr : dr;
+            di = dg ? xi : di;
+        }
+        // the four wavefronts' sums, in lanes 0, 16, 32, 48, added in order
+        auto over_waves = [](float v) -> float {
+            float t = 0.0f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) t += read_lane(v, 16 * k);
+            return t;
+        };
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            off[g] += dpp_mov<0xB1>(off[g]);
+            off[g] += dpp_mov<0x4E>(off[g]);
+            off[g] += dpp_mov<0x141>(off[g]);
+            off[g] += dpp_mov<0x140>(off[g]);
+        }
+        const float offs = over_waves((off[0] + off[1]) + (off[2] + off[3]));
+        if (mode == QE_FIT_PHASE_INSENSITIVE) {
+            float fv;
+            fitness_pi(offs, N, &fv, g_out, delta_out);
+            return fv;
+        }
+        // a diagonal entry belongs to row group j mod 4: the columns of a group
+        // (lanes 4 and 8 apart), then the groups
+        auto total = [&](float v) -> float {
+            v += dpp_mov<0x1B>(dpp_mov<0x141>(v));     // lane ^ 4: l ^ 7, then l ^ 3
+            v += dpp_mov<0x128>(v);                    // lane ^ 8
+            v += dpp_mov<0xB1>(v);
+            v += dpp_mov<0x4E>(v);
+            return over_waves(v);
+        };
+        const float tr = total(dr), ti = total(di);
+        const float am = sqrtf(tr * tr + ti * ti);
+        float er = 1.0f, ei = 0.0f;
+        if (am > 0.0f) { er = tr / am; ei = ti / am; }
+        const float xr = dr - er, xi = di - ei;
+        const float dlt = 0.5f * (offs + total(xr * xr + xi * xi));
+        *g_out = am / (float)N;
+        *delta_out = dlt;
+        return 1.0f - sqrtf(clamp01(dlt / (float)N));
+    }
+
+    __device__ __forceinline__ Real fitness_groups(int mode, Real* g_out, Real* delta_out, int w, Real (*red)[3]) {
         const int lane = (int)lane_id();
         const int key = (j % Q) == (int)q ? j / Q : -1;       // register of the diagonal entry
         Real off = (Real)0, dr = (Real)0, di = (Real)0;
