@@ -101,6 +101,25 @@ __device__ __forceinline__ SlotFull load_slot_full(const LoopArgs& a, uint32_t i
     return f;
 }
 
+__device__ __forceinline__ void stash_full(float4 (*s)[64], int lane, const SlotFull& f) {
+    s[0][lane] = make_float4(__uint_as_float(f.r.theta), __uint_as_float(f.r.best_theta), f.r.best_f,
+                             __uint_as_float(f.r.key));
+    s[1][lane] = make_float4(f.q.q[0], f.q.q[1], f.q.q[2], f.q.q[3]);
+    s[2][lane] = make_float4(f.q.q[4], f.q.q[5], f.q.bq[0], f.q.bq[1]);
+    s[3][lane] = make_float4(f.q.bq[2], f.q.bq[3], f.q.bq[4], f.q.bq[5]);
+}
+
+__device__ __forceinline__ SlotFull unstash_full(float4 (*s)[64], int lane) {
+    const float4 r = s[0][lane], x = s[1][lane], y = s[2][lane], z = s[3][lane];
+    SlotFull f;
+    f.r.theta = __float_as_uint(r.x);
+    f.r.best_theta = __float_as_uint(r.y);
+    f.r.best_f = r.z;
+    f.r.key = __float_as_uint(r.w);
+    f.q = QState{{x.x, x.y, x.z, x.w, y.x, y.y}, {y.z, y.w, z.x, z.y, z.z, z.w}};
+    return f;
+}
+
 __device__ __forceinline__ SlotState state_of(const SlotFull& f) {
     SlotState st;
     st.theta = f.r.theta;
@@ -322,7 +341,8 @@ __device__ void commit_alone(const LoopArgs& a, uint32_t i, uint32_t s, float v,
 // CPB = 4 circuits per workgroup one, a column per lane).  With
 // several wavefronts and SAMPLE only the first samples; the others take its
 // descriptors from xch (two buffers of 64 entries, by chunk parity, so one
-// barrier per chunk separates a chunk's writes from the next chunk's).
+// barrier per chunk separates a chunk's writes from the next chunk's; the
+// register-resident layout exchanges chunk 0 only).
 template <int NQ, int W, int CPB>
 constexpr int circuit_waves() { return W == 0 ? (NQ == 6 && CPB == 1 ? 4 : 1) : W; }
 
@@ -332,7 +352,7 @@ __device__ __forceinline__ void eval_circuit(const LoopArgs& a, uint32_t gen, ui
                                              uint32_t* slots_out, uint16_t* gates_out,
                                              uint32_t* angles_out, float* f_out, bool writer,
                                              bool decide, float2* M, uint4* gt, float (*red)[3],
-                                             void* xch = nullptr) {
+                                             void* xch = nullptr, float4 (*stash)[64] = nullptr) {
     constexpr int WV = circuit_waves<NQ, W, CPB>();
     const uint32_t i = ci / (uint32_t)a.P, k = ci % (uint32_t)a.P;
     const int lane = (int)lane_id();
@@ -347,7 +367,9 @@ __device__ __forceinline__ void eval_circuit(const LoopArgs& a, uint32_t gen, ui
     // (the flags exist only for sampled generations whose duplicates were
     // found beforehand, and then L <= KEEP * 64)
     auto is_alone = [&](uint32_t word) -> bool { return a.dup && !(word & DUP_SHARED); };
-    SlotFull full0{};                       // the records of the lane's slot in chunk 0
+    // the records of the lane's slot in chunk 0; in LDS (stash) while the gates
+    // run in registers, whose number sets the occupancy there
+    SlotFull full0{};
     using SrcT = std::conditional_t<ISING, uint2, uint32_t>;
     auto own = [&](int ch) -> SrcT {
         const int p = ch * 64 + lane;
@@ -430,9 +452,31 @@ __device__ __forceinline__ void eval_circuit(const LoopArgs& a, uint32_t gen, ui
         RegMatrix<float, NQ, NQ == 6 && WV == 1 ? 64 : reg_columns<NQ>()> mat;
         mat.place(wave);
         const SrcT dv0 = src(0);
+        const bool keep = SAMPLE && stash && a.dup && writer;
+        if (keep) stash_full(stash, lane, full0);
+        if constexpr (SAMPLE) {
+            // the other chunks are sampled before the matrix takes its registers,
+            // and read back from the circuit's output
+            const int chunks = (L + 63) >> 6;
+            for (int ch = 1; ch < chunks; ++ch)
+                if (writer) own(ch);
+            if (WV > 1 && chunks > 1) __syncthreads();
+        }
+        auto rest = [&](int ch) -> SrcT {
+            const int p = ch * 64 + lane;
+            const uint16_t* g = SAMPLE ? gates_out : gates_in;
+            if constexpr (ISING) {
+                const uint32_t* an = SAMPLE ? angles_out : angles_in;
+                return p < L ? make_uint2((uint32_t)g[(size_t)ci * L + p], an[(size_t)ci * L + p])
+                             : make_uint2(0u, 0u);
+            } else {
+                return p < L ? (uint32_t)g[(size_t)ci * L + p] : 0u;
+            }
+        };
         mat.load(T);
-        ok = mat.template run<true>(L, src, dv0);
+        ok = mat.template run<true>(L, rest, dv0);
         fv = mat.fitness(a.fit_mode, &gd, &dd, wave, red);
+        if (keep) full0 = unstash_full(stash, lane);
     } else {
         float gd, dd;
         RowMap map{};
@@ -484,8 +528,7 @@ __global__ __launch_bounds__(256) void population_kernel(LoopArgs a, uint64_t ge
                                                          const uint16_t* __restrict__ gates_in,
                                                          const uint32_t* __restrict__ angles_in,
                                                          uint32_t* __restrict__ slots_out,
-                                                         uint16_t* __restrict__ gates_out,
-                                                         uint32_t* __restrict__ angles_out,
+                                                         uint16_t* gates_out, uint32_t* angles_out,
                                                          float* __restrict__ f_out, bool decide) {
     const uint32_t gen = gen_of(a, gen64);
     // (no gates given: the GA population of the generation)
@@ -498,13 +541,16 @@ __global__ __launch_bounds__(256) void population_kernel(LoopArgs a, uint64_t ge
         // workgroup of four
         constexpr int WV = circuit_waves<NQ, W, CPB>();
         static_assert(WV == 1 || CPB == 1, "one circuit per workgroup of several wavefronts");
+        constexpr bool STASH = SAMPLE && NQ >= 4;
         __shared__ float red[4][3];
         __shared__ uint2 xch[WV > 1 ? 128 : 1];
+        __shared__ float4 stash[STASH ? CPB : 1][4][64];
         const uint32_t ci = __builtin_amdgcn_readfirstlane(WV == 1 ? bid * CPB + (uint32_t)wave : bid);
         if (ci >= total) return;
         eval_circuit<NQ, 0, SAMPLE, ISING, CPB>(a, gen, ci, gates_in, angles_in, slots_out, gates_out,
                                            angles_out, f_out, WV == 1 || threadIdx.x < 64, decide, nullptr,
-                                           nullptr, red, WV == 1 ? nullptr : static_cast<void*>(xch));
+                                           nullptr, red, WV == 1 ? nullptr : static_cast<void*>(xch),
+                                           STASH ? stash[WV == 1 ? wave % CPB : 0] : nullptr);
     } else {
         // W = 1: CPB circuits per workgroup, one per wavefront (no barrier
         // is shared, so a wavefront past the end may leave); W > 1: one

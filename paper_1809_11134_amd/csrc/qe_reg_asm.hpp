@@ -19,9 +19,9 @@
 // slot to wire, 4 bits each).  A gate whose wire is in a lane slot first
 // exchanges that slot with a register bit, by choice one that the next gate
 // does not use.  4 registers (width 4): every wire keeps its slot (entries 0,
-// 1: register bits, 2, 3: lane slots); a body brings a lane slot into the
-// registers and back itself (4 exchanges each way), which costs less than
-// keeping the maps: with 4 registers one gate in one needs an exchange.
+// 1: register bits, 2, 3: lane slots) and the bodies deal with the lane slots
+// themselves: with 4 registers every other gate would need an exchange, and
+// keeping the maps would cost more scalar instructions than that saves.
 //
 // 64 registers (width 6, one column per lane): every wire is a register bit, so
 // a gate's word is its entry.  Tables of 64 entries (target 8 t, control c):
@@ -125,8 +125,8 @@ struct SlotMap {
 
 // u + iv = a - b, p + iq = (a + b) / 2: a' = p - hs v + i (q + hs u), b' = p + hs v
 // + i (q - hs u); HP = hs, HM = -hs
-#define QR_CV(P, E, HP, HM)                                                                          \
-    QR_ROWS2(E, QR_SUB##P(QR_T##P(0), QR_X##P(QR_A), QR_X##P(QR_P))                                  \
+#define QR_CVROW(P, HP, HM)                                                                          \
+                QR_SUB##P(QR_T##P(0), QR_X##P(QR_A), QR_X##P(QR_P))                                  \
                 QR_SUB##P(QR_T##P(1), QR_Y##P(QR_A), QR_Y##P(QR_P))                                  \
                 QR_ADD##P(QR_X##P(QR_A), QR_X##P(QR_A), QR_X##P(QR_P))                               \
                 QR_ADD##P(QR_Y##P(QR_A), QR_Y##P(QR_A), QR_Y##P(QR_P))                               \
@@ -135,8 +135,10 @@ struct SlotMap {
                 QR_FMA##P(QR_X##P(QR_A), HM, QR_T##P(1), QR_X##P(QR_P))                              \
                 QR_FMA##P(QR_Y##P(QR_A), HP, QR_T##P(0), QR_Y##P(QR_P))                              \
                 QR_FMAC##P(QR_X##P(QR_P), HP, QR_T##P(1))                                            \
-                QR_FMAC##P(QR_Y##P(QR_P), HM, QR_T##P(0)))
-#define QR_CNOT(P, E) QR_ROWS2(E, QR_XCH##P("v_swap_b32", QR_A, QR_P))
+                QR_FMAC##P(QR_Y##P(QR_P), HM, QR_T##P(0))
+#define QR_CV(P, E, HP, HM) QR_ROWS2(E, QR_CVROW(P, HP, HM))
+#define QR_CXROW(P) QR_XCH##P("v_swap_b32", QR_A, QR_P)
+#define QR_CNOT(P, E) QR_ROWS2(E, QR_CXROW(P))
 #define QR_NOT(P, E) QR_ROWS1(E, QR_XCH##P("v_swap_b32", QR_A, QR_P))
 #define QR_H(P, E)                                                                                   \
     QR_ROWS1(E, QR_SUB##P(QR_T##P(0), QR_X##P(QR_A), QR_X##P(QR_P))                                  \
@@ -208,22 +210,66 @@ struct SlotMap {
 #define QR_ONE16 "0,5,10,15"
 #define QR_SETTC ".set QT,\\n>>2\n.set QC,\\n&3\n"
 // widths 5, 6: target and control are register bits
-#define QR_TWO_16(P, LS, name, text) QR_BODY(name, QR_TWO16, QR_SETTC text)
-#define QR_ONE_16(P, LS, name, text) QR_BODY(name, QR_ONE16, QR_SETTC text)
-// width 4: slots 2, 3 are lane slots, exchanged with a register bit around the
-// body
-#define QR_AROUND4(P, text)                                                                          \
-    ".set QT,\\n>>2\n.set QC,\\n&3\n.set QS0,-1\n.set QS1,-1\n"                                      \
-    ".if (QT>1)&(QC<2)\n.set QS0,QT-2\n.set QK0,1-QC\n.set QT,QK0\n.endif\n"                         \
-    ".if (QT<2)&(QC>1)\n.set QS0,QC-2\n.set QK0,1-QT\n.set QC,QK0\n.endif\n"                         \
-    ".if (QT>1)&(QC>1)\n.set QS0,QT-2\n.set QK0,0\n.if QT!=QC\n.set QS1,QC-2\n.endif\n"              \
-    ".set QT,0\n.set QC,1\n.endif\n"                                                                 \
-    ".if QS0>=0\n" QR_LANE2(P, 4, "QS0", "QK0") ".endif\n"                                           \
-    ".if QS1>=0\n" QR_LANE2(P, 4, "QS1", "1") ".endif\n" text                                        \
-    ".if QS1>=0\n" QR_LANE2(P, 4, "QS1", "1") ".endif\n"                                             \
-    ".if QS0>=0\n" QR_LANE2(P, 4, "QS0", "QK0") ".endif\n"
-#define QR_TWO_4(P, LS, name, text) QR_BODY(name, QR_TWO16, QR_AROUND4(P, text))
-#define QR_ONE_4(P, LS, name, text) QR_BODY(name, QR_ONE16, QR_AROUND4(P, text))
+#define QR_TWO_16(name, text) QR_BODY(name, QR_TWO16, QR_SETTC text)
+#define QR_ONE_16(name, text) QR_BODY(name, QR_ONE16, QR_SETTC text)
+// width 4: slots 2, 3 are lane slots (S = 0, 1).  A lane slot's target is
+// exchanged with a register bit around the body (of a controlled gate with a
+// register control: only the rows it changes); a lane slot's control, and the
+// one row that T changes, are masked lanes; the diagonal rotations take the
+// sign of B from the lane.
+#define QR_SET4 ".set QT,\\n>>2\n.set QC,\\n&3\n"
+#define QR_MASK(slot)      /* the lanes whose lane slot (2 or 3) is 1 */                              \
+    ".if (" slot ")==2\n.set QML,0xffff0000\n.set QMH,0xffff0000\n.else\n.set QML,0\n.set QMH,0xffffffff\n.endif\n"
+#define QR_EXEC "s_mov_b32 exec_lo,QML\ns_mov_b32 exec_hi,QMH\n"
+#define QR_EXEC_ALL "s_mov_b64 exec,-1\n"
+#define QR_LANEROWS(P, S)                                                                            \
+    "s_nop 1\n.if (" S ")==0\n" QR_ROWS2(4, QR_XCH##P("v_permlane16_swap_b32", QR_A, QR_P))          \
+    ".else\n" QR_ROWS2(4, QR_XCH##P("v_permlane32_swap_b32", QR_A, QR_P)) ".endif\n"
+#define QR_CTL4(P, name, row)                                                                        \
+    QR_BODY(name, QR_TWO16, QR_SET4                                                                  \
+        ".if (QT<2)&(QC<2)\n" QR_ROWS2(4, row)                                                       \
+        ".elseif QT<2\n" QR_MASK("QC") QR_EXEC QR_ROWS1(4, row) QR_EXEC_ALL                          \
+        ".elseif QC<2\n.set QS0,QT-2\n.set QT,1-QC\n"                                                \
+        QR_LANEROWS(P, "QS0") QR_ROWS2(4, row) QR_LANEROWS(P, "QS0")                                 \
+        ".else\n.set QS0,QT-2\n.set QT,0\n" QR_LANE2(P, 4, "QS0", "0")                               \
+        QR_MASK("QC") QR_EXEC QR_ROWS1(4, row) QR_EXEC_ALL QR_LANE2(P, 4, "QS0", "0") ".endif\n")
+#define QR_ONE4(P, name, text)                                                                       \
+    QR_BODY(name, QR_ONE16, QR_SET4                                                                  \
+        ".if QT<2\n" text ".else\n.set QS0,QT-2\n.set QT,0\n"                                        \
+        QR_LANE2(P, 4, "QS0", "0") text QR_LANE2(P, 4, "QS0", "0") ".endif\n")
+#define QR_TROW(P)                                                                                   \
+    QR_SUB##P(QR_T##P(0), QR_X##P(QR_A), QR_Y##P(QR_A)) QR_ADD##P(QR_Y##P(QR_A), QR_X##P(QR_A), QR_Y##P(QR_A)) \
+    QR_MUL##P(QR_X##P(QR_A), QR_A##P, QR_T##P(0)) QR_MUL##P(QR_Y##P(QR_A), QR_A##P, QR_Y##P(QR_A))
+#define QR_T4(P)                                                                                     \
+    QR_BODY("t", QR_ONE16, QR_SET4                                                                   \
+        ".if QT<2\n" QR_ROWS(4, "((\\a>>QT)&1)==1", QR_TROW(P))                                      \
+        ".else\n" QR_MASK("QT") QR_EXEC QR_ROWS(4, "1", QR_TROW(P)) QR_EXEC_ALL ".endif\n")
+// temporary 3: B, negated in the lanes of the mask; then row a times A - i B3, or
+// (odd rows) A + i B3
+#define QR_SIGN32                                                                                    \
+    "v_mov_b32 v[QRT+3]," QR_B32 "\ns_mov_b32 s50,QML\ns_mov_b32 s51,QMH\n"                          \
+    "v_cndmask_b32_e64 v[QRT+3],v[QRT+3],-v[QRT+3],s[50:51]\n"
+#define QR_SIGN64                                                                                    \
+    "v_mov_b32 v[QRT+6],s62\nv_mov_b32 v[QRT+7],s63\ns_mov_b32 s50,QML\ns_mov_b32 s51,QMH\n"         \
+    "v_cndmask_b32_e64 v[QRT+7],v[QRT+7],-v[QRT+7],s[50:51]\n"
+#define QR_PHASE(P, odd)                                                                             \
+    ".irp a," QR_ELEMS4 "\n"                                                                         \
+    QR_MUL##P(QR_T##P(0), QR_T##P(3), QR_Y##P(QR_A)) QR_MUL##P(QR_T##P(1), QR_T##P(3), QR_X##P(QR_A)) \
+    QR_MUL##P(QR_X##P(QR_A), QR_A##P, QR_X##P(QR_A)) QR_MUL##P(QR_Y##P(QR_A), QR_A##P, QR_Y##P(QR_A)) \
+    ".if " odd "\n"                                                                                  \
+    QR_SUB##P(QR_X##P(QR_A), QR_X##P(QR_A), QR_T##P(0)) QR_ADD##P(QR_Y##P(QR_A), QR_Y##P(QR_A), QR_T##P(1)) \
+    ".else\n"                                                                                        \
+    QR_ADD##P(QR_X##P(QR_A), QR_X##P(QR_A), QR_T##P(0)) QR_SUB##P(QR_Y##P(QR_A), QR_Y##P(QR_A), QR_T##P(1)) \
+    ".endif\n.endr\n"
+#define QR_RZ4(P)                                                                                    \
+    QR_BODY("rz", QR_ONE16, QR_SET4                                                                  \
+        ".if QT<2\n" QR_RZ(P, 4) ".else\n" QR_MASK("QT") QR_SIGN##P QR_PHASE(P, "0") ".endif\n")
+#define QR_ZZ4(P)                                                                                    \
+    QR_BODY("zz", QR_TWO16, QR_SET4                                                                  \
+        ".if (QT<2)&(QC<2)\n" QR_ZZ(P, 4)                                                            \
+        ".elseif QT<2\n" QR_MASK("QC") QR_SIGN##P QR_PHASE(P, "((\\a>>QT)&1)==1")                    \
+        ".elseif QC<2\n" QR_MASK("QT") QR_SIGN##P QR_PHASE(P, "((\\a>>QC)&1)==1")                    \
+        ".else\n.set QML,0xffff0000\n.set QMH,0x0000ffff\n" QR_SIGN##P QR_PHASE(P, "0") ".endif\n")
 
 #define QR_TAB(two, one)                                                                             \
     ".irp n," QR_ELEMS16 "\n.if (\\n>>2)==(\\n&3)\ns_branch .Lqr%=" one "\\n\n.else\n"               \
@@ -233,14 +279,18 @@ struct SlotMap {
     "s_branch .Lqr%=e\n.endif\n.endr\n"
 #define QR_TABLES0 QR_TAB("cv", "h") QR_TAB("cd", "t") QR_TAB("cx", "x")
 #define QR_TABLES1 QR_TABLES0 QR_TAB("zz", "rx") QR_TAB1("ry") QR_TAB1("rz")
-#define QR_BODIES0(P, E, LS)                                                                         \
-    QR_TWO_##E(P, LS, "cv", QR_CV(P, E, "0.5", "-0.5"))                                              \
-    QR_TWO_##E(P, LS, "cd", QR_CV(P, E, "-0.5", "0.5"))                                              \
-    QR_TWO_##E(P, LS, "cx", QR_CNOT(P, E)) QR_ONE_##E(P, LS, "h", QR_H(P, E))                        \
-    QR_ONE_##E(P, LS, "t", QR_TG(P, E)) QR_ONE_##E(P, LS, "x", QR_NOT(P, E))
-#define QR_BODIES1(P, E, LS)                                                                         \
-    QR_BODIES0(P, E, LS) QR_TWO_##E(P, LS, "zz", QR_ZZ(P, E)) QR_ONE_##E(P, LS, "rx", QR_RX(P, E))   \
-    QR_ONE_##E(P, LS, "ry", QR_RY(P, E)) QR_ONE_##E(P, LS, "rz", QR_RZ(P, E))
+#define QR_BODIES16_0(P)                                                                             \
+    QR_TWO_16("cv", QR_CV(P, 16, "0.5", "-0.5")) QR_TWO_16("cd", QR_CV(P, 16, "-0.5", "0.5"))        \
+    QR_TWO_16("cx", QR_CNOT(P, 16)) QR_ONE_16("h", QR_H(P, 16)) QR_ONE_16("t", QR_TG(P, 16))         \
+    QR_ONE_16("x", QR_NOT(P, 16))
+#define QR_BODIES16_1(P)                                                                             \
+    QR_BODIES16_0(P) QR_TWO_16("zz", QR_ZZ(P, 16)) QR_ONE_16("rx", QR_RX(P, 16))                     \
+    QR_ONE_16("ry", QR_RY(P, 16)) QR_ONE_16("rz", QR_RZ(P, 16))
+#define QR_BODIES4_0(P)                                                                              \
+    QR_CTL4(P, "cv", QR_CVROW(P, "0.5", "-0.5")) QR_CTL4(P, "cd", QR_CVROW(P, "-0.5", "0.5"))        \
+    QR_CTL4(P, "cx", QR_CXROW(P)) QR_ONE4(P, "h", QR_H(P, 4)) QR_T4(P) QR_ONE4(P, "x", QR_NOT(P, 4))
+#define QR_BODIES4_1(P)                                                                              \
+    QR_BODIES4_0(P) QR_ZZ4(P) QR_ONE4(P, "rx", QR_RX(P, 4)) QR_ONE4(P, "ry", QR_RY(P, 4)) QR_RZ4(P)
 #define QR_SCALARS0(P)
 #define QR_SCALARS1(P) QR_ANGLE##P
 #define QR_START0(P) QR_CONST##P
@@ -261,7 +311,7 @@ struct SlotMap {
     "s_add_u32 s42,s42,1\n"                                                                          \
     "v_readlane_b32 s43,%[p],s42\n"                                                                  \
     "s_setpc_b64 s[48:49]\n"                                                                         \
-    ".Lqr%=tab:\n" QR_TABLES##ANG QR_BODIES##ANG(P, 4, 2)                                            \
+    ".Lqr%=tab:\n" QR_TABLES##ANG QR_BODIES4_##ANG(P)                                            \
     ".Lqr%=e:\n"
 
 // Widths 5, 6: the word is 4 * target wire, 4 * control wire (target again for a
@@ -318,7 +368,7 @@ struct SlotMap {
     ".Lqr%=tab:\n" QR_TABLES##ANG                                                                    \
     ".Lqr%=xt:\n.irp n,0,1,2,3,4,5,6,7,8,9,10,11,12,13,14,15,16,17,18,19,20,21,22,23\n"              \
     ".if ((\\n>>2)>(\\n&3))&((\\n>>2)<4+" #LS ")\ns_branch .Lqr%=v\\n\n.else\ns_branch .Lqr%=e\n.endif\n.endr\n" \
-    QR_BODIES##ANG(P, 16, LS)                                                                        \
+    QR_BODIES16_##ANG(P)                                                                        \
     ".irp n,4,8,9,12,13,14\n.Lqr%=v\\n:\n"                                                           \
     QR_ROWS(16, "(((\\a>>(\\n>>2))&1)==0)&(((\\a>>(\\n&3))&1)==1)",                                  \
             QR_XCH##P("v_swap_b32", QR_A, "\\a+(1<<(\\n>>2))-(1<<(\\n&3))"))                         \
