@@ -357,7 +357,8 @@ qe_status check_ctx(qe_ctx* c, bool need_targets) {
 // decisions were those of gen - 1, whose kernels cleared the mask of gen's
 // parity.
 qe_status prepare_decisions(qe_ctx* c, uint64_t gen, uint64_t count, hipStream_t s) {
-    if (c->prob.algorithm != QE_ALG_QEQEA) return QE_OK;
+    // (with the shared-slot search the decisions come with the slot words)
+    if (c->prob.algorithm != QE_ALG_QEQEA || c->la.dup) return QE_OK;
     if (gen != c->next_decision_gen) QE_HIP(launch_mutmask_clear(c->la, s));
     c->next_decision_gen = gen + count;
     return QE_OK;
@@ -742,6 +743,7 @@ qe_status create_impl(const qe_problem* p_in, const int32_t* inst_n, const int32
         // fused kernel commits the elitism of the slots one circuit alone used
         if (I * P * L > (size_t)DEDUP_MIN_TOTAL && P * L <= (size_t)DEDUP_MAX_ENTRIES && L <= 256 && S < ((size_t)1 << 31)) {
             ALLOC(a.dup, 2 * I * P * L);
+            ALLOC(a.aux, 2 * I * P * L);
             ALLOC(a.shared_list, 2 * I * P * L);
             ALLOC(a.shared_count, 2 * I);
         }
@@ -959,6 +961,8 @@ qe_status qe_update(qe_ctx* c, uint64_t gen, const uint32_t* slots, const uint16
         if (!fused) {
             QE_TRY(prepare_decisions(c, gen, 1, s));
             QE_HIP(launch_mutation_decisions(c->la, gen, s));
+            // (the mask of that parity held the decisions of its words' generation)
+            if (c->la.dup && c->words_gen[gen & 1] != (int64_t)gen) c->words_gen[gen & 1] = -1;
         }
         // after qe_sample_eval with no slot array the fused kernel has committed
         // the unshared slots (the search's list names the shared ones), and

@@ -141,7 +141,8 @@ struct LoopArgs {
     // generation g sets bit ind of mask g & 1 for every individual that
     // mutates and clears mask (g + 1) & 1, which generation g - 1 consumed.
     // The host clears both before a generation that does not follow the
-    // previous one.
+    // previous one.  With the shared-slot search (dup) the search of generation
+    // g writes mask g & 1 whole instead.
     uint32_t* mutmask;                 // [2][I][MW]
     uint32_t MW;                       // words per instance: ceil(P / 32)
     float* inst_best_f;                // per instance
@@ -167,6 +168,11 @@ struct LoopArgs {
     // in buffer g & 1, so that the search of the next generation can run
     // while the current one's words are read (null otherwise)
     uint32_t* dup;
+    // with dup, in the same layout: what decoding an entry's slot needs besides
+    // the slot's state: for a rotation slot bit 31, its wire in bits 24..26 and
+    // the 24 bits of its measurement draw; for a template slot its descriptor's
+    // wire fields (target in bits 0..3, control in bits 4..7)
+    uint32_t* aux;
     // with dup: per generation parity and population, the entries whose slot
     // is shared ({entry index within the population, slot}, [2][I][P * L])
     // and their number ([2][I])

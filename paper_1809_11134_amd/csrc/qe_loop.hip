@@ -30,6 +30,11 @@ __device__ __forceinline__ uint32_t* dup_words(const LoopArgs& a, uint32_t gen) 
     return a.dup + (size_t)(gen & 1u) * ((size_t)a.I * a.P * a.L);
 }
 
+__device__ __forceinline__ uint32_t* aux_words(const LoopArgs& a, uint32_t gen) {
+    return a.aux + (size_t)(gen & 1u) * ((size_t)a.I * a.P * a.L);
+}
+constexpr uint32_t AUX_ROT = 0x80000000u;
+
 // ------------------------------------------------------------- measurement
 // Born-rule measurement of a qutrit (3 complex amplitudes, unnormalised):
 // u in [0,1) from the top 24 bits of w scales the cumulative weights.
@@ -132,20 +137,11 @@ __device__ __forceinline__ SlotState state_of(const SlotFull& f) {
 // Decodes slot s of instance i: rotation slot -> NOT on its wire when the
 // measured axis is x and the angle rounds to a half turn, else I; template
 // slot (c, t) -> controlled V^q with q the angle in quarter turns.
-// (FULL: the whole records are loaded and returned in *full)
-template <bool FULL = false>
-__device__ __forceinline__ uint16_t decode_slot(const LoopArgs& a, uint32_t gen, uint32_t i,
-                                                uint32_t s, SlotFull* full = nullptr) {
+__device__ __forceinline__ uint16_t decode_slot(const LoopArgs& a, uint32_t gen, uint32_t i, uint32_t s) {
     const uint32_t LP = (uint32_t)a.L * (uint32_t)a.P;
     const uint32_t r = s / LP;
     const bool rot = r < (uint32_t)a.n;
-    SlotState st;
-    if constexpr (FULL) {
-        *full = load_slot_full(a, i, s, rot);
-        st = state_of(*full);
-    } else {
-        st = load_slot_state(a, i, s, rot);
-    }
+    const SlotState st = load_slot_state(a, i, s, rot);
     // every lane measures (a wavefront with any rotation slot runs the draw
     // anyway) while the loads are in flight; template slots ignore the outcome
     const u32x4 w = draw(a.seed, TAG_MEASURE, gen, i, s);
@@ -166,19 +162,11 @@ __device__ __forceinline__ uint16_t decode_slot(const LoopArgs& a, uint32_t gen,
 // rotation about the measured axis (outcome 0, 1, 2 = x, y, z) on w, a
 // template slot on the unordered pair (a, b) the interaction J on (a, b);
 // both take the slot's angle.  Returns {descriptor, angle}.
-template <bool FULL = false>
-__device__ __forceinline__ uint2 decode_ising(const LoopArgs& a, uint32_t gen, uint32_t i, uint32_t s,
-                                              SlotFull* full = nullptr) {
+__device__ __forceinline__ uint2 decode_ising(const LoopArgs& a, uint32_t gen, uint32_t i, uint32_t s) {
     const uint32_t LP = (uint32_t)a.L * (uint32_t)a.P;
     const uint32_t r = s / LP;
     const bool rot = r < (uint32_t)a.n;
-    SlotState st;
-    if constexpr (FULL) {
-        *full = load_slot_full(a, i, s, rot);
-        st = state_of(*full);
-    } else {
-        st = load_slot_state(a, i, s, rot);
-    }
+    const SlotState st = load_slot_state(a, i, s, rot);
     const u32x4 w = draw(a.seed, TAG_MEASURE, gen, i, s);   // every lane, as in decode_slot
     anchor(w.x);
     anchor(st.q0.x);
@@ -188,6 +176,26 @@ __device__ __forceinline__ uint2 decode_ising(const LoopArgs& a, uint32_t gen, u
     int pa, pb;
     upair_of(a.n, (int)r - a.n, &pa, &pb);
     return make_uint2(make_desc(KIND_ZZ, pa, pb), st.theta);
+}
+
+// The same for a slot whose search left its aux word (the region, and a
+// rotation slot's measurement draw, are known then): the whole records are
+// loaded and returned in *f.  The angle is written to *angle (Ising library).
+__device__ __forceinline__ uint32_t decode_known(const LoopArgs& a, uint32_t i, uint32_t s, uint32_t aux,
+                                                 bool ising, SlotFull* f, uint32_t* angle) {
+    const bool rot = (aux & AUX_ROT) != 0u;
+    *f = load_slot_full(a, i, s, rot);
+    const SlotState st = state_of(*f);
+    anchor(st.q0.x);
+    anchor(st.q2.x);
+    const int axis = measure_amps(st.q0, st.q1, st.q2, aux << 8);
+    const uint32_t wire = (aux >> 24) & 7u;
+    *angle = st.theta;
+    if (ising) return rot ? (uint32_t)(KIND_RX + axis) | (wire << 4) : (uint32_t)KIND_ZZ | (aux << 4);
+    const uint32_t q = ((st.theta + 0x20000000u) >> 30) & 3u;
+    if (rot) return (axis == 0 && q == 2u) ? (uint32_t)KIND_NOT | (wire << 4) : 0u;
+    // quarter turns 1, 2, 3: CV, CNOT, CV+
+    return q == 0u ? 0u : ((0x4230u >> (4u * q)) & 15u) | (aux << 4);
 }
 
 // Segment index of Eq. 10 from the SAMPLE draw of position pos: the
@@ -358,15 +366,15 @@ __device__ __forceinline__ void eval_circuit(const LoopArgs& a, uint32_t gen, ui
     const int lane = (int)lane_id();
     const int L = a.L;
     const float* T = a.target32 + (size_t)2 * i * ((size_t)1 << (2 * NQ));
+    // (with the shared-slot search the decisions are made already)
+    decide = decide && !a.dup;
     if (SAMPLE && decide && writer && lane == 0) clear_next_mask(a, gen, i, k);
     constexpr int KEEP = 4;                 // chunks of 64 slots kept for the scatter
     uint32_t kept[KEEP];
     bool alone[KEEP];                       // no other circuit of the generation uses the slot
 #pragma unroll
     for (int c = 0; c < KEEP; ++c) { kept[c] = 0xFFFFFFFFu; alone[c] = false; }
-    // (the flags exist only for sampled generations whose duplicates were
-    // found beforehand, and then L <= KEEP * 64)
-    auto is_alone = [&](uint32_t word) -> bool { return a.dup && !(word & DUP_SHARED); };
+    // (alone only in contexts with the shared-slot search, and then L <= KEEP * 64)
     // the records of the lane's slot in chunk 0; in LDS (stash) while the gates
     // run in registers, whose number sets the occupancy there
     SlotFull full0{};
@@ -381,46 +389,49 @@ __device__ __forceinline__ void eval_circuit(const LoopArgs& a, uint32_t gen, ui
                 return p < L ? (uint32_t)gates_in[(size_t)ci * L + p] : 0u;
         }
         const bool pos = p < L;
+        auto put = [&](int ch_, uint32_t s, bool al) {
+#pragma unroll
+            for (int c = 0; c < KEEP; ++c)
+                if (c == ch_) { kept[c] = s; alone[c] = al; }
+        };
+        auto emit = [&](uint32_t s, uint32_t d, uint32_t ang) -> SrcT {
+            if (writer) {
+                if (slots_out) slots_out[(size_t)ci * L + p] = s;
+                gates_out[(size_t)ci * L + p] = (uint16_t)d;
+                if constexpr (ISING) angles_out[(size_t)ci * L + p] = ang;
+            }
+            if constexpr (ISING) return make_uint2(d, ang);
+            else return d;
+        };
+        if (a.dup) {
+            // after the shared-slot search: the entry's slot and what decodes it
+            if (!pos) return SrcT{};
+            const uint32_t word = dup_words(a, gen)[(size_t)ci * L + p], aux = aux_words(a, gen)[(size_t)ci * L + p];
+            const uint32_t s = word & ~DUP_SHARED;
+            put(ch, s, !(word & DUP_SHARED));
+            SlotFull f;
+            uint32_t ang;
+            const uint32_t d = decode_known(a, i, s, aux, ISING, &f, &ang);
+            if (ch == 0) full0 = f;
+            return emit(s, d, ang);
+        }
         const bool dec = decide && writer && p == L;
         if (!pos && !dec) return SrcT{};
         // one Philox pass: position lanes draw their entry's individual and
-        // region (or, after the shared-slot search, read the slot it drew),
-        // lane L the mutation decision of individual k
-        uint32_t word = 0u;
-        if (a.dup && pos) {
-            word = dup_words(a, gen)[(size_t)ci * L + p];
-        } else {
-            const u32x4 w = draw(a.seed, pos ? (uint32_t)TAG_SAMPLE : (uint32_t)TAG_MUT_IND, gen, i,
-                                 pos ? k * (uint32_t)L + (uint32_t)p : k);
-            if (!pos) {
-                if ((uint64_t)w.x < a.thr_pm) mark_mutation(a, gen, i, k);
-                return SrcT{};
-            }
-            word = slot_of_draw(a, w, (uint32_t)p);
+        // region, lane L the mutation decision of individual k
+        const u32x4 w = draw(a.seed, pos ? (uint32_t)TAG_SAMPLE : (uint32_t)TAG_MUT_IND, gen, i,
+                             pos ? k * (uint32_t)L + (uint32_t)p : k);
+        if (!pos) {
+            if ((uint64_t)w.x < a.thr_pm) mark_mutation(a, gen, i, k);
+            return SrcT{};
         }
-        const uint32_t s = a.dup ? (word & ~DUP_SHARED) : word;
-        const bool al = is_alone(word);
-#pragma unroll
-        for (int c = 0; c < KEEP; ++c)
-            if (c == ch) { kept[c] = s; alone[c] = al; }
+        const uint32_t s = slot_of_draw(a, w, (uint32_t)p);
+        put(ch, s, false);
         if constexpr (ISING) {
-            // (whole records only where the fused kernel may commit them)
-            const uint2 g = (ch == 0 && a.dup) ? decode_ising<true>(a, gen, i, s, &full0)
-                                               : decode_ising(a, gen, i, s);
-            if (writer) {
-                if (slots_out) slots_out[(size_t)ci * L + p] = s;
-                gates_out[(size_t)ci * L + p] = (uint16_t)g.x;
-                angles_out[(size_t)ci * L + p] = g.y;
-            }
-            return g;
+            const uint2 g = decode_ising(a, gen, i, s);
+            return emit(s, g.x, g.y);
         } else {
-            const uint16_t d = (ch == 0 && a.dup) ? decode_slot<true>(a, gen, i, s, &full0)
-                                                  : decode_slot(a, gen, i, s);
-            if (writer) {
-                if (slots_out) slots_out[(size_t)ci * L + p] = s;
-                gates_out[(size_t)ci * L + p] = d;
-            }
-            return (uint32_t)d;
+            return emit(s, (uint32_t)decode_slot(a, gen, i, s), 0u);
         }
     };
     // the circuit's descriptors, chunk ch (every wavefront of the circuit
@@ -586,14 +597,25 @@ __global__ void scatter_kernel(LoopArgs a, const uint32_t* __restrict__ slots,
     atomicMax(&a.slot[(size_t)i * a.S + s].key, seg_key(fv));
 }
 
-// Mutation decisions for the step-by-step path (qe_update): one thread per
-// individual.
-__global__ void mutation_decision_kernel(LoopArgs a, uint64_t gen64) {
-    const uint32_t id = blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= (uint32_t)a.I * (uint32_t)a.P) return;
-    const uint32_t gen = gen_of(a, gen64), i = id / (uint32_t)a.P, ind = id % (uint32_t)a.P;
-    clear_next_mask(a, gen, i, ind);
-    if (mutates(a, gen, i, ind)) mark_mutation(a, gen, i, ind);
+// The decisions of up to 64 individuals from 64 * block on, one per lane, written
+// as whole words of the generation's mask.
+__device__ __forceinline__ void decide_64(const LoopArgs& a, uint32_t gen, uint32_t i, uint32_t block) {
+    const uint32_t ind = block * 64u + lane_id();
+    const uint64_t m = __ballot(ind < (uint32_t)a.P && mutates(a, gen, i, ind));
+    const uint32_t w = block * 2u + lane_id();
+    if (lane_id() < 2u && w < a.MW) mask_of(a, gen, i)[w] = (uint32_t)(m >> (32u * lane_id()));
+}
+
+// Mutation decisions for the step-by-step path (qe_update): one wavefront per
+// 64 individuals of a population.  (The other parity's mask is emptied as the
+// fused kernel does, but where the search writes masks whole.)
+__global__ void mutation_decision_kernel(LoopArgs a, uint64_t gen64, uint32_t per) {
+    const uint32_t wv = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    if (wv >= (uint32_t)a.I * per) return;
+    const uint32_t gen = gen_of(a, gen64), i = wv / per, block = wv % per;
+    decide_64(a, gen, i, block);
+    const uint32_t w = block * 2u + lane_id();
+    if (!a.dup && lane_id() < 2u && w < a.MW) mask_of(a, gen + 1u, i)[w] = 0u;
 }
 
 __global__ void mutmask_clear_kernel(LoopArgs a) {
@@ -710,22 +732,46 @@ __device__ __forceinline__ uint32_t dedup_hash(uint32_t x) {
 }
 
 // Population i's search, by a whole workgroup of 256 threads, with keys the
-// dedup_table(P * L) words of dynamic LDS.
+// dedup_table(P * L) words of dynamic LDS.  It also prepares what the fused
+// kernel would draw with one wavefront per circuit for a few of its lanes: the
+// rotation slots' measurement draws (gathered in LDS, one per lane) and the
+// individuals' mutation decisions, and it knows each entry's region without
+// the divisions that take a slot index apart.
 __device__ __forceinline__ void dedup_population(const LoopArgs& a, uint32_t gen, uint32_t i,
                                                  uint32_t* keys) {
     constexpr uint32_t EMPTY = 0xFFFFFFFFu;
     constexpr int PER = DEDUP_MAX_ENTRIES / 256;
     const uint32_t L = (uint32_t)a.L, LP = L * (uint32_t)a.P, T = dedup_table(LP);
+    __shared__ uint32_t n_shared, n_rot, code[MAX_QUBITS * MAX_QUBITS];
     for (uint32_t t = threadIdx.x; t < T; t += 256) keys[t] = EMPTY;
+    if (threadIdx.x == 0) { n_shared = 0u; n_rot = 0u; }
+    if (threadIdx.x < a.R) {
+        // a region's part of the aux word
+        const int r = (int)threadIdx.x;
+        int x, y;
+        uint32_t c = AUX_ROT | ((uint32_t)r << 24);
+        if (r >= a.n) {
+            if (a.lib == LIB_ISING) {
+                upair_of(a.n, r - a.n, &x, &y);
+                c = (uint32_t)x | ((uint32_t)y << 4);
+            } else {
+                pair_of(a.n, r - a.n, &x, &y);       // (control, target)
+                c = (uint32_t)y | ((uint32_t)x << 4);
+            }
+        }
+        code[r] = c;
+    }
     __syncthreads();
-    uint32_t sl[PER], at[PER];
+    uint32_t sl[PER], at[PER];               // slot; table place, the region in the upper half
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
         const uint32_t e = (uint32_t)u * 256u + threadIdx.x;
         sl[u] = 0u;
         at[u] = 0u;
         if (e >= LP) continue;
-        const uint32_t s = sample_slot(a, gen, i, e / L, e % L);      // < 2^31
+        const u32x4 w = draw(a.seed, TAG_SAMPLE, gen, i, e);
+        const uint32_t region = scale_u32(w.y, a.R);
+        const uint32_t s = slot_of_draw(a, w, e % L);      // < 2^31
         uint32_t h = (uint32_t)(((uint64_t)dedup_hash(s) * T) >> 32);
         // the table holds at most LP <= T / 2 slots: a free entry is always
         // found
@@ -739,26 +785,53 @@ __device__ __forceinline__ void dedup_population(const LoopArgs& a, uint32_t gen
             h = h + 1u == T ? 0u : h + 1u;
         }
         sl[u] = s;
-        at[u] = h;
+        at[u] = h | (region << 16);
     }
-    __shared__ uint32_t n_shared;
-    if (threadIdx.x == 0) n_shared = 0u;
     __syncthreads();
     const size_t base = (size_t)(gen & 1u) * a.I + i;
     uint32_t* out = dup_words(a, gen) + (size_t)i * LP;
+    uint32_t* aux = aux_words(a, gen) + (size_t)i * LP;
     uint2* list = a.shared_list + base * LP;
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
         const uint32_t e = (uint32_t)u * 256u + threadIdx.x;
         if (e >= LP) continue;
-        const uint32_t sh = keys[at[u]] & DUP_SHARED;
+        const uint32_t sh = keys[at[u] & 0xFFFFu] & DUP_SHARED;
         out[e] = sl[u] | sh;
         // the shared entries, for the update (in no particular order: each
         // entry's work on its slot does not depend on the others')
         if (sh) list[atomicAdd(&n_shared, 1u)] = make_uint2(e, sl[u]);
+        const uint32_t c = code[at[u] >> 16];
+        if (!(c & AUX_ROT)) aux[e] = c;
     }
     __syncthreads();
     if (threadIdx.x == 0) a.shared_count[base] = n_shared;
+    // the rotation entries, in the table's place ({entry, region}, slot: two
+    // words of the table per entry at most)
+    static_assert(DEDUP_MAX_ENTRIES <= 1 << 16, "entry and region in a word");
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const uint32_t e = (uint32_t)u * 256u + threadIdx.x;
+        const bool rot = e < LP && (code[at[u] >> 16] & AUX_ROT);
+        const uint64_t m = __ballot(rot);
+        if (!m) continue;
+        uint32_t first = 0u;
+        if (lane_id() == 0) first = atomicAdd(&n_rot, (uint32_t)__popcll(m));
+        first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
+        if (rot) {
+            const uint32_t k = first + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            keys[2u * k] = e | (at[u] & 0xFFFF0000u);
+            keys[2u * k + 1u] = sl[u];
+        }
+    }
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < n_rot; k += 256u) {
+        const uint32_t er = keys[2u * k], s = keys[2u * k + 1u];
+        const u32x4 w = draw(a.seed, TAG_MEASURE, gen, i, s);
+        aux[er & 0xFFFFu] = code[er >> 16] | (w.x >> 8);
+    }
+    for (uint32_t b = threadIdx.x >> 6; b * 64u < (uint32_t)a.P; b += 4u) decide_64(a, gen, i, b);
 }
 
 __global__ __launch_bounds__(256) void dedup_kernel(LoopArgs a, uint64_t gen64) {
@@ -1500,7 +1573,8 @@ hipError_t launch_qeqea_fused(const LoopArgs& a, uint64_t gen, uint32_t* slots, 
 }
 
 hipError_t launch_mutation_decisions(const LoopArgs& a, uint64_t gen, hipStream_t s) {
-    mutation_decision_kernel<<<blocks((size_t)a.I * a.P, 256), 256, 0, s>>>(a, gen);
+    const uint32_t per = ((uint32_t)a.P + 63u) / 64u;
+    mutation_decision_kernel<<<blocks((size_t)a.I * per, 4), 256, 0, s>>>(a, gen, per);
     return hipGetLastError();
 }
 
