@@ -748,6 +748,7 @@ qe_status create_impl(const qe_problem* p_in, const int32_t* inst_n, const int32
             ALLOC(a.shared_count, 2 * I);
         }
         ALLOC(a.su3_tab, (size_t)4 * SU3_TAB);
+        ALLOC(a.inst_units, I);
     } else {
         ALLOC(a.genomes[0], (size_t)genes);
         ALLOC(a.genomes[1], (size_t)genes);
@@ -914,6 +915,7 @@ qe_status qe_set_targets(qe_ctx* c, const void* t, void* stream) {
     }
     QE_HIP(hipMemcpyAsync((void*)c->la.target64, t, reals * sizeof(double), hipMemcpyDeviceToDevice, s));
     QE_HIP(launch_c128_to_c64(c->la.target64, (float*)c->la.target32, (int64_t)reals, s));
+    if (c->prob.algorithm == QE_ALG_QEQEA) QE_HIP(launch_target_units(c->la, s));
     c->targets_set = true;
     return QE_OK;
 }

@@ -137,6 +137,7 @@ struct LoopArgs {
     uint16_t* genomes[2];              // GA double buffer
     const float* target32;             // [I][N][N] complex64
     const double* target64;            // [I][N][N] complex128
+    uint32_t* inst_units;              // [I] QEQEA: target32 holds only 0, +-1 and +-i
     // Mutation decisions as bitmaps, double-buffered by generation parity:
     // generation g sets bit ind of mask g & 1 for every individual that
     // mutates and clears mask (g + 1) & 1, which generation g - 1 consumed.
@@ -228,6 +229,7 @@ hipError_t launch_state_gather(const LoopArgs& a, int which, void* dst, hipStrea
 hipError_t launch_ga_eval(const LoopArgs& a, uint64_t gen, float* f, hipStream_t s);
 hipError_t launch_ga_update(const LoopArgs& a, uint64_t gen, const float* f, hipStream_t s);
 hipError_t launch_c128_to_c64(const double* src, float* dst, int64_t n_reals, hipStream_t s);
+hipError_t launch_target_units(const LoopArgs& a, hipStream_t s);
 hipError_t launch_gen_advance(uint64_t* gen_ptr, uint64_t by, hipStream_t s);
 hipError_t launch_gen_set(uint64_t* gen_ptr, uint64_t v, hipStream_t s);
 // cand: elite_cand_keys(I, P) 64-bit keys of device workspace.

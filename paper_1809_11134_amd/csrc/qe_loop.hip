@@ -485,7 +485,8 @@ __device__ __forceinline__ void eval_circuit(const LoopArgs& a, uint32_t gen, ui
             }
         };
         mat.load(T);
-        ok = mat.template run<true>(L, rest, dv0);
+        const bool units = SAMPLE && !ISING && __builtin_amdgcn_readfirstlane((int)a.inst_units[i]) != 0;
+        ok = mat.template run<true, SAMPLE && !ISING>(L, rest, dv0, units);
         fv = mat.fitness(a.fit_mode, &gd, &dd, wave, red);
         if (keep) full0 = unstash_full(stash, lane);
     } else {
@@ -1457,6 +1458,21 @@ __global__ void c128_to_c64_kernel(const double* __restrict__ src, float* __rest
     if (idx < n) dst[idx] = (float)src[idx];
 }
 
+// Whether every entry of population i's target is 0, +-1 or +-i (one workgroup
+// each; uniform widths).
+__global__ __launch_bounds__(64) void target_units_kernel(LoopArgs a) {
+    const size_t NN = (size_t)1 << (2 * a.n);
+    const float* T = a.target32 + 2 * NN * blockIdx.x;
+    bool bad = false;
+    for (size_t e = threadIdx.x; e < NN; e += 64) {
+        const float x = T[2 * e], y = T[2 * e + 1];
+        // (one part zero, the other 0 or +-1; NaN fails)
+        bad = bad || !((x == 0.0f && (y == 0.0f || y * y == 1.0f)) || (y == 0.0f && x * x == 1.0f));
+    }
+    const bool units = __ballot(bad) == 0ull;
+    if (threadIdx.x == 0) a.inst_units[blockIdx.x] = units ? 1u : 0u;
+}
+
 // ---------------------------------------------------------------- launchers
 static inline unsigned blocks(size_t n, unsigned bs) { return (unsigned)((n + bs - 1) / bs); }
 
@@ -1480,6 +1496,11 @@ hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
 
 hipError_t launch_c128_to_c64(const double* src, float* dst, int64_t n_reals, hipStream_t s) {
     if (n_reals > 0) c128_to_c64_kernel<<<blocks((size_t)n_reals, 256), 256, 0, s>>>(src, dst, n_reals);
+    return hipGetLastError();
+}
+
+hipError_t launch_target_units(const LoopArgs& a, hipStream_t s) {
+    target_units_kernel<<<a.I, 64, 0, s>>>(a);
     return hipGetLastError();
 }
 

@@ -122,18 +122,19 @@ struct RegMatrix {
 
     // The word of a gate (its descriptor checked) for reg_gates: table, target and
     // control (the target again for a single-wire gate).
-    static __device__ __forceinline__ uint32_t gate_word(uint32_t d) {
+    // (exact: the bodies for exact values of a sampled circuit)
+    static __device__ __forceinline__ uint32_t gate_word(uint32_t d, bool exact) {
         const uint32_t kind = d & 15u, t = (d >> 4) & 15u;
         const uint32_t c = kind_two_wire((int)kind) ? (d >> 8) & 15u : t;
         if constexpr (LB == 0) {
             // tables by kind: NOT 2, CNOT 1, CV, CV+ 0, H 0, T 1, R_x 3, R_y 4, R_z 5, J 2
-            const uint32_t table = (uint32_t)(0x25431000120ull >> (4u * kind)) & 15u;
+            const uint32_t table = (uint32_t)((exact ? 0x33120ull : 0x25431000120ull) >> (4u * kind)) & 15u;
             const uint32_t ts = NQ - 1 - t, cs = NQ - 1 - c;
             const bool flip = kind == KIND_ZZ && ts > cs;            // (symmetric: one order)
             return 256u * table + 32u * (flip ? cs : ts) + 4u * (flip ? ts : cs);
         }
         // tables by kind: NOT, CNOT 2, CV 0, CV+ 1, H 0, T 1, R_x 3, R_y 4, R_z 5, J 3
-        const uint32_t table = (uint32_t)(0x35431010220ull >> (4u * kind)) & 15u;
+        const uint32_t table = (uint32_t)((exact ? 0x43220ull : 0x35431010220ull) >> (4u * kind)) & 15u;
         if constexpr (NQ == 4) {
             // entries 0, 1: row bits 2, 3 (register bits); 2, 3: row bits 0, 1 (lane
             // slots); wire w is row bit 3 - w
@@ -148,9 +149,14 @@ struct RegMatrix {
     // Applies the circuit; false if a descriptor was invalid (M is then
     // garbage).  RESTORE: and leaves the slots in canonical order.  dv0: the
     // source's first chunk, fetched by the caller.
-    template <bool RESTORE, typename GateSrc, typename SrcT>
-    __device__ __forceinline__ bool run(int L, GateSrc&& src, const SrcT dv0) {
+    // NCV: the source only yields what the QEQEA sampler decodes; units: the target
+    // holds only 0, +-1 and +-i.
+    template <bool RESTORE, bool NCV = false, typename GateSrc, typename SrcT>
+    __device__ __forceinline__ bool run(int L, GateSrc&& src, const SrcT dv0, bool units = false) {
         constexpr bool ANG = src_angled<GateSrc>();
+        static_assert(!NCV || !ANG, "sampled discrete circuits hold no angles");
+        constexpr int GATES = ANG ? GATES_ANGLED : (NCV ? GATES_SAMPLED : GATES_DISCRETE);
+        uint32_t cvs = 0u;                     // CV and CV+ gates so far
         const int lane = (int)lane_id();
         L = __builtin_amdgcn_readfirstlane(L);
         const int chunks = (L + 63) >> 6;
@@ -170,11 +176,16 @@ struct RegMatrix {
             const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(todo >> 32),
                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)todo, 0u));
             const int to = 4 * (int)(live ? rank : cnt + (uint32_t)lane - rank);
-            const uint32_t word = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(live ? gate_word(dv) : 0u));
+            bool exact = false;
+            if constexpr (NCV) {
+                cvs += (uint32_t)__popcll(__ballot(live && kind >= KIND_CV));
+                exact = units && cvs <= EXACT_CV_MAX;
+            }
+            const uint32_t word = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(live ? gate_word(dv, exact) : 0u));
             Real gc = (Real)0.70710678118654752440084436210485, gs = (Real)0;
             if constexpr (LB == 0) {           // (CV and CV+ come with their signs)
-                if (kind == KIND_CV) gc = (Real)0.5;
-                if (kind == KIND_CVDG) gc = (Real)-0.5;
+                if (kind == KIND_CV) gc = exact ? (Real)1 : (Real)0.5;
+                if (kind == KIND_CVDG) gc = exact ? (Real)-1 : (Real)-0.5;
                 gs = -gc;
             }
             if constexpr (ANG)
@@ -183,7 +194,7 @@ struct RegMatrix {
                 gc = permute(to, gc);
                 gs = permute(to, gs);
             }
-            reg_gates<NQ, ANG>(x, word, cnt, gc, gs, map, RESTORE && ch + 1 >= chunks);
+            reg_gates<NQ, GATES>(x, word, cnt, gc, gs, map, RESTORE && ch + 1 >= chunks);
             if (++ch < chunks) dvv = src(ch);
         } while (ch < chunks);
         return true;
