@@ -7,17 +7,25 @@
 // in C++ the same bodies under a dispatch cost 16 to 50 register moves per gate
 // (the compiler turns the dispatch into a chain of merges and copies what a
 // body swapped at each) and a tree of compares; here a gate costs its
-// arithmetic, about 20 scalar instructions and three branches.
+// arithmetic, a dozen scalar instructions and two branches.
 //
-// Tables of 16 entries (target 4 t, control c; t = c: a single-wire gate):
+// What bounds it: the VALU's and the scalar unit's issue slots together (a SIMD
+// issues one of each per four cycles and a wavefront one at a time): ten more
+// instructions per gate of n = 5 circuits cost the fused generation of 65536 of
+// them (180 us) 17 us as scalar and 9 us as vector instructions.  Hence the words
+// that are s_bfe operands, the maps that are shift amounts, the gate count that
+// carries out, and the loop's head at the end of every body (against a plain loop of
+// about 20 scalar instructions a gate and 54 an exchange: 185 -> 176 us there).
+//
+// Tables of 64 entries (target 8 t, control c; t = c: a single-wire gate):
 //   0 CV, H   1 CV+, T   2 CNOT, NOT   3 interaction, R_x   4 R_y   5 R_z
 // (sampled circuits, which hold no other kinds: 0 CV  1 CV+  2 CNOT, NOT and 3 CV
-// 4 CV+ of exact values) and, with 16 registers per lane, the exchanges of register bits 0..3 and
-// lane slots 4, 5 (row: the higher, column: the lower, always a register
-// bit).  Entries that nothing has lead to the block's end.
+// 4 CV+ of exact values); with 16 registers per lane also the exchanges of register
+// bits 0..3 and lane slots 4, 5 (4 times the higher, plus the lower, always a
+// register bit).  Entries that nothing has lead to the block's end.
 //
 // 16 registers (widths 5, 6): a wire is in any slot (maps W: wire to slot, S:
-// slot to wire, 4 bits each).  A gate whose wire is in a lane slot first
+// slot to wire).  A gate whose wire is in a lane slot first
 // exchanges that slot with a register bit, by choice one that the next gate
 // does not use.  4 registers (width 4): every wire keeps its slot (entries 0,
 // 1: register bits, 2, 3: lane slots) and the bodies deal with the lane slots
@@ -25,9 +33,9 @@
 // keeping the maps would cost more scalar instructions than that saves.
 //
 // 64 registers (width 6, one column per lane): every wire is a register bit, so
-// a gate's word is its entry.  Tables of 64 entries (target 8 t, control c):
+// a gate's word is its entry, in the tables
 //   0 CV and CV+, H   1 CNOT, T   2 interaction (t < c), NOT   3 R_x   4 R_y   5 R_z
-// (sampled circuits: 3 CV and CV+ of exact values)
+// (sampled circuits: 2 NOT and 3 CV and CV+ of exact values)
 //
 // Multiplies and adds stay separate (one rounding each) except in CV, whose
 // last step is a fused multiply-add of exact halves.
@@ -76,8 +84,8 @@ __device__ __forceinline__ void reg_set(f64x32& x, int i, double v) {
     else x.hi[i - 16] = v;
 }
 
-// Wave-uniform maps between wires and slots, 4 bits per entry: register bit k is
-// slot k, lane slot s slot 4 + s.
+// Wave-uniform maps: wire w's slot in bits 4 w.. of w2s, slot s's wire times 4 in bits
+// 5 s.. of s2w; register bit k is slot k, lane slot s slot 4 + s.
 struct SlotMap {
     uint32_t w2s, s2w;
 };
@@ -231,10 +239,10 @@ constexpr uint32_t EXACT_CV_MAX = 36;
     QR_SWAPS(P, E, "v_permlane32_swap_b32", K) ".endif\n"
 #define QR_LANE1(P, E, S, K) "s_nop 1\n" QR_SWAPS(P, E, "v_permlane32_swap_b32", K)
 
-#define QR_BODY(name, list, text) ".irp n," list "\n.Lqr%=" name "\\n:\n" text "s_branch .Lqr%=l\n.endr\n"
-#define QR_TWO16 "1,2,3,4,6,7,8,9,11,12,13,14"
-#define QR_ONE16 "0,5,10,15"
-#define QR_SETTC ".set QT,\\n>>2\n.set QC,\\n&3\n"
+#define QR_BODY(name, list, text) ".irp n," list "\n.Lqr%=" name "\\n:\n" text "qrnext%=\n.endr\n"
+#define QR_TWO16 "1,2,3,8,10,11,16,17,19,24,25,26"
+#define QR_ONE16 "0,9,18,27"
+#define QR_SETTC ".set QT,\\n>>3\n.set QC,\\n&7\n"
 // widths 5, 6: target and control are register bits
 #define QR_TWO_16(name, text) QR_BODY(name, QR_TWO16, QR_SETTC text)
 #define QR_ONE_16(name, text) QR_BODY(name, QR_ONE16, QR_SETTC text)
@@ -243,7 +251,6 @@ constexpr uint32_t EXACT_CV_MAX = 36;
 // register control: only the rows it changes); a lane slot's control, and the
 // one row that T changes, are masked lanes; the diagonal rotations take the
 // sign of B from the lane.
-#define QR_SET4 ".set QT,\\n>>2\n.set QC,\\n&3\n"
 #define QR_MASK(slot)      /* the lanes whose lane slot (2 or 3) is 1 */                              \
     ".if (" slot ")==2\n.set QML,0xffff0000\n.set QMH,0xffff0000\n.else\n.set QML,0\n.set QMH,0xffffffff\n.endif\n"
 #define QR_EXEC "s_mov_b32 exec_lo,QML\ns_mov_b32 exec_hi,QMH\n"
@@ -252,7 +259,7 @@ constexpr uint32_t EXACT_CV_MAX = 36;
     "s_nop 1\n.if (" S ")==0\n" QR_ROWS2(4, QR_XCH##P("v_permlane16_swap_b32", QR_A, QR_P))          \
     ".else\n" QR_ROWS2(4, QR_XCH##P("v_permlane32_swap_b32", QR_A, QR_P)) ".endif\n"
 #define QR_CTL4(P, name, row)                                                                        \
-    QR_BODY(name, QR_TWO16, QR_SET4                                                                  \
+    QR_BODY(name, QR_TWO16, QR_SETTC                                                                  \
         ".if (QT<2)&(QC<2)\n" QR_ROWS2(4, row)                                                       \
         ".elseif QT<2\n" QR_MASK("QC") QR_EXEC QR_ROWS1(4, row) QR_EXEC_ALL                          \
         ".elseif QC<2\n.set QS0,QT-2\n.set QT,1-QC\n"                                                \
@@ -260,14 +267,14 @@ constexpr uint32_t EXACT_CV_MAX = 36;
         ".else\n.set QS0,QT-2\n.set QT,0\n" QR_LANE2(P, 4, "QS0", "0")                               \
         QR_MASK("QC") QR_EXEC QR_ROWS1(4, row) QR_EXEC_ALL QR_LANE2(P, 4, "QS0", "0") ".endif\n")
 #define QR_ONE4(P, name, text)                                                                       \
-    QR_BODY(name, QR_ONE16, QR_SET4                                                                  \
+    QR_BODY(name, QR_ONE16, QR_SETTC                                                                  \
         ".if QT<2\n" text ".else\n.set QS0,QT-2\n.set QT,0\n"                                        \
         QR_LANE2(P, 4, "QS0", "0") text QR_LANE2(P, 4, "QS0", "0") ".endif\n")
 #define QR_TROW(P)                                                                                   \
     QR_SUB##P(QR_T##P(0), QR_X##P(QR_A), QR_Y##P(QR_A)) QR_ADD##P(QR_Y##P(QR_A), QR_X##P(QR_A), QR_Y##P(QR_A)) \
     QR_MUL##P(QR_X##P(QR_A), QR_A##P, QR_T##P(0)) QR_MUL##P(QR_Y##P(QR_A), QR_A##P, QR_Y##P(QR_A))
 #define QR_T4(P)                                                                                     \
-    QR_BODY("t", QR_ONE16, QR_SET4                                                                   \
+    QR_BODY("t", QR_ONE16, QR_SETTC                                                                   \
         ".if QT<2\n" QR_ROWS(4, "((\\a>>QT)&1)==1", QR_TROW(P))                                      \
         ".else\n" QR_MASK("QT") QR_EXEC QR_ROWS(4, "1", QR_TROW(P)) QR_EXEC_ALL ".endif\n")
 // temporary 3: B, negated in the lanes of the mask; then row a times A - i B3, or
@@ -288,24 +295,24 @@ constexpr uint32_t EXACT_CV_MAX = 36;
     QR_ADD##P(QR_X##P(QR_A), QR_X##P(QR_A), QR_T##P(0)) QR_SUB##P(QR_Y##P(QR_A), QR_Y##P(QR_A), QR_T##P(1)) \
     ".endif\n.endr\n"
 #define QR_RZ4(P)                                                                                    \
-    QR_BODY("rz", QR_ONE16, QR_SET4                                                                  \
+    QR_BODY("rz", QR_ONE16, QR_SETTC                                                                  \
         ".if QT<2\n" QR_RZ(P, 4) ".else\n" QR_MASK("QT") QR_SIGN##P QR_PHASE(P, "0") ".endif\n")
 #define QR_ZZ4(P)                                                                                    \
-    QR_BODY("zz", QR_TWO16, QR_SET4                                                                  \
+    QR_BODY("zz", QR_TWO16, QR_SETTC                                                                  \
         ".if (QT<2)&(QC<2)\n" QR_ZZ(P, 4)                                                            \
         ".elseif QT<2\n" QR_MASK("QC") QR_SIGN##P QR_PHASE(P, "((\\a>>QT)&1)==1")                    \
         ".elseif QC<2\n" QR_MASK("QT") QR_SIGN##P QR_PHASE(P, "((\\a>>QC)&1)==1")                    \
         ".else\n.set QML,0xffff0000\n.set QMH,0x0000ffff\n" QR_SIGN##P QR_PHASE(P, "0") ".endif\n")
 
-#define QR_TAB(two, one)                                                                             \
-    ".irp n," QR_ELEMS16 "\n.if (\\n>>2)==(\\n&3)\ns_branch .Lqr%=" one "\\n\n.else\n"               \
-    "s_branch .Lqr%=" two "\\n\n.endif\n.endr\n"
-#define QR_TAB1(one)                                                                                 \
-    ".irp n," QR_ELEMS16 "\n.if (\\n>>2)==(\\n&3)\ns_branch .Lqr%=" one "\\n\n.else\n"               \
-    "s_branch .Lqr%=e\n.endif\n.endr\n"
-#define QR_TAB2(two)                                                                                 \
-    ".irp n," QR_ELEMS16 "\n.if (\\n>>2)==(\\n&3)\ns_branch .Lqr%=e\n.else\n"                          \
-    "s_branch .Lqr%=" two "\\n\n.endif\n.endr\n"
+// a table: bodies of two wires and of one, by name (QRN slots, those from QRL on
+// lead to the exchange)
+#define QR_TABLE(test, two, one)                                                                     \
+    ".irp n," QR_ELEMS64 "\n.if ((\\n>>3)>=QRN)|((\\n&7)>=QRN)|(" test ")\ns_branch .Lqr%=e\n"       \
+    ".elseif ((\\n>>3)>=QRL)|((\\n&7)>=QRL)\ns_branch .Lqr%=s\n"                                     \
+    ".elseif (\\n>>3)==(\\n&7)\ns_branch .Lqr%=" one "\n.else\ns_branch .Lqr%=" two "\n.endif\n.endr\n"
+#define QR_TAB(two, one) QR_TABLE("0", two "\\n", one "\\n")
+#define QR_TAB1(one) QR_TABLE("(\\n>>3)!=(\\n&7)", "e", one "\\n")
+#define QR_TAB2(two) QR_TABLE("(\\n>>3)==(\\n&7)", two "\\n", "e")
 #define QR_TABLES0 QR_TAB("cv", "h") QR_TAB("cd", "t") QR_TAB("cx", "x")
 #define QR_TABLES1 QR_TABLES0 QR_TAB("zz", "rx") QR_TAB1("ry") QR_TAB1("rz")
 #define QR_TABLES2 QR_TAB2("cv") QR_TAB2("cd") QR_TAB("cx", "x") QR_TAB2("cw") QR_TAB2("ce")
@@ -337,26 +344,32 @@ constexpr uint32_t EXACT_CV_MAX = 36;
 #define QR_START0(P) QR_CONST##P
 #define QR_START1(P)
 
-// s[40:41] the tables' address, s42 the next gate's lane, s43 its word
-#define QR_HEAD(P, BASE, TMP, ANG)                                                                   \
-    ".set QRB," BASE "\n.set QRT," TMP "\n"                                                          \
-    "s_getpc_b64 s[40:41]\n.Lqr%=p:\ns_add_u32 s40,s40,.Lqr%=tab-.Lqr%=p\ns_addc_u32 s41,s41,0\n"    \
-    "s_mov_b32 s42,0\n" QR_START##ANG(P) "v_readlane_b32 s43,%[p],s42\n"
+// s[40:41] the tables' address, s43 the next gate's word, s42 its lane (mod 64): the
+// gates lie in the lanes up to 62 (the first in lane 63 - cnt), so that counting
+// s42 up carries out behind the last.  qrnext: goes to the next gate's body, or
+// leaves (the end of every body has its own copy: one branch fewer per gate).
+#define QR_HEAD(BASE, TMP, N, L) ".set QRB," BASE "\n.set QRT," TMP "\n.set QRN," N "\n.set QRL," L "\n"
+#define QR_PC(rest)                                                                                  \
+    "s_getpc_b64 s[40:41]\n.Lqr%=p:\n" rest "s_sub_u32 s42,-1,%[cnt]\nv_readlane_b32 s43,%[p],s42\n"
+#define QR_COUNT(end) "s_add_u32 s42,s42,1\ns_cbranch_scc1 .Lqr%=" end "\n"
 
-// Widths 4: the word is the gate's entry (bytes).
+// Width 4, and 64 registers: the word is the gate's entry (bytes).
+#define QR_ENTRY                                                                                     \
+    QR_COUNT("e") "s_add_u32 s48,s40,s43\ns_addc_u32 s49,s41,0\nv_readlane_b32 s43,%[p],s42\n"       \
+    "s_setpc_b64 s[48:49]\n"
 #define QR_TEXT4(P, BASE, TMP, ANG)                                                                  \
-    QR_HEAD(P, BASE, TMP, ANG)                                                                       \
-    ".Lqr%=l:\n"                                                                                     \
-    "s_cmp_ge_u32 s42,%[cnt]\ns_cbranch_scc1 .Lqr%=e\n"                                              \
-    "s_add_u32 s48,s40,s43\ns_addc_u32 s49,s41,0\n" QR_SCALARS##ANG(P)                               \
-    "s_add_u32 s42,s42,1\n"                                                                          \
-    "v_readlane_b32 s43,%[p],s42\n"                                                                  \
-    "s_setpc_b64 s[48:49]\n"                                                                         \
-    ".Lqr%=tab:\n" QR_TABLES##ANG QR_BODIES4_##ANG(P)                                            \
-    ".Lqr%=e:\n"
+    QR_HEAD(BASE, TMP, "4", "8") QR_START##ANG(P)                                                    \
+    QR_PC("s_add_u32 s40,s40,.Lqr%=tab-.Lqr%=p\ns_addc_u32 s41,s41,0\n")                             \
+    ".macro qrnext%=\n" QR_SCALARS##ANG(P) QR_ENTRY ".endm\nqrnext%=\n"                              \
+    ".Lqr%=tab:\n" QR_TABLES##ANG QR_BODIES4_##ANG(P) ".Lqr%=e:\n"
 
-// Widths 5, 6: the word is 4 * target wire, 4 * control wire (target again for a
-// single-wire gate) in bits 8.., the table (bytes) in bits 16...
+// Widths 5, 6: the word holds 4 * target wire (bits 0..4), the table (bits 5..7), 4 *
+// control wire (target again for a single-wire gate; bits 8..12), and 4 in bits
+// 16.. and 24.., so that it and its half from bit 8 on are s_bfe's offset and width
+// of the wires' slots in W.  A gate is in s45, s46 (its slots) and s50 (its table).
+#define QR_GO16                                                                                      \
+    "s_lshl3_add_u32 s47,s45,s46\ns_lshl1_add_u32 s47,s50,s47\ns_lshl2_add_u32 s48,s47,s40\n"         \
+    "s_addc_u32 s49,s41,0\ns_setpc_b64 s[48:49]\n"
 #define QR_WANT(slot, wire, label)                                                                   \
     "s_bfe_u32 s47,%[W],0x40000+4*" wire "\ns_cmp_eq_u32 s47," slot "\ns_cbranch_scc1 " label "\n"
 #define QR_CALL(label)                                                                               \
@@ -367,49 +380,46 @@ constexpr uint32_t EXACT_CV_MAX = 36;
 #define QR_LANE_BACK2(L0, L1)                                                                        \
     QR_WANT("4", L0, ".Lqr%=r1")                                                                     \
     /* (from the other lane slot by way of register bit 0) */                                        \
-    "s_mov_b32 s50,s47\ns_cmp_lt_u32 s47,4\ns_cbranch_scc1 .Lqr%=r0\n"                               \
-    "s_mov_b32 s50,0\n" QR_CALL("c0") "s_mov_b32 s50,0\n"                                            \
+    "s_mov_b32 s54,s47\ns_cmp_lt_u32 s47,4\ns_cbranch_scc1 .Lqr%=r0\n"                               \
+    "s_mov_b32 s54,0\n" QR_CALL("c0") "s_mov_b32 s54,0\n"                                            \
     ".Lqr%=r0:\ns_mov_b32 s47,4\n" QR_CALL("c1") ".Lqr%=r1:\n"                                       \
-    QR_WANT("5", L1, ".Lqr%=r2") "s_mov_b32 s50,s47\ns_mov_b32 s47,5\n" QR_CALL("c2") ".Lqr%=r2:\n"
+    QR_WANT("5", L1, ".Lqr%=r2") "s_mov_b32 s54,s47\ns_mov_b32 s47,5\n" QR_CALL("c2") ".Lqr%=r2:\n"
 #define QR_LANE_BACK1(L0, L1)                                                                        \
-    QR_WANT("4", L0, ".Lqr%=r2") "s_mov_b32 s50,s47\ns_mov_b32 s47,4\n" QR_CALL("c2") ".Lqr%=r2:\n"
+    QR_WANT("4", L0, ".Lqr%=r2") "s_mov_b32 s54,s47\ns_mov_b32 s47,4\n" QR_CALL("c2") ".Lqr%=r2:\n"
+// exchanges slots s47 and s54 in the maps and in the registers; then to s[58:59]
+#define QR_EXCHANGE                                                                                  \
+    "s_lshl2_add_u32 s51,s54,s54\ns_lshl2_add_u32 s52,s47,s47\n"                                     \
+    "s_lshr_b32 s53,%[S],s51\ns_lshr_b32 s55,%[S],s52\n"                                             \
+    "s_xor_b32 s48,s53,s55\ns_and_b32 s48,s48,31\ns_lshl_b32 s51,s48,s51\ns_lshl_b32 s52,s48,s52\n"   \
+    "s_xor_b32 %[S],%[S],s51\ns_xor_b32 %[S],%[S],s52\n"                                             \
+    "s_xor_b32 s48,s54,s47\ns_lshl_b32 s53,s48,s53\ns_lshl_b32 s55,s48,s55\n"                        \
+    "s_xor_b32 %[W],%[W],s53\ns_xor_b32 %[W],%[W],s55\n"                                             \
+    "s_lshl2_add_u32 s51,s47,s54\ns_lshl2_add_u32 s48,s51,s56\ns_addc_u32 s49,s57,0\ns_setpc_b64 s[48:49]\n"
+#define QR_WHICH1 "s_mov_b32 s47,4\n"
+#define QR_WHICH2 "s_cmp_gt_u32 s45,3\ns_cselect_b32 s47,s45,s46\n"
 #define QR_TEXT16(P, BASE, TMP, LS, ANG, L0, L1, R0, R1, R2)                                         \
-    QR_HEAD(P, BASE, TMP, ANG)                                                                       \
-    "s_getpc_b64 s[58:59]\n.Lqr%=q:\ns_add_u32 s58,s58,.Lqr%=g-.Lqr%=q\ns_addc_u32 s59,s59,0\n"      \
-    ".Lqr%=l:\n"                                                                                     \
-    "s_cmp_ge_u32 s42,%[cnt]\ns_cbranch_scc1 .Lqr%=b\n"                                              \
-    "s_mov_b32 s44,s43\n" QR_SCALARS##ANG(P)                                                         \
-    "s_add_u32 s42,s42,1\n"                                                                          \
+    QR_HEAD(BASE, TMP, "4+" #LS, "4") QR_START##ANG(P)                                               \
+    QR_PC("s_add_u32 s56,s40,.Lqr%=xt-.Lqr%=p\ns_addc_u32 s57,s41,0\n"                                \
+          "s_add_u32 s58,s40,.Lqr%=g-.Lqr%=p\ns_addc_u32 s59,s41,0\n"                                 \
+          "s_add_u32 s40,s40,.Lqr%=tab-.Lqr%=p\ns_addc_u32 s41,s41,0\n")                              \
+    ".macro qrnext%=\n" QR_SCALARS##ANG(P) QR_COUNT("b")                                             \
+    "s_lshr_b32 s47,s43,8\ns_bfe_u32 s45,%[W],s43\ns_bfe_u32 s46,%[W],s47\ns_and_b32 s50,s43,0xe0\n"  \
     "v_readlane_b32 s43,%[p],s42\n" /* (past the last gate it only steers a choice) */               \
-    ".Lqr%=g:\n"                                                                                     \
-    "s_lshr_b32 s47,s44,8\ns_lshr_b32 s45,%[W],s44\ns_lshr_b32 s46,%[W],s47\n"                       \
-    "s_and_b32 s45,s45,15\ns_and_b32 s46,s46,15\ns_or_b32 s47,s45,s46\n"                             \
-    "s_cmp_gt_u32 s47,3\ns_cbranch_scc1 .Lqr%=s\n"                                                   \
-    "s_lshr_b32 s47,s44,16\ns_lshl2_add_u32 s47,s46,s47\ns_lshl4_add_u32 s47,s45,s47\n"              \
-    "s_add_u32 s48,s40,s47\ns_addc_u32 s49,s41,0\ns_setpc_b64 s[48:49]\n"                            \
-    /* a wire of the gate in lane slot s47: the register bit s50 it goes to is not the gate's */     \
+    QR_GO16 ".endm\nqrnext%=\n"                                                                      \
+    /* a wire of the gate in lane slot s47: the register bit s54 it goes to is not the gate's */     \
     /* other wire's nor, if it can be, the next gate's */                                            \
     ".Lqr%=s:\n"                                                                                     \
-    "s_cmp_gt_u32 s45,3\ns_cselect_b32 s47,s45,s46\n"                                                \
-    "s_mov_b32 s50,0\ns_bitset1_b32 s50,s45\ns_bitset1_b32 s50,s46\n"                                \
-    "s_lshr_b32 s52,s43,8\ns_lshr_b32 s51,%[W],s43\ns_lshr_b32 s52,%[W],s52\n"                       \
-    "s_and_b32 s51,s51,15\ns_and_b32 s52,s52,15\n"                                                   \
-    "s_mov_b32 s53,s50\ns_bitset1_b32 s53,s51\ns_bitset1_b32 s53,s52\n"                              \
-    "s_andn2_b32 s53,15,s53\ns_cselect_b32 s51,s53,0\ns_andn2_b32 s50,15,s50\n"                      \
-    "s_cmp_eq_u32 s51,0\ns_cselect_b32 s50,s50,s51\ns_ff1_i32_b32 s50,s50\n"                         \
-    /* slots s47 and s50 change wires, in the maps and in the registers; then to s[58:59] */         \
-    ".Lqr%=x:\n"                                                                                     \
-    "s_lshl_b32 s51,s50,2\ns_lshl_b32 s52,s47,2\ns_lshr_b32 s53,%[S],s51\ns_lshr_b32 s54,%[S],s52\n" \
-    "s_and_b32 s53,s53,15\ns_and_b32 s54,s54,15\ns_xor_b32 s55,s53,s54\n"                            \
-    "s_lshl_b32 s51,s55,s51\ns_lshl_b32 s52,s55,s52\ns_xor_b32 %[S],%[S],s51\ns_xor_b32 %[S],%[S],s52\n" \
-    "s_lshl_b32 s53,s53,2\ns_lshl_b32 s54,s54,2\ns_xor_b32 s55,s50,s47\n"                            \
-    "s_lshl_b32 s53,s55,s53\ns_lshl_b32 s54,s55,s54\ns_xor_b32 %[W],%[W],s53\ns_xor_b32 %[W],%[W],s54\n" \
-    "s_lshl2_add_u32 s51,s50,.Lqr%=xt-.Lqr%=tab\ns_lshl4_add_u32 s51,s47,s51\n"                      \
-    "s_add_u32 s48,s40,s51\ns_addc_u32 s49,s41,0\ns_setpc_b64 s[48:49]\n"                            \
+    "s_lshr_b32 s52,s43,8\ns_bfe_u32 s51,%[W],s43\ns_bfe_u32 s52,%[W],s52\n"                         \
+    "s_mov_b32 s53,15\ns_bitset0_b32 s53,s45\ns_bitset0_b32 s53,s46\n"                               \
+    "s_mov_b32 s54,s53\ns_bitset0_b32 s54,s51\ns_bitset0_b32 s54,s52\n"                              \
+    "s_cmp_lg_u32 s54,0\ns_cselect_b32 s54,s54,s53\ns_ff1_i32_b32 s54,s54\n" QR_WHICH##LS            \
+    "s_cmp_eq_u32 s45,s47\ns_cselect_b32 s45,s54,s45\ns_cmp_eq_u32 s46,s47\ns_cselect_b32 s46,s54,s46\n" \
+    ".Lqr%=x:\n" QR_EXCHANGE                                                                         \
+    ".Lqr%=g:\n" QR_GO16                                                                             \
     ".Lqr%=tab:\n" QR_TABLES##ANG                                                                    \
     ".Lqr%=xt:\n.irp n,0,1,2,3,4,5,6,7,8,9,10,11,12,13,14,15,16,17,18,19,20,21,22,23\n"              \
     ".if ((\\n>>2)>(\\n&3))&((\\n>>2)<4+" #LS ")\ns_branch .Lqr%=v\\n\n.else\ns_branch .Lqr%=e\n.endif\n.endr\n" \
-    QR_BODIES16_##ANG(P)                                                                        \
+    QR_BODIES16_##ANG(P)                                                                             \
     ".irp n,4,8,9,12,13,14\n.Lqr%=v\\n:\n"                                                           \
     QR_ROWS(16, "(((\\a>>(\\n>>2))&1)==0)&(((\\a>>(\\n&3))&1)==1)",                                  \
             QR_XCH##P("v_swap_b32", QR_A, "\\a+(1<<(\\n>>2))-(1<<(\\n&3))"))                         \
@@ -418,36 +428,24 @@ constexpr uint32_t EXACT_CV_MAX = 36;
     QR_LANE##LS(P, 16, "(\\n>>2)-4", "\\n&3") "s_setpc_b64 s[58:59]\n.endif\n.endr\n"                \
     /* after the last gate */                                                                        \
     ".Lqr%=b:\ns_cmp_eq_u32 %[restore],0\ns_cbranch_scc1 .Lqr%=e\n" QR_LANE_BACK##LS(L0, L1)         \
-    QR_WANT("0", R0, ".Lqr%=r3") "s_mov_b32 s50,0\n" QR_CALL("c3") ".Lqr%=r3:\n"                     \
-    QR_WANT("1", R1, ".Lqr%=r4") "s_mov_b32 s50,1\n" QR_CALL("c4") ".Lqr%=r4:\n"                     \
-    QR_WANT("2", R2, ".Lqr%=e") "s_mov_b32 s50,2\n" QR_CALL("c5")                                    \
+    QR_WANT("0", R0, ".Lqr%=r3") "s_mov_b32 s54,0\n" QR_CALL("c3") ".Lqr%=r3:\n"                     \
+    QR_WANT("1", R1, ".Lqr%=r4") "s_mov_b32 s54,1\n" QR_CALL("c4") ".Lqr%=r4:\n"                     \
+    QR_WANT("2", R2, ".Lqr%=e") "s_mov_b32 s54,2\n" QR_CALL("c5")                                    \
     ".Lqr%=e:\n"
 
 // Width 6, 64 registers: the gate's scalars always come with it (CV and CV+
 // share a body: A, B = +-1/2, which keeps the bodies within 40 KB of
 // instruction cache).
-#define QR_SET8 ".set QT,\\n>>3\n.set QC,\\n&7\n"
 #define QR_TWO64 "1,2,3,4,5,8,10,11,12,13,16,17,19,20,21,24,25,26,28,29,32,33,34,35,37,40,41,42,43,44"
 #define QR_ONE64 "0,9,18,27,36,45"
 #define QR_UP64 "1,2,3,4,5,10,11,12,13,19,20,21,28,29,37"      /* t < c */
-#define QR_B2_64(name, text) QR_BODY(name, QR_TWO64, QR_SET8 text)
-#define QR_B1_64(name, text) QR_BODY(name, QR_ONE64, QR_SET8 text)
-#define QR_T2_64(two, one)                                                                           \
-    ".irp n," QR_ELEMS64 "\n.if ((\\n>>3)>5)|((\\n&7)>5)\ns_branch .Lqr%=e\n"                         \
-    ".elseif (\\n>>3)==(\\n&7)\ns_branch .Lqr%=" one "\\n\n.else\ns_branch .Lqr%=" two "\\n\n.endif\n.endr\n"
-#define QR_TU_64(up, one)                                                                            \
-    ".irp n," QR_ELEMS64 "\n.if ((\\n>>3)>5)|((\\n&7)>5)|((\\n>>3)>(\\n&7))\ns_branch .Lqr%=e\n"         \
-    ".elseif (\\n>>3)==(\\n&7)\ns_branch .Lqr%=" one "\\n\n.else\ns_branch .Lqr%=" up "\\n\n.endif\n.endr\n"
-#define QR_T1_64(one)                                                                                \
-    ".irp n," QR_ELEMS64 "\n.if ((\\n>>3)==(\\n&7))&((\\n>>3)<6)\ns_branch .Lqr%=" one "\\n\n.else\n"  \
-    "s_branch .Lqr%=e\n.endif\n.endr\n"
-#define QR_TABLES64_0 QR_T2_64("cv", "h") QR_T2_64("cx", "t") QR_T1_64("x")
+#define QR_B2_64(name, text) QR_BODY(name, QR_TWO64, QR_SETTC text)
+#define QR_B1_64(name, text) QR_BODY(name, QR_ONE64, QR_SETTC text)
+#define QR_TABU(up, one) QR_TABLE("(\\n>>3)>(\\n&7)", up "\\n", one "\\n")
+#define QR_TABLES64_0 QR_TAB("cv", "h") QR_TAB("cx", "t") QR_TAB1("x")
 #define QR_TABLES64_1                                                                                \
-    QR_T2_64("cv", "h") QR_T2_64("cx", "t") QR_TU_64("zz", "x") QR_T1_64("rx") QR_T1_64("ry") QR_T1_64("rz")
-#define QR_T2E_64(two)                                                                               \
-    ".irp n," QR_ELEMS64 "\n.if ((\\n>>3)>5)|((\\n&7)>5)|((\\n>>3)==(\\n&7))\ns_branch .Lqr%=e\n"        \
-    ".else\ns_branch .Lqr%=" two "\\n\n.endif\n.endr\n"
-#define QR_TABLES64_2 QR_T2E_64("cv") QR_T2E_64("cx") QR_T1_64("x") QR_T2E_64("cw")
+    QR_TAB("cv", "h") QR_TAB("cx", "t") QR_TABU("zz", "x") QR_TAB1("rx") QR_TAB1("ry") QR_TAB1("rz")
+#define QR_TABLES64_2 QR_TAB2("cv") QR_TAB2("cx") QR_TAB1("x") QR_TAB2("cw")
 // (the signs of CV and CV+ as factors +-1: A, B)
 #define QR_CVROW8S(P)                                                                                \
                 QR_SUB##P(QR_T##P(0), QR_X##P(QR_A), QR_X##P(QR_P))                                  \
@@ -465,26 +463,21 @@ constexpr uint32_t EXACT_CV_MAX = 36;
     QR_B2_64("cv", QR_CV(32, 64, QR_A32, QR_B32)) QR_B2_64("cx", QR_CNOT(32, 64))                    \
     QR_B1_64("h", QR_H(32, 64)) QR_B1_64("t", QR_TG(32, 64)) QR_B1_64("x", QR_NOT(32, 64))
 #define QR_BODIES64_1                                                                                \
-    QR_BODIES64_0 QR_BODY("zz", QR_UP64, QR_SET8 QR_ZZ(32, 64)) QR_B1_64("rx", QR_RX(32, 64))                        \
+    QR_BODIES64_0 QR_BODY("zz", QR_UP64, QR_SETTC QR_ZZ(32, 64)) QR_B1_64("rx", QR_RX(32, 64))                        \
     QR_B1_64("ry", QR_RY(32, 64)) QR_B1_64("rz", QR_RZ(32, 64))
 #define QR_TEXT64(ANG)                                                                               \
-    ".set QRB,16\n.set QRT,144\n"                                                                    \
-    "s_getpc_b64 s[40:41]\n.Lqr%=p:\ns_add_u32 s40,s40,.Lqr%=tab-.Lqr%=p\ns_addc_u32 s41,s41,0\n"    \
-    "s_mov_b32 s42,0\nv_readlane_b32 s43,%[p],s42\n"                                                 \
-    ".Lqr%=l:\n"                                                                                     \
-    "s_cmp_ge_u32 s42,%[cnt]\ns_cbranch_scc1 .Lqr%=e\n"                                              \
-    "s_add_u32 s48,s40,s43\ns_addc_u32 s49,s41,0\n" QR_ANGLE32                                       \
-    "s_add_u32 s42,s42,1\nv_readlane_b32 s43,%[p],s42\ns_setpc_b64 s[48:49]\n"                       \
+    QR_HEAD("16", "144", "6", "8") QR_PC("s_add_u32 s40,s40,.Lqr%=tab-.Lqr%=p\ns_addc_u32 s41,s41,0\n") \
+    ".macro qrnext%=\n" QR_ANGLE32 QR_ENTRY ".endm\nqrnext%=\n"                                      \
     ".Lqr%=tab:\n" QR_TABLES64_##ANG QR_BODIES64_##ANG ".Lqr%=e:\n"
 
 #define QR_CLOBBER                                                                                   \
     "scc", "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", "s48", "s49", "s50", "s51", "s52", \
-        "s53", "s54", "s55", "s58", "s59", "s60", "s61", "s62", "s63"
+        "s53", "s54", "s55", "s56", "s57", "s58", "s59", "s60", "s61", "s62", "s63"
 
 // A wave-uniform value, into a scalar register.
 __device__ __forceinline__ uint32_t scalar(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 
-// A chunk's gates: words in p (gate i in lane i, cnt of them), with ANG the
+// A chunk's cnt gates: words in p (gate i in lane (i - 1 - cnt) mod 64), with angles the
 // gates' scalars (cos, sin of theta / 2; 1 / sqrt 2 for H and T) in gc, gs.
 // restore: leaves the slots in canonical order (slot: row bit; lane slot s:
 // row bit s, register bit k: row bit LS + k).  Every lane is active.

@@ -15,7 +15,7 @@
 // circuits at n = 5, 0.51 at n = 6).
 //
 // What bounds it: the VALU instructions of the gate bodies (10 per row pair of
-// a CV).  Against the same gates on M in LDS (run_lds_path) there is no LDS
+// a CV) and the scalar instructions of their dispatch.  Against the same gates on M in LDS (run_lds_path) there is no LDS
 // traffic, no address arithmetic, no gate table and no LDS round trip per
 // gate, and the occupancy is set by about 60 VGPRs instead of 8 to 32 KB of
 // LDS per circuit.
@@ -83,7 +83,7 @@ struct RegMatrix {
             for (int p = 0; p < NQ; ++p) {
                 const uint32_t w = NQ - 1 - p;
                 map.w2s |= (uint32_t)p << (4 * w);
-                map.s2w |= w << (4 * p);
+                map.s2w |= 4u * w << (5 * p);
             }
         }
     }
@@ -139,9 +139,9 @@ struct RegMatrix {
             // entries 0, 1: row bits 2, 3 (register bits); 2, 3: row bits 0, 1 (lane
             // slots); wire w is row bit 3 - w
             const uint32_t ts = (5u - t) & 3u, cs = (5u - c) & 3u;
-            return 64u * table + 16u * ts + 4u * cs;
+            return 256u * table + 32u * ts + 4u * cs;
         } else {
-            return (table << 22) | (4u * c << 8) | (4u * t);
+            return 0x04040000u | (4u * c << 8) | (table << 5) | (4u * t);
         }
     }
 
@@ -170,12 +170,12 @@ struct RegMatrix {
             if (__ballot(in && !desc_valid<ANG>(dv, NQ))) return false;
             const int kind = (int)(dv & 15u);
             const bool live = in && kind != KIND_I;
-            // the gates in order into lanes 0, 1, ... (the others behind them)
+            // the gates in order into the lanes up to 62, the others behind them
             const uint64_t todo = __ballot(live);
             const uint32_t cnt = (uint32_t)__popcll(todo);
             const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(todo >> 32),
                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)todo, 0u));
-            const int to = 4 * (int)(live ? rank : cnt + (uint32_t)lane - rank);
+            const int to = 4 * (int)(((live ? rank - cnt : (uint32_t)lane - rank) - 1u) & 63u);
             bool exact = false;
             if constexpr (NCV) {
                 cvs += (uint32_t)__popcll(__ballot(live && kind >= KIND_CV));
@@ -210,7 +210,7 @@ struct RegMatrix {
     // Row-major store of M (the slots in any order).
     template <typename C2>
     __device__ __forceinline__ void store(C2* U, bool ok) const {
-        auto bit = [&](int slot) -> uint32_t { return NQ - 1 - ((map.s2w >> (4 * slot)) & 15u); };
+        auto bit = [&](int slot) -> uint32_t { return NQ - 1 - ((map.s2w >> (5 * slot + 2)) & 7u); };
         uint32_t row = q;                       // the lane slots' part
         if constexpr (!G::STATIC) {
             row = 0u;
