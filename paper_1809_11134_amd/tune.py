@@ -39,9 +39,10 @@ from . import inputs, qe
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
-# (lds, waves, cpb) per width: the register kernel, then the LDS schedules
-CANDIDATES = {4: [(0, 1, 4), (0, 1, 1), (1, 1, 4), (1, 1, 1)],
-              5: [(0, 1, 4), (0, 1, 1), (1, 1, 4), (1, 1, 1), (1, 2, 1)],
+# (lds, waves, cpb) per width: the register kernel, then the LDS schedules.  Ties go
+# to the first: one circuit per workgroup leaves no wavefront waiting for others.
+CANDIDATES = {4: [(0, 1, 1), (0, 1, 4), (1, 1, 4), (1, 1, 1)],
+              5: [(0, 1, 1), (0, 1, 4), (1, 1, 4), (1, 1, 1), (1, 2, 1)],
               6: [(0, 4, 1), (1, 4, 1)]}
 LENGTHS = {0: 20, 1: 48}
 TIE = 0.02
@@ -62,11 +63,11 @@ def _median_us(fn, reps):
     return t[len(t) // 2]
 
 
-def _qeqea_fused_us(n, L, P, library, reps, rng, dev):
+def _qeqea_fused_us(n, L, P, library, reps, rng, dev, I=1):
     tg = torch.from_numpy(inputs.random_target_gates(rng, n, 12, permutation=True).astype(np.int16)[None]).to(dev)
-    ctx = qe.Context(n, library, qe.ALG_QEQEA, L, P, 1, prob_mutation=0.1, mutation_range=math.pi / 4,
+    ctx = qe.Context(n, library, qe.ALG_QEQEA, L, P, I, prob_mutation=0.1, mutation_range=math.pi / 4,
                      seed=inputs.SEED_BASE)
-    ctx.set_targets(qe.build_unitary(tg, n, tg.shape[1], precision=1))
+    ctx.set_targets(qe.build_unitary(tg, n, tg.shape[1], precision=1).repeat(I, 1, 1))
     out = ctx.sample_eval(0)
     if library == qe.LIB_ISING:
         s, gq, a, f = out
@@ -96,6 +97,8 @@ def time_schedule(n, L, cls, sched, reps, rng, dev, log):
         ga.close()
     elif cls == qe.SCHED_SAMPLED:
         parts["fused"] = _qeqea_fused_us(n, L, P, qe.LIB_NCV, reps, rng, dev)
+        # (many populations: where a schedule's occupancy shows)
+        parts["many"] = _qeqea_fused_us(n, L, 64, qe.LIB_NCV, reps, rng, dev, I=512)
     else:
         B = {4: 4096, 5: 8192, 6: 2048}[n]
         g, a = inputs.random_ising_circuits(rng, B, n, L, discrete_frac=0.0)
@@ -104,6 +107,7 @@ def time_schedule(n, L, cls, sched, reps, rng, dev, log):
         T = qe.build_unitary(gd[:1], n, L, precision=0, angles=ad[:1])[0]
         parts["eval"] = _median_us(lambda: qe.eval_fitness(gd, T, n=n, L=L, angles=ad), reps)
         parts["fused"] = _qeqea_fused_us(n, L, P, qe.LIB_ISING, reps, rng, dev)
+        parts["many"] = _qeqea_fused_us(n, L, 64, qe.LIB_ISING, reps, rng, dev, I=512)
     log(f"n={n} L={L} {CLASSES[cls]} schedule lds={sched[0]} waves={sched[1]} cpb={sched[2]}: " +
         ", ".join(f"{k} {v:.1f} us" for k, v in parts.items()))
     return sum(parts.values())
