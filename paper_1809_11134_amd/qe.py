@@ -125,13 +125,15 @@ def _call(name, *args):
 
 
 def _stream(stream):
+    """Handle of the stream, or of the current device's current one (0.4 us; building
+    torch's stream object takes 2.9 us, a quarter of a small call)."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _dev(t, dtype):
