@@ -239,6 +239,8 @@ constexpr int MIX_SORT = 1024, MIX_PER = 16, MIX_REP = 4;
 __global__ __launch_bounds__(MIX_SORT) void mix_bucket_kernel(BatchArgs a, int32_t* order, int32_t* meta) {
     constexpr int K = MIX_BUCKETS * MIX_LCLASSES * MIX_REP;
     __shared__ int cnt[K], cursor[K];
+    __shared__ uint16_t sorted[MIX_PER * MIX_SORT];
+    static_assert(MIX_PER * MIX_SORT <= 1 << 16, "a tile's circuits in 16 bits");
     const int tid = threadIdx.x;
     for (int k = tid; k < K; k += MIX_SORT) cnt[k] = 0;
     int key[MIX_PER], rank[MIX_PER];
@@ -299,12 +301,19 @@ __global__ __launch_bounds__(MIX_SORT) void mix_bucket_kernel(BatchArgs a, int32
         meta[8 + MIX_BUCKETS] = item;
     }
     __syncthreads();
-    for (int b0 = 0; b0 < a.B; b0 += MIX_PER * MIX_SORT) {
-        if (!one_tile) read_tile(b0);
+    if (one_tile) {
 #pragma unroll
         for (int c = 0; c < MIX_PER; ++c)
-            if (key[c] >= 0)
-                order[one_tile ? cursor[key[c]] + rank[c] : atomicAdd(&cursor[key[c]], 1)] = b0 + c * MIX_SORT + tid;
+            if (key[c] >= 0) sorted[cursor[key[c]] + rank[c]] = (uint16_t)(c * MIX_SORT + tid);
+        __syncthreads();
+        for (int p = tid; p < a.B; p += MIX_SORT) order[p] = sorted[p];
+        return;
+    }
+    for (int b0 = 0; b0 < a.B; b0 += MIX_PER * MIX_SORT) {
+        read_tile(b0);
+#pragma unroll
+        for (int c = 0; c < MIX_PER; ++c)
+            if (key[c] >= 0) order[atomicAdd(&cursor[key[c]], 1)] = b0 + c * MIX_SORT + tid;
     }
 }
 
