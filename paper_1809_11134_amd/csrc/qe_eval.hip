@@ -202,10 +202,12 @@ __global__ __launch_bounds__(64 * W) void lds32_kernel(BatchArgs a, float* __res
 // ----------------------------------------------- mixed widths, one launch
 // Circuits of a mixed-width batch are ordered by cost, widest first and,
 // within a width, longest first (classes of 8 gates), by a one-workgroup
-// counting sort; one launch then gives every workgroup (4 wavefronts) one
-// work item: a circuit of width 6 (4 waves) or four of the other widths (one
-// wave each; register-resident for 4 and 5, one entry per lane below), so an
-// item's circuits have similar lengths.  Workgroups are
+// counting sort; one launch then gives every workgroup one work item.  In large
+// batches that is one circuit for one wavefront (register-resident for widths 4 to
+// 6, one entry per lane below; four circuits per workgroup held a finished one's
+// registers until the others ended: 16384 circuits 90.0 -> 86.5 us, 256 GA
+// populations of 64 73.9 -> 71.4); in small ones a circuit of width 6 for four
+// wavefronts or four of the other widths, of similar lengths.  Workgroups are
 // dispatched in index order, so the heaviest items start first
 // (longest-processing-time order).
 constexpr int MIX_BUCKETS = 7;          // widths 6..1, then malformed widths
@@ -223,10 +225,9 @@ __device__ __forceinline__ int mix_key(const BatchArgs& a, int b) {
     const int lc = len >= 120 ? 0 : (len < 8 ? MIX_LCLASSES - 1 : MIX_LCLASSES - 1 - (int)(len >> 3));
     return mix_bucket(a.nq[b]) * MIX_LCLASSES + lc;
 }
-// circuits per work item: four, or (width 6 with 16 columns per wavefront) one
-// of four wavefronts
+// circuits per work item
 __host__ __device__ __forceinline__ bool mix_columns(int B) { return B >= MIX_COLUMNS_MIN; }
-__device__ __forceinline__ int mix_per_item(int k, bool columns) { return k == 0 && !columns ? 1 : 4; }
+__device__ __forceinline__ int mix_per_item(int k, bool columns) { return k == 0 || columns ? 1 : 4; }
 
 // meta: [0..7) first order position, [8..15) first item (8 entries, the last
 // the total), [16..23) count per bucket.
@@ -349,7 +350,7 @@ __device__ __forceinline__ void mix_wave_item(const BatchArgs& a, int b, float* 
 
 // COLUMNS: circuits of width 6 with one column per lane (large batches).  (They
 // and the other widths in two launches, so that the small widths keep the
-// occupancy of 52 VGPRs: no gain at 16384 circuits, 92 us either way, and 55
+// occupancy of 52 VGPRs: no gain at 16384 circuits, and 55
 // against 37 us at 4096, where each launch ends in a nearly empty round.)
 template <bool COLUMNS>
 __global__ __launch_bounds__(256) void mix_kernel(BatchArgs a, const int32_t* __restrict__ order,
@@ -365,7 +366,7 @@ __global__ __launch_bounds__(256) void mix_kernel(BatchArgs a, const int32_t* __
     const int wave = (int)(threadIdx.x >> 6);
     const int per = mix_per_item(k, COLUMNS);
     const int local = (item - meta[8 + k]) * per;
-    const int sub = per == 1 ? 0 : wave;
+    const int sub = per == 1 ? 0 : wave;       // (COLUMNS: one wavefront)
     int b = local + sub < meta[16 + k] ? order[meta[k] + local + sub] : -1;
     if (b >= a.B) b = -1;        // an order written for another batch never indexes past this one
     b = __builtin_amdgcn_readfirstlane(b);
@@ -533,7 +534,7 @@ hipError_t launch_mix_eval(const BatchArgs& a, const int32_t* work, float* f, fl
     // (the workgroups past the items leave: how many there are of each width is
     // known on the device only)
     const int32_t* order = work + MIX_WORK_META;
-    if (mix_columns(a.B)) mix_kernel<true><<<a.B / 4 + MIX_BUCKETS, 256, 0, s>>>(a, order, work, f, g, delta);
+    if (mix_columns(a.B)) mix_kernel<true><<<a.B, 64, 0, s>>>(a, order, work, f, g, delta);
     else mix_kernel<false><<<a.B, 256, 0, s>>>(a, order, work, f, g, delta);
     return hipGetLastError();
 }
