@@ -18,8 +18,8 @@ synchronisations and HIP events) give the median.
 
 Prints one JSON line (the metric is circuit-fitness evaluations per second)
 with a roofline entry for the dominant kernel (the fused sampling + fitness
-kernel, against the LDS bandwidth measured by a probe kernel in the same
-run) and one for the update kernel (against HBM), each timed launch by launch
+kernel: the bytes that the per-gate method moves with the product in LDS, against
+the LDS bandwidth measured by a probe kernel in the same run) and one for the update kernel (against HBM), each timed launch by launch
 with HIP events on the launch stream, and the CPU oracle's rate on a bounded
 sample of the same workload on one host core and on all of them.  The
 "secondary" object adds the other workloads of the study: the n=6 precision
@@ -315,8 +315,8 @@ def secondary_qeqea_ising(dev, gens=100, reps=50):
     ctx.close()
     return {"workload": w["name"], "generations": gens,
             "evals_per_s": gens * I * P / (ms * 1e-3), "ms_per_generation": ms / gens,
-            "kernel": "population_kernel<4,1,true,true> (sampling + Ising decode + Eq. 11 fitness "
-                      "+ segment max, LDS-staged)",
+            "kernel": "population_kernel<4,0,true,true> (sampling + Ising decode + Eq. 11 fitness "
+                      "+ segment max, register-resident)",
             "kernel_us": kern_ms * 1e3, "algorithmic_lds_bytes_per_launch": lds,
             "lds_gbps": achieved, "lds_frac": achieved / LDS_PEAK_GBPS,
             "alu_tflops": flops / (kern_ms / 1e3) / 1e12,
@@ -569,11 +569,12 @@ def update_algorithmic_bytes(ctx, gen, dev):
 
 
 def sampled_schedule(n, L):
-    """(wavefronts per circuit, circuits per workgroup) of the fused QEQEA
-    kernel for width n and length L (the sampled library class)."""
+    """(wavefronts per circuit of the LDS-staged layout, 0 the register-resident one;
+    circuits per workgroup) of the fused QEQEA kernel for width n and length L (the
+    sampled library class)."""
     from paper_1809_11134_amd import qe
-    _, waves, cpb = qe.get_schedule_lib(n, 1 if L >= 32 else 0, qe.SCHED_SAMPLED)
-    return waves, (cpb if waves == 1 else 1)
+    lds, waves, cpb = qe.get_schedule_lib(n, 1 if L >= 32 else 0, qe.SCHED_SAMPLED)
+    return (waves if lds else 0), (cpb if waves == 1 else 1)
 
 
 def secondary_qeqea_n4(dev, K, W):
@@ -718,8 +719,8 @@ def main():
     qe.load()
     src = source_hash()
 
-    # the per-gate kernels read and write every element they touch once, so
-    # their LDS ceiling is the probe's copy rate (equal reads and writes)
+    # the per-gate method reads and writes every element it touches once, so
+    # its LDS ceiling is the probe's copy rate (equal reads and writes)
     lds_probe = measure_lds_peak(dev)
     LDS_PEAK_GBPS = lds_probe["copy_b128"]
     log(f"LDS probe: {lds_probe} GB/s -> peak {LDS_PEAK_GBPS:.0f} GB/s for equal reads and writes "
@@ -751,8 +752,11 @@ def main():
                 "traffic": traffic_from_profiles("qeqea_fused_n5", src),
                 "kernel": f"population_kernel<5,{waves},true,false,{cpb}> (circuit construction from the "
                           f"slot words + Eq. 11 fitness + elitism of the slots a circuit alone used + "
-                          f"segment max of the shared ones + mutation decisions, LDS-staged, {waves} "
-                          f"wavefront(s) per circuit, {cpb} circuit(s) per workgroup)",
+                          f"segment max of the shared ones, " +
+                          (f"LDS-staged, {waves} wavefront(s)" if waves else
+                           "register-resident: the LDS bytes are those the per-gate method moves with "
+                           "the product in LDS; one wavefront") +
+                          f" per circuit, {cpb} circuit(s) per workgroup)",
                 "kernel_us": round(fused_us, 3), "algorithmic_lds_bytes_per_launch": lds_bytes,
                 "peak_source": "LDS probe kernel in this run, copy mode (each 16-byte word read and "
                                "written once, the mix of the per-gate updates)",
