@@ -44,9 +44,9 @@ Sched schedule_for(int n, int L, int lib_class = SCHED_DISCRETE);
 // Fewest circuits of width 6 for which the register-resident kernels hold one
 // column per lane (one wavefront per circuit) instead of 16 columns per
 // wavefront (four per circuit): with fewer, the longer chain of one wavefront
-// is not hidden.  48 gates: 512 circuits 23.0 us either way, 768 24.3 against
-// 27.4, 8192 93 against 153; Ising 768 44.2 against 40.6, 1024 45.5 against
-// 48.9, 8192 205 against 259.
+// is not hidden.  48 gates: 512 circuits 23.5 us against 21.7, 640 23.2 against
+// 25.3, 8192 94 against 145; Ising 768 44.6 against 39.5, 1024 45.4 against
+// 48.2, 8192 206 against 260.
 constexpr uint32_t reg6_columns_min(bool angled) { return angled ? 1024u : 640u; }
 // MFMA paths: the fewest non-identity gates a group needs to be fused into a
 // block (smaller groups go gate by gate in FP32), per width and length class

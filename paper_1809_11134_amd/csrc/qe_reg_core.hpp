@@ -14,11 +14,14 @@
 // registers) and stays there (0.29 exchanges per two-wire gate of random
 // circuits at n = 5, 0.51 at n = 6).
 //
-// What bounds it: the VALU instructions of the gate bodies (10 per row pair of
-// a CV) and the scalar instructions of their dispatch.  Against the same gates on M in LDS (run_lds_path) there is no LDS
-// traffic, no address arithmetic, no gate table and no LDS round trip per
-// gate, and the occupancy is set by about 60 VGPRs instead of 8 to 32 KB of
-// LDS per circuit.
+// What bounds it: the VALU instructions of the gate bodies (8 or 10 per row pair of
+// a CV) and the scalar instructions of their dispatch.  Against the same gates on
+// M in LDS (run_lds_path) there is no LDS traffic, no address arithmetic, no gate
+// table and no LDS round trip per gate, and the occupancy is set by about 70 VGPRs
+// instead of 8 to 32 KB of LDS per circuit.  Measured: 8192 circuits of 48 gates
+// (n = 6) 175 -> 84 us; the fused kernel of 65536 circuits of 40 gates (n = 5) 225 ->
+// 170 us, its VALU busy 98 % of the time; FP64, 2048 circuits of 40 gates (n = 5),
+// against the generic body 76 -> 19 us.
 //
 // The arithmetic of each element (one rounding per operation, the same
 // operations in the same gate order) and the order of the reduction are those
