@@ -272,10 +272,7 @@ struct qe_ctx {
     bool targets_set = false;
     // ctx-owned device buffers
     std::vector<void*> owned;
-    uint16_t* gates = nullptr;    // [I*P*L]
-    // GA: the circuits of the last generation run are still genomes[last_parity]
-    // (-1: they have been kept in `gates`, or none was run)
-    int last_parity = -1;
+    uint16_t* gates = nullptr;    // [I*P*L] (GA: see LoopArgs::ga_last)
     uint32_t* angles = nullptr;   // [I*P*L] (Ising library)
     float* f = nullptr;           // [I*P]
     uint64_t* d_gen = nullptr;
@@ -388,16 +385,6 @@ BatchArgs mixed_batch(const qe_ctx* c, const uint16_t* gates, const uint64_t* ge
     return b;
 }
 
-// GA: before genomes[parity] is overwritten from outside the generation loop,
-// the last generation's circuits (qe_elite_recheck without gates) move from
-// there to c->gates.
-qe_status keep_last_gates(qe_ctx* c, int parity, hipStream_t s) {
-    if (c->last_parity < 0 || c->last_parity != parity) return QE_OK;
-    QE_HIP(launch_ga_copy(c->la, (uint64_t)parity, c->gates, s));
-    c->last_parity = -1;
-    return QE_OK;
-}
-
 void note_words(qe_ctx* c, uint64_t gen) {
     if (c->la.dup) c->words_gen[gen & 1] = (int64_t)gen;
 }
@@ -426,7 +413,7 @@ qe_status enqueue_generation(qe_ctx* c, const LoopArgs& a, uint64_t gen, float* 
             QE_HIP(launch_mix_eval(mixed_batch(c, nullptr, a.gen_ptr, gen), c->mix_order, f, nullptr, nullptr, s));
         else
             QE_HIP(launch_ga_eval(a, gen, f, s));
-        QE_HIP(launch_ga_update(a, gen, f, s));
+        QE_HIP(launch_ga_update(a, gen, f, nullptr, s));
     }
     return QE_OK;
 }
@@ -752,6 +739,7 @@ qe_status create_impl(const qe_problem* p_in, const int32_t* inst_n, const int32
     } else {
         ALLOC(a.genomes[0], (size_t)genes);
         ALLOC(a.genomes[1], (size_t)genes);
+        ALLOC(a.ga_last, 2);
     }
     float* t32 = nullptr;
     double* t64 = nullptr;
@@ -850,6 +838,8 @@ qe_status create_impl(const qe_problem* p_in, const int32_t* inst_n, const int32
         if (e == hipSuccess) e = launch_qeqea_init(a, nullptr);
     } else if (e == hipSuccess) {
         e = launch_ga_init(a, nullptr);
+        if (e == hipSuccess) e = launch_fill_i32(reinterpret_cast<int32_t*>(a.ga_last), 1, (int32_t)GA_LAST_KEPT, nullptr);
+        if (e == hipSuccess) e = launch_fill_i32(reinterpret_cast<int32_t*>(a.ga_last) + 1, 1, 0, nullptr);
     }
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking);
@@ -976,8 +966,7 @@ qe_status qe_update(qe_ctx* c, uint64_t gen, const uint32_t* slots, const uint16
                                    words));
         if (words) note_words(c, gen + 1);
     } else {
-        QE_TRY(keep_last_gates(c, (int)((gen + 1) & 1), s));
-        QE_HIP(launch_ga_update(c->la, gen, f, s));
+        QE_HIP(launch_ga_update(c->la, gen, f, c->gates, s));
     }
     return QE_OK;
 }
@@ -988,7 +977,6 @@ qe_status qe_generation(qe_ctx* c, uint64_t gen, float* f, void* stream) {
     QE_TRY(prepare_decisions(c, gen, 1, (hipStream_t)stream));
     if (c->prob.algorithm == QE_ALG_QEQEA) QE_TRY(ensure_words(c, gen, (hipStream_t)stream));
     QE_TRY(enqueue_generation(c, c->la, gen, f ? f : c->f, (hipStream_t)stream));
-    if (c->prob.algorithm == QE_ALG_GA) c->last_parity = (int)(gen & 1);
     note_words(c, gen + 1);
     return QE_OK;
 }
@@ -1059,7 +1047,6 @@ qe_status qe_run_graph(qe_ctx* c, uint64_t first_gen, int32_t n_gen, float* f_hi
     if (c->prob.algorithm == QE_ALG_QEQEA) QE_TRY(ensure_words(c, first_gen, s));
     QE_HIP(launch_gen_set(c->d_gen, first_gen, s));
     QE_HIP(hipGraphLaunch(ex, s));
-    if (c->prob.algorithm == QE_ALG_GA) c->last_parity = (int)((first_gen + (uint64_t)n_gen - 1) & 1);
     note_words(c, first_gen + (uint64_t)n_gen - 1);
     note_words(c, first_gen + (uint64_t)n_gen);
     return QE_OK;
@@ -1069,8 +1056,9 @@ qe_status qe_elite_recheck(qe_ctx* c, const uint16_t* gates, const uint32_t* ang
                            int32_t k, int32_t* idx, double* f64, void* stream) {
     QE_TRY(check_ctx(c, true));
     if (!f || !idx || !f64) return fail(QE_ERR_INVALID, "NULL buffer");
+    const bool last = !gates && c->prob.algorithm == QE_ALG_GA;
     if (!gates) {
-        gates = c->last_parity >= 0 ? c->la.genomes[c->last_parity] : c->gates;
+        gates = c->gates;
         angles = c->angles;
     } else if (is_ising(c) && !angles) {
         return fail(QE_ERR_INVALID, "the Ising library needs angles_dev");
@@ -1080,7 +1068,7 @@ qe_status qe_elite_recheck(qe_ctx* c, const uint16_t* gates, const uint32_t* ang
     if (c->prob.size_of_population > 4096) return fail(QE_ERR_UNSUPPORTED, "elite selection needs P <= 4096");
     hipStream_t s = (hipStream_t)stream;
     QE_HIP(launch_elite_select(c->la, f, k, idx, c->elite_cand, s));
-    QE_HIP(launch_elite_eval(c->la, gates, angles, k, idx, f64, s));
+    QE_HIP(launch_elite_eval(c->la, gates, angles, k, idx, f64, last, s));
     return QE_OK;
 }
 
@@ -1232,7 +1220,10 @@ qe_status qe_restore(qe_ctx* c, const void* buf, size_t size) {
     for (auto& s : secs) payload += s.bytes;
     if (h.payload != payload || size < sizeof(h) + payload) return fail(QE_ERR_INVALID, "checkpoint size mismatch");
     QE_HIP(hipDeviceSynchronize());
-    if (c->last_parity >= 0) QE_TRY(keep_last_gates(c, c->last_parity, nullptr));
+    if (c->prob.algorithm == QE_ALG_GA) {
+        QE_HIP(launch_ga_keep(c->la, c->gates, nullptr));
+        QE_HIP(hipDeviceSynchronize());
+    }
     const char* p = static_cast<const char*>(buf) + sizeof(h);
     for (auto& s : secs) {
         QE_HIP(hipMemcpy(s.ptr, p, s.bytes, hipMemcpyHostToDevice));

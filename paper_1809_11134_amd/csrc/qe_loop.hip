@@ -301,6 +301,14 @@ __global__ void qeqea_sample_kernel(LoopArgs a, uint64_t gen64, uint32_t* __rest
     }
 }
 
+// Moves the last generation's circuits to the context's own buffer, unless they are
+// there.  (qe_restore; qe_update does it in its update kernel.)
+__global__ void ga_keep_kernel(LoopArgs a, uint16_t* __restrict__ kept) {
+    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t at = a.ga_last[0];
+    if (idx < (size_t)a.genes && at < GA_LAST_KEPT) kept[idx] = a.genomes[at][idx];
+}
+
 __global__ void ga_copy_kernel(LoopArgs a, uint64_t gen64, uint16_t* __restrict__ gates) {
     const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= (size_t)a.genes) return;
@@ -1142,6 +1150,11 @@ __global__ void state_gather_kernel(LoopArgs a, int which, void* __restrict__ ds
 // gene replaces its parent's, so every child gene is written once and no
 // workgroup waits for another.  A population of 4096 x 20 genes on one
 // workgroup with a serial prefix took 253 us.
+// RUN: the update of a whole generation, whose circuits stay in genomes[gen & 1],
+// as the context's word says from here on.  Otherwise (qe_update) the genes
+// written over move to `kept` if the word names them, each by the thread that
+// writes its place (a generation doing that took 0.9 us more of 19 at P = 4096,
+// L = 20); the last workgroup to have read the word changes it.
 constexpr int GA_MAX_P = 4096;
 constexpr int GA_BLOCK = 256;
 
@@ -1149,15 +1162,28 @@ constexpr int GA_BLOCK = 256;
 // parents and the cuts
 static inline size_t ga_lds_bytes(int P, int pairs) { return (size_t)((P + 2) & ~1) * 8 + (size_t)pairs * 16; }
 
+template <bool RUN>
 __global__ __launch_bounds__(GA_BLOCK) void ga_update_kernel(LoopArgs a, uint64_t gen64,
-                                                             const float* __restrict__ f, uint32_t parts) {
+                                                             const float* __restrict__ f, uint32_t parts,
+                                                             uint16_t* __restrict__ kept) {
     extern __shared__ __align__(16) unsigned long long pre[];
     __shared__ unsigned long long wsum[GA_BLOCK / 64];
     __shared__ float bestv[GA_BLOCK / 64];
     __shared__ int besti[GA_BLOCK / 64];
+    __shared__ bool keep;
     const uint32_t gen = gen_of(a, gen64);
     const uint32_t i = blockIdx.x / parts, part = blockIdx.x % parts;
     const int P = a.P, tid = threadIdx.x, wave = tid >> 6;
+    if (RUN) {
+        if (blockIdx.x == 0 && tid == 0) a.ga_last[0] = gen & 1u;
+    } else if (tid == 0) {
+        keep = __hip_atomic_load(a.ga_last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == ((gen + 1u) & 1u);
+        __threadfence();
+        if (atomicAdd(a.ga_last + 1, 1u) == gridDim.x - 1u) {
+            a.ga_last[1] = 0u;
+            if (keep) a.ga_last[0] = GA_LAST_KEPT;
+        }
+    }
     // population i's width, genome length and genomes (mixed populations
     // carry their own)
     const int n = a.inst_n ? a.inst_n[i] : a.n, L = a.inst_L ? a.inst_L[i] : a.L;
@@ -1260,6 +1286,7 @@ __global__ __launch_bounds__(GA_BLOCK) void ga_update_kernel(LoopArgs a, uint64_
         const u32x4 m = draw(a.seed, TAG_GA_MUT, gen, i, (uint32_t)e);
         uint16_t g = cur[(size_t)(k == 0 ? bi : parent) * L + pos];
         if (k != 0 && (uint64_t)m.x < a.thr_pg) g = lib_desc(a.lib, n, (int)scale_u32(m.y, nl));
+        if (!RUN && keep) kept[base + e] = nxt[e];
         nxt[e] = g;
     };
     for (int e = tid; e < np * L; e += GA_BLOCK) {
@@ -1384,10 +1411,19 @@ __global__ __launch_bounds__(1024) void elite_select_kernel(LoopArgs a, const fl
     }
 }
 
+// The circuits to re-check: those given, or (last; GA) the last generation's,
+// which are still a population unless they were moved to `gates`.
+__device__ __forceinline__ const uint16_t* last_circuits(const LoopArgs& a, const uint16_t* gates, bool last) {
+    if (!last) return gates;
+    const uint32_t at = a.ga_last[0];
+    return at < GA_LAST_KEPT ? a.genomes[at] : gates;
+}
+
 // Mixed populations (discrete libraries): widths differ from circuit to circuit.
 __global__ __launch_bounds__(256) void elite_eval_kernel(LoopArgs a, const uint16_t* __restrict__ gates,
                                                          int k, const int32_t* __restrict__ idx,
-                                                         double* __restrict__ f64) {
+                                                         double* __restrict__ f64, bool last) {
+    gates = last_circuits(a, gates, last);
     const int i = blockIdx.x / k, e = blockIdx.x % k;
     const int c = idx[(size_t)i * k + e];
     uint32_t err = (c < 0 || c >= a.P) ? (uint32_t)QE_DEVERR_RANGE : 0u;
@@ -1405,7 +1441,8 @@ template <int NQ, bool ANG>
 __global__ __launch_bounds__(256) void elite64_kernel(LoopArgs a, const uint16_t* __restrict__ gates,
                                                       const uint32_t* __restrict__ angles, int k,
                                                       const int32_t* __restrict__ idx,
-                                                      double* __restrict__ f64) {
+                                                      double* __restrict__ f64, bool last) {
+    gates = last_circuits(a, gates, last);
     constexpr bool WHOLE = NQ == 6;
     __shared__ double red[4][3];
     const int wave = WHOLE ? (int)(threadIdx.x >> 6) : 0, lane = (int)lane_id();
@@ -1518,6 +1555,11 @@ hipError_t launch_qeqea_sample(const LoopArgs& a, uint64_t gen, uint32_t* slots,
                                uint32_t* angles, hipStream_t s) {
     qeqea_sample_kernel<<<blocks((size_t)a.I * a.P * a.L, 256), 256, 0, s>>>(a, gen, slots, gates, angles);
     return hipGetLastError();
+}
+
+hipError_t launch_ga_keep(const LoopArgs& a, uint16_t* kept, hipStream_t s) {
+    ga_keep_kernel<<<blocks((size_t)a.genes, 256), 256, 0, s>>>(a, kept);
+    return launch_fill_i32(reinterpret_cast<int32_t*>(a.ga_last), 1, (int32_t)GA_LAST_KEPT, s);
 }
 
 hipError_t launch_ga_copy(const LoopArgs& a, uint64_t gen, uint16_t* gates, hipStream_t s) {
@@ -1666,7 +1708,7 @@ hipError_t launch_state_gather(const LoopArgs& a, int which, void* dst, hipStrea
     return hipGetLastError();
 }
 
-hipError_t launch_ga_update(const LoopArgs& a, uint64_t gen, const float* f, hipStream_t s) {
+hipError_t launch_ga_update(const LoopArgs& a, uint64_t gen, const float* f, uint16_t* kept, hipStream_t s) {
     // one round of gene pairs per thread, as long as the populations together
     // make no more than two workgroups per compute unit: every workgroup
     // repeats its population's prefix and draws (256 populations of 64: 10.8 us
@@ -1678,7 +1720,10 @@ hipError_t launch_ga_update(const LoopArgs& a, uint64_t gen, const float* f, hip
     const uint64_t least = std::max<uint64_t>(1, ((uint64_t)half + 1023) / 1024);
     const uint32_t parts = (uint32_t)std::max<uint64_t>(least, std::min({rounds, most, (uint64_t)half}));
     const int share = (half + (int)parts - 1) / (int)parts;
-    ga_update_kernel<<<(unsigned)a.I * parts, GA_BLOCK, ga_lds_bytes(a.P, share), s>>>(a, gen, f, parts);
+    if (kept)
+        ga_update_kernel<false><<<(unsigned)a.I * parts, GA_BLOCK, ga_lds_bytes(a.P, share), s>>>(a, gen, f, parts, kept);
+    else
+        ga_update_kernel<true><<<(unsigned)a.I * parts, GA_BLOCK, ga_lds_bytes(a.P, share), s>>>(a, gen, f, parts, kept);
     return hipGetLastError();
 }
 
@@ -1705,17 +1750,17 @@ hipError_t launch_elite_select(const LoopArgs& a, const float* f, int k, int32_t
 }
 
 hipError_t launch_elite_eval(const LoopArgs& a, const uint16_t* gates, const uint32_t* angles, int k,
-                             const int32_t* idx, double* f64, hipStream_t s) {
+                             const int32_t* idx, double* f64, bool last, hipStream_t s) {
     const unsigned nc = (unsigned)a.I * (unsigned)k;
     if (a.inst_n) {
-        elite_eval_kernel<<<nc, 256, generic_lds_bytes(a.n, sizeof(double)), s>>>(a, gates, k, idx, f64);
+        elite_eval_kernel<<<nc, 256, generic_lds_bytes(a.n, sizeof(double)), s>>>(a, gates, k, idx, f64, last);
         return hipGetLastError();
     }
     auto go = [&](auto nq) {
         constexpr int NQ = decltype(nq)::value;
         const unsigned wgs = NQ == 6 ? nc : (nc + 3) / 4;
-        if (angles) elite64_kernel<NQ, true><<<wgs, 256, 0, s>>>(a, gates, angles, k, idx, f64);
-        else elite64_kernel<NQ, false><<<wgs, 256, 0, s>>>(a, gates, nullptr, k, idx, f64);
+        if (angles) elite64_kernel<NQ, true><<<wgs, 256, 0, s>>>(a, gates, angles, k, idx, f64, last);
+        else elite64_kernel<NQ, false><<<wgs, 256, 0, s>>>(a, gates, nullptr, k, idx, f64, last);
     };
     switch (a.n) {
         case 1: go(std::integral_constant<int, 1>{}); break;
