@@ -61,16 +61,14 @@ __global__ __launch_bounds__(64 * WPB) void wave_kernel(BatchArgs a, Real* __res
 // One circuit on its W wavefronts (W = 4 at n = 6, else 1; `wave` the circuit's
 // wavefront): the fitness of circuit b (n = 6: every wavefront of the workgroup
 // calls it, red is LDS).
-// strict: a NaN residual gives NaN (QE_PATH_FP32_REG and FP64); without it the
-// radicand is clamped as in the LDS-staged kernels.
 __device__ __forceinline__ int64_t uniform64(int64_t v) {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 template <typename Real, int NQ, bool ANG, int COLS = reg_columns<NQ>()>
-__device__ __forceinline__ void reg_item(const BatchArgs& a, int b, Item it, int wave, bool strict,
-                                         Real (*red)[3], Real* __restrict__ f, Real* __restrict__ g,
+__device__ __forceinline__ void reg_item(const BatchArgs& a, int b, Item it, int wave, Real (*red)[3],
+                                         Real* __restrict__ f, Real* __restrict__ g,
                                          Real* __restrict__ delta) {
     const int lane = (int)lane_id();
     if (it.err == 0 && it.n != NQ) it.err = QE_DEVERR_WIDTH;
@@ -89,7 +87,6 @@ __device__ __forceinline__ void reg_item(const BatchArgs& a, int b, Item it, int
             it.err = QE_DEVERR_DESC;
         } else {
             fv = M.fitness(a.mode, &gv, &dv, wave, red);
-            if (strict && !(dv == dv)) fv = dv;
             if (!(fv == fv)) it.err = QE_DEVERR_NUMERIC;
         }
     }
@@ -105,7 +102,7 @@ __device__ __forceinline__ void reg_item(const BatchArgs& a, int b, Item it, int
 // wavefront) one per workgroup.
 template <typename Real, int NQ, bool FILTER, bool ANG, int COLS = reg_columns<NQ>()>
 __global__ __launch_bounds__(256) void reg_kernel(BatchArgs a, Real* __restrict__ f, Real* __restrict__ g,
-                                                  Real* __restrict__ delta, bool strict) {
+                                                  Real* __restrict__ delta) {
     __shared__ Real red[4][3];
     const int wave = (int)(threadIdx.x >> 6);
     constexpr bool WHOLE = RegGeom<NQ, COLS>::W == 4;
@@ -113,7 +110,7 @@ __global__ __launch_bounds__(256) void reg_kernel(BatchArgs a, Real* __restrict_
     if (b >= a.B) return;
     const Item it = resolve(a, b);
     if (FILTER && it.n != NQ) return;
-    reg_item<Real, NQ, ANG, COLS>(a, b, it, WHOLE ? wave : 0, strict, red, f, g, delta);
+    reg_item<Real, NQ, ANG, COLS>(a, b, it, WHOLE ? wave : 0, red, f, g, delta);
 }
 
 // Unitaries of a uniform-width batch: the product started from the identity.
@@ -373,11 +370,11 @@ __global__ __launch_bounds__(256) void mix_kernel(BatchArgs a, const int32_t* __
     if (b < 0) return;           // (four wavefronts per circuit: the whole workgroup)
     switch (k) {
         case 0:
-            if constexpr (COLUMNS) reg_item<float, 6, false, 64>(a, b, resolve(a, b), 0, false, red, f, g, delta);
-            else reg_item<float, 6, false>(a, b, resolve(a, b), wave, false, red, f, g, delta);
+            if constexpr (COLUMNS) reg_item<float, 6, false, 64>(a, b, resolve(a, b), 0, red, f, g, delta);
+            else reg_item<float, 6, false>(a, b, resolve(a, b), wave, red, f, g, delta);
             break;
-        case 1: reg_item<float, 5, false>(a, b, resolve(a, b), 0, false, red, f, g, delta); break;
-        case 2: reg_item<float, 4, false>(a, b, resolve(a, b), 0, false, red, f, g, delta); break;
+        case 1: reg_item<float, 5, false>(a, b, resolve(a, b), 0, red, f, g, delta); break;
+        case 2: reg_item<float, 4, false>(a, b, resolve(a, b), 0, red, f, g, delta); break;
         case 3: mix_wave_item<3>(a, b, f, g, delta); break;
         case 4: mix_wave_item<2>(a, b, f, g, delta); break;
         case 5: mix_wave_item<1>(a, b, f, g, delta); break;
@@ -428,17 +425,17 @@ static void launch_width(const BatchArgs& a, int n, int path, float* f, float* g
                          hipStream_t s) {
     const dim3 wgrid((a.B + WPB - 1) / WPB), wblock(64 * WPB);
     constexpr int LIB = ANG ? SCHED_ISING : SCHED_DISCRETE;
-    const bool lds = use_lds(n, path, sched_len(a), LIB), strict = path == QE_PATH_FP32_REG;
+    const bool lds = use_lds(n, path, sched_len(a), LIB);
     switch (n) {
         case 1: wave_kernel<float, 1, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
         case 2: wave_kernel<float, 2, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
         case 3: wave_kernel<float, 3, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta); break;
         case 4:
             if (lds) lds32_kernel<4, 1, FILTER, ANG><<<a.B, 64, 0, s>>>(a, f, g, delta);
-            else reg_kernel<float, 4, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta, strict);
+            else reg_kernel<float, 4, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta);
             break;
         case 5:
-            if (!lds) reg_kernel<float, 5, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta, strict);
+            if (!lds) reg_kernel<float, 5, FILTER, ANG><<<wgrid, wblock, 0, s>>>(a, f, g, delta);
             else if (schedule_for(5, sched_len(a), LIB).waves == 2)
                 lds32_kernel<5, 2, FILTER, ANG><<<a.B, 128, 0, s>>>(a, f, g, delta);
             else
@@ -447,8 +444,8 @@ static void launch_width(const BatchArgs& a, int n, int path, float* f, float* g
         default:
             if (lds) lds32_kernel<6, 4, FILTER, ANG><<<a.B, 256, 0, s>>>(a, f, g, delta);
             else if ((uint32_t)a.B >= reg6_columns_min(ANG))
-                reg_kernel<float, 6, FILTER, ANG, 64><<<wgrid, wblock, 0, s>>>(a, f, g, delta, strict);
-            else reg_kernel<float, 6, FILTER, ANG><<<a.B, 256, 0, s>>>(a, f, g, delta, strict);
+                reg_kernel<float, 6, FILTER, ANG, 64><<<wgrid, wblock, 0, s>>>(a, f, g, delta);
+            else reg_kernel<float, 6, FILTER, ANG><<<a.B, 256, 0, s>>>(a, f, g, delta);
             break;
     }
 }
@@ -546,9 +543,9 @@ static void launch_fp64_width(const BatchArgs& a, double* f, double* g, double* 
         case 1: wave_kernel<double, 1, false, ANG><<<wgs, 64 * WPB, 0, s>>>(a, f, g, delta); break;
         case 2: wave_kernel<double, 2, false, ANG><<<wgs, 64 * WPB, 0, s>>>(a, f, g, delta); break;
         case 3: wave_kernel<double, 3, false, ANG><<<wgs, 64 * WPB, 0, s>>>(a, f, g, delta); break;
-        case 4: reg_kernel<double, 4, false, ANG><<<wgs, 64 * WPB, 0, s>>>(a, f, g, delta, true); break;
-        case 5: reg_kernel<double, 5, false, ANG><<<wgs, 64 * WPB, 0, s>>>(a, f, g, delta, true); break;
-        default: reg_kernel<double, 6, false, ANG><<<a.B, 256, 0, s>>>(a, f, g, delta, true); break;
+        case 4: reg_kernel<double, 4, false, ANG><<<wgs, 64 * WPB, 0, s>>>(a, f, g, delta); break;
+        case 5: reg_kernel<double, 5, false, ANG><<<wgs, 64 * WPB, 0, s>>>(a, f, g, delta); break;
+        default: reg_kernel<double, 6, false, ANG><<<a.B, 256, 0, s>>>(a, f, g, delta); break;
     }
 }
 

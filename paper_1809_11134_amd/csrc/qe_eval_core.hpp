@@ -103,9 +103,9 @@ using complex_of = std::conditional_t<sizeof(Real) == 8, complex128, float2>;
 
 __device__ __forceinline__ float real_sqrt(float x) { return sqrtf(x); }
 __device__ __forceinline__ double real_sqrt(double x) { return sqrt(x); }
-// (the two treat NaN differently, each as its kernels always have)
-__device__ __forceinline__ float clamp01(float x) { return fminf(fmaxf(x, 0.0f), 1.0f); }
-__device__ __forceinline__ double clamp01(double x) { return x < 0.0 ? 0.0 : (x > 1.0 ? 1.0 : x); }
+// x within [0, 1]; NaN stays NaN (fminf and fmaxf would make it 0, a perfect fitness).
+template <typename Real>
+__device__ __forceinline__ Real clamp01(Real x) { return x < (Real)0 ? (Real)0 : (x > (Real)1 ? (Real)1 : x); }
 __device__ __forceinline__ float read_lane(float v, int g) {
     return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), g));
 }
@@ -120,8 +120,7 @@ __device__ __forceinline__ double read_lane(double v, int g) {
 template <typename Real>
 __device__ __forceinline__ void fitness_pi(Real offs, int N, Real* f, Real* g, Real* delta) {
     const Real r = offs / (Real)N;
-    const Real q = r < (Real)0 ? (Real)0 : (r > (Real)1 ? (Real)1 : r);
-    *f = (Real)1 - sqrt(q);
+    *f = (Real)1 - sqrt(clamp01(r));
     *g = (Real)1 - r;
     *delta = offs;
 }
@@ -133,11 +132,9 @@ template <typename Real>
 __device__ __forceinline__ FitOut<Real> finish_fitness(Real off, Real dre, Real dim, bool hasd, int N,
                                                        int mode = QE_FIT_EQ11) {
     FitOut<Real> o;
-    const Real nan = (Real)__builtin_nan("");
     const Real offs = wave_sum(off);
     if (mode == QE_FIT_PHASE_INSENSITIVE) {
         fitness_pi(offs, N, &o.f, &o.g, &o.delta);
-        if (!(o.f == o.f)) o.f = nan;
         return o;
     }
     const Real tre = wave_sum(dre), tim = wave_sum(dim);
@@ -154,7 +151,6 @@ __device__ __forceinline__ FitOut<Real> finish_fitness(Real off, Real dre, Real 
     o.f = (Real)1 - real_sqrt(clamp01(delta / (Real)N));
     o.g = a / (Real)N;
     o.delta = delta;
-    if (!(o.f == o.f) || !(delta == delta)) o.f = nan;
     return o;
 }
 
@@ -842,9 +838,7 @@ __device__ __forceinline__ void lds_fitness(const Real* Mr, const Real* Mi, int 
             fitness_pi(off, N, &fv, &gv, &dl);
         } else {
             dl = (Real)0.5 * (off + D);
-            Real q = dl / (Real)N;
-            q = q < 0 ? (Real)0 : (q > 1 ? (Real)1 : q);
-            fv = (Real)1 - sqrt(q);
+            fv = (Real)1 - sqrt(clamp01(dl / (Real)N));
             gv = am / (Real)N;
         }
         if (ok && !(fv == fv)) err = QE_DEVERR_NUMERIC;
@@ -1019,10 +1013,9 @@ __device__ __forceinline__ float canonical_fitness(const float2* M, const RowMap
     float dl = 0.0f;
     if (j % Q == q) { const float xr = d.x - er, xi = d.y - ei; dl = xr * xr + xi * xi; }
     const float dlt = 0.5f * (offs + total(dl));
-    const float qq = fminf(fmaxf(dlt / (float)N, 0.0f), 1.0f);
     *g_out = am / (float)N;
     *delta_out = dlt;
-    return 1.0f - sqrtf(qq);
+    return 1.0f - sqrtf(clamp01(dlt / (float)N));
 }
 
 // wavefronts of the canonical reduction per width

@@ -358,8 +358,7 @@ __global__ __launch_bounds__(64 * (1 << (NQ - 4))) void mfma_kernel(BatchArgs a,
 #pragma unroll
         for (int w = 0; w < W; ++w) D += red[w][0];
         float dlt = 0.5f * (offs + D);
-        const float q = fminf(fmaxf(dlt / (float)N, 0.0f), 1.0f);
-        float fv = 1.0f - sqrtf(q), gv = am / (float)N;
+        float fv = 1.0f - sqrtf(clamp01(dlt / (float)N)), gv = am / (float)N;
         if (a.mode == QE_FIT_PHASE_INSENSITIVE) fitness_pi(offs, N, &fv, &gv, &dlt);
         const float nan = __builtin_nanf("");
         if (ok && !(fv == fv)) it.err = QE_DEVERR_NUMERIC;
