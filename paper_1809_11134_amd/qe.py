@@ -415,16 +415,18 @@ class Context:
         return (slots, gates, angles) if self.ising else (slots, gates)
 
     def eval_population(self, gates, angles=None, stream=None):
+        # (a converted argument is held until the call returns: the next conversion or
+        # output would be allocated in its place)
+        g, a = _gates(gates), _angles(angles)
         f = torch.empty(self.circuits, dtype=torch.float32, device=gates.device)
-        _call("qe_eval_population", self.handle, _ptr(_gates(gates)), _ptr(_angles(angles)), _ptr(f),
-              _stream(stream))
+        _call("qe_eval_population", self.handle, _ptr(g), _ptr(a), _ptr(f), _stream(stream))
         return f
 
     def update(self, gen, slots, gates, f, angles=None, stream=None):
         """slots None: right after sample_eval(gen), which left the segment
         keys and decisions (the slots are drawn again)."""
-        _call("qe_update", self.handle, gen, _ptr(slots), _ptr(_gates(gates)), _ptr(_angles(angles)),
-              _ptr(f.contiguous()), _stream(stream))
+        g, a, f = _gates(gates), _angles(angles), f.contiguous()
+        _call("qe_update", self.handle, gen, _ptr(slots), _ptr(g), _ptr(a), _ptr(f), _stream(stream))
 
     def generation(self, gen, f=None, stream=None):
         if f is None:
@@ -457,11 +459,11 @@ class Context:
         _call("qe_run_graph", self.handle, first_gen, n_gen, _ptr(f_hist), _stream(stream))
 
     def elite_recheck(self, gates, f, k, stream=None, angles=None):
+        g, a, f = _gates(gates) if gates is not None else None, _angles(angles), f.contiguous()
         idx = torch.empty((self.I, k), dtype=torch.int32, device=f.device)
         f64 = torch.empty((self.I, k), dtype=torch.float64, device=f.device)
-        _call("qe_elite_recheck", self.handle, _ptr(_gates(gates) if gates is not None else None),
-              _ptr(_angles(angles)), _ptr(f.contiguous()), k,
-              _ptr(idx), _ptr(f64), _stream(stream))
+        _call("qe_elite_recheck", self.handle, _ptr(g), _ptr(a), _ptr(f), k, _ptr(idx), _ptr(f64),
+              _stream(stream))
         return idx, f64
 
     def get_best(self, instance=0, with_fp64=True, with_angles=False):
