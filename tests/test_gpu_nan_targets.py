@@ -38,12 +38,10 @@ def check(f, bad=(1, 2)):
     assert qe.device_errors() == qe.DEVERR_NUMERIC
 
 
-@pytest.mark.parametrize("n", [2, 3, 4, 5, 6])
-@pytest.mark.parametrize("path", [*PATHS, "fp64", "angles"])
+@pytest.mark.parametrize("path,n", [(p, n) for p in [*PATHS, "fp64", "angles"]
+                                    for n in ((5, 6) if "16" in p else (2, 3, 4, 5, 6))])   # (MFMA: 5 and 6)
 @pytest.mark.parametrize("B", [3, 1030])
 def test_evaluation(dev, n, path, B):
-    if path in ("bf16", "fp16_raw") and n < 5:
-        pytest.skip("MFMA paths: widths 5 and 6")
     rng = np.random.default_rng(n)
     L = 9
     g = inputs.random_circuits(rng, B, n, L, inputs.LIB_NCV)
