@@ -739,7 +739,7 @@ qe_status create_impl(const qe_problem* p_in, const int32_t* inst_n, const int32
     } else {
         ALLOC(a.genomes[0], (size_t)genes);
         ALLOC(a.genomes[1], (size_t)genes);
-        ALLOC(a.ga_last, 2);
+        ALLOC(a.ga_last, I * ga_update_parts((int)I, (int)P, (int)L));
     }
     float* t32 = nullptr;
     double* t64 = nullptr;
@@ -838,8 +838,9 @@ qe_status create_impl(const qe_problem* p_in, const int32_t* inst_n, const int32
         if (e == hipSuccess) e = launch_qeqea_init(a, nullptr);
     } else if (e == hipSuccess) {
         e = launch_ga_init(a, nullptr);
-        if (e == hipSuccess) e = launch_fill_i32(reinterpret_cast<int32_t*>(a.ga_last), 1, (int32_t)GA_LAST_KEPT, nullptr);
-        if (e == hipSuccess) e = launch_fill_i32(reinterpret_cast<int32_t*>(a.ga_last) + 1, 1, 0, nullptr);
+        if (e == hipSuccess)
+            e = launch_fill_i32(reinterpret_cast<int32_t*>(a.ga_last), (int64_t)I * ga_update_parts((int)I, (int)P, (int)L),
+                                (int32_t)GA_LAST_KEPT, nullptr);
     }
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking);

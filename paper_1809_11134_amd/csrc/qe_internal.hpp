@@ -137,8 +137,9 @@ struct LoopArgs {
     uint16_t* genomes[2];              // GA double buffer
     // GA: where the circuits of the last generation run are (qe_elite_recheck
     // without gates): genomes[0], genomes[1] or GA_LAST_KEPT, the context's own
-    // buffer; then a count of workgroups.  On the device, so that it follows
-    // captured calls when they are replayed.
+    // buffer.  On the device, so that it follows captured calls when they are
+    // replayed.  A word per workgroup of the update, which alone reads and writes
+    // it there; between launches all are equal.
     uint32_t* ga_last;
     const float* target32;             // [I][N][N] complex64
     const double* target64;            // [I][N][N] complex128
@@ -236,6 +237,7 @@ hipError_t launch_ga_eval(const LoopArgs& a, uint64_t gen, float* f, hipStream_t
 // kept: the last generation's circuits move there if they are written over (NULL:
 // the update of a whole generation, whose circuits they become)
 hipError_t launch_ga_update(const LoopArgs& a, uint64_t gen, const float* f, uint16_t* kept, hipStream_t s);
+uint32_t ga_update_parts(int I, int P, int L);      // workgroups per population
 hipError_t launch_ga_keep(const LoopArgs& a, uint16_t* kept, hipStream_t s);
 hipError_t launch_c128_to_c64(const double* src, float* dst, int64_t n_reals, hipStream_t s);
 hipError_t launch_target_units(const LoopArgs& a, hipStream_t s);

@@ -1151,10 +1151,11 @@ __global__ void state_gather_kernel(LoopArgs a, int which, void* __restrict__ ds
 // workgroup waits for another.  A population of 4096 x 20 genes on one
 // workgroup with a serial prefix took 253 us.
 // RUN: the update of a whole generation, whose circuits stay in genomes[gen & 1],
-// as the context's word says from here on.  Otherwise (qe_update) the genes
-// written over move to `kept` if the word names them, each by the thread that
-// writes its place (a generation doing that took 0.9 us more of 19 at P = 4096,
-// L = 20); the last workgroup to have read the word changes it.
+// as the workgroup's word of a.ga_last says from here on.  Otherwise (qe_update) the
+// genes written over move to `kept` if the word names them, each by the thread that
+// writes its place.  (A generation doing that took 0.9 us more of 19 at P = 4096,
+// L = 20; one word for all, changed by the last workgroup to have read it, cost
+// 0.05 us a workgroup, 254 against 87 us for the step of 4096 populations of 16.)
 constexpr int GA_MAX_P = 4096;
 constexpr int GA_BLOCK = 256;
 
@@ -1175,14 +1176,10 @@ __global__ __launch_bounds__(GA_BLOCK) void ga_update_kernel(LoopArgs a, uint64_
     const uint32_t i = blockIdx.x / parts, part = blockIdx.x % parts;
     const int P = a.P, tid = threadIdx.x, wave = tid >> 6;
     if (RUN) {
-        if (blockIdx.x == 0 && tid == 0) a.ga_last[0] = gen & 1u;
+        if (tid == 0) a.ga_last[blockIdx.x] = gen & 1u;
     } else if (tid == 0) {
-        keep = __hip_atomic_load(a.ga_last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == ((gen + 1u) & 1u);
-        __threadfence();
-        if (atomicAdd(a.ga_last + 1, 1u) == gridDim.x - 1u) {
-            a.ga_last[1] = 0u;
-            if (keep) a.ga_last[0] = GA_LAST_KEPT;
-        }
+        keep = a.ga_last[blockIdx.x] == ((gen + 1u) & 1u);
+        if (keep) a.ga_last[blockIdx.x] = GA_LAST_KEPT;
     }
     // population i's width, genome length and genomes (mixed populations
     // carry their own)
@@ -1559,7 +1556,8 @@ hipError_t launch_qeqea_sample(const LoopArgs& a, uint64_t gen, uint32_t* slots,
 
 hipError_t launch_ga_keep(const LoopArgs& a, uint16_t* kept, hipStream_t s) {
     ga_keep_kernel<<<blocks((size_t)a.genes, 256), 256, 0, s>>>(a, kept);
-    return launch_fill_i32(reinterpret_cast<int32_t*>(a.ga_last), 1, (int32_t)GA_LAST_KEPT, s);
+    return launch_fill_i32(reinterpret_cast<int32_t*>(a.ga_last), (int64_t)a.I * ga_update_parts(a.I, a.P, a.L),
+                           (int32_t)GA_LAST_KEPT, s);
 }
 
 hipError_t launch_ga_copy(const LoopArgs& a, uint64_t gen, uint16_t* gates, hipStream_t s) {
@@ -1708,18 +1706,22 @@ hipError_t launch_state_gather(const LoopArgs& a, int which, void* dst, hipStrea
     return hipGetLastError();
 }
 
-hipError_t launch_ga_update(const LoopArgs& a, uint64_t gen, const float* f, uint16_t* kept, hipStream_t s) {
+uint32_t ga_update_parts(int I, int P, int L) {
     // one round of gene pairs per thread, as long as the populations together
     // make no more than two workgroups per compute unit: every workgroup
     // repeats its population's prefix and draws (256 populations of 64: 10.8 us
     // at 512 workgroups in all, 11.4 at 1024, 16.0 at 2048)
-    const int half = a.P / 2;
-    const uint64_t rounds = ((uint64_t)half * a.L + GA_BLOCK - 1) / GA_BLOCK;
-    const uint64_t most = std::max<uint64_t>(1, 512 / (uint64_t)a.I);
+    const int half = P / 2;
+    const uint64_t rounds = ((uint64_t)half * L + GA_BLOCK - 1) / GA_BLOCK;
+    const uint64_t most = std::max<uint64_t>(1, 512 / (uint64_t)I);
     // (and at most 1024 pairs a workgroup: 48 KB of LDS in all)
     const uint64_t least = std::max<uint64_t>(1, ((uint64_t)half + 1023) / 1024);
-    const uint32_t parts = (uint32_t)std::max<uint64_t>(least, std::min({rounds, most, (uint64_t)half}));
-    const int share = (half + (int)parts - 1) / (int)parts;
+    return (uint32_t)std::max<uint64_t>(least, std::min({rounds, most, (uint64_t)half}));
+}
+
+hipError_t launch_ga_update(const LoopArgs& a, uint64_t gen, const float* f, uint16_t* kept, hipStream_t s) {
+    const uint32_t parts = ga_update_parts(a.I, a.P, a.L);
+    const int share = (a.P / 2 + (int)parts - 1) / (int)parts;
     if (kept)
         ga_update_kernel<false><<<(unsigned)a.I * parts, GA_BLOCK, ga_lds_bytes(a.P, share), s>>>(a, gen, f, parts, kept);
     else
