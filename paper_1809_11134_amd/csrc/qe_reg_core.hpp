@@ -194,20 +194,13 @@ struct RegMatrix {
             if constexpr (ANG)
                 if (in && kind_ising(kind)) half_angle(angle_of(dvv), &gc, &gs);
             if constexpr (ANG || LB == 0) {
-                gc = permute(to, gc);
-                gs = permute(to, gs);
+                gc = push_lane(to, gc);
+                gs = push_lane(to, gs);
             }
             reg_gates<NQ, GATES>(x, word, cnt, gc, gs, map, RESTORE && ch + 1 >= chunks);
             if (++ch < chunks) dvv = src(ch);
         } while (ch < chunks);
         return true;
-    }
-    static __device__ __forceinline__ float permute(int to, float v) {
-        return __int_as_float(__builtin_amdgcn_ds_permute(to, __float_as_int(v)));
-    }
-    static __device__ __forceinline__ double permute(int to, double v) {
-        return __hiloint2double(__builtin_amdgcn_ds_permute(to, __double2hiint(v)),
-                                __builtin_amdgcn_ds_permute(to, __double2loint(v)));
     }
 
     // Row-major store of M (the slots in any order).
