@@ -272,7 +272,8 @@ struct qe_ctx {
     bool targets_set = false;
     // ctx-owned device buffers
     std::vector<void*> owned;
-    uint16_t* gates = nullptr;    // [I*P*L] (GA: see LoopArgs::ga_last)
+    uint16_t* gates = nullptr;    // [I*P*L]
+    uint32_t* ga_last = nullptr;  // GA: where the last generation's circuits are (GA_LAST_KEPT: in gates)
     uint32_t* angles = nullptr;   // [I*P*L] (Ising library)
     float* f = nullptr;           // [I*P]
     uint64_t* d_gen = nullptr;
@@ -413,7 +414,7 @@ qe_status enqueue_generation(qe_ctx* c, const LoopArgs& a, uint64_t gen, float* 
             QE_HIP(launch_mix_eval(mixed_batch(c, nullptr, a.gen_ptr, gen), c->mix_order, f, nullptr, nullptr, s));
         else
             QE_HIP(launch_ga_eval(a, gen, f, s));
-        QE_HIP(launch_ga_update(a, gen, f, nullptr, s));
+        QE_HIP(launch_ga_update(a, gen, f, c->ga_last, nullptr, s));
     }
     return QE_OK;
 }
@@ -739,7 +740,7 @@ qe_status create_impl(const qe_problem* p_in, const int32_t* inst_n, const int32
     } else {
         ALLOC(a.genomes[0], (size_t)genes);
         ALLOC(a.genomes[1], (size_t)genes);
-        ALLOC(a.ga_last, I * ga_update_parts((int)I, (int)P, (int)L));
+        ALLOC(c->ga_last, I * ga_update_parts((int)I, (int)P, (int)L));
     }
     float* t32 = nullptr;
     double* t64 = nullptr;
@@ -839,7 +840,7 @@ qe_status create_impl(const qe_problem* p_in, const int32_t* inst_n, const int32
     } else if (e == hipSuccess) {
         e = launch_ga_init(a, nullptr);
         if (e == hipSuccess)
-            e = launch_fill_i32(reinterpret_cast<int32_t*>(a.ga_last), (int64_t)I * ga_update_parts((int)I, (int)P, (int)L),
+            e = launch_fill_i32(reinterpret_cast<int32_t*>(c->ga_last), (int64_t)I * ga_update_parts((int)I, (int)P, (int)L),
                                 (int32_t)GA_LAST_KEPT, nullptr);
     }
     if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -967,7 +968,7 @@ qe_status qe_update(qe_ctx* c, uint64_t gen, const uint32_t* slots, const uint16
                                    words));
         if (words) note_words(c, gen + 1);
     } else {
-        QE_HIP(launch_ga_update(c->la, gen, f, c->gates, s));
+        QE_HIP(launch_ga_update(c->la, gen, f, c->ga_last, c->gates, s));
     }
     return QE_OK;
 }
@@ -1057,7 +1058,7 @@ qe_status qe_elite_recheck(qe_ctx* c, const uint16_t* gates, const uint32_t* ang
                            int32_t k, int32_t* idx, double* f64, void* stream) {
     QE_TRY(check_ctx(c, true));
     if (!f || !idx || !f64) return fail(QE_ERR_INVALID, "NULL buffer");
-    const bool last = !gates && c->prob.algorithm == QE_ALG_GA;
+    const uint32_t* last = gates ? nullptr : c->ga_last;
     if (!gates) {
         gates = c->gates;
         angles = c->angles;
@@ -1222,7 +1223,7 @@ qe_status qe_restore(qe_ctx* c, const void* buf, size_t size) {
     if (h.payload != payload || size < sizeof(h) + payload) return fail(QE_ERR_INVALID, "checkpoint size mismatch");
     QE_HIP(hipDeviceSynchronize());
     if (c->prob.algorithm == QE_ALG_GA) {
-        QE_HIP(launch_ga_keep(c->la, c->gates, nullptr));
+        QE_HIP(launch_ga_keep(c->la, c->ga_last, c->gates, nullptr));
         QE_HIP(hipDeviceSynchronize());
     }
     const char* p = static_cast<const char*>(buf) + sizeof(h);

@@ -303,9 +303,9 @@ __global__ void qeqea_sample_kernel(LoopArgs a, uint64_t gen64, uint32_t* __rest
 
 // Moves the last generation's circuits to the context's own buffer, unless they are
 // there.  (qe_restore; qe_update does it in its update kernel.)
-__global__ void ga_keep_kernel(LoopArgs a, uint16_t* __restrict__ kept) {
+__global__ void ga_keep_kernel(LoopArgs a, const uint32_t* __restrict__ last, uint16_t* __restrict__ kept) {
     const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t at = a.ga_last[0];
+    const uint32_t at = last[0];
     if (idx < (size_t)a.genes && at < GA_LAST_KEPT) kept[idx] = a.genomes[at][idx];
 }
 
@@ -1151,7 +1151,7 @@ __global__ void state_gather_kernel(LoopArgs a, int which, void* __restrict__ ds
 // workgroup waits for another.  A population of 4096 x 20 genes on one
 // workgroup with a serial prefix took 253 us.
 // RUN: the update of a whole generation, whose circuits stay in genomes[gen & 1],
-// as the workgroup's word of a.ga_last says from here on.  Otherwise (qe_update) the
+// as the workgroup's word of `last` says from here on.  Otherwise (qe_update) the
 // genes written over move to `kept` if the word names them, each by the thread that
 // writes its place.  (A generation doing that took 0.9 us more of 19 at P = 4096,
 // L = 20; one word for all, changed by the last workgroup to have read it, cost
@@ -1166,6 +1166,7 @@ static inline size_t ga_lds_bytes(int P, int pairs) { return (size_t)((P + 2) & 
 template <bool RUN>
 __global__ __launch_bounds__(GA_BLOCK) void ga_update_kernel(LoopArgs a, uint64_t gen64,
                                                              const float* __restrict__ f, uint32_t parts,
+                                                             uint32_t* __restrict__ last,
                                                              uint16_t* __restrict__ kept) {
     extern __shared__ __align__(16) unsigned long long pre[];
     __shared__ unsigned long long wsum[GA_BLOCK / 64];
@@ -1176,10 +1177,10 @@ __global__ __launch_bounds__(GA_BLOCK) void ga_update_kernel(LoopArgs a, uint64_
     const uint32_t i = blockIdx.x / parts, part = blockIdx.x % parts;
     const int P = a.P, tid = threadIdx.x, wave = tid >> 6;
     if (RUN) {
-        if (tid == 0) a.ga_last[blockIdx.x] = gen & 1u;
+        if (tid == 0) last[blockIdx.x] = gen & 1u;
     } else if (tid == 0) {
-        keep = a.ga_last[blockIdx.x] == ((gen + 1u) & 1u);
-        if (keep) a.ga_last[blockIdx.x] = GA_LAST_KEPT;
+        keep = last[blockIdx.x] == ((gen + 1u) & 1u);
+        if (keep) last[blockIdx.x] = GA_LAST_KEPT;
     }
     // population i's width, genome length and genomes (mixed populations
     // carry their own)
@@ -1410,16 +1411,17 @@ __global__ __launch_bounds__(1024) void elite_select_kernel(LoopArgs a, const fl
 
 // The circuits to re-check: those given, or (last; GA) the last generation's,
 // which are still a population unless they were moved to `gates`.
-__device__ __forceinline__ const uint16_t* last_circuits(const LoopArgs& a, const uint16_t* gates, bool last) {
+__device__ __forceinline__ const uint16_t* last_circuits(const LoopArgs& a, const uint16_t* gates,
+                                                         const uint32_t* last) {
     if (!last) return gates;
-    const uint32_t at = a.ga_last[0];
+    const uint32_t at = last[0];
     return at < GA_LAST_KEPT ? a.genomes[at] : gates;
 }
 
 // Mixed populations (discrete libraries): widths differ from circuit to circuit.
 __global__ __launch_bounds__(256) void elite_eval_kernel(LoopArgs a, const uint16_t* __restrict__ gates,
                                                          int k, const int32_t* __restrict__ idx,
-                                                         double* __restrict__ f64, bool last) {
+                                                         double* __restrict__ f64, const uint32_t* __restrict__ last) {
     gates = last_circuits(a, gates, last);
     const int i = blockIdx.x / k, e = blockIdx.x % k;
     const int c = idx[(size_t)i * k + e];
@@ -1438,7 +1440,7 @@ template <int NQ, bool ANG>
 __global__ __launch_bounds__(256) void elite64_kernel(LoopArgs a, const uint16_t* __restrict__ gates,
                                                       const uint32_t* __restrict__ angles, int k,
                                                       const int32_t* __restrict__ idx,
-                                                      double* __restrict__ f64, bool last) {
+                                                      double* __restrict__ f64, const uint32_t* __restrict__ last) {
     gates = last_circuits(a, gates, last);
     constexpr bool WHOLE = NQ == 6;
     __shared__ double red[4][3];
@@ -1554,9 +1556,9 @@ hipError_t launch_qeqea_sample(const LoopArgs& a, uint64_t gen, uint32_t* slots,
     return hipGetLastError();
 }
 
-hipError_t launch_ga_keep(const LoopArgs& a, uint16_t* kept, hipStream_t s) {
-    ga_keep_kernel<<<blocks((size_t)a.genes, 256), 256, 0, s>>>(a, kept);
-    return launch_fill_i32(reinterpret_cast<int32_t*>(a.ga_last), (int64_t)a.I * ga_update_parts(a.I, a.P, a.L),
+hipError_t launch_ga_keep(const LoopArgs& a, uint32_t* last, uint16_t* kept, hipStream_t s) {
+    ga_keep_kernel<<<blocks((size_t)a.genes, 256), 256, 0, s>>>(a, last, kept);
+    return launch_fill_i32(reinterpret_cast<int32_t*>(last), (int64_t)a.I * ga_update_parts(a.I, a.P, a.L),
                            (int32_t)GA_LAST_KEPT, s);
 }
 
@@ -1719,13 +1721,14 @@ uint32_t ga_update_parts(int I, int P, int L) {
     return (uint32_t)std::max<uint64_t>(least, std::min({rounds, most, (uint64_t)half}));
 }
 
-hipError_t launch_ga_update(const LoopArgs& a, uint64_t gen, const float* f, uint16_t* kept, hipStream_t s) {
+hipError_t launch_ga_update(const LoopArgs& a, uint64_t gen, const float* f, uint32_t* last, uint16_t* kept,
+                            hipStream_t s) {
     const uint32_t parts = ga_update_parts(a.I, a.P, a.L);
     const int share = (a.P / 2 + (int)parts - 1) / (int)parts;
-    if (kept)
-        ga_update_kernel<false><<<(unsigned)a.I * parts, GA_BLOCK, ga_lds_bytes(a.P, share), s>>>(a, gen, f, parts, kept);
-    else
-        ga_update_kernel<true><<<(unsigned)a.I * parts, GA_BLOCK, ga_lds_bytes(a.P, share), s>>>(a, gen, f, parts, kept);
+    const unsigned grid = (unsigned)a.I * parts;
+    const size_t lds = ga_lds_bytes(a.P, share);
+    if (kept) ga_update_kernel<false><<<grid, GA_BLOCK, lds, s>>>(a, gen, f, parts, last, kept);
+    else ga_update_kernel<true><<<grid, GA_BLOCK, lds, s>>>(a, gen, f, parts, last, kept);
     return hipGetLastError();
 }
 
@@ -1752,7 +1755,7 @@ hipError_t launch_elite_select(const LoopArgs& a, const float* f, int k, int32_t
 }
 
 hipError_t launch_elite_eval(const LoopArgs& a, const uint16_t* gates, const uint32_t* angles, int k,
-                             const int32_t* idx, double* f64, bool last, hipStream_t s) {
+                             const int32_t* idx, double* f64, const uint32_t* last, hipStream_t s) {
     const unsigned nc = (unsigned)a.I * (unsigned)k;
     if (a.inst_n) {
         elite_eval_kernel<<<nc, 256, generic_lds_bytes(a.n, sizeof(double)), s>>>(a, gates, k, idx, f64, last);
