@@ -412,7 +412,10 @@ qe_status qe_lib_table(int32_t library, int32_t n_qubits, uint16_t* table_host);
  * one-element-per-lane kernel; mixed-width batches evaluated in one launch
  * the register-resident one).  Process-wide; the defaults come from the
  * tuning table measured on MI355X and can be overridden by the environment
- * variable QE_SCHEDULE="n:lds,n:lds,...". */
+ * variable QE_SCHEDULE="n:lds,n:lds,...".  The table's choice gives way where
+ * QEQEA circuits over {I, NOT, CNOT, CV, CV+} are longer than what it was tuned
+ * on (more than 64 or 128 gates, by width and number of circuits: LDS-staged);
+ * a schedule set here, by the calls below or by QE_SCHEDULE holds everywhere. */
 qe_status qe_set_schedule(int32_t n_qubits, int32_t lds);
 qe_status qe_get_schedule(int32_t n_qubits, int32_t* lds);
 

@@ -185,6 +185,7 @@ void load_schedule_env() {
                     v.lds = l ? 1 : 0;
                     if (got >= 3) v.waves = w;
                     if (got >= 4) v.cpb = c;
+                    v.chosen = true;
                     if (sched_ok(n, v.lds, v.waves, v.cpb)) g_sched[n][k][cl] = v;
                 }
         }
@@ -442,7 +443,10 @@ qe_status qe_set_schedule(int32_t n, int32_t lds) {
     std::call_once(g_sched_once, load_schedule_env);
     if (n < 1 || n > MAX_QUBITS) return fail(QE_ERR_INVALID, "width must be 1..6");
     for (int l = 0; l < 2; ++l)
-        for (int c = 0; c < SCHED_CLASSES; ++c) g_sched[n][l][c].lds = lds ? 1 : 0;
+        for (int c = 0; c < SCHED_CLASSES; ++c) {
+            g_sched[n][l][c].lds = lds ? 1 : 0;
+            g_sched[n][l][c].chosen = true;
+        }
     return QE_OK;
 }
 
@@ -458,7 +462,7 @@ qe_status qe_set_schedule_ex(int32_t n, int32_t lclass, int32_t lds, int32_t wav
     if (lclass != 0 && lclass != 1) return fail(QE_ERR_INVALID, "lclass must be 0 (L < 32) or 1 (L >= 32)");
     if (!sched_ok(n, lds, waves, cpb))
         return fail(QE_ERR_INVALID, "no such schedule: lds 0/1; waves 1 (n <= 5), 2 (n = 5) or 4 (n = 6); cpb 1 or 4");
-    set_classes(n, lclass, Sched{lds, waves, cpb});
+    set_classes(n, lclass, Sched{lds, waves, cpb, true});
     return QE_OK;
 }
 
@@ -491,7 +495,7 @@ qe_status qe_set_schedule_lib(int32_t n, int32_t lclass, int32_t lib_class, int3
         return fail(QE_ERR_INVALID, "lib_class must be QE_SCHED_DISCRETE, QE_SCHED_SAMPLED or QE_SCHED_ISING");
     if (!sched_ok(n, lds, waves, cpb))
         return fail(QE_ERR_INVALID, "no such schedule: lds 0/1; waves 1 (n <= 5), 2 (n = 5) or 4 (n = 6); cpb 1 or 4");
-    g_sched[n][lclass][lib_class] = Sched{lds, waves, cpb};
+    g_sched[n][lclass][lib_class] = Sched{lds, waves, cpb, true};
     return QE_OK;
 }
 

@@ -35,6 +35,7 @@ struct BatchArgs {
 // population kernels
 struct Sched {
     int lds, waves, cpb;
+    bool chosen = false;    // set by the caller (qe_set_schedule*, QE_SCHEDULE), not the tuning table
 };
 // Library class of a schedule (QE_SCHED_*): circuits as given in a discrete
 // library, circuits the QEQEA sampler decodes (only {I, NOT, CNOT, CV, CV+}:
@@ -48,6 +49,22 @@ Sched schedule_for(int n, int L, int lib_class = SCHED_DISCRETE);
 // 25.3, 8192 94 against 145; Ising 768 44.6 against 39.5, 1024 45.4 against
 // 48.2, 8192 206 against 260.
 constexpr uint32_t reg6_columns_min(bool angled) { return angled ? 1024u : 640u; }
+// Sampled circuits of {I, NOT, CNOT, CV, CV+} that run LDS-staged although the table
+// (tuned on up to 48 gates) says register-resident.  There every chunk of 64 gates
+// after the first is sampled before the first gate runs; LDS-staged, the random
+// gathers of one wavefront's chunks pass while others' gates run.  Microseconds per
+// generation, register-resident / LDS-staged:
+//   n = 4, 4096 circuits: 96 gates 57.1 / 58.2, 192 115 / 112, 1024 681 / 625;
+//          1500 circuits: 192 50.5 / 51.2, 1024 270 / 262; 64: 1024 85 / 88
+//   n = 5, 4096 circuits: 96 gates 73.9 / 76.4, 192 139 / 139, 512 347 / 312;
+//          1024: 65 26.5 / 27.2, 192 60.3 / 55.1; 512: 65 23.9 / 23.2, 96 28.5 / 27.6
+//   n = 6, 512 circuits: 65 gates 31.7 / 32.8, 192 63.4 / 60.7, 1024 286 / 255 (from
+//          640 circuits on a column per lane: 4096 of 200 gates 203 / 334)
+constexpr bool long_sampled_lds(int n, int L, uint32_t circuits) {
+    if (n == 4) return L > 128 && circuits >= 2048u;
+    if (n == 5) return L > 128 || (L > 64 && circuits <= 512u);
+    return L > 128 && circuits < reg6_columns_min(false);
+}
 // MFMA paths: the fewest non-identity gates a group needs to be fused into a
 // block (smaller groups go gate by gate in FP32), per width and length class
 int mfma_min_block(int n, int L);

@@ -1572,7 +1572,11 @@ static void launch_population(const LoopArgs& a, uint64_t gen, const uint16_t* g
                               uint32_t* sout, uint16_t* gout, uint32_t* aout, float* f, hipStream_t s,
                               bool decide = false) {
     const uint32_t total = (uint32_t)a.I * (uint32_t)a.P;
-    const Sched sc = schedule_for(a.n, a.L, a.lib == LIB_ISING ? SCHED_ISING : (SAMPLE ? SCHED_SAMPLED : SCHED_DISCRETE));
+    Sched sc = schedule_for(a.n, a.L, a.lib == LIB_ISING ? SCHED_ISING : (SAMPLE ? SCHED_SAMPLED : SCHED_DISCRETE));
+    if (SAMPLE && a.lib != LIB_ISING && a.n >= 4 && !sc.chosen && long_sampled_lds(a.n, a.L, total)) {
+        sc.lds = 1;
+        if (a.n == 4) sc.cpb = 4;     // (4096 circuits of 256 gates 150.7 us, one per workgroup 153.7)
+    }
     auto go = [&](auto nq, auto w, auto cpb, auto ising) {
         constexpr int NQ = decltype(nq)::value, W = decltype(w)::value, CPB = decltype(cpb)::value;
         constexpr int WV = circuit_waves<NQ, W, CPB>();
