@@ -910,8 +910,8 @@ qe_status qe_set_targets(qe_ctx* c, const void* t, void* stream) {
                                             "modulus 0 or 1 (permutations with phases)");
     }
     QE_HIP(hipMemcpyAsync((void*)c->la.target64, t, reals * sizeof(double), hipMemcpyDeviceToDevice, s));
-    QE_HIP(launch_c128_to_c64(c->la.target64, (float*)c->la.target32, (int64_t)reals, s));
-    if (c->prob.algorithm == QE_ALG_QEQEA) QE_HIP(launch_target_units(c->la, s));
+    if (c->prob.algorithm == QE_ALG_QEQEA) QE_HIP(launch_target_copy(c->la, s));
+    else QE_HIP(launch_c128_to_c64(c->la.target64, (float*)c->la.target32, (int64_t)reals, s));
     c->targets_set = true;
     return QE_OK;
 }

@@ -258,7 +258,7 @@ hipError_t launch_ga_update(const LoopArgs& a, uint64_t gen, const float* f, uin
 uint32_t ga_update_parts(int I, int P, int L);      // workgroups per population
 hipError_t launch_ga_keep(const LoopArgs& a, uint32_t* last, uint16_t* kept, hipStream_t s);
 hipError_t launch_c128_to_c64(const double* src, float* dst, int64_t n_reals, hipStream_t s);
-hipError_t launch_target_units(const LoopArgs& a, hipStream_t s);
+hipError_t launch_target_copy(const LoopArgs& a, hipStream_t s);
 hipError_t launch_gen_advance(uint64_t* gen_ptr, uint64_t by, hipStream_t s);
 hipError_t launch_gen_set(uint64_t* gen_ptr, uint64_t v, hipStream_t s);
 // cand: elite_cand_keys(I, P) 64-bit keys of device workspace.

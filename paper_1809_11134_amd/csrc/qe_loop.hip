@@ -1494,19 +1494,22 @@ __global__ void c128_to_c64_kernel(const double* __restrict__ src, float* __rest
     if (idx < n) dst[idx] = (float)src[idx];
 }
 
-// Whether every entry of population i's target is 0, +-1 or +-i (one workgroup
-// each; uniform widths).
-__global__ __launch_bounds__(64) void target_units_kernel(LoopArgs a) {
-    const size_t NN = (size_t)1 << (2 * a.n);
-    const float* T = a.target32 + 2 * NN * blockIdx.x;
+// QEQEA: the same copy, one workgroup per population, which also finds whether every
+// entry of its target is 0, +-1 or +-i (uniform widths).  (As a kernel of its own the
+// check cost qe_set_targets 3 us, 7 at 64 targets of n = 6.)
+__global__ __launch_bounds__(1024) void target_copy_kernel(LoopArgs a, float* __restrict__ dst) {
+    const int NN = 1 << (2 * a.n);
+    const complex128* T = reinterpret_cast<const complex128*>(a.target64) + (size_t)NN * blockIdx.x;
+    float2* T32 = reinterpret_cast<float2*>(dst) + (size_t)NN * blockIdx.x;
     bool bad = false;
-    for (size_t e = threadIdx.x; e < NN; e += 64) {
-        const float x = T[2 * e], y = T[2 * e + 1];
+    for (int e = (int)threadIdx.x; e < NN; e += (int)blockDim.x) {
+        const float x = (float)T[e].x, y = (float)T[e].y;
+        T32[e] = make_float2(x, y);
         // (one part zero, the other 0 or +-1; NaN fails)
         bad = bad || !((x == 0.0f && (y == 0.0f || y * y == 1.0f)) || (y == 0.0f && x * x == 1.0f));
     }
-    const bool units = __ballot(bad) == 0ull;
-    if (threadIdx.x == 0) a.inst_units[blockIdx.x] = units ? 1u : 0u;
+    const bool some = __syncthreads_or(bad ? 1 : 0) != 0;
+    if (threadIdx.x == 0) a.inst_units[blockIdx.x] = some ? 0u : 1u;
 }
 
 // ---------------------------------------------------------------- launchers
@@ -1535,8 +1538,8 @@ hipError_t launch_c128_to_c64(const double* src, float* dst, int64_t n_reals, hi
     return hipGetLastError();
 }
 
-hipError_t launch_target_units(const LoopArgs& a, hipStream_t s) {
-    target_units_kernel<<<a.I, 64, 0, s>>>(a);
+hipError_t launch_target_copy(const LoopArgs& a, hipStream_t s) {
+    target_copy_kernel<<<a.I, std::clamp(1 << (2 * a.n), 64, 1024), 0, s>>>(a, const_cast<float*>(a.target32));
     return hipGetLastError();
 }
 

@@ -79,3 +79,33 @@ def test_width_6_layouts(dev, oracle, lib, P, L):
     assert torch.equal(out[-1], lds)
     ctx.close()
     assert qe.device_errors() == 0
+
+
+@pytest.mark.parametrize("n,P,L", [(4, 9, 64), (5, 9, 90), (5, 90, 200), (6, 9, 200), (6, 220, 70)])
+def test_exact_values_end_in_registers(dev, oracle, n, P, L):
+    # the bodies for exact values and the end of their reach (36 CV gates), register
+    # schedule set; targets of units, with one other entry (the first or the last
+    # looked at), of no zero at all
+    N, rng = 1 << n, np.random.default_rng(n)
+    T = np.stack([np.eye(N)[rng.permutation(N)].astype(np.complex128) for _ in range(3)] +
+                 [1j ** rng.integers(0, 4, (N, N))])
+    T[1], T[2] = np.eye(N), np.eye(N)
+    T[1, 0, 0], T[2, N - 1, N - 1] = np.exp(0.3j), 0.75
+    T = torch.from_numpy(T).to(dev)
+    saved = {(c, k): qe.get_schedule_lib(n, c, k) for c in (0, 1) for k in (0, 1, 2)}
+    try:
+        qe.set_schedule(n, 0)
+        ctx = qe.Context(n, qe.LIB_NCV, qe.ALG_QEQEA, L, P, 4, prob_mutation=0.3, seed=L)
+        ctx.set_targets(T)
+        for gen in range(2):
+            slots, g, f = ctx.sample_eval(gen)
+            for i in range(4):
+                one = g.view(4, P, L)[i].contiguous()
+                want = qe.eval_fitness(one, T[i].to(torch.complex64), n=n, L=L, target_stride=0, path=qe.PATH_FP32_LDS)[0]
+                assert torch.equal(f.view(4, P)[i], want), i
+            ctx.update(gen, slots, g, f)
+        ctx.close()
+    finally:
+        for (c, k), v in saved.items():
+            qe.set_schedule_lib(n, c, k, *v)
+    assert qe.device_errors() == 0
