@@ -208,8 +208,12 @@ __global__ __launch_bounds__(64 * W) void lds32_kernel(BatchArgs a, float* __res
 // dispatched in index order, so the heaviest items start first
 // (longest-processing-time order).
 constexpr int MIX_BUCKETS = 7;          // widths 6..1, then malformed widths
-// Fewest circuits of a mixed batch whose width-6 ones run with one column per
-// lane.
+// Fewest circuits of a mixed batch that run one per workgroup, those of width 6 with
+// one column per lane.  The line is that of widths 3 to 6 in equal parts (8 to 64
+// gates, sort included, us: 3072 circuits 34.2 against 33.6 the other way, 4095 37.5
+// against 38.8, 8192 50.5 against 56.7).  Other mixes cross elsewhere (width 6 alone
+// at 1300: 2048 36 against 41; widths 2 to 5 lose: 8192 35.8 against 33.3), but only
+// the device knows the widths, and the launch needs its shape before.
 constexpr int MIX_COLUMNS_MIN = 4096;
 constexpr int MIX_LCLASSES = 16;        // lengths >= 120, 112..119, ..., 8..15, < 8
 
@@ -463,7 +467,8 @@ hipError_t launch_eval_fp32(const BatchArgs& a, int path, float* f, float* g, fl
     } else if (a.uniform_n > 0) {
         launch_width<false, false>(a, a.uniform_n, path, f, g, delta, s);
     } else if (path == QE_PATH_FP32 && work) {
-        // one launch over width-sorted work items (LDS-staged for n >= 4)
+        // one launch over width-sorted work items (register-resident for n >= 4,
+        // whatever the schedule says)
         mix_bucket_kernel<<<1, MIX_SORT, 0, s>>>(a, work + MIX_WORK_META, work);
         return launch_mix_eval(a, work, f, g, delta, s);
     } else {

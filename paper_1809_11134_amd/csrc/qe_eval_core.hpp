@@ -969,12 +969,13 @@ __device__ __forceinline__ void lds_generic_body(int n, int L, const uint16_t* g
 // Eq. 11 (or the phase-insensitive form) of one circuit from its product in
 // LDS, in an order fixed by the width alone.  WR wavefronts share the work
 // (WR = 1 for widths up to 5, whose kernels may run one or two wavefronts per
-// circuit; WR = 4 for width 6, whose kernels all run four): lane l of
+// circuit; WR = 4 for width 6, where they run four): lane l of
 // wavefront w takes column j = w (N / WR) + l mod (N / WR) and the logical
 // rows r = q, q + Q, q + 2Q, ... (q = l div (N / WR), Q = 64 WR / N) in
 // increasing order (row r is stored at A r ^ b); the wavefront's reduction
 // tree adds its lanes and the WR wavefront sums are added in order.  Every
-// LDS-staged schedule of a width therefore gives the same bits.  WR > 1:
+// schedule of a width therefore gives the same bits (the register-resident core
+// forms the same sums).  WR > 1:
 // every wavefront of the circuit calls it (it holds workgroup barriers) with
 // `w` its index and red 4 x 3 floats of LDS.  Returns f on every lane; g,
 // delta out.

@@ -45,9 +45,10 @@ Sched schedule_for(int n, int L, int lib_class = SCHED_DISCRETE);
 // Fewest circuits of width 6 for which the register-resident kernels hold one
 // column per lane (one wavefront per circuit) instead of 16 columns per
 // wavefront (four per circuit): with fewer, the longer chain of one wavefront
-// is not hidden.  48 gates: 512 circuits 23.5 us against 21.7, 640 23.2 against
-// 25.3, 8192 94 against 145; Ising 768 44.6 against 39.5, 1024 45.4 against
-// 48.2, 8192 206 against 260.
+// is not hidden.  Random circuits of 48 gates, back to back, us: {H, T, CNOT, CV,
+// CV+} 512 circuits 22.8 against 20.9, 640 22.7 against 25.4, 8192 93 against 143 (83
+// where most are near a target and hold identity gates); Ising 768 43.3 against 36.8,
+// 1024 43.5 against 44.4, 8192 201 against 254.
 constexpr uint32_t reg6_columns_min(bool angled) { return angled ? 1024u : 640u; }
 // Sampled circuits of {I, NOT, CNOT, CV, CV+} that run LDS-staged although the table
 // (tuned on up to 48 gates) says register-resident.  There every chunk of 64 gates

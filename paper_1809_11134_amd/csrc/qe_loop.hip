@@ -561,7 +561,10 @@ __global__ __launch_bounds__(256) void population_kernel(LoopArgs a, uint64_t ge
         // workgroup of four
         constexpr int WV = circuit_waves<NQ, W, CPB>();
         static_assert(WV == 1 || CPB == 1, "one circuit per workgroup of several wavefronts");
-        constexpr bool STASH = SAMPLE && NQ >= 4;
+        constexpr bool STASH = SAMPLE && NQ >= 4 && WV == 1;
+        static_assert(WV == 1 || DEDUP_MIN_TOTAL / 256 >= (int)reg6_columns_min(ISING),
+                      "contexts with the shared-slot search (at most 256 positions) hold more circuits than run "
+                      "on four wavefronts each");
         __shared__ float red[4][3];
         __shared__ uint2 xch[WV > 1 ? 128 : 1];
         __shared__ float4 stash[STASH ? CPB : 1][4][64];
@@ -570,7 +573,7 @@ __global__ __launch_bounds__(256) void population_kernel(LoopArgs a, uint64_t ge
         eval_circuit<NQ, 0, SAMPLE, ISING, CPB>(a, gen, ci, gates_in, angles_in, slots_out, gates_out,
                                            angles_out, f_out, WV == 1 || threadIdx.x < 64, decide, nullptr,
                                            nullptr, red, WV == 1 ? nullptr : static_cast<void*>(xch),
-                                           STASH ? stash[WV == 1 ? wave % CPB : 0] : nullptr);
+                                           STASH ? stash[wave % CPB] : nullptr);
     } else {
         // W = 1: CPB circuits per workgroup, one per wavefront (no barrier
         // is shared, so a wavefront past the end may leave); W > 1: one
@@ -659,7 +662,6 @@ __device__ __forceinline__ void su3_step(float* q, int j, int ai, const float* t
     }
 }
 
-// Amplitudes of a qutrit record (the first 48 of its 64 bytes).
 // Elitism (Sec. IV-E.1) of a used slot whose segment fitness is v: strictly
 // better -> the state becomes the best, otherwise the best state is restored.
 // Returns whether the best copy changed.
@@ -1718,8 +1720,11 @@ hipError_t launch_state_gather(const LoopArgs& a, int which, void* dst, hipStrea
 uint32_t ga_update_parts(int I, int P, int L) {
     // one round of gene pairs per thread, as long as the populations together
     // make no more than two workgroups per compute unit: every workgroup
-    // repeats its population's prefix and draws (256 populations of 64: 10.8 us
-    // at 512 workgroups in all, 11.4 at 1024, 16.0 at 2048)
+    // repeats its population's prefix and draws (generations of n = 2 with 512,
+    // 1024 and 2048 workgroups in all, us: 256 populations of 64 x 36 39.5, 40.7,
+    // 41.5; 16 of 1024 x 30 36.4, 38.2, 38.2; 32 of 4096 x 20 153, 156, 168; 20 of
+    // 333 x 100 48.2, 49.4, 50.3; 256 workgroups are within 1.5 % of 512 but for
+    // 4 of 1000 x 40, 20.3 against 21.2)
     const int half = P / 2;
     const uint64_t rounds = ((uint64_t)half * L + GA_BLOCK - 1) / GA_BLOCK;
     const uint64_t most = std::max<uint64_t>(1, 512 / (uint64_t)I);

@@ -11,8 +11,9 @@
 // bits of the register index.  The gates run in reg_gates (qe_reg_asm.hpp): at
 // n = 5, 6 a wire that a gate needs and that sits in a lane slot is exchanged
 // with a register slot (v_permlane16/32_swap, one instruction per pair of
-// registers) and stays there (0.29 exchanges per two-wire gate of random
-// circuits at n = 5, 0.51 at n = 6).
+// registers) and stays there (per two-wire gate of random circuits 0.29 exchanges
+// at n = 5, 0.51 at n = 6; 6.5 for the 24 gates that act in a sampled circuit of 40
+// at n = 5).
 //
 // What bounds it: the VALU instructions of the gate bodies (8 or 10 per row pair of
 // a CV) and the scalar instructions of their dispatch.  Against the same gates on
