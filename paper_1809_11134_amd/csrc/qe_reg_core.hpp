@@ -294,24 +294,15 @@ struct RegMatrix {
     __device__ __forceinline__ Real fitness_groups(int mode, Real* g_out, Real* delta_out, int w, Real (*red)[3]) {
         const int lane = (int)lane_id();
         const int key = (j % Q) == (int)q ? j / Q : -1;       // register of the diagonal entry
-        // FP32: one sum, in the order of canonical_fitness.  FP64: four sums of every
-        // fourth element, as the 256 threads of the generic body have them at n = 5;
-        // 16 terms in one chain were up to 1.19 times as far off (root mean square of
-        // one column's energy: 0.86 against 0.73 units of 2^-53; with four sums 0.65).
-        constexpr int SUMS = sizeof(Real) == 8 ? 4 : 1;
-        Real part[SUMS], dr = (Real)0, di = (Real)0;
-#pragma unroll
-        for (int c = 0; c < SUMS; ++c) part[c] = (Real)0;
+        Real off = (Real)0, dr = (Real)0, di = (Real)0;
 #pragma unroll
         for (int m = 0; m < E; ++m) {
             const bool dg = m == key;
             const Real xr = re(m), xi = im(m), m2 = xr * xr + xi * xi;
-            part[m % SUMS] += dg ? (Real)0 : m2;
+            off += dg ? (Real)0 : m2;
             dr = dg ? xr : dr;
             di = dg ? xi : di;
         }
-        Real off = part[0];
-        if constexpr (SUMS == 4) off = (part[0] + part[1]) + (part[2] + part[3]);
         // sums over the circuit's wavefronts, added in order
         auto total = [&](Real x) -> Real {
             const Real s = wave_sum(x);
