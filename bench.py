@@ -18,8 +18,10 @@ synchronisations and HIP events) give the median.
 
 Prints one JSON line (the metric is circuit-fitness evaluations per second)
 with a roofline entry for the dominant kernel (the fused sampling + fitness
-kernel: the bytes that the per-gate method moves with the product in LDS, against
-the LDS bandwidth measured by a probe kernel in the same run) and one for the update kernel (against HBM), each timed launch by launch
+kernel: register-resident, its vector instruction issue slots, counted in the
+committed profile of the same source, against those the GPU has; LDS-staged, the
+bytes of the per-gate method against the LDS bandwidth measured by a probe kernel in
+the same run) and one for the update kernel (against HBM), each timed launch by launch
 with HIP events on the launch stream, and the CPU oracle's rate on a bounded
 sample of the same workload on one host core and on all of them.  The
 "secondary" object adds the other workloads of the study: the n=6 precision
@@ -43,9 +45,11 @@ METRIC = "circuit-fitness evals/sec (n=4..6), FP32 vs BF16-MFMA at stated fitnes
 FP32_VECTOR_PEAK_TFLOPS = 157.3   # MI355X, 256 CUs x 4 SIMD x 16 lanes x 2 x 2 (packed) x 2.4 GHz
 LDS_SPEC_GBPS = 256 * 128 * 2.4   # MI355X LDS from unit counts: 256 CUs x 128 B/clock x 2.4 GHz
 HBM_PEAK_GBPS = 8000.0            # MI355X HBM3E, published
-# The LDS peak the rooflines divide by: the best rate of the LDS probe kernel
-# measured in this run (set by main), the unit-count figure until then.
+# The LDS peak that LDS-staged kernels are held against: the best rate of the LDS
+# probe kernel measured in this run (set by main), the unit-count figure until then.
 LDS_PEAK_GBPS = LDS_SPEC_GBPS
+# Vector instruction issue: 256 CUs x 4 SIMDs, one wave instruction per 4 cycles, 2.4 GHz
+VALU_ISSUE_PEAK_G = 256 * 4 * 2.4 / 4
 
 
 def log(msg):
@@ -99,7 +103,9 @@ def algorithmic_lds_bytes(gates, n):
     return float(per_kind[kinds].sum() + circuits * 16.0 * NN)
 
 
-def traffic_from_profiles(kernel_key, src_hash):
+def counted_in_profiles(kernel_key, src_hash, field):
+    """A counter's mean per launch from the committed profile, None if the kernels'
+    source has changed since it was taken."""
     path = os.path.join(ROOT, "profiles", f"pmc_{kernel_key}_traffic.txt")   # JSON text
     if not os.path.exists(path):
         return None
@@ -107,7 +113,30 @@ def traffic_from_profiles(kernel_key, src_hash):
         d = json.load(fh)
     if d.get("source_hash") != src_hash:
         return None
-    return d.get("hbm_bytes_per_launch")
+    return d.get(field)
+
+
+def traffic_from_profiles(kernel_key, src_hash):
+    return counted_in_profiles(kernel_key, src_hash, "hbm_bytes_per_launch")
+
+
+def valu_issue(kernel_key, src_hash, us):
+    """Vector instruction issue slots per second of a kernel (counted per launch), in
+    10^9, and their share of the GPU's; None where nothing was counted."""
+    slots = counted_in_profiles(kernel_key, src_hash, "valu_issue_slots_per_launch")
+    if slots is None:
+        return {"valu_issue_gslots": None, "valu_issue_frac": None}
+    rate = slots / (us * 1e-6) / 1e9
+    return {"valu_issue_gslots": rate, "valu_issue_frac": rate / VALU_ISSUE_PEAK_G}
+
+
+def method_rates(lds_bytes, flops, us):
+    """What the per-gate method needs for the circuits, per second: FP32 work, and the
+    LDS bytes it would move with the product in LDS (the register-resident kernels
+    move none of them, so no share of a peak is given)."""
+    alu = flops / (us * 1e-6) / 1e12
+    return {"alu_tflops": alu, "alu_frac": alu / FP32_VECTOR_PEAK_TFLOPS,
+            "lds_equivalent_bytes_per_launch": lds_bytes, "lds_equivalent_gbps": lds_bytes / (us * 1e-6) / 1e9}
 
 
 def cpu_model():
@@ -236,9 +265,7 @@ def secondary_precision(dev, reps=5):
                               "max_abs_df": float(err.max()), "p99_abs_df": float(np.quantile(err, 0.99)),
                               "elite32_agreement": agree, "kendall_tau": float(kendalltau(f, f64)[0])}
         if path == qe.PATH_FP32:
-            # the per-gate model's LDS bytes for these circuits against the LDS peak
-            out["paths"][name]["algorithmic_lds_bytes"] = lds
-            out["paths"][name]["lds_frac"] = lds / (us * 1e-6) / 1e9 / LDS_PEAK_GBPS
+            out["paths"][name].update(method_rates(lds, algorithmic_flops(w["gates"], n), us))
     qe.set_mfma_min_block(n, lc, tuned_mb)
     return out
 
@@ -278,7 +305,7 @@ def secondary_qeqea_ising(dev, gens=100, reps=50):
     """The bench shape (n=4, P=4096, L=30) with the Ising library of Sec. III
     (rotations about the measured axis and interactions, continuous angles):
     a graph of `gens` whole generations, and the fused sampling + fitness
-    kernel timed over `reps` back-to-back launches with its LDS roofline."""
+    kernel timed over `reps` back-to-back launches."""
     import numpy as np
     import torch
     from paper_1809_11134_amd import inputs, qe
@@ -310,16 +337,13 @@ def secondary_qeqea_ising(dev, gens=100, reps=50):
     gh = gates.cpu().numpy()
     lds = algorithmic_lds_bytes(gh, n)
     flops = algorithmic_flops(gh, n)
-    achieved = lds / (kern_ms / 1e3) / 1e9
     best = ctx.get_best(0)
     ctx.close()
     return {"workload": w["name"], "generations": gens,
             "evals_per_s": gens * I * P / (ms * 1e-3), "ms_per_generation": ms / gens,
             "kernel": "population_kernel<4,0,true,true> (sampling + Ising decode + Eq. 11 fitness "
                       "+ segment max, register-resident)",
-            "kernel_us": kern_ms * 1e3, "algorithmic_lds_bytes_per_launch": lds,
-            "lds_gbps": achieved, "lds_frac": achieved / LDS_PEAK_GBPS,
-            "alu_tflops": flops / (kern_ms / 1e3) / 1e12,
+            "kernel_us": kern_ms * 1e3, **method_rates(lds, flops, kern_ms * 1e3),
             "best_f_fp32": best[1], "best_f_fp64": best[2]}
 
 
@@ -580,20 +604,20 @@ def sampled_schedule(n, L):
 def secondary_qeqea_n4(dev, K, W):
     """n=4, library {I,NOT,CNOT,CV,CV+}, one QEQEA population of 4096
     circuits x 30 gates: the graph of K generations + the FP64 re-check
-    (timed as the headline), and its fused kernel against the LDS peak."""
+    (timed as the headline), and its fused kernel against the GPU's vector issue."""
     from paper_1809_11134_amd import inputs
     w = inputs.workload_qeqea_n4()
     ctx = qeqea_context(w, dev)
     ms, times, gen, err = qeqea_graph_run(ctx, K, W, dev)
     fused_us, upd_us, gates, _ = time_generation_kernels(ctx, gen, 50, dev)
-    lds = algorithmic_lds_bytes(gates.cpu().numpy(), w["n"])
+    gh = gates.cpu().numpy()
     ctx.close()
     return {"workload": w["name"], "generations": K, "evals_per_s": K * w["P"] / (ms * 1e-3),
             "ms_per_generation": ms / K, "replay_ms": times, "elite_fp32_vs_fp64_max_abs_df": err,
             "fused_kernel": "population_kernel<4,{},true,false,{}>".format(*sampled_schedule(4, w["L"])),
             "fused_kernel_us": fused_us,
-            "update_kernel_us": upd_us, "algorithmic_lds_bytes_per_launch": lds,
-            "lds_frac": lds / (fused_us * 1e-6) / 1e9 / LDS_PEAK_GBPS,
+            "update_kernel_us": upd_us, **valu_issue("qeqea_fused_n4", source_hash(), fused_us),
+            **method_rates(algorithmic_lds_bytes(gh, w["n"]), algorithmic_flops(gh, w["n"]), fused_us),
             "traffic": traffic_from_profiles("qeqea_fused_n4", source_hash())}
 
 
@@ -601,9 +625,8 @@ def secondary_mixed_ga(dev, gens=50, reps=10):
     """256 GA populations of 64 circuits, population i on n_i ~ U{3..6}
     wires with genomes of L_i ~ U[8,64] gates of {H,T,CNOT,CV,CV+} and its
     own target (16384 evaluations per generation): the graph of `gens`
-    generations (genome copy, one cost-sorted evaluation launch, the GA
-    update of every population), and the evaluation launch alone against the
-    LDS peak."""
+    generations (one cost-sorted evaluation launch, the GA update of every
+    population), and the evaluation launch alone."""
     import numpy as np
     import torch
     from paper_1809_11134_amd import inputs, qe
@@ -635,16 +658,16 @@ def secondary_mixed_ga(dev, gens=50, reps=10):
     torch.cuda.synchronize()
     eval_us = e0.elapsed_time(e1) / reps * 1e3
     flat = gates.cpu().numpy().view(np.uint16)
-    lds, o = 0.0, 0
+    lds, flops, o = 0.0, 0.0, 0
     for n, L in zip(w["widths"], w["lengths"]):
         lds += algorithmic_lds_bytes(flat[o:o + P * L].reshape(P, L), n)
+        flops += algorithmic_flops(flat[o:o + P * L].reshape(P, L), n)
         o += P * L
     best = max(ctx.get_best(i, with_fp64=False)[1] for i in range(I))
     ctx.close()
     return {"workload": w["name"], "generations": gens, "evals_per_s": gens * I * P / (ms * 1e-3),
             "ms_per_generation": ms / gens, "eval_kernel": "mix_kernel (cost order fixed at creation)",
-            "eval_kernel_us": eval_us, "algorithmic_lds_bytes_per_launch": lds,
-            "lds_frac": lds / (eval_us * 1e-6) / 1e9 / LDS_PEAK_GBPS, "best_f": best}
+            "eval_kernel_us": eval_us, **method_rates(lds, flops, eval_us), "best_f": best}
 
 
 def secondary_uneven(dev, reps=7):
@@ -668,17 +691,17 @@ def secondary_uneven(dev, reps=7):
     nqd, goffd = torch.from_numpy(nq).to(dev), torch.from_numpy(goff).to(dev)
     batch, keep, B = qe.make_batch(g, flat, nq=nqd, goff=goffd, toff=toff, target_stride=None)
     us, _ = _timed_eval(batch, qe.PATH_FP32, B, reps, dev)
-    # the per-gate model's LDS bytes, width by width
-    lds = 0.0
+    # what the per-gate method needs, width by width
+    lds = flops = 0.0
     for n in range(1, 7):
         rows = np.nonzero(nq == n)[0]
         if len(rows) == 0:
             continue
         flat_g = np.concatenate([gates[goff[b]:goff[b + 1]] for b in rows])
         lds += algorithmic_lds_bytes(flat_g, n) + (len(rows) - 1) * 16.0 * float(1 << (2 * n))
+        flops += algorithmic_flops(flat_g[None], n) + (len(rows) - 1) * 4.0 * float(1 << (2 * n))
     return {"workload": w["name"], "circuits": len(nq), "evals_per_s": len(nq) / (us * 1e-6),
-            "kernel_us": us, "algorithmic_lds_bytes": lds,
-            "lds_frac": lds / (us * 1e-6) / 1e9 / LDS_PEAK_GBPS}
+            "kernel_us": us, **method_rates(lds, flops, us)}
 
 
 def main():
@@ -719,8 +742,8 @@ def main():
     qe.load()
     src = source_hash()
 
-    # the per-gate method reads and writes every element it touches once, so
-    # its LDS ceiling is the probe's copy rate (equal reads and writes)
+    # LDS-staged, the per-gate method reads and writes every element it touches
+    # once, so its LDS ceiling is the probe's copy rate (equal reads and writes)
     lds_probe = measure_lds_peak(dev)
     LDS_PEAK_GBPS = lds_probe["copy_b128"]
     log(f"LDS probe: {lds_probe} GB/s -> peak {LDS_PEAK_GBPS:.0f} GB/s for equal reads and writes "
@@ -744,29 +767,30 @@ def main():
     gh = gates.cpu().numpy()
     flops = algorithmic_flops(gh, n)
     lds_bytes = algorithmic_lds_bytes(gh, n)
-    achieved = lds_bytes / (fused_us * 1e-6) / 1e9
-    alu = flops / (fused_us * 1e-6) / 1e12
     waves, cpb = sampled_schedule(n, L)
-    roofline = {"bound": "lds", "achieved": round(achieved, 2), "peak": round(LDS_PEAK_GBPS, 1),
-                "unit": "GB/s", "frac": round(achieved / LDS_PEAK_GBPS, 6),
-                "traffic": traffic_from_profiles("qeqea_fused_n5", src),
-                "kernel": f"population_kernel<5,{waves},true,false,{cpb}> (circuit construction from the "
-                          f"slot words + Eq. 11 fitness + elitism of the slots a circuit alone used + "
-                          f"segment max of the shared ones, " +
-                          (f"LDS-staged, {waves} wavefront(s)" if waves else
-                           "register-resident: the LDS bytes are those the per-gate method moves with "
-                           "the product in LDS; one wavefront") +
-                          f" per circuit, {cpb} circuit(s) per workgroup)",
-                "kernel_us": round(fused_us, 3), "algorithmic_lds_bytes_per_launch": lds_bytes,
-                "peak_source": "LDS probe kernel in this run, copy mode (each 16-byte word read and "
-                               "written once, the mix of the per-gate updates)",
-                "lds_probe_gbps": lds_probe,
-                "frac_of_read_peak": round(achieved / lds_probe["read_b128"], 6),
-                "frac_of_unit_count_peak": round(achieved / LDS_SPEC_GBPS, 6),
-                "algorithmic_flops_per_launch": flops, "alu_tflops": round(alu, 4),
-                "alu_frac": round(alu / FP32_VECTOR_PEAK_TFLOPS, 6)}
-    log(f"fused kernel: {fused_us:.2f} us/launch, {achieved:.1f} GB/s algorithmic LDS "
-        f"({achieved / LDS_PEAK_GBPS:.3f} of the measured peak)")
+    kernel = (f"population_kernel<5,{waves},true,false,{cpb}> (circuit construction from the "
+              f"slot words + Eq. 11 fitness + elitism of the slots a circuit alone used + "
+              f"segment max of the shared ones, " +
+              (f"LDS-staged, {waves} wavefront(s)" if waves else "register-resident, one wavefront") +
+              f" per circuit, {cpb} circuit(s) per workgroup)")
+    rates = method_rates(lds_bytes, flops, fused_us)
+    if waves:
+        ach = rates["lds_equivalent_gbps"]
+        roofline = {"bound": "lds", "achieved": ach, "peak": LDS_PEAK_GBPS, "unit": "GB/s",
+                    "frac": ach / LDS_PEAK_GBPS,
+                    "peak_source": "LDS probe kernel in this run, copy mode (each 16-byte word read and "
+                                   "written once, the mix of the per-gate updates)"}
+    else:
+        v = valu_issue("qeqea_fused_n5", src, fused_us)
+        roofline = {"bound": "valu_issue", "achieved": v["valu_issue_gslots"], "peak": VALU_ISSUE_PEAK_G,
+                    "unit": "G issue slots/s", "frac": v["valu_issue_frac"],
+                    "peak_source": "256 CUs x 4 SIMDs x 2.4 GHz / 4 cycles per wave instruction; the kernel's "
+                                   "slots from the committed counters (null if its source changed since)"}
+    roofline.update({"traffic": traffic_from_profiles("qeqea_fused_n5", src), "kernel": kernel,
+                     "kernel_us": round(fused_us, 3), "algorithmic_flops_per_launch": flops, **rates,
+                     "lds_probe_gbps": lds_probe})
+    share = f"{roofline['frac']:.3f}" if roofline["frac"] is not None else "no counters for this source"
+    log(f"fused kernel: {fused_us:.2f} us/launch, {roofline['bound']} {share}, {rates['alu_tflops']:.1f} TFLOP/s")
     upd_bytes, commit_bytes, upd_counts = update_algorithmic_bytes(ctx, gen, dev)
     roofline["commit_hbm_bytes_per_launch"] = commit_bytes
     roofline["commit_note"] = ("elitism of the slots one circuit alone used, committed by this kernel "
